@@ -47,8 +47,9 @@ struct BwdArgs {
 // dq pass
 // ------------------------------------------------------------------------------------
 //
-// Two shapes of workgroup, as in the forward.  NW = 8: 256 rows, a ring of three slots of a whole 64-key tile
-// (K and V: 96 KB), one workgroup per CU, one barrier per tile.  NW = 4: 128 rows, a ring of four slots of HALF
+// Two shapes of workgroup, as in the forward (and the same items: 32 rows of one q head per wave, wave_rows()).
+// NW = 8: a ring of three slots of a whole 64-key tile
+// (K and V: 96 KB), one workgroup per CU, one barrier per tile.  NW = 4: a ring of four slots of HALF
 // a tile (32 keys of K and V: 64 KB), one barrier per half, two workgroups per CU: for packings whose key
 // loops are short, where a workgroup's fixed costs (a quarter of its life with one workgroup per CU) then
 // overlap with the other workgroup's loop and fewer rows ride along through tiles they cannot see.
@@ -66,21 +67,22 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(BwdArgs a) {
     int tile, head;
     if (!decode_item(blockIdx.x, a.n_tiles, a.Hq, a.Hkv, tile, head)) return;
     const TileDesc td = (BM == 256 ? a.sched.tiles256 : a.sched.tiles128)[tile];
-    const int ti = td.ti;
     GroupDesc gd;
     gd.tok_base = td.tok_base; gd.Lp = td.Lp; gd.Tg = td.Tg; gd.G = 0; gd.roff = nullptr;
     const int Lp = gd.Lp, Tg = gd.Tg;
-    const int t0 = ((Tg + BM - 1) / BM - 1 - ti) * BM;   // a group's last tile first: it carries the most work
-    const int64_t T_total = a.tab[1];
-    if (a.resp_only && t0 + BM <= Lp) return;      // a tile of prompt rows only
-
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
+    const WaveRows wr = wave_rows<NW>(td, head, a.Hq / a.Hkv, w);
+    head = wr.head;
+    const int t0 = wr.t0, t1 = wr.t1;
+    const int64_t T_total = a.tab[1];
+    if (t0 >= Tg || (a.resp_only && t1 <= Lp)) return;      // past the group's end, or prompt rows only
+
     const int c = l & 31, hh = l >> 5, j = l & 15, c16 = (l >> 4) & 1;
 
-    const int t = t0 + 32 * w + c;
+    const int tw0 = wr.tw0;
+    const int t = tw0 + c;
     const bool valid = t < Tg;
     const int tm = valid ? t : -1;
-    const int tw0 = t0 + 32 * w;
     const bool wave_valid = tw0 < Tg;
     const int tw1 = min(tw0 + 31, Tg - 1);
     // first own-segment key of this lane's row and of the workgroup's first response row (0 on the prompt)
@@ -207,7 +209,6 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(BwdArgs a) {
         __syncthreads();
     }
 
-    const int t1 = min(t0 + BM, Tg);
     int n1 = (min(Lp, t1) + BN - 1) / BN, k2b = n1, k2e = n1;
     if (t1 > Lp) {
         k2b = max(n1, b2 / BN);
@@ -860,7 +861,7 @@ hipError_t launch_bwd_bf16(const Problem& p, hipStream_t s) {
     a.tab = p.tab; a.sched = p.sched; a.n_groups = p.n_groups; a.Hq = p.Hq; a.Hkv = p.Hkv; a.scale = p.scale; a.c = p.scale * LOG2E;
     a.resp_only = p.resp_only; a.accumulate = p.accumulate;
     if (p.stages & STAGE_DQ) {
-        // short key loops: the 128-row shape, two workgroups per CU (the forward's rule, see bwd_dq_kernel)
+        // short key loops: the four-wave shape, two workgroups per CU (the forward's rule, see bwd_dq_kernel)
         const bool small = use_small_shape(p);
         a.n_tiles = count_tiles(p, small ? 128 : 256);
         const int grid = grid_for_items(a.n_tiles, p.Hq, p.Hkv);

@@ -174,6 +174,36 @@ __device__ __forceinline__ bool decode_item(int bid, int n_tiles, int Hq, int Hk
     return tile < n_tiles;
 }
 
+// Rows of a workgroup of NW waves.  A row tile of 32 NW rows x the rep = Hq / Hkv q heads that share a kv head
+// is cut into rep workgroups, not one per head: its NW x rep items (32 rows of one head) are numbered row block
+// first, head second, and workgroup i takes items i NW .. i NW + NW - 1, one per wave.  All items read the same
+// K/V tiles, so a tile is copied for as many rows as before, but the workgroup spans about 32 NW / rep rows
+// instead of 32 NW, and a wave rides along through fewer tiles that only other rows of the workgroup see (past its own
+// diagonal, other responses' keys).  Against one head per workgroup (executed steps and time, one box):
+//   64 groups of 128 + 16 x 256 tokens, 28 / 4 heads   -15 %   fwd 2.88 -> 2.63 ms, dq pass 4.04 -> 3.60 ms
+//   64 groups of 1000 tokens, 32 / 8 heads             -13 %   fwd 0.88 -> 0.84 ms, dq pass 1.27 -> 1.15 ms
+//   4 x (4096 + 16 x 320), 32 / 8                       -2 %   fwd 1.97 -> 1.94 ms, dq pass 2.81 -> 2.74 ms
+//   16384 + 32 x 160, 40 / 8                            -1 %   fwd 4.04 -> 4.00 ms, dq pass 5.72 -> 5.55 ms
+// With one q head per kv head the two cuts are the same.
+struct WaveRows {
+    int head;           // q head of this wave
+    int tw0;            // its first row (group-local)
+    int t0, t1;         // rows of the workgroup
+};
+template <int NW>
+__device__ __forceinline__ WaveRows wave_rows(const TileDesc& td, int head, int rep, int w) {
+    const int kvh = head / rep;
+    const int i = rep - 1 - (head - kvh * rep);              // last rows first: they carry the most work
+    const int base = ((td.Tg + 32 * NW - 1) / (32 * NW) - 1 - td.ti) * (32 * NW);
+    const int f = i * NW + w, rb = f / rep;
+    WaveRows r;
+    r.head = kvh * rep + (f - rb * rep);
+    r.tw0 = base + 32 * rb;
+    r.t0 = base + 32 * (i * NW / rep);
+    r.t1 = min(base + 32 * ((i * NW + NW - 1) / rep) + 32, td.Tg);
+    return r;
+}
+
 __host__ __device__ inline int grid_for_items(int n_tiles, int Hq, int Hkv) {
     const int rep = Hq / Hkv;
     if (Hkv % 8 == 0) return 8 * (n_tiles * rep * (Hkv / 8));

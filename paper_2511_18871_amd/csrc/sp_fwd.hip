@@ -1,8 +1,8 @@
 // Forward shared-prompt attention, bf16 MFMA path (gfx950).
 //
-// One workgroup owns a tile of 256 consecutive packed query rows of one group and one
-// q head; wave w (of 8) owns 32 of those rows.  Keys/values stream through LDS in tiles of
-// 64 keys.  Per tile a wave computes S^T = K Q^T (keys x queries) so that every lane
+// One workgroup owns eight (or four) items of one group and one kv head, an item being 32 consecutive
+// packed query rows of one of the q heads that read this kv head; a wave owns one item (wave_rows() in
+// sp_common.hpp).  Keys/values stream through LDS in tiles of 64 keys.  Per tile a wave computes S^T = K Q^T (keys x queries) so that every lane
 // holds scores of ONE query (column) and the online softmax needs a single
 // cross-lane exchange, then O^T += V^T P^T with V read transposed from LDS.
 //
@@ -52,8 +52,8 @@ struct FwdArgs {
 // barrier; the K and V tiles of the following two steps are copied into LDS meanwhile.
 // ------------------------------------------------------------------------------------
 //
-// Two shapes of workgroup.  NW = 8: 256 rows, four K and four V buffers (128 KB of LDS), one workgroup
-// per CU: the shape for long key loops.  NW = 4: 128 rows, two K and two V buffers (64 KB), one step
+// Two shapes of workgroup.  NW = 8: eight items, four K and four V buffers (128 KB of LDS), one workgroup
+// per CU: the shape for long key loops.  NW = 4: four items, two K and two V buffers (64 KB), one step
 // per barrier, TWO workgroups per CU: each workgroup's fixed costs (table lookups, first loads,
 // epilogue, the gap before the next dispatch) then overlap with the other's key loop, which is what
 // batches of short groups need, where a workgroup runs only a handful of steps.
@@ -77,21 +77,22 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd_kernel(FwdArgs a) {      // tw
     if (!decode_item(blockIdx.x - set * a.blocks_per_set, a.n_tiles, a.Hq, a.Hkv, tile, head)) return;
     // the tile's descriptor: one 32-byte load instead of a bisection over the groups and the group's entry
     const TileDesc td = (BM == 256 ? a.sched.tiles256 : a.sched.tiles128)[tile];
-    const int ti = td.ti;
     GroupDesc gd;
     gd.tok_base = td.tok_base; gd.Lp = td.Lp; gd.Tg = td.Tg; gd.G = 0; gd.roff = nullptr;
     const int Lp = gd.Lp, Tg = gd.Tg;
-    const int t0 = ((Tg + BM - 1) / BM - 1 - ti) * BM;   // a group's last tile first: it carries the most work
-    const int T_total = a.tab[1];
-    if (a.resp_only && t0 + BM <= Lp) return;      // a tile of prompt rows only
-
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
+    const WaveRows wr = wave_rows<NW>(td, head, a.Hq / a.Hkv, w);
+    head = wr.head;
+    const int t0 = wr.t0, t1 = wr.t1;
+    const int T_total = a.tab[1];
+    if (t0 >= Tg || (a.resp_only && t1 <= Lp)) return;      // past the group's end, or prompt rows only
+
     const int c = l & 31, hh = l >> 5, j16 = l & 15, c16 = (l >> 4) & 1;
 
-    const int t = t0 + 32 * w + c;
+    const int tw0 = wr.tw0;
+    const int t = tw0 + c;
     const bool valid = t < Tg;
     const int tm = valid ? t : -1;
-    const int tw0 = t0 + 32 * w;
     const bool wave_valid = tw0 < Tg;
     const int tw1 = min(tw0 + 31, Tg - 1);
     // first own-segment key of this lane's row and of the workgroup's first response row (0 on the prompt)
@@ -110,7 +111,6 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd_kernel(FwdArgs a) {      // tw
         for (int ks = 0; ks < 8; ++ks) qreg[ks] = *reinterpret_cast<const bf16x8*>(qp + 16 * ks);
     }
 
-    const int t1 = min(t0 + BM, Tg);
     int n1, k2b, k2e;
     if (NAIVE) {
         n1 = (t1 + BN - 1) / BN; k2b = k2e = n1;
@@ -503,8 +503,8 @@ hipError_t launch_fwd_bf16(const Problem& p, hipStream_t s) {
     a.tab = p.tab; a.n_groups = p.n_groups; a.sched = p.sched;
     a.Hq = p.Hq; a.Hkv = p.Hkv; a.c = p.scale * LOG2E; a.naive = p.naive; a.resp_only = p.resp_only;
     a.o_lo = n_sets == 1 ? (__bf16*)p.o_lo_out : nullptr;
-    // Short key loops: the 128-row shape, two workgroups per CU (see fwd_kernel).  The naive baseline keeps
-    // the 256-row shape whatever the packing (its loops are long by construction).
+    // Short key loops: the four-wave shape, two workgroups per CU (see fwd_kernel).  The naive baseline keeps
+    // the eight-wave shape whatever the packing (its loops are long by construction).
     const bool small = !p.naive && use_small_shape(p);
     const int bm = small ? 128 : 256;
     a.n_tiles = count_tiles(p, bm);
