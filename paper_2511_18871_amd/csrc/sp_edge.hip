@@ -123,7 +123,7 @@ __global__ __launch_bounds__(128) void short_rows_kernel(const __bf16* __restric
         }
     }
     const float Dr = pair_sum(acc);                  // both lanes of a row hold its D
-    if (r < n_rows && hh == 0) D[(int64_t)h * T_total + tok] = Dr;
+    if (r < n_rows && hh == 0) D[(int64_t)h * T_total + tok] = -Dr;      // the plane holds -D
     if (!WITH_DQ) return;
 
     // dQ^T (d x rows) = scale * K^T (d x keys) dS^T (keys x rows), dS = P (dP - D) in fp32, fed as value + remainder
