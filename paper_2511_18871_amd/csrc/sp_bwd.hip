@@ -447,19 +447,29 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(BwdArgs a) {
 // ------------------------------------------------------------------------------------
 // dkdv pass
 // ------------------------------------------------------------------------------------
-// A workgroup of 8 waves owns 128 keys of one kv head.  Wave w works on key block kb = w & 3
-// (32 keys, one per lane column) and on row half qh = w >> 2 of every 64-row query tile, so
-// the two waves of a SIMD share their keys and split the rows.  K and V of the 128 keys stay
-// in LDS for the whole kernel (B operands are re-read per step, which keeps a wave under 256
-// registers); Q/dO tiles stream through a double buffer.  The two row halves' partial dK/dV
-// are added through LDS at the end, in a fixed order.
-__shared__ __attribute__((aligned(1024))) char dkdv_ldsKV[2][128 * 256];       // [K | V] of the 128 keys
-__shared__ __attribute__((aligned(1024))) char dkdv_lds[2][2 * TILE_BYTES];    // [buffer][Q | dO]
-__shared__ __attribute__((aligned(256))) float dkdv_ldsLD[2][2][64];           // [buffer][-lse / scale | -D][row]
-
+// A workgroup owns 128 keys of one kv head and streams Q/dO row tiles through a double buffer.
+// Bound: bf16 MFMA (32 per wave and 32 rows x 32 keys).  Two shapes:
+//   NW = 4: wave w owns 32 keys and every row, in tiles of 32 rows.  Its K rows stay in 32 registers and its V rows in
+//     LDS in the order the lanes read them: 64.5 KB of LDS, TWO workgroups per CU that do not wait for one another, so
+//     that one's barriers, first loads, stores and steps without work (other responses' rows) lie under the other's MFMAs.
+//   NW = 8: wave w owns key block w & 3 and the row half w >> 2 of tiles of 64 rows, K and V in LDS, one workgroup per
+//     CU; the two halves' partial sums are added through LDS at the end, in a fixed order.  Half as many steps per
+//     workgroup: for packings with too few workgroups to fill the chip (dkdv_head_split), where the longest one counts.
+// The LDS addresses of a step's operands are whole sums in registers plus constants (two steps per turn of the loop, one
+// per buffer); left to the compiler they were 25 additions per step, and K did not fit the registers.
+// 8 -> 4 waves with these addresses, one box: 16K prompt with 32 answers 7.67 -> 7.24 ms, 64 groups of a short prompt
+// and 16 answers 4.44 -> 3.95 ms, 64 groups of 1000 tokens 1.33 -> 1.07 ms, response rows under an 8K prompt 0.77 -> 0.67 ms.
+template <int NW>
 __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const TileDesc td, const int kvh, const int hr_only) {
     const int ti = td.ti;
-    constexpr int BNK = 128, BQ = 64;
+    constexpr int BNK = 128, BQ = 8 * NW;
+    constexpr bool K_REG = NW == 4;                 // the wave's K rows stay in registers, only V in LDS
+    constexpr int QT_BYTES = BQ * 256;              // a Q (or dO) tile
+    constexpr int CH = BQ / (4 * NW);               // 4-row chunks of a Q (or dO) tile that a wave copies
+    // NW = 8: [K | V] of the 128 keys, swizzled rows.  NW = 4: the eight V operands of each wave in lane order
+    __shared__ __attribute__((aligned(1024))) char dkdv_ldsKV[K_REG ? 128 * 256 : 2 * 128 * 256];
+    __shared__ __attribute__((aligned(1024))) char dkdv_lds[2][2 * QT_BYTES];                // [buffer][Q | dO]
+    __shared__ __attribute__((aligned(256))) float dkdv_ldsLD[2][2][BQ];                     // [buffer][-lse / scale | -D][row]
     constexpr int RD = 3;      // LDS operand ring depth (prefetch distance RD - 1 MFMAs)
     const int s0 = ti * BNK;
     GroupDesc gd;
@@ -469,7 +479,7 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const TileDesc td, c
 
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
     const int c = l & 31, hh = l >> 5, j = l & 15, c16 = (l >> 4) & 1;
-    const int kb = w & 3, qh = w >> 2;
+    const int kb = NW == 8 ? w & 3 : (w + ti) & 3, qh = w >> 2;
 
     // this lane's key (a column of S) and the rows [s, e_s) that may see it
     const int s = s0 + 32 * kb + c;
@@ -496,19 +506,46 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const TileDesc td, c
     const int64_t q_stride = (int64_t)a.Hq * 128;
     const int64_t kv_stride = (int64_t)a.Hkv * 128;
 
+    bf16x8 kreg[8];                                   // NW = 4 only
     // K/V of the tile -> LDS (64 chunks of 4 rows; 8 per wave).  Keys past the group's end
     // re-read its last row; such lanes are masked everywhere (e_s = 0).
     {
         const __bf16* kb_ = a.k + ((int64_t)gd.tok_base * a.Hkv + kvh) * 128;
         const __bf16* vb_ = a.v + ((int64_t)gd.tok_base * a.Hkv + kvh) * 128;
+        if constexpr (!K_REG) {
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int ci = w * 8 + u;                  // 0..31 K, 32..63 V
-            const int row = 4 * (ci & 31) + (l >> 4);
-            const int gran = (l & 15) ^ swz(row);
-            const int sk = min(s0 + row, Tg - 1);
-            const __bf16* src = (ci < 32 ? kb_ : vb_) + (int64_t)sk * kv_stride + gran * 8;
-            async_copy16(src, &dkdv_ldsKV[ci >> 5][(ci & 31) * 1024]);
+            for (int u = 0; u < 8; ++u) {
+                const int ci = w * 8 + u;              // 0..31 K, 32..63 V
+                const int row = 4 * (ci & 31) + (l >> 4);
+                const int gran = (l & 15) ^ swz(row);
+                const int sk = min(s0 + row, Tg - 1);
+                const __bf16* src = (ci < 32 ? kb_ : vb_) + (int64_t)sk * kv_stride + gran * 8;
+                async_copy16(src, &dkdv_ldsKV[ci * 1024]);
+            }
+        } else {
+            // this wave's 32 rows of V, then of K, row-contiguous through its quarter of the Q/dO buffers and from
+            // there in operand layout to their place
+            char* const stg = &dkdv_lds[0][0] + 8192 * w;
+#pragma unroll
+            for (int which = 0; which < 2; ++which) {
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int row = 4 * u + (l >> 4);
+                    const int sk = min(ws0 + row, Tg - 1);
+                    async_copy16((which == 0 ? vb_ : kb_) + (int64_t)sk * kv_stride + ((l & 15) ^ swz(row)) * 8, stg + 1024 * u);
+                }
+                wait_vm0();
+                asm volatile("" ::: "memory");
+#pragma unroll
+                for (int ks = 0; ks < 8; ++ks) {
+                    const bf16x8 x = lds_read_row8(stg, c, 2 * ks + hh);
+                    if (which == 0) *reinterpret_cast<bf16x8*>(&dkdv_ldsKV[1024 * (8 * w + ks) + 16 * l]) = x;
+                    else kreg[ks] = x;
+                }
+                __builtin_amdgcn_s_waitcnt(0xC07F);    // lgkmcnt(0): the buffers may be overwritten
+                asm volatile("" ::: "memory");
+            }
+            __syncthreads();
         }
     }
     // Row tiles are walked from the LAST one down to the workgroup's own keys: workgroups that
@@ -521,10 +558,10 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const TileDesc td, c
     // wave that queues more than a few of them stalls at issue, so all eight waves share them.)
     // Rows past the group's end re-read its last row; they are masked (t < e_s <= Tg fails).
     const unsigned qstride_b = (unsigned)(q_stride * 2);
-    unsigned voff[2];
+    unsigned voff[CH];
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-        const int row = 4 * (2 * w + u) + (l >> 4);
+    for (int u = 0; u < CH; ++u) {
+        const int row = 4 * (CH * w + u) + (l >> 4);
         voff[u] = row * qstride_b + (((l & 15) ^ swz(row)) << 4);
     }
     auto sgpr64 = [](const void* p) -> uint64_t {
@@ -539,27 +576,34 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const TileDesc td, c
     const int head0 = kvh * rep_all + hr_only;          // first q head this workgroup walks
     const uint64_t qbase_s = sgpr64(a.q + ((int64_t)gd.tok_base * a.Hq + head0) * 128);
     const uint64_t gbase_s = sgpr64(a.d_o + ((int64_t)gd.tok_base * a.Hq + head0) * 128);
-    const unsigned m0buf[2] = {lds_u32(dkdv_lds[0]) + 2048u * w, lds_u32(dkdv_lds[1]) + 2048u * w};
+    const unsigned m0buf[2] = {lds_u32(dkdv_lds[0]) + 1024u * CH * w, lds_u32(dkdv_lds[1]) + 1024u * CH * w};
     const unsigned tile_bytes = BQ * qstride_b;
     auto issue_tile = [&](int qt, int hr, int buf) {
         const uint64_t off = (uint64_t)(unsigned)qt * tile_bytes + (unsigned)hr * 256u;
         const unsigned m0 = m0buf[buf];
         if (qt * BQ + BQ <= Tg) {
 #pragma unroll
-            for (int u = 0; u < 2; ++u) async_copy16_sm(qbase_s + off, voff[u], m0 + 1024u * u);
+            for (int u = 0; u < CH; ++u) async_copy16_sm(qbase_s + off, voff[u], m0 + 1024u * u);
 #pragma unroll
-            for (int u = 0; u < 2; ++u) async_copy16_sm(gbase_s + off, voff[u], m0 + TILE_BYTES + 1024u * u);
+            for (int u = 0; u < CH; ++u) async_copy16_sm(gbase_s + off, voff[u], m0 + QT_BYTES + 1024u * u);
         } else {
             const int last = Tg - 1 - qt * BQ;
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int row = 4 * (2 * w + u) + (l >> 4);
+            for (int u = 0; u < CH; ++u) {
+                const int row = 4 * (CH * w + u) + (l >> 4);
                 const unsigned vo = min(row, last) * qstride_b + (((l & 15) ^ swz(row)) << 4);
                 async_copy16_sm(qbase_s + off, vo, m0 + 1024u * u);
-                async_copy16_sm(gbase_s + off, vo, m0 + TILE_BYTES + 1024u * u);
+                async_copy16_sm(gbase_s + off, vo, m0 + QT_BYTES + 1024u * u);
             }
         }
-        if (w < 2) {        // wave 0: -lse / scale of the 64 rows, wave 1: -D (the first wave of a SIMD has slack)
+        if constexpr (NW == 4) {      // wave 0: -lse / scale of the 32 rows in its low lanes, -D in its high lanes
+            if (w == 0) {
+                const int head = head0 + hr;
+                const int t = min(qt * BQ + c, Tg - 1);
+                const float* src = (hh == 0 ? a.nL : a.nD) + (int64_t)head * T_total + gd.tok_base + t;
+                async_copy4(src, reinterpret_cast<char*>(&dkdv_ldsLD[buf][0][0]));
+            }
+        } else if (w < 2) {        // wave 0: -lse / scale of the 64 rows, wave 1: -D (the first wave of a SIMD has slack)
             const int head = head0 + hr;
             const int t = min(qt * BQ + l, Tg - 1);
             const float* src = (w == 0 ? a.nL : a.nD) + (int64_t)head * T_total + gd.tok_base + t;
@@ -573,8 +617,27 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const TileDesc td, c
 #pragma unroll
         for (int r = 0; r < 16; ++r) { dkacc[db][r] = 0.f; dvacc[db][r] = 0.f; }
     const float cs = a.c_kv;
-    const char* ldsK = dkdv_ldsKV[0];
-    const char* ldsV = dkdv_ldsKV[1];
+    // LDS addresses of the operands within buffer 0, opaque so that they are kept as sums: row operands of Q (dO: + QT_BYTES),
+    // transposed operands of Q, rows + 8 part of the block's first 16 rows (last 16: + 4096, the swizzle repeats)
+    unsigned rowA[8], trA[4][2];
+    const unsigned lds0 = lds_u32(dkdv_lds[0]);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) { rowA[i] = lds0 + tile_off(32 * qh + c, 2 * i + hh); asm volatile("" : "+v"(rowA[i])); }
+#pragma unroll
+    for (int db = 0; db < 4; ++db)
+#pragma unroll
+        for (int part = 0; part < 2; ++part) {
+            const int col4 = 32 * db + 16 * c16 + 4 * (j & 3);
+            trA[db][part] = lds0 + tile_off(32 * qh + 4 * hh + (j >> 2) + 8 * part, col4 >> 3) + ((col4 & 4) << 1);
+            asm volatile("" : "+v"(trA[db][part]));
+        }
+    unsigned opB = lds_u32(dkdv_ldsKV) + (K_REG ? 8192 * w + 16 * l : 0);
+    asm volatile("" : "+v"(opB));
+    auto at_lds = [](unsigned addr) { return (lds_char*)(uintptr_t)addr; };
+    typedef __attribute__((address_space(3))) const bf16x8 lds_bf16x8;
+    typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+    const char* ldsK = dkdv_ldsKV;
+    const char* ldsV = dkdv_ldsKV + 128 * 256;
     typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
     // The products S and dP start from the row's plane values instead of zero: S accumulates on top of -lse / scale and dP
@@ -605,12 +668,11 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const TileDesc td, c
     int qt_n = qt, hr_n = 1;                  // step 1
     if (hr_n == rep) { hr_n = 0; --qt_n; }
     if (n_steps > 0) issue_tile(qt, hr, 0);
-    for (int it = 0; it < n_steps; ++it) {
-        const int buf = it & 1;
+    auto step = [&](const int it, auto buf_tag) {
+        constexpr int buf = decltype(buf_tag)::value;
         wait_vm0();
         __syncthreads();
-        const char* ldsQ = dkdv_lds[buf];
-        const char* ldsG = dkdv_lds[buf] + TILE_BYTES;
+        constexpr int offQ = buf * 2 * QT_BYTES, offG = offQ + QT_BYTES;
         const float* ldsL = dkdv_ldsLD[buf][0];
         const float* ldsD = dkdv_ldsLD[buf][1];
         const int r0 = qt * BQ + 32 * qh;              // this wave's 32 rows
@@ -626,23 +688,22 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const TileDesc td, c
         // an exposed LDS round trip).  Slice i: 0..7 S = Q K^T, 8..15 dP = dO V^T, 16..23 and 24..31 the dV / dK
         // updates for the first and the last 16 rows of the block (A operand only: P and dS are in registers).
         auto ldt = [&](int mm, int i, int part) {       // dV for even i, dK for odd i; db = i / 2
-            const int col4 = 32 * (i >> 1) + 16 * c16 + 4 * (j & 3);
-            const int row4 = 32 * qh + 16 * mm + 4 * hh + (j >> 2);
-            return lds_read_tr4((i & 1) ? ldsQ : ldsG, row4 + 8 * part, col4);
+            return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)at_lds(trA[i >> 1][part] + ((i & 1) ? offQ : offG) + 4096 * mm));
         };
         auto fetchA = [&](int i) -> bf16x8 {
-            if (i < 8) return lds_read_row8(ldsQ, 32 * qh + c, 2 * i + hh);
-            if (i < 16) return lds_read_row8(ldsG, 32 * qh + c, 2 * (i - 8) + hh);
+            if (i < 8) return *(lds_bf16x8*)at_lds(rowA[i] + offQ);
+            if (i < 16) return *(lds_bf16x8*)at_lds(rowA[i - 8] + offG);
             return cat4(ldt((i - 16) >> 3, i & 7, 0), ldt((i - 16) >> 3, i & 7, 1));
         };
-        auto fetchB = [&](int i) -> bf16x8 {
+        auto fetchB = [&](int i) -> bf16x8 {            // NW = 4: i >= 8 only
+            if (K_REG) return *(lds_bf16x8*)at_lds(opB + 1024 * (i & 7));
             return lds_read_row8(i < 8 ? ldsK : ldsV, 32 * kb + c, 2 * (i & 7) + hh);
         };
         bf16x8 ra[RD], rb[RD];
         auto advance = [&](int i) {                      // fetch the operands of slice i + RD - 1
             const int n = i + RD - 1;
             if (n < 32) ra[n % RD] = fetchA(n);
-            if (n < 16) rb[n % RD] = fetchB(n);
+            if (n < 16 && (n >= 8 || !K_REG)) rb[n % RD] = fetchB(n);
         };
         // rows of a plane in accumulator layout: the initial value of a product over this wave's 32 rows
         auto rows16 = [&](const float* plane, int gq, f32x16& acc) {
@@ -657,16 +718,16 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const TileDesc td, c
 #pragma unroll
             for (int gq = 0; gq < 4; ++gq) rows16(ldsL, gq, sacc);
 #pragma unroll
-            for (int i = 0; i < RD - 1; ++i) { ra[i] = fetchA(i); rb[i] = fetchB(i); }
+            for (int i = 0; i < RD - 1; ++i) { ra[i] = fetchA(i); if (!K_REG) rb[i] = fetchB(i); }
         }
         __builtin_amdgcn_sched_barrier(0);
         if (it + 1 < n_steps) issue_tile(qt_n_issue, hr_n_issue, buf ^ 1);
-        if (skip) continue;
+        if (skip) return;
 #pragma unroll
         for (int i = 0; i < 8; ++i) {       // S - lse / scale = Q K^T on top of the row's plane value
             advance(i);
             if (i >= 4) rows16(ldsD, i - 4, pacc);
-            sacc = mfma32(ra[i % RD], rb[i % RD], sacc);
+            sacc = mfma32(ra[i % RD], K_REG ? kreg[i] : rb[i % RD], sacc);
             __builtin_amdgcn_sched_barrier(0);
         }
         // every row of the half sees every key of the wave
@@ -732,21 +793,47 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const TileDesc td, c
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
+    };
+    // two steps a turn: the buffer is a constant of the code, and the LDS addresses need no arithmetic per step
+    for (int it = 0; it < n_steps; it += 2) {
+        step(it, std::integral_constant<int, 0>{});
+        if (it + 1 < n_steps) step(it + 1, std::integral_constant<int, 1>{});
     }
     };
     sweep(std::false_type{}, qt1, qt0);
     {   // the steps that can hold short rows: row tile 0 under a prompt of at least EDGE_LEN tokens, else all
-        const int f_hi = Lp >= EDGE_LEN ? min(qt1, 1) : qt1;
+        const int f_hi = Lp >= EDGE_LEN ? min(qt1, EDGE_LEN / BQ) : qt1;
         if (f_hi > qt0) {
             __syncthreads();                       // every wave has left the main sweep's last buffer
             sweep(std::true_type{}, f_hi, qt0);
         }
     }
 
+    const int64_t orow = ((int64_t)(gd.tok_base + (valid ? s : 0)) * a.Hkv + kvh) * 128 + 4 * hh;
+    if constexpr (NW == 4) {
+        if (!valid) return;
+#pragma unroll
+        for (int pass = 0; pass < 2; ++pass) {
+            const f32x16* acc = pass == 0 ? dkacc : dvacc;
+            __bf16* out = pass == 0 ? a.dk : a.dv;
+            const float mul = pass == 0 ? a.scale : 1.0f;
+#pragma unroll
+            for (int db = 0; db < 4; ++db)
+#pragma unroll
+                for (int gq = 0; gq < 4; ++gq) {
+                    bf16x4 x;
+                    bf16x4 old = {0, 0, 0, 0};
+                    if (a.accumulate) old = *reinterpret_cast<const bf16x4*>(out + orow + 32 * db + 8 * gq);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) x[e] = (__bf16)(acc[db][4 * gq + e] * mul + (float)old[e]);
+                    *reinterpret_cast<bf16x4*>(out + orow + 32 * db + 8 * gq) = x;
+                }
+        }
+        return;
+    }
     // add the two row halves: waves 4..7 park their partial sums in LDS (the Q/dO buffers,
     // 16 KB per wave), waves 0..3 add them and write the result.  dK first, then dV.
     float* xch = reinterpret_cast<float*>(&dkdv_lds[0][0]) + (size_t)kb * 4096 + l * 4;
-    const int64_t orow = ((int64_t)(gd.tok_base + (valid ? s : 0)) * a.Hkv + kvh) * 128 + 4 * hh;
 #pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
         f32x16* acc = pass == 0 ? dkacc : dvacc;
@@ -787,7 +874,8 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const TileDesc td, c
     }
 }
 
-__global__ __launch_bounds__(512) void bwd_dkdv_kernel(BwdArgs a) {
+template <int NW>
+__global__ __launch_bounds__(64 * NW, 2) void bwd_dkdv_kernel(BwdArgs a) {
     int tile, kvh, hr_only = 0;
     if (a.head_split) {
         int head;
@@ -796,7 +884,7 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(BwdArgs a) {
         hr_only = head % (a.Hq / a.Hkv);
     } else if (!decode_item(blockIdx.x, a.n_tiles, a.Hkv, a.Hkv, tile, kvh)) return;
     // key tiles in ascending order: the first prompt tile is seen by every row (most work)
-    dkdv_body(a, a.sched.tiles128[tile], kvh, hr_only);
+    dkdv_body<NW>(a, a.sched.tiles128[tile], kvh, hr_only);
 }
 
 // Second stage of the head-split dkdv pass: dk = scale * sum_hr partial[0][hr], dv = sum_hr
@@ -866,13 +954,13 @@ hipError_t launch_bwd_bf16(const Problem& p, hipStream_t s) {
         a.partial = p.dkdv_partial;
         if (a.head_split) {
             const int grid = grid_for_items(a.n_tiles, p.Hq, p.Hkv);
-            hipLaunchKernelGGL(bwd_dkdv_kernel, dim3(grid), dim3(512), 0, s, a);
+            hipLaunchKernelGGL(bwd_dkdv_kernel<8>, dim3(grid), dim3(512), 0, s, a);
             const int64_t n4 = p.total_tokens * p.Hkv * 32;
             hipLaunchKernelGGL(dkdv_reduce_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, a.partial, a.dk, a.dv,
                                n4, p.Hq / p.Hkv, p.scale, a.accumulate);
         } else {
             const int grid = grid_for_items(a.n_tiles, p.Hkv, p.Hkv);
-            hipLaunchKernelGGL(bwd_dkdv_kernel, dim3(grid), dim3(512), 0, s, a);
+            hipLaunchKernelGGL(bwd_dkdv_kernel<4>, dim3(grid), dim3(256), 0, s, a);
         }
         e = hipGetLastError();
     }
