@@ -56,6 +56,12 @@ struct BwdArgs {
 // a tile (32 keys of K and V: 64 KB), one barrier per half, two workgroups per CU: for packings whose key
 // loops are short, where a workgroup's fixed costs (a quarter of its life with one workgroup per CU) then
 // overlap with the other workgroup's loop and fewer rows ride along through tiles they cannot see.
+// Bound: bf16 MFMA (24 per wave, 32 rows and 32 keys; 16 LDS reads and about 100 vector instructions beside them).  The
+// loop holds neither address arithmetic nor spills: a turn is a whole turn of the ring, so that slots are constants, the
+// operand addresses are whole sums in registers, the mask is a word of bits per lane, the operand ring runs through M
+// and D, and dP starts at -D.  One box, before -> after, us: 16K prompt with 32 answers 5440 -> 5190, four long prompts
+// 2750 -> 2515, 64 groups of a short prompt and 16 answers 3640 -> 3110, 64 groups of 1000 tokens 1100 -> 990, response
+// rows under an 8K prompt 630 -> 545.
 template <int NW>
 __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(BwdArgs a) {
     constexpr int BM = 32 * NW, BN = 64;
@@ -271,9 +277,13 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(BwdArgs a) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[db][r] = 0.f;
     const float cs = a.c;
-    float dsum = 0.f;      // sum over this lane's keys of P * dP: an O-free, fp32 evaluation of D
+    float dsum = 0.f;      // sum over this lane's keys of P (dP - D): what D lacks to an O-free, fp32 evaluation of it
     const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 
+    f32x16 nD16;           // dP accumulates on top of -D: dS = P acc, and sum P acc = sum P dP - D (sum P = 1)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) nD16[r] = -Dq;
+    asm volatile("" : "+v"(nD16));
     // Work is cut into halves of 32 keys (two per 64-key tile).  For half h a wave runs
     //   M(h): S^T, dP^T of the half (16 MFMAs);  V(h): P^T = exp2(S^T c - L), dS^T = P^T (dP^T - D)
     //   (16 elements of vector work);  D(h): dQ^T += K^T dS^T (8 MFMAs),
@@ -281,33 +291,44 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(BwdArgs a) {
     // V(h) is spread over the slices of D(h-1) (its first NE1 elements) and M(h+1) (the rest).
     // Each slice is {LDS read for the MFMA RD-1 ahead, one MFMA, a piece of vector work}, fenced.
     // Masking is done beforehand on S (masked score = -inf gives P = 0 and dS = 0), so the
-    // pipeline body is the same for every tile; the half past the last one is masked whole.
+    // pipeline body is the same for every tile; what the last stage computes of the half past the last one is
+    // not used.
     const int H = 2 * total;
     auto s0_of = [&](int h) { return tile_at(h >> 1) * BN + 32 * (h & 1); };
     auto needs_mask = [&](int h) -> bool {
-        if (h >= H || !wave_valid) return true;
+        if (h >= H) return false;
+        if (!wave_valid) return true;
         const int s0 = s0_of(h);
         return !((s0 + 31 <= tw0) && (s0 + 32 <= Lp || s0 >= st_last));
     };
-    auto mask = [&](int h, f32x16& S, f32x16& P) {
-        const bool none = h >= H;
-        const int s0 = none ? 0 : s0_of(h);
+    auto mask = [&](int h, f32x16& S) {
+        const int s0 = s0_of(h);
+        mask16(S, (low_bits(min(Lp, tm + 1) - s0) | (low_bits(tm + 1 - s0) & ~low_bits(st - s0))) >> (4 * hh));
+    };
+    // LDS addresses of the operands within slot 0, opaque so that they are kept as whole sums (see the dkdv pass); `at`
+    // = the slot's and the half's offset, a constant of the code
+    unsigned rowA[8], trA[4][2];
+    {
+        const unsigned lds0 = lds_u32(&lds[0][0]);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int key = s0 + 8 * (r >> 2) + 4 * hh + (r & 3);
-            const bool ok = !none && key <= tm && (key < Lp || key >= st);
-            S[r] = ok ? S[r] : -INFINITY;
-            P[r] = none ? 0.f : P[r];
-        }
+        for (int i = 0; i < 8; ++i) { rowA[i] = lds0 + tile_off(c, 2 * i + hh); asm volatile("" : "+v"(rowA[i])); }
+#pragma unroll
+        for (int db = 0; db < 4; ++db)
+#pragma unroll
+            for (int part = 0; part < 2; ++part) {
+                const int col4 = 32 * db + 16 * c16 + 4 * (j & 3);
+                trA[db][part] = lds0 + tile_off(4 * hh + (j >> 2) + 8 * part, col4 >> 3) + ((col4 & 4) << 1);
+                asm volatile("" : "+v"(trA[db][part]));
+            }
+    }
+    // operand of slice i of a stage: 0..15 those of M, K rows then V rows; 16..23 those of D, slice 16 + i of D: db = i / 2,
+    // 16-key step i % 2 (read transposed).  They pass through one ring of RD registers, read RD - 1 slices ahead.
+    auto fetch = [&](int atM, int atD, int i) -> bf16x8 {
+        if (i < 16) return lds_at_row8(rowA[i & 7] + atM + ((i & 8) ? V_OFF : 0));
+        const int n = i - 16, at = atD + 4096 * (n & 1);
+        return cat4(lds_at_tr4(trA[n >> 1][0] + at), lds_at_tr4(trA[n >> 1][1] + at));
     };
-    auto ldm = [&](const char* slot, int half, int i) {      // operand i of M: K rows for i < 8 (S), V rows after (dP)
-        return lds_read_row8(slot + ((i & 8) ? V_OFF : 0), 32 * half + c, 2 * (i & 7) + hh);
-    };
-    auto ldd = [&](const char* slot, int half, int i, int part) {   // MFMA i of D: db = i / 2, 16-key step mm = i % 2
-        const int col4 = 32 * (i >> 1) + 16 * c16 + 4 * (j & 3);
-        const int row4 = 32 * half + 16 * (i & 1) + 4 * hh + (j >> 2);
-        return lds_read_tr4(slot, row4 + 8 * part, col4);
-    };
+    bf16x8 ring[RD];
     auto pack2 = [&](float x, float y) -> unsigned {
         typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
         bf16x2 v = {(__bf16)x, (__bf16)y};
@@ -321,62 +342,55 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(BwdArgs a) {
     };
     auto v_consume = [&](f32x16& S, f32x16& P, int r, float p) {
         dsum = __builtin_fmaf(p, P[r], dsum);
-        S[r] = p * (P[r] - Dq);
+        S[r] = p * P[r];
         asm volatile("" : "+v"(dsum), "+v"(S[r]));
     };
     // One pipeline stage for half h: Sc/Pc hold S, dP of half h (elements < NE1 already turned
     // into dS), Sn/Pn receive half h+1.
     auto stage = [&](int h, f32x16& Sc, f32x16& Pc, f32x16& Sn, f32x16& Pn,
-                     const char* slotM, int halfM, const char* slotD, int halfD) {
+                     auto m_tag, auto d_tag, auto off_tag, auto next_tag) {
+        constexpr int atM = decltype(m_tag)::value, atD = decltype(d_tag)::value;
+        constexpr int OFF = decltype(off_tag)::value;       // ring position of this stage's first operand
         unsigned pk[8];
-        {   // M(h+1) with the rest of V(h)
-            bf16x8 ring[RD];
+        // M(h+1) with the rest of V(h)
 #pragma unroll
-            for (int i = 0; i < RD - 1; ++i) ring[i] = ldm(slotM, halfM, i);
-            __builtin_amdgcn_sched_barrier(0);
+        for (int i = 0; i < 16; ++i) {
+            ring[(i + RD - 1 + OFF) % RD] = fetch(atM, atD, i + RD - 1);
+            if (i & 8) Pn = mfma32(ring[(i + OFF) % RD], goreg[i & 7], i == 8 ? nD16 : Pn);
+            else Sn = mfma32(ring[(i + OFF) % RD], qreg[i & 7], i == 0 ? zero16 : Sn);
+            float tcur = 0.f;
+            if (NE1 + i < 16) { tcur = v_issue(Sc, NE1 + i); asm volatile("" : "+v"(tcur)); }
+            if (i >= 1 && NE1 + i - 1 < 16) v_consume(Sc, Pc, NE1 + i - 1, tprev);
+            tprev = tcur;
+            if (i >= 12) {
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                if (i + RD - 1 < 16) ring[(i + RD - 1) % RD] = ldm(slotM, halfM, i + RD - 1);
-                if (i & 8) Pn = mfma32(ring[i % RD], goreg[i & 7], i == 8 ? zero16 : Pn);
-                else Sn = mfma32(ring[i % RD], qreg[i & 7], i == 0 ? zero16 : Sn);
-                float tcur = 0.f;
-                if (NE1 + i < 16) { tcur = v_issue(Sc, NE1 + i); asm volatile("" : "+v"(tcur)); }
-                if (i >= 1 && NE1 + i - 1 < 16) v_consume(Sc, Pc, NE1 + i - 1, tprev);
-                tprev = tcur;
-                if (i >= 12) {
-#pragma unroll
-                    for (int q = 2 * (i - 12); q < 2 * (i - 12) + 2; ++q) {
-                        pk[q] = pack2(Sc[2 * q], Sc[2 * q + 1]);
-                        asm volatile("" : "+v"(pk[q]));
-                    }
+                for (int q = 2 * (i - 12); q < 2 * (i - 12) + 2; ++q) {
+                    pk[q] = pack2(Sc[2 * q], Sc[2 * q + 1]);
+                    asm volatile("" : "+v"(pk[q]));
                 }
-                __builtin_amdgcn_sched_barrier(0);
             }
+            __builtin_amdgcn_sched_barrier(0);
         }
-        if (needs_mask(h + 1)) mask(h + 1, Sn, Pn);
+        if (needs_mask(h + 1)) mask(h + 1, Sn);
+        const float dsum_h = dsum;
         __builtin_amdgcn_sched_barrier(0);
-        {   // D(h) with the first NE1 elements of V(h+1)
-            typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-            const bf16x8 db8[2] = {__builtin_bit_cast(bf16x8, u32x4{pk[0], pk[1], pk[2], pk[3]}),
-                                   __builtin_bit_cast(bf16x8, u32x4{pk[4], pk[5], pk[6], pk[7]})};
-            s16x4 ring[RD][2];
+        // D(h) with the first NE1 elements of V(h+1); the ring runs on into the next stage where its tile is resident (NEXT)
+        typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+        const bf16x8 db8[2] = {__builtin_bit_cast(bf16x8, u32x4{pk[0], pk[1], pk[2], pk[3]}),
+                               __builtin_bit_cast(bf16x8, u32x4{pk[4], pk[5], pk[6], pk[7]})};
+        constexpr int NEXT = decltype(next_tag)::value;
 #pragma unroll
-            for (int i = 0; i < RD - 1; ++i) { ring[i][0] = ldd(slotD, halfD, i, 0); ring[i][1] = ldd(slotD, halfD, i, 1); }
+        for (int i = 0; i < 8; ++i) {
+            if (i + RD - 1 < 8) ring[(16 + i + RD - 1 + OFF) % RD] = fetch(atM, atD, 16 + i + RD - 1);
+            else if (NEXT >= 0) ring[(16 + i + RD - 1 + OFF) % RD] = fetch(NEXT, 0, i + RD - 1 - 8);
+            acc[i >> 1] = mfma32(ring[(16 + i + OFF) % RD], db8[i & 1], acc[i >> 1]);
+            float tcur = 0.f;
+            if (i < NE1) { tcur = v_issue(Sn, i); asm volatile("" : "+v"(tcur)); }
+            if (i >= 1 && i - 1 < NE1) v_consume(Sn, Pn, i - 1, tprev);
+            tprev = tcur;
             __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                if (i + RD - 1 < 8) {
-                    ring[(i + RD - 1) % RD][0] = ldd(slotD, halfD, i + RD - 1, 0);
-                    ring[(i + RD - 1) % RD][1] = ldd(slotD, halfD, i + RD - 1, 1);
-                }
-                acc[i >> 1] = mfma32(cat4(ring[i % RD][0], ring[i % RD][1]), db8[i & 1], acc[i >> 1]);
-                float tcur = 0.f;
-                if (i < NE1) { tcur = v_issue(Sn, i); asm volatile("" : "+v"(tcur)); }
-                if (i >= 1 && i - 1 < NE1) v_consume(Sn, Pn, i - 1, tprev);
-                tprev = tcur;
-                __builtin_amdgcn_sched_barrier(0);
-            }
         }
+        if (h + 1 >= H) dsum = dsum_h;          // the half past the last one (stale LDS) contributes to nothing
     };
 
     f32x16 SA, PA, SB, PB;
@@ -389,21 +403,37 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(BwdArgs a) {
         // M(0) and the first NE1 elements of V(0), unpipelined
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-            if (i & 8) PA = mfma32(ldm(lds[0], 0, i), goreg[i & 7], i == 8 ? zero16 : PA);
-            else SA = mfma32(ldm(lds[0], 0, i), qreg[i & 7], i == 0 ? zero16 : SA);
+            if (i & 8) PA = mfma32(fetch(0, 0, i), goreg[i & 7], i == 8 ? nD16 : PA);
+            else SA = mfma32(fetch(0, 0, i), qreg[i & 7], i == 0 ? zero16 : SA);
         }
-        if (needs_mask(0)) mask(0, SA, PA);
+        if (needs_mask(0)) mask(0, SA);
 #pragma unroll
         for (int r = 0; r < NE1; ++r) v_consume(SA, PA, r, v_issue(SA, r));
+        // the first operands of a stage behind a barrier are fetched ahead of the issue of the next copies
+        auto prime = [&](int atM) {
+#pragma unroll
+            for (int i = 0; i < RD - 1; ++i) ring[i] = fetch(atM, 0, i);
+            __builtin_amdgcn_sched_barrier(0);
+        };
         if constexpr (NW == 8) {
-        int slot = 0;
-        for (int it = 0; it < total; ++it) {
-            const int slot1 = slot == 2 ? 0 : slot + 1, slot2 = slot == 0 ? 2 : slot - 1;
+        // tile `it` lives in slot it % 3; a turn of the loop is a turn of the ring
+        auto tile_stages = [&](int it, auto slot_tag) {
+            constexpr int S = decltype(slot_tag)::value, S1 = (S + 1) % 3, S2 = (S + 2) % 3, HALF = 32 * 256;
+            constexpr int A0 = S * SLOT_BYTES, A1 = A0 + HALF, A2 = S1 * SLOT_BYTES;       // halves 2 it, 2 it + 1, 2 it + 2
             if (it > 0) { wait_vm0(); __syncthreads(); }
-            issue(it + 2, slot2);           // into the slot of tile it-1, which every wave has left
-            stage(2 * it, SA, PA, SB, PB, lds[slot], 1, lds[slot], 0);
-            stage(2 * it + 1, SB, PB, SA, PA, lds[slot1], 0, lds[slot], 1);
-            slot = slot1;
+            prime(A1);
+            issue(it + 2, S2);              // into the slot of tile it-1, which every wave has left
+            stage(2 * it, SA, PA, SB, PB, std::integral_constant<int, A1>{}, std::integral_constant<int, A0>{},
+                  std::integral_constant<int, 0>{}, std::integral_constant<int, A2>{});
+            stage(2 * it + 1, SB, PB, SA, PA, std::integral_constant<int, A2>{}, std::integral_constant<int, A1>{},
+                  std::integral_constant<int, 24 % RD>{}, std::integral_constant<int, -1>{});
+        };
+        for (int it = 0; it < total; it += 3) {
+            tile_stages(it, std::integral_constant<int, 0>{});
+            if (it + 1 >= total) break;
+            tile_stages(it + 1, std::integral_constant<int, 1>{});
+            if (it + 2 >= total) break;
+            tile_stages(it + 2, std::integral_constant<int, 2>{});
         }
         } else {
         // Half h lives in slot h % 4.  Stage h reads the slots of h + 1 (M) and h (D); at the barrier in
@@ -411,23 +441,29 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(BwdArgs a) {
         // which is issued then: two stages ahead of the M that needs it.
         // (Leaving the half issued at the previous barrier in flight across the barrier, vmcnt(4) instead of
         // vmcnt(0), measured the same: the other workgroup of the CU covers the wait.)
-        for (int h = 0; h < H; h += 2) {
+        auto half_stage = [&](int h, auto slot_tag, f32x16& Sc, f32x16& Pc, f32x16& Sn, f32x16& Pn) {
+            constexpr int S = decltype(slot_tag)::value, A0 = S * SLOT_BYTES, A1 = ((S + 1) & 3) * SLOT_BYTES;
             if (h > 0) { wait_vm0(); __syncthreads(); }
-            issue(h + 3, (h + 3) & 3);
-            stage(h, SA, PA, SB, PB, lds[(h + 1) & 3], 0, lds[h & 3], 0);
-            wait_vm0();
-            __syncthreads();
-            issue(h + 4, h & 3);
-            stage(h + 1, SB, PB, SA, PA, lds[(h + 2) & 3], 0, lds[(h + 1) & 3], 0);
+            prime(A1);
+            issue(h + 3, (S + 3) & 3);
+            stage(h, Sc, Pc, Sn, Pn, std::integral_constant<int, A1>{}, std::integral_constant<int, A0>{},
+                  std::integral_constant<int, 0>{}, std::integral_constant<int, -1>{});
+        };
+        for (int h = 0; h < H; h += 4) {
+            half_stage(h, std::integral_constant<int, 0>{}, SA, PA, SB, PB);
+            half_stage(h + 1, std::integral_constant<int, 1>{}, SB, PB, SA, PA);
+            if (h + 2 >= H) break;
+            half_stage(h + 2, std::integral_constant<int, 2>{}, SA, PA, SB, PB);
+            half_stage(h + 3, std::integral_constant<int, 3>{}, SB, PB, SA, PA);
         }
         }
     }
 
-    // D = sum_s P dP equals rowsum(dO * O) exactly, but does not inherit the bf16 rounding of O.
+    // D + sum_s P (dP - D) = sum_s P dP equals rowsum(dO * O) exactly, but does not inherit the bf16 rounding of O.
     // Publish it for the dkdv pass (this workgroup owns these rows of D, so overwriting is safe).
     dsum = pair_sum(dsum);
     const bool store = valid && !(a.resp_only && t < Lp);
-    if (store && hh == 0) a.nD[(int64_t)head * T_total + gd.tok_base + t] = -dsum;
+    if (store && hh == 0) a.nD[(int64_t)head * T_total + gd.tok_base + t] = -(Dq + dsum);
     // rows that see at most EDGE_LEN keys are written by the edge kernel (fp32 dS): not stored here
     const bool short_row = (t < Lp ? 0 : Lp) + t - st + 1 <= EDGE_LEN;
     if (store && !short_row) {
@@ -633,9 +669,6 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const TileDesc td, c
         }
     unsigned opB = lds_u32(dkdv_ldsKV) + (K_REG ? 8192 * w + 16 * l : 0);
     asm volatile("" : "+v"(opB));
-    auto at_lds = [](unsigned addr) { return (lds_char*)(uintptr_t)addr; };
-    typedef __attribute__((address_space(3))) const bf16x8 lds_bf16x8;
-    typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
     const char* ldsK = dkdv_ldsKV;
     const char* ldsV = dkdv_ldsKV + 128 * 256;
     typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
@@ -688,15 +721,15 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const TileDesc td, c
         // an exposed LDS round trip).  Slice i: 0..7 S = Q K^T, 8..15 dP = dO V^T, 16..23 and 24..31 the dV / dK
         // updates for the first and the last 16 rows of the block (A operand only: P and dS are in registers).
         auto ldt = [&](int mm, int i, int part) {       // dV for even i, dK for odd i; db = i / 2
-            return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)at_lds(trA[i >> 1][part] + ((i & 1) ? offQ : offG) + 4096 * mm));
+            return lds_at_tr4(trA[i >> 1][part] + ((i & 1) ? offQ : offG) + 4096 * mm);
         };
         auto fetchA = [&](int i) -> bf16x8 {
-            if (i < 8) return *(lds_bf16x8*)at_lds(rowA[i] + offQ);
-            if (i < 16) return *(lds_bf16x8*)at_lds(rowA[i - 8] + offG);
+            if (i < 8) return lds_at_row8(rowA[i] + offQ);
+            if (i < 16) return lds_at_row8(rowA[i - 8] + offG);
             return cat4(ldt((i - 16) >> 3, i & 7, 0), ldt((i - 16) >> 3, i & 7, 1));
         };
         auto fetchB = [&](int i) -> bf16x8 {            // NW = 4: i >= 8 only
-            if (K_REG) return *(lds_bf16x8*)at_lds(opB + 1024 * (i & 7));
+            if (K_REG) return lds_at_row8(opB + 1024 * (i & 7));
             return lds_read_row8(i < 8 ? ldsK : ldsV, 32 * kb + c, 2 * (i & 7) + hh);
         };
         bf16x8 ra[RD], rb[RD];
@@ -732,13 +765,7 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const TileDesc td, c
         }
         // every row of the half sees every key of the wave
         const bool full = r0 >= max(ws1, row_lo) && ws0 + 31 < Tg && r0 + 32 <= e_min;
-        if (!full) {
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int t = r0 + 8 * (r >> 2) + 4 * hh + (r & 3);
-                sacc[r] = (t >= s_lo && t < e_s) ? sacc[r] : -INFINITY;
-            }
-        }
+        if (!full) mask16(sacc, (low_bits(e_s - r0) & ~low_bits(s_lo - r0)) >> (4 * hh));
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < 8; ++i) {       // dP - D = dO V^T on top of -D, with the exponentials of rows 0..7 of the block

@@ -240,6 +240,26 @@ __device__ __forceinline__ s16x4 lds_read_tr4(const char* tile, int row, int col
         (__attribute__((address_space(3))) s16x4*)(p));
 }
 
+// The same two reads at an LDS byte address
+__device__ __forceinline__ bf16x8 lds_at_row8(unsigned addr) {
+    return *(__attribute__((address_space(3))) const bf16x8*)(uintptr_t)addr;
+}
+__device__ __forceinline__ s16x4 lds_at_tr4(unsigned addr) {
+    return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(uintptr_t)addr);
+}
+
+// the n lowest bits set (none for n <= 0, all from 32 on)
+__device__ __forceinline__ unsigned low_bits(int n) { return n <= 0 ? 0u : 0xffffffffu >> (32 - min(n, 32)); }
+// Masks a 32 x 32 score block: S[r], of row (or key) 8 (r / 4) + 4 (lane / 32) + r % 4 of the block, becomes -inf unless
+// bit 8 (r / 4) + r % 4 of `bits` is set.  Two instructions per score; comparing each index took five, or a branch.
+__device__ __forceinline__ void mask16(f32x16& S, unsigned bits) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const unsigned keep = (unsigned)__builtin_amdgcn_sbfe((int)bits, 8 * (r >> 2) + (r & 3), 1);
+        S[r] = __uint_as_float((__float_as_uint(S[r]) & keep) | (0xff800000u & ~keep));
+    }
+}
+
 __device__ __forceinline__ bf16x8 cat4(s16x4 a, s16x4 b) {
     s16x8 r = __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
     return __builtin_bit_cast(bf16x8, r);
