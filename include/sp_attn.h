@@ -226,6 +226,7 @@ sp_status sp_attn_bwd_batched_static(const void* q, const void* k, const void* v
  *          to the backward makes D use o + o_lo.  bf16 only (SP_ERR_UNSUPPORTED with SP_F32). */
 #define SP_FLAG_RESPONSE_ROWS   1u
 #define SP_FLAG_ACCUMULATE_DKDV 2u
+#define SP_FLAG_ZERO_PROMPT_ROWS 4u        /* sp_attn_logprob_bwd_ex only */
 sp_status sp_attn_fwd_batched_ex(const void* q, const void* k, const void* v, void* o, float* lse,
                                  int32_t n_groups, const int32_t* prompt_lens,
                                  const int32_t* Gs, const int32_t* resp_lens_flat,
@@ -312,6 +313,9 @@ sp_status sp_attn_rope_qk(const void* q, void* q_out, int32_t n_q_heads,
  * sp_attn_logprob_bwd   dlogits[t, v] = g[t] * (1[v == labels[t]] - exp(logits[t, v] - lse[t]))
  *     g  DEVICE fp32 [T_total] = dL/dlogp;  dlogits  DEVICE [T_total, vocab], dtype elements
  *     (may not alias logits)
+ * sp_attn_logprob_bwd_ex  the same with a flags word: SP_FLAG_ZERO_PROMPT_ROWS sets the prompt rows of dlogits to
+ *                       zero in the same launch (a caller's fill of the whole tensor would write the response
+ *                       rows twice).  Other bits: SP_ERR_INVALID_ARG.
  * sp_attn_grpo_loss     loss = -1/R sum_k (L_k - beta D_k) over the R non-empty responses, with one
  *                       advantage A_k per response (adv: DEVICE fp32 [total_responses], responses in
  *                       packing order over all groups), |o_k| its token count and, per token,
@@ -329,6 +333,11 @@ sp_status sp_attn_logprob_bwd(const void* logits, const int32_t* labels, const f
                               const float* g, void* dlogits, int64_t vocab,
                               int32_t n_groups, const int32_t* prompt_lens,
                               const int32_t* Gs, const int32_t* resp_lens_flat, sp_dtype dtype,
+                              void* workspace, size_t workspace_bytes, void* stream);
+sp_status sp_attn_logprob_bwd_ex(const void* logits, const int32_t* labels, const float* lse,
+                              const float* g, void* dlogits, int64_t vocab,
+                              int32_t n_groups, const int32_t* prompt_lens,
+                              const int32_t* Gs, const int32_t* resp_lens_flat, sp_dtype dtype, uint32_t flags,
                               void* workspace, size_t workspace_bytes, void* stream);
 sp_status sp_attn_grpo_loss(const float* logp, const float* logp_old, const float* logp_ref,
                             const float* adv, float eps_low, float eps_high, float beta,

@@ -19,11 +19,11 @@ SP_BF16, SP_F32 = 0, 1
 SP_SCHED_SHARED, SP_SCHED_NAIVE_CAUSAL = 0, 1
 
 SP_BWD_STAGE_ROWSUM, SP_BWD_STAGE_DKDV, SP_BWD_STAGE_DQ, SP_BWD_STAGE_ALL = 1, 2, 4, 7
-SP_FLAG_RESPONSE_ROWS, SP_FLAG_ACCUMULATE_DKDV = 1, 2
+SP_FLAG_RESPONSE_ROWS, SP_FLAG_ACCUMULATE_DKDV, SP_FLAG_ZERO_PROMPT_ROWS = 1, 2, 4
 
 EXPORTS = ("sp_attn_workspace_bytes", "sp_attn_reserve_bytes", "sp_attn_fwd", "sp_attn_bwd", "sp_attn_fwd_batched",
            "sp_attn_bwd_batched", "sp_attn_bwd_batched_static", "sp_attn_bwd_batched_stages", "sp_attn_fwd_multi", "sp_attn_rope", "sp_attn_rope_qk", "sp_attn_fwd_batched_ex", "sp_attn_bwd_batched_ex",
-           "sp_attn_loss_workspace_bytes", "sp_attn_logprob_fwd", "sp_attn_logprob_bwd", "sp_attn_grpo_loss",
+           "sp_attn_loss_workspace_bytes", "sp_attn_logprob_fwd", "sp_attn_logprob_bwd", "sp_attn_logprob_bwd_ex", "sp_attn_grpo_loss",
            "sp_attn_segment_table", "sp_attn_row_tile", "sp_attn_mfma_ceiling", "sp_attn_probe_atomic_add", "sp_attn_set_small_shape_steps", "sp_attn_last_error", "sp_attn_version")
 
 _lib = None
@@ -83,6 +83,8 @@ def load_library() -> ctypes.CDLL:
     lib.sp_attn_logprob_fwd.argtypes = [vp, vp, vp, vp, i64, i32, ip, ip, ip, ctypes.c_int, vp, sz, vp]
     lib.sp_attn_logprob_bwd.restype = ctypes.c_int
     lib.sp_attn_logprob_bwd.argtypes = [vp, vp, vp, vp, vp, i64, i32, ip, ip, ip, ctypes.c_int, vp, sz, vp]
+    lib.sp_attn_logprob_bwd_ex.restype = ctypes.c_int
+    lib.sp_attn_logprob_bwd_ex.argtypes = [vp, vp, vp, vp, vp, i64, i32, ip, ip, ip, ctypes.c_int, ctypes.c_uint32, vp, sz, vp]
     lib.sp_attn_grpo_loss.restype = ctypes.c_int
     lib.sp_attn_grpo_loss.argtypes = [vp, vp, vp, vp, f32, f32, f32, vp, vp, i32, ip, ip, ip, vp, sz, vp]
     lib.sp_attn_rope.restype = ctypes.c_int
@@ -314,12 +316,18 @@ def sp_attn_logprob_bwd(logits, labels, lse, g, prompt_lens: Sequence[int], Gs: 
                         resp_lens_flat: Sequence[int], dlogits=None, workspace=None, stream=None):
     lib = load_library()
     T, V = logits.shape
-    dlogits = torch.zeros_like(logits) if dlogits is None else dlogits
+    flags = 0
+    if dlogits is None:
+        # the launch itself zeroes the prompt rows when it covers every row of the tensor
+        if logits.is_contiguous() and T == sum(prompt_lens) + sum(resp_lens_flat):
+            dlogits, flags = torch.empty_like(logits), SP_FLAG_ZERO_PROMPT_ROWS
+        else:
+            dlogits = torch.zeros_like(logits)
     workspace = _loss_ws(T, len(prompt_lens), len(resp_lens_flat), logits.device, workspace)
-    _check(lib.sp_attn_logprob_bwd(logits.data_ptr(), labels.data_ptr(), lse.data_ptr(), g.data_ptr(),
-                                   dlogits.data_ptr(), V, len(prompt_lens), _i32(prompt_lens), _i32(Gs),
-                                   _i32(resp_lens_flat), _dtype_code(logits), workspace.data_ptr(), workspace.numel(),
-                                   _stream_ptr(stream)))
+    _check(lib.sp_attn_logprob_bwd_ex(logits.data_ptr(), labels.data_ptr(), lse.data_ptr(), g.data_ptr(),
+                                      dlogits.data_ptr(), V, len(prompt_lens), _i32(prompt_lens), _i32(Gs),
+                                      _i32(resp_lens_flat), _dtype_code(logits), flags, workspace.data_ptr(),
+                                      workspace.numel(), _stream_ptr(stream)))
     return dlogits
 
 

@@ -473,7 +473,16 @@ sp_status sp_attn_logprob_bwd(const void* logits, const int32_t* labels, const f
                               void* dlogits, int64_t vocab, int32_t n_groups, const int32_t* prompt_lens,
                               const int32_t* Gs, const int32_t* resp_lens_flat, sp_dtype dtype, void* workspace,
                               size_t workspace_bytes, void* stream) {
+    return sp_attn_logprob_bwd_ex(logits, labels, lse, g, dlogits, vocab, n_groups, prompt_lens, Gs, resp_lens_flat, dtype, 0u,
+                                  workspace, workspace_bytes, stream);
+}
+
+sp_status sp_attn_logprob_bwd_ex(const void* logits, const int32_t* labels, const float* lse, const float* g,
+                                 void* dlogits, int64_t vocab, int32_t n_groups, const int32_t* prompt_lens,
+                                 const int32_t* Gs, const int32_t* resp_lens_flat, sp_dtype dtype, uint32_t flags,
+                                 void* workspace, size_t workspace_bytes, void* stream) {
     g_err[0] = 0;
+    if (flags & ~SP_FLAG_ZERO_PROMPT_ROWS) return fail(SP_ERR_INVALID_ARG, "unknown flags 0x%x", flags);
     if (!logits || !labels || !lse || !g || !dlogits) return fail(SP_ERR_INVALID_ARG, "a pointer is NULL");
     if (misaligned(logits) || misaligned(dlogits)) return fail(SP_ERR_INVALID_ARG, "tensor pointer is not 16-byte aligned");
     if (vocab < 1) return fail(SP_ERR_INVALID_ARG, "vocab=%lld", (long long)vocab);
@@ -482,7 +491,7 @@ sp_status sp_attn_logprob_bwd(const void* logits, const int32_t* labels, const f
     sp_status st = loss_setup(n_groups, prompt_lens, Gs, resp_lens_flat, workspace, workspace_bytes, (hipStream_t)stream, L, &scratch);
     if (st != SP_OK) return st;
     hipError_t e = sp::launch_logprob_bwd(logits, labels, lse, g, dlogits, table_of(workspace), L.total_tokens, vocab,
-                                          dtype == SP_F32, (hipStream_t)stream);
+                                          dtype == SP_F32, (flags & SP_FLAG_ZERO_PROMPT_ROWS) != 0, (hipStream_t)stream);
     if (e != hipSuccess) return fail(SP_ERR_DEVICE, "HIP launch failed: %s", hipGetErrorString(e));
     return SP_OK;
 }

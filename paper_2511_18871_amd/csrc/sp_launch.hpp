@@ -71,7 +71,7 @@ hipError_t launch_rope(const void* x, void* y, int H, const void* x2, void* y2, 
 hipError_t launch_logprob_fwd(const void* z, const int* y, float* logp, float* lse, const int* tab,
                               int64_t total_tokens, int64_t V, bool f32, hipStream_t s);
 hipError_t launch_logprob_bwd(const void* z, const int* y, const float* lse, const float* g, void* dz,
-                              const int* tab, int64_t total_tokens, int64_t V, bool f32, hipStream_t s);
+                              const int* tab, int64_t total_tokens, int64_t V, bool f32, bool zero_prompt, hipStream_t s);
 hipError_t launch_grpo(const float* logp, const float* old, const float* ref, const float* adv, float* g,
                        float* J, float* loss, const int* tab, int n_resp, int n_nonempty, float eps_low,
                        float eps_high, float beta, hipStream_t s);
