@@ -16,6 +16,7 @@
 // neither pass exchanges dS between lanes or accumulates through memory.
 #include "sp_common.hpp"
 #include "sp_launch.hpp"
+#include "sp_edge.hpp"
 #include <type_traits>
 
 namespace sp {
@@ -63,7 +64,7 @@ struct BwdArgs {
 // 2750 -> 2515, 64 groups of a short prompt and 16 answers 3640 -> 3110, 64 groups of 1000 tokens 1100 -> 990, response
 // rows under an 8K prompt 630 -> 545.
 template <int NW>
-__global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(BwdArgs a) {
+__global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(BwdArgs a, EdgeArgs edge, int short_blocks, int row_blocks) {
     constexpr int BM = 32 * NW, BN = 64;
     constexpr int RD = 3;                       // LDS operand ring depth (prefetch distance RD - 1 MFMAs)
     constexpr int NE1 = 5;                      // elements of a half's vector work done under the previous D stage
@@ -73,8 +74,24 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(BwdArgs a) {
     constexpr int V_OFF = SLOT_BYTES / 2;                                    // where V starts inside a slot
     __shared__ __attribute__((aligned(1024))) char lds[NSLOT][SLOT_BYTES];
 
+    // Workgroups ahead of the row tiles' (a multiple of 8, so that those keep their XCDs) or, NW = 8, behind them: the rows
+    // that see at most EDGE_LEN keys, two waves per (segment, q head).  As a launch of their own they had the chip to
+    // themselves for 7 to 10 us of latency (37 us for 2048 pairs); beside row tiles, us for both, before -> after: two small
+    // groups 28.4 -> 21.2, one 1K prompt 93 -> 88, 64 groups of 1000 tokens 1048 -> 1034, four long prompts 2553 -> 2545,
+    // 16K prompt 5331 -> 5323 (ahead: 5350; the 64 groups behind: 1050).
+    constexpr int PAIRS = NW == 8 ? 3 : 2;          // that the LDS holds
+    static_assert(PAIRS * EDGE_LDS <= NSLOT * SLOT_BYTES && 2 * PAIRS <= NW, "short rows do not fit");
+    const int sb = (int)blockIdx.x - (NW == 8 ? row_blocks : 0), rb = (int)blockIdx.x - (NW == 8 ? 0 : short_blocks);
+    if (NW == 8 ? sb >= 0 : rb < 0) {
+        const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), i = min(w >> 1, PAIRS - 1);
+        for (int64_t p0 = (int64_t)PAIRS * sb; p0 < edge.n_pairs; p0 += (int64_t)PAIRS * short_blocks) {
+            short_rows_body<true>(edge, w < 2 * PAIRS ? p0 + i : edge.n_pairs, w & 1, &lds[0][0] + EDGE_LDS * i);
+            __syncthreads();
+        }
+        return;
+    }
     int tile, head;
-    if (!decode_item(blockIdx.x, a.n_tiles, a.Hq, a.Hkv, tile, head)) return;
+    if (!decode_item(rb, a.n_tiles, a.Hq, a.Hkv, tile, head)) return;
     const TileDesc td = (BM == 256 ? a.sched.tiles256 : a.sched.tiles128)[tile];
     GroupDesc gd;
     gd.tok_base = td.tok_base; gd.Lp = td.Lp; gd.Tg = td.Tg; gd.G = 0; gd.roff = nullptr;
@@ -463,10 +480,10 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(BwdArgs a) {
     // Publish it for the dkdv pass (this workgroup owns these rows of D, so overwriting is safe).
     dsum = pair_sum(dsum);
     const bool store = valid && !(a.resp_only && t < Lp);
-    if (store && hh == 0) a.nD[(int64_t)head * T_total + gd.tok_base + t] = -(Dq + dsum);
-    // rows that see at most EDGE_LEN keys are written by the edge kernel (fp32 dS): not stored here
+    // rows that see at most EDGE_LEN keys are written by the workgroups above (fp32 dS): not stored here
     const bool short_row = (t < Lp ? 0 : Lp) + t - st + 1 <= EDGE_LEN;
     if (store && !short_row) {
+        if (hh == 0) a.nD[(int64_t)head * T_total + gd.tok_base + t] = -(Dq + dsum);
         __bf16* op = a.dq + ((int64_t)(gd.tok_base + t) * a.Hq + head) * 128 + 4 * hh;
 #pragma unroll
         for (int db = 0; db < 4; ++db)
@@ -968,11 +985,11 @@ hipError_t launch_bwd_bf16(const Problem& p, hipStream_t s) {
         const bool small = use_small_shape(p);
         a.n_tiles = count_tiles(p, small ? 128 : 256);
         const int grid = grid_for_items(a.n_tiles, p.Hq, p.Hkv);
-        if (small) hipLaunchKernelGGL(bwd_dq_kernel<4>, dim3(grid), dim3(256), 0, s, a);
-        else hipLaunchKernelGGL(bwd_dq_kernel<8>, dim3(grid), dim3(512), 0, s, a);
+        const EdgeArgs edge = edge_args(p);
+        const int shorts = (edge_blocks(edge, small ? 2 : 3) + 7) & ~7, total = grid + shorts;
+        if (small) hipLaunchKernelGGL(bwd_dq_kernel<4>, dim3(total), dim3(256), 0, s, a, edge, shorts, grid);
+        else hipLaunchKernelGGL(bwd_dq_kernel<8>, dim3(total), dim3(512), 0, s, a, edge, shorts, grid);
         e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        e = launch_short_rows(p, true, s);
         if (e != hipSuccess) return e;
     }
     if (p.stages & STAGE_DKDV) {

@@ -460,8 +460,8 @@ hipError_t launch_rowsum(const Problem& p, bool f32, hipStream_t s) {
                                (const uint32_t*)nullptr, ninv);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        // exact D for the rows that see only a few keys (sp_edge.hip)
-        e = launch_short_rows(p, false, s);
+        // exact D for the rows that see only a few keys (sp_edge.hpp)
+        e = launch_short_rows(p, s);
         if (e != hipSuccess) return e;
     }
     else
