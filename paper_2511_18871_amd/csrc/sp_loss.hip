@@ -41,19 +41,14 @@ struct RowSplit {
     }
 };
 
-// Running (m, s): the sum of exponentials is s 2^r(m), m the largest element so far and r(m) = m log2(e) rounded; lse_of()
-// makes up for that rounding.  Where two r are subtracted, neither product may be fused with the subtraction.  M_FLOOR instead of -inf as the start, so that elements of -inf contribute 0.
-constexpr float M_FLOOR = -1.0e38f;
+// Running (m, s): the sum of exponentials is s e^m, m the largest element so far.  Differences are taken before they are
+// scaled, so that they are exact at any magnitude: scaled apart, the roundings of two products of 1e10 differ by powers of
+// two that overflow.  The lowest finite value instead of -inf as the start, so that elements of -inf contribute 0.
+constexpr float M_LOWEST = -3.402823466e38f;
 __device__ __forceinline__ void ms_merge(float& m, float& s, float m2, float s2) {
-#pragma clang fp contract(off)
     const float mn = fmaxf(m, m2);
-    s = s * __builtin_amdgcn_exp2f(m * LOG2E - mn * LOG2E) + s2 * __builtin_amdgcn_exp2f(m2 * LOG2E - mn * LOG2E);
+    s = s * __expf(m - mn) + s2 * __expf(m2 - mn);
     m = mn;
-}
-__device__ __forceinline__ float lse_of(float m, float s) {
-#pragma clang fp contract(off)
-    const float r = m * LOG2E;
-    return m + (__builtin_amdgcn_logf(s) - __builtin_fmaf(m, LOG2E, -r)) * LN2;
 }
 
 __device__ __forceinline__ void block_lse(float& m, float& s, float* sh) {
@@ -77,29 +72,28 @@ __global__ __launch_bounds__(LT) void logprob_fwd_kernel(const T* __restrict__ z
     const GroupDesc gd = load_group(tab, find_group_of_token(tab, tok));
     if (tok - gd.tok_base < gd.Lp) return;              // prompt row: discarded
     const T* row = z + tok * V;
-    float m = M_FLOOR, s = 0.f;
+    float m = M_LOWEST, s = 0.f;
     constexpr int N = Ld<T>::N;
     typedef typename Ld<T>::vec Vec;
     const RowSplit<T> rs(row, V);
     const Vec* rv = reinterpret_cast<const Vec*>(row + rs.head);
     auto add = [&](auto n_tag, const auto& x) {         // n vectors
-#pragma clang fp contract(off)
         constexpr int n = decltype(n_tag)::value;
         float mx = (float)x[0][0];
 #pragma unroll
         for (int u = 0; u < n; ++u)
 #pragma unroll
             for (int e = 0; e < N; ++e) mx = fmaxf(mx, (float)x[u][e]);
-        const float mn = fmaxf(m, mx), r = mn * LOG2E;
+        const float mn = fmaxf(m, mx);
         float acc = 0.f;
 #pragma unroll
         for (int u = 0; u < n; ++u) {
             float part = 0.f;
 #pragma unroll
-            for (int e = 0; e < N; ++e) part += __builtin_amdgcn_exp2f(__builtin_fmaf((float)x[u][e], LOG2E, -r));
+            for (int e = 0; e < N; ++e) part += __expf((float)x[u][e] - mn);
             acc += part;
         }
-        s = s * __builtin_amdgcn_exp2f(m * LOG2E - r) + acc;
+        s = s * __expf(m - mn) + acc;
         m = mn;
     };
     int64_t i = threadIdx.x;
@@ -124,7 +118,7 @@ __global__ __launch_bounds__(LT) void logprob_fwd_kernel(const T* __restrict__ z
     }
     block_lse(m, s, sh);
     if (threadIdx.x == 0) {
-        const float L = lse_of(m, s);
+        const float L = m + __logf(s);
         const int label = y[tok];
         lse[tok] = L;
         logp[tok] = (label >= 0 && label < V) ? (float)row[label] - L : -INFINITY;

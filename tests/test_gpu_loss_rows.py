@@ -38,3 +38,52 @@ def test_rows_of_any_vocabulary(V, dtype):
     err = np.abs(dz[resp] - rdz[resp])
     tol = 1e-5 * max(1.0, float(np.abs(rdz).max())) if dtype == torch.float32 else 2.0 ** -8 * np.abs(rdz[resp]) + 1e-5
     assert float((err - tol).max()) <= 0.0
+
+
+LOWEST = {torch.bfloat16: float(torch.finfo(torch.bfloat16).min), torch.float32: float(torch.finfo(torch.float32).min)}
+
+
+@pytest.mark.parametrize("dtype,V", [(torch.bfloat16, 300), (torch.bfloat16, 4097), (torch.bfloat16, 65543),
+                                     (torch.float32, 300), (torch.float32, 4097), (torch.float32, 40001)])
+@pytest.mark.parametrize("mask", [-1e9, -1e10, -1e11, -1e12, -1e20, -1e30, -1e37, "lowest", float("-inf")])
+def test_rows_masked_with_any_low_value(mask, dtype, V):
+    """Rows of which a first part, a last part, all but one element or every element holds a mask value, and rows whose
+    maximum is as large; one vocabulary per workgroup size."""
+    mask = LOWEST[dtype] if mask == "lowest" else mask
+    pl, Gs, rl = PACK
+    T = sum(pl) + sum(rl)
+    gen = torch.Generator().manual_seed(V)
+    z = (3.0 * torch.randn(T, V, generator=gen)).to(dtype)
+    idx = lo.response_index(pl, Gs, rl)
+    rows = np.flatnonzero(idx >= 0)
+    y = torch.full((T,), V // 2, dtype=torch.int32)
+    z[rows[0], :V // 2] = mask
+    z[rows[1], V // 2 + 1:] = mask
+    z[rows[2], :] = mask
+    z[rows[2], V // 2] = 1.5
+    whole = [rows[3], rows[4]]
+    if np.isfinite(mask):
+        z[rows[3], :] = mask                             # the whole row
+        z[rows[4], :] = -mask                            # as large, positive
+        z[rows[4], ::2] = mask
+        z[rows[4], V // 2] = -mask
+    z[rows[5], 1::2] = mask
+    z[rows[5], V // 2] = 0.25
+    g = torch.randn(T, generator=gen)
+    z64 = z.to(torch.float64).numpy()
+    rlogp, rlse = lo.logprob_fwd(z64, y.numpy(), idx)
+    rdz = lo.logprob_bwd(z64, y.numpy(), g.numpy().astype(np.float64), idx)
+    logp, lse = B.sp_attn_logprob_fwd(z.cuda(), y.cuda(), pl, Gs, rl)
+    dz = B.sp_attn_logprob_bwd(z.cuda(), y.cuda(), lse, g.cuda(), pl, Gs, rl)
+    torch.cuda.synchronize()
+    logp, lse, dz = logp.cpu().double().numpy(), lse.cpu().double().numpy(), dz.cpu().double().numpy()
+    assert np.all(np.isfinite(lse[rows])) and np.all(np.isfinite(logp[rows])) and np.all(np.isfinite(dz[rows]))
+    # fp32: the sum as in the tests above; where the row's maximum is large, lse itself (and logp, a difference from it) is
+    # rounded to a spacing of float32
+    tol = 2e-5 + 2.0 ** -23 * np.abs(rlse[rows])
+    assert np.all(np.abs(lse[rows] - rlse[rows]) <= tol)
+    assert np.all(np.abs(logp[rows] - rlogp[rows]) <= tol)
+    keep = [t for t in rows if t not in whole]           # exp(z - lse) has no digits where lse is rounded that coarsely
+    err = np.abs(dz[keep] - rdz[keep])
+    gtol = 1e-5 * max(1.0, float(np.abs(rdz).max())) if dtype == torch.float32 else 2.0 ** -8 * np.abs(rdz[keep]) + 1e-5
+    assert float((err - gtol).max()) <= 0.0
