@@ -236,8 +236,14 @@ __device__ __forceinline__ float lane_value(float x, int lane) {      // of a wa
     return __uint_as_float((unsigned)__builtin_amdgcn_readlane((int)__float_as_uint(x), lane));
 }
 // acc[e] += sum over j < n of lane j's p * row j's element l + 64 e; p is 0 in the lanes from n on.  Row j at base + j * stride.
+// The last ROWS rows may run past n: they repeat row n - 1 with weight 0, which is nothing unless that row holds an
+// infinity (0 * inf).  A sum that became NaN is therefore taken once more over the n rows alone, one by one; excluding the
+// repeated rows with a select per row instead cost the tiny group above 52.8 -> 60.3 us a training pass.
 template <int PER>
 __device__ __forceinline__ void add_rows(float (&acc)[PER], float p, const float* __restrict__ base, int64_t stride, int n, int l) {
+    float start[PER];
+#pragma unroll
+    for (int e = 0; e < PER; ++e) start[e] = acc[e];
     for (int j0 = 0; j0 < n; j0 += ROWS) {
         float x[ROWS][PER];
 #pragma unroll
@@ -249,6 +255,21 @@ __device__ __forceinline__ void add_rows(float (&acc)[PER], float p, const float
             const float pj = lane_value(p, j0 + u);
 #pragma unroll
             for (int e = 0; e < PER; ++e) acc[e] = __builtin_fmaf(pj, x[u][e], acc[e]);
+        }
+    }
+    bool is_nan = false;             // by its bits: the build takes float comparisons to see no NaN
+#pragma unroll
+    for (int e = 0; e < PER; ++e) {
+        asm volatile("" : "+v"(acc[e]));
+        is_nan |= (__float_as_uint(acc[e]) & 0x7fffffffu) > 0x7f800000u;
+    }
+    if (__builtin_amdgcn_ballot_w64(is_nan)) {
+#pragma unroll
+        for (int e = 0; e < PER; ++e) acc[e] = start[e];
+        for (int j = 0; j < n; ++j) {
+            const float pj = lane_value(p, j);
+#pragma unroll
+            for (int e = 0; e < PER; ++e) acc[e] = __builtin_fmaf(pj, base[j * stride + l + 64 * e], acc[e]);
         }
     }
 }
