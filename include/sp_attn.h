@@ -143,7 +143,7 @@ sp_status sp_attn_bwd_batched(const void* q, const void* k, const void* v,
 /* The backward runs in three stages that a caller may enqueue separately, e.g. to time them:
  *   SP_BWD_STAGE_ROWSUM  D[h, t] = sum_j d_o[t,h,j] * o[t,h,j] (o plus the forward's rounding residual
  *                        when the workspace holds a valid reserve or o_lo is given) and
- *                        the scaled lse -> workspace.  Needs o, d_o, lse; on the bf16 path also q, k, v:
+ *                        lse * log2(e) -> workspace.  Needs o, d_o, lse; on the bf16 path also q, k, v:
  *                        rows that see at most 64 keys get D from its definition sum_s P*dP in fp32.
  *   SP_BWD_STAGE_DQ      dq      (needs D in the same workspace; o unused).  On the bf16 path it
  *                        also REPLACES D in the workspace by sum_s P*dP, the same quantity
@@ -157,7 +157,7 @@ sp_status sp_attn_bwd_batched(const void* q, const void* k, const void* v,
  * run to run.  To overlap the two gradient passes, give each its own workspace and run ROWSUM on
  * both.  Output pointers of stages that are not requested may be NULL.
  * A bf16 call that holds both ROWSUM and DQ (and is not in response-rows mode) runs no separate
- * rowsum kernel: the dq pass, which loads every row of d_o anyway, forms D and the scaled lse in its
+ * rowsum kernel: the dq pass, which loads every row of d_o anyway, forms D and lse * log2(e) in its
  * prologue, with the same operations in the same order, so that the results equal those of the
  * stages enqueued one by one bit for bit.
  * sp_attn_bwd_batched(...) is this call with SP_BWD_STAGE_ALL. */

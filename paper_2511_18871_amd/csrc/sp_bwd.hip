@@ -26,9 +26,9 @@ constexpr int TILE_BYTES = 64 * 256;   // 64 rows x 128 bf16
 
 struct BwdArgs {
     const __bf16* q; const __bf16* k; const __bf16* v; const __bf16* d_o;
-    // planes read by the dkdv pass as initial values of its accumulators: -D, and -lse / scale (see dkdv_body), written by
-    // the rowsum stage (or the dq pass, below)
-    const float* lse; float* nD; float* nL;
+    // planes read by the dkdv pass: -D (the initial value of its dP accumulators) and L2 = lse * log2(e), written by the
+    // rowsum stage (or the dq pass, below)
+    const float* lse; float* nD; float* L2;
     // dq pass with the rowsum stage folded in: D = rowsum(dO * (o + residual)) is formed in the prologue from
     // the dO rows the pass loads anyway, and the two planes are written for the dkdv pass
     int fused_rowsum;
@@ -38,7 +38,6 @@ struct BwdArgs {
     Schedule sched;      // tile descriptors and per-token segment bounds, written by the schedule kernel of the call
     int n_tiles, n_groups, Hq, Hkv;
     float scale, c;      // c = scale * log2(e)
-    float c_kv, ninv_kv; // the dkdv pass's c, and -1 / scale
     int resp_only;       // only response rows are computed (dq) / contribute (dk, dv)
     int accumulate;      // dk, dv are added to what the output buffers hold
     // dkdv pass on small problems: one workgroup per (key tile, Q head) instead of per (key tile,
@@ -222,9 +221,9 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(BwdArgs a, EdgeArgs 
             const float y0 = x0 + x2, y1 = x1 + x3;
             Dq = pair_sum(y0 + y1);
             if (!valid) Dq = 0.f;
-            else if (hh == 0) a.nL[(int64_t)head * T_total + gd.tok_base + t] = lse_row * a.ninv_kv;
         }
         Lq = lse_row * LOG2E;
+        if (a.fused_rowsum && valid && hh == 0) a.L2[(int64_t)head * T_total + gd.tok_base + t] = Lq;
         // the shares overlap the ring slots that the first tile copies (of other waves, too) are about to fill
         lds_reads_done();
         __syncthreads();
@@ -534,7 +533,8 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const TileDesc td, c
     // NW = 8: [K | V] of the 128 keys, swizzled rows.  NW = 4: the eight V operands of each wave in lane order
     __shared__ __attribute__((aligned(1024))) char dkdv_ldsKV[K_REG ? 128 * 256 : 2 * 128 * 256];
     __shared__ __attribute__((aligned(1024))) char dkdv_lds[2][2 * QT_BYTES];                // [buffer][Q | dO]
-    __shared__ __attribute__((aligned(256))) float dkdv_ldsLD[2][2][BQ];                     // [buffer][-lse / scale | -D][row]
+    __shared__ __attribute__((aligned(256))) float dkdv_ldsLD[2][2][BQ];                     // [buffer][L2 | -D][row]
+    __shared__ int dkdv_ldsEnd[BNK];                // e_s of the tile's keys, below
     constexpr int RD = 3;      // LDS operand ring depth (prefetch distance RD - 1 MFMAs)
     const int s0 = ti * BNK;
     GroupDesc gd;
@@ -564,7 +564,8 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const TileDesc td, c
 
     // with only response rows contributing, the rows start at the end of the prompt
     const int row_lo = a.resp_only ? Lp : 0;
-    const int s_lo = max(s, row_lo);                   // first row that contributes to this lane's key
+    // (a step that masks reads e_s back: held in a register it was spilled, and its reload waited for the tile copies)
+    if (hh == 0) dkdv_ldsEnd[32 * kb + c] = e_s;
     const int qt0 = max(s0, row_lo) / BQ, qt1 = (row_end + BQ - 1) / BQ;
     const int rep_all = a.Hq / a.Hkv;
     const int rep = a.head_split ? 1 : rep_all;        // q heads this workgroup walks
@@ -641,6 +642,7 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const TileDesc td, c
     const int head0 = kvh * rep_all + hr_only;          // first q head this workgroup walks
     const uint64_t qbase_s = sgpr64(a.q + ((int64_t)gd.tok_base * a.Hq + head0) * 128);
     const uint64_t gbase_s = sgpr64(a.d_o + ((int64_t)gd.tok_base * a.Hq + head0) * 128);
+    const uint64_t l2_s = sgpr64(a.L2), nd_s = sgpr64(a.nD);       // (selected per lane, not loaded per lane and step)
     const unsigned m0buf[2] = {lds_u32(dkdv_lds[0]) + 1024u * CH * w, lds_u32(dkdv_lds[1]) + 1024u * CH * w};
     const unsigned tile_bytes = BQ * qstride_b;
     auto issue_tile = [&](int qt, int hr, int buf) {
@@ -661,17 +663,17 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const TileDesc td, c
                 async_copy16_sm(gbase_s + off, vo, m0 + QT_BYTES + 1024u * u);
             }
         }
-        if constexpr (NW == 4) {      // wave 0: -lse / scale of the 32 rows in its low lanes, -D in its high lanes
+        if constexpr (NW == 4) {      // wave 0: L2 of the 32 rows in its low lanes, -D in its high lanes
             if (w == 0) {
                 const int head = head0 + hr;
                 const int t = min(qt * BQ + c, Tg - 1);
-                const float* src = (hh == 0 ? a.nL : a.nD) + (int64_t)head * T_total + gd.tok_base + t;
+                const float* src = (const float*)(uintptr_t)(hh == 0 ? l2_s : nd_s) + (int64_t)head * T_total + gd.tok_base + t;
                 async_copy4(src, reinterpret_cast<char*>(&dkdv_ldsLD[buf][0][0]));
             }
-        } else if (w < 2) {        // wave 0: -lse / scale of the 64 rows, wave 1: -D (the first wave of a SIMD has slack)
+        } else if (w < 2) {        // wave 0: L2 of the 64 rows, wave 1: -D (the first wave of a SIMD has slack)
             const int head = head0 + hr;
             const int t = min(qt * BQ + l, Tg - 1);
-            const float* src = (w == 0 ? a.nL : a.nD) + (int64_t)head * T_total + gd.tok_base + t;
+            const float* src = (w == 0 ? a.L2 : a.nD) + (int64_t)head * T_total + gd.tok_base + t;
             async_copy4(src, reinterpret_cast<char*>(&dkdv_ldsLD[buf][w][0]));
         }
     };
@@ -681,7 +683,7 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const TileDesc td, c
     for (int db = 0; db < 4; ++db)
 #pragma unroll
         for (int r = 0; r < 16; ++r) { dkacc[db][r] = 0.f; dvacc[db][r] = 0.f; }
-    const float cs = a.c_kv;
+    const float cs = a.c;
     // LDS addresses of the operands within buffer 0, opaque so that they are kept as sums: row operands of Q (dO: + QT_BYTES),
     // transposed operands of Q, rows + 8 part of the block's first 16 rows (last 16: + 4096, the swizzle repeats)
     unsigned rowA[8], trA[4][2];
@@ -698,14 +700,15 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const TileDesc td, c
         }
     unsigned opB = lds_u32(dkdv_ldsKV) + (K_REG ? 8192 * w + 16 * l : 0);
     asm volatile("" : "+v"(opB));
+    const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     const char* ldsK = dkdv_ldsKV;
     const char* ldsV = dkdv_ldsKV + 128 * 256;
     typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
-    // The products S and dP start from the row's plane values instead of zero: S accumulates on top of -lse / scale and dP
-    // on top of -D, so P = exp2(acc c) and dS = P acc cost one multiplication each per element, and lse and D of
-    // the rows occupy no registers of their own (10 spilled registers before, none now).  One box: 16K prompt with 32 answers
-    // 8.02 -> 7.90 ms, four long prompts 3.80 -> 3.72, 64 groups of 1000 tokens 1.26 -> 1.23.
+    // dP accumulates on top of -D, so that dS = P acc is one multiplication per element and D of the rows occupies no
+    // registers of its own; S starts from zero and L2 is subtracted within the exponent's fma.  (S seeded with -lse / scale
+    // in the same way ran 0.4 % faster, but each of its partial sums then rounds at the magnitude of lse / scale, which
+    // doubles the error of P on ordinary inputs, and -lse / scale leaves float32 under a scale of 1e-30.)
     // Within a step the vector work is folded under the MFMAs: the exponentials of the first 8
     // rows run under the dP MFMAs (S is complete by then), those of the last 8 rows under the
     // first half of the dV/dK MFMAs (which only need the first 8 rows of P and dS).  Masking is
@@ -774,11 +777,11 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const TileDesc td, c
             for (int e = 0; e < 4; ++e) acc[4 * gq + e] = x[e];
         };
         f32x16 sacc, pacc;
+        f32x4 Lr[2];                                     // L2 of rows 8 gq + 4 hh .. + 3 of the block, in Lr[gq & 1]
+        auto rowsL = [&](int gq) { Lr[gq & 1] = *reinterpret_cast<const f32x4*>(&ldsL[32 * qh + 8 * gq + 4 * hh]); };
         // the first operands are fetched ahead of the issue of the next tile's copies, which every wave takes
         // part in whether it has work in this step or not
         if (!skip) {
-#pragma unroll
-            for (int gq = 0; gq < 4; ++gq) rows16(ldsL, gq, sacc);
 #pragma unroll
             for (int i = 0; i < RD - 1; ++i) { ra[i] = fetchA(i); if (!K_REG) rb[i] = fetchB(i); }
         }
@@ -786,22 +789,29 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const TileDesc td, c
         if (it + 1 < n_steps) issue_tile(qt_n_issue, hr_n_issue, buf ^ 1);
         if (skip) return;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {       // S - lse / scale = Q K^T on top of the row's plane value
+        for (int i = 0; i < 8; ++i) {       // S = Q K^T
             advance(i);
             if (i >= 4) rows16(ldsD, i - 4, pacc);
-            sacc = mfma32(ra[i % RD], K_REG ? kreg[i] : rb[i % RD], sacc);
+            if (i == 4 || i == 5) rowsL(i - 4);
+            sacc = mfma32(ra[i % RD], K_REG ? kreg[i] : rb[i % RD], i == 0 ? zero16 : sacc);
             __builtin_amdgcn_sched_barrier(0);
         }
         // every row of the half sees every key of the wave
         const bool full = r0 >= max(ws1, row_lo) && ws0 + 31 < Tg && r0 + 32 <= e_min;
-        if (!full) mask16(sacc, (low_bits(e_s - r0) & ~low_bits(s_lo - r0)) >> (4 * hh));
+        if (!full) {
+            int lane;                                    // again, so that nothing of the mask lives across steps
+            asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=&v"(lane));
+            const int key = 32 * kb + (lane & 31);
+            mask16(sacc, (low_bits(dkdv_ldsEnd[key] - r0) & ~low_bits(max(s0 + key, row_lo) - r0)) >> (4 * (lane >> 5)));
+        }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < 8; ++i) {       // dP - D = dO V^T on top of -D, with the exponentials of rows 0..7 of the block
             advance(8 + i);
             pacc = mfma32(ra[(8 + i) % RD], rb[(8 + i) % RD], pacc);
-            sacc[i] = __builtin_amdgcn_exp2f(sacc[i] * cs);      // P
+            sacc[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[i], cs, -Lr[i >> 2][i & 3]));      // P
             asm volatile("" : "+v"(sacc[i]));
+            if (i == 3) rowsL(2);
             __builtin_amdgcn_sched_barrier(0);
         }
         unsigned pp[8], dd[8];       // packed bf16 pairs of P and dS: [4 * mm + r / 2]
@@ -815,13 +825,14 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const TileDesc td, c
             const bf16x8 p8 = __builtin_bit_cast(bf16x8, u32x4{pp[0], pp[1], pp[2], pp[3]});
             const bf16x8 d8 = __builtin_bit_cast(bf16x8, u32x4{dd[0], dd[1], dd[2], dd[3]});
             float tprev = 0.f;
+            rowsL(3);
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
                 advance(16 + i);
                 const bf16x8 A = ra[(16 + i) % RD];
                 if (i & 1) dkacc[i >> 1] = mfma32(A, d8, dkacc[i >> 1]);
                 else dvacc[i >> 1] = mfma32(A, p8, dvacc[i >> 1]);
-                float tcur = __builtin_amdgcn_exp2f(sacc[8 + i] * cs);
+                float tcur = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[8 + i], cs, -Lr[i >> 2][i & 3]));
                 asm volatile("" : "+v"(tcur));
                 if (i >= 1) {
                     sacc[8 + i - 1] = tprev;
@@ -987,10 +998,9 @@ hipError_t launch_bwd_bf16(const Problem& p, hipStream_t s) {
     BwdArgs a{};
     a.fused_rowsum = fused; a.o = (const __bf16*)p.o; a.o_lo = (const __bf16*)p.o_lo; a.lo_flag = p.o_lo_flag;
     a.q = (const __bf16*)p.q; a.k = (const __bf16*)p.k; a.v = (const __bf16*)p.v; a.d_o = (const __bf16*)p.d_o;
-    a.lse = p.lse; a.nD = p.Dbuf; a.nL = p.Dbuf + (int64_t)p.Hq * p.total_tokens;
+    a.lse = p.lse; a.nD = p.Dbuf; a.L2 = p.Dbuf + (int64_t)p.Hq * p.total_tokens;
     a.dq = (__bf16*)p.dq; a.dk = (__bf16*)p.dk; a.dv = (__bf16*)p.dv;
     a.tab = p.tab; a.sched = p.sched; a.n_groups = p.n_groups; a.Hq = p.Hq; a.Hkv = p.Hkv; a.scale = p.scale; a.c = p.scale * LOG2E;
-    a.c_kv = plane_scale(p.scale) * LOG2E; a.ninv_kv = -1.0f / plane_scale(p.scale);
     a.resp_only = p.resp_only; a.accumulate = p.accumulate;
     if (p.stages & STAGE_DQ) {
         // short key loops: the four-wave shape, two workgroups per CU (the forward's rule, see bwd_dq_kernel)

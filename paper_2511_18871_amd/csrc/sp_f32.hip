@@ -109,8 +109,8 @@ __global__ __launch_bounds__(256) void rowsum_kernel(const T* __restrict__ d_o, 
                                                      const float* __restrict__ lse, float* __restrict__ D,
                                                      int64_t T_total, int Hq, int dh,
                                                      const int* __restrict__ tab, int resp_only,
-                                                     const T* __restrict__ o_lo, float ninv_scale) {
-    constexpr bool BF = std::is_same<T, __bf16>::value;        // the bf16 planes hold -D and -lse / scale
+                                                     const T* __restrict__ o_lo) {
+    constexpr bool BF = std::is_same<T, __bf16>::value;        // the bf16 planes hold -D and lse * log2(e)
     const int64_t gw = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     const int l = threadIdx.x & 63;
     if (gw >= T_total * Hq) return;
@@ -140,7 +140,7 @@ __global__ __launch_bounds__(256) void rowsum_kernel(const T* __restrict__ d_o, 
     acc = wave_sum(acc);
     if (l == 0) {
         D[(int64_t)h * T_total + tok] = BF ? -acc : acc;
-        if (BF) D[(int64_t)Hq * T_total + (int64_t)h * T_total + tok] = lse[(int64_t)h * T_total + tok] * ninv_scale;
+        if (BF) D[(int64_t)Hq * T_total + (int64_t)h * T_total + tok] = lse[(int64_t)h * T_total + tok] * LOG2E;
     }
 }
 
@@ -156,7 +156,7 @@ __global__ __launch_bounds__(256) void rowsum_bf16_kernel(const __bf16* __restri
                                                           const float* __restrict__ lse, float* __restrict__ D,
                                                           int64_t T_total, int Hq, const int* __restrict__ tab,
                                                           int resp_only, const __bf16* __restrict__ o_lo,
-                                                          const uint32_t* __restrict__ lo_flag, float ninv_scale) {
+                                                          const uint32_t* __restrict__ lo_flag) {
     extern __shared__ float rs_sum[];                  // [Hq][RS_TOK]
     __shared__ int rs_skip[RS_TOK];
     // the residual is the workspace's reserve: usable only if the tag check of this call said so
@@ -208,9 +208,9 @@ __global__ __launch_bounds__(256) void rowsum_bf16_kernel(const __bf16* __restri
         if (tl < ntok) {
             const int64_t idx = (int64_t)h * T_total + tok0 + tl;
             D[idx] = -rs_sum[i];
-            // second plane: -lse / scale, the initial value of the dkdv pass's score accumulators
-            const float nl = lse[idx] * ninv_scale;
-            D[(int64_t)Hq * T_total + idx] = rs_skip[tl] ? 0.f : nl;
+            // second plane: the row's logsumexp in base-2 units, as the dkdv pass consumes it
+            const float l2 = lse[idx] * LOG2E;
+            D[(int64_t)Hq * T_total + idx] = rs_skip[tl] ? 0.f : l2;
         }
     }
 }
@@ -464,21 +464,20 @@ hipError_t launch_prepare(const int32_t* host_words, int n_words, int* dev_tab, 
 }
 
 hipError_t launch_rowsum(const Problem& p, bool f32, hipStream_t s) {
-    const float ninv = -1.0f / plane_scale(p.scale);
     const int grid = blocks_for_waves(p.total_tokens * p.Hq);
     if (f32)
         hipLaunchKernelGGL(rowsum_kernel<float>, dim3(grid), dim3(256), 0, s, (const float*)p.d_o,
-                           (const float*)p.o, p.lse, p.Dbuf, p.total_tokens, p.Hq, p.head_dim, p.tab, p.resp_only, (const float*)nullptr, ninv);
+                           (const float*)p.o, p.lse, p.Dbuf, p.total_tokens, p.Hq, p.head_dim, p.tab, p.resp_only, (const float*)nullptr);
     else if (rowsum_fast_path(p)) {
         const dim3 g((unsigned)((p.total_tokens + RS_TOK - 1) / RS_TOK));
         const size_t lds = (size_t)p.Hq * RS_TOK * sizeof(float);
         if (p.o_lo)
             hipLaunchKernelGGL(rowsum_bf16_kernel<true>, g, dim3(256), lds, s, (const __bf16*)p.d_o, (const __bf16*)p.o,
-                               p.lse, p.Dbuf, p.total_tokens, p.Hq, p.tab, p.resp_only, (const __bf16*)p.o_lo, p.o_lo_flag, ninv);
+                               p.lse, p.Dbuf, p.total_tokens, p.Hq, p.tab, p.resp_only, (const __bf16*)p.o_lo, p.o_lo_flag);
         else
             hipLaunchKernelGGL(rowsum_bf16_kernel<false>, g, dim3(256), lds, s, (const __bf16*)p.d_o, (const __bf16*)p.o,
                                p.lse, p.Dbuf, p.total_tokens, p.Hq, p.tab, p.resp_only, (const __bf16*)nullptr,
-                               (const uint32_t*)nullptr, ninv);
+                               (const uint32_t*)nullptr);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         // exact D for the rows that see only a few keys (sp_edge.hpp)
@@ -488,7 +487,7 @@ hipError_t launch_rowsum(const Problem& p, bool f32, hipStream_t s) {
     else
         hipLaunchKernelGGL(rowsum_kernel<__bf16>, dim3(grid), dim3(256), 0, s, (const __bf16*)p.d_o,
                            (const __bf16*)p.o, p.lse, p.Dbuf, p.total_tokens, p.Hq, p.head_dim, p.tab, p.resp_only,
-                           (const __bf16*)(p.o_lo_flag ? nullptr : p.o_lo), ninv);      // this fallback does not consult the reserve
+                           (const __bf16*)(p.o_lo_flag ? nullptr : p.o_lo));      // this fallback does not consult the reserve
     return hipGetLastError();
 }
 

@@ -126,10 +126,6 @@ inline bool use_small_shape(const Problem& p) {
 // Packings that the bandwidth-shaped bf16 rowsum kernel takes (its per-head sums of 16 tokens fit its LDS)
 inline bool rowsum_fast_path(const Problem& p) { return p.head_dim == 128 && (size_t)p.Hq * 16 * sizeof(float) <= 32768; }
 
-// The dkdv pass starts its score accumulators at -lse / scale, so that P = exp2(acc * scale * log2(e)).  Below 1e-30 a
-// scale contributes nothing to a finite score and its reciprocal could overflow: such a scale is taken as 1e-30.
-inline float plane_scale(float scale) { return scale < 1e-30f ? 1e-30f : scale; }
-
 inline int count_tiles(const Problem& p, int bm) {
     int n = 0;
     for (int g = 0; g < p.n_groups; ++g) n += (p.host_group_tokens[g] + bm - 1) / bm;
