@@ -393,6 +393,13 @@ sp_status sp_attn_probe_atomic_add(float* buf, int64_t rows, int32_t heads, int3
 sp_status sp_attn_row_tile(int32_t n_groups, const int32_t* prompt_lens, const int32_t* Gs,
                            const int32_t* resp_lens_flat, int32_t* rows, int64_t* steps_256, int64_t* steps_128);
 
+/* Which workgroup shape the dkdv pass of a bf16 backward on this packing takes: *waves = 8 or 4 (eight walk a key
+ * tile faster, of four-wave workgroups two share a CU; the rule compares when either would be through).  flags as in
+ * sp_attn_bwd_batched_ex.  Host arithmetic on the lengths; no device work; for tools and tests.  Errors as the host checks
+ * of sp_attn_bwd_batched_ex. */
+sp_status sp_attn_dkdv_waves(int32_t n_groups, const int32_t* prompt_lens, const int32_t* Gs, const int32_t* resp_lens_flat,
+                             int32_t n_q_heads, int32_t n_kv_heads, uint32_t flags, int32_t* waves);
+
 /* Tuning knob, process-wide (no counterpart in the paper).  The bf16 kernels come in two workgroup
  * shapes: 256 query rows with one workgroup per CU, for long key loops, and 128 rows with two
  * workgroups per CU, whose fixed per-workgroup costs overlap and which execute less work that no row of

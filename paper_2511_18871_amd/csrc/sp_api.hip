@@ -549,6 +549,26 @@ sp_status sp_attn_row_tile(int32_t n_groups, const int32_t* prompt_lens, const i
     return SP_OK;
 }
 
+sp_status sp_attn_dkdv_waves(int32_t n_groups, const int32_t* prompt_lens, const int32_t* Gs, const int32_t* resp_lens_flat,
+                             int32_t n_q_heads, int32_t n_kv_heads, uint32_t flags, int32_t* waves) {
+    g_err[0] = 0;
+    if (!waves) return fail(SP_ERR_INVALID_ARG, "waves is NULL");
+    if (flags & ~(unsigned)(SP_FLAG_RESPONSE_ROWS | SP_FLAG_ACCUMULATE_DKDV))
+        return fail(SP_ERR_INVALID_ARG, "unknown bits in flags=0x%x", flags);
+    sp_status st = check_geometry(n_q_heads, n_kv_heads, 128, 1.f, SP_BF16);
+    if (st != SP_OK) return st;
+    Layout L;
+    st = build_table(n_groups, prompt_lens, Gs, resp_lens_flat, L);
+    if (st != SP_OK) return st;
+    sp::Problem p{};
+    p.n_groups = n_groups; p.Hq = n_q_heads; p.Hkv = n_kv_heads;
+    p.resp_only = (flags & SP_FLAG_RESPONSE_ROWS) != 0;
+    p.host_group_tokens = L.group_tokens.data();
+    p.host_table = L.words.data();
+    *waves = sp::dkdv_head_split(L.total_tokens, n_groups, n_q_heads, n_kv_heads) ? 8 : sp::dkdv_waves(p);
+    return SP_OK;
+}
+
 namespace {
 constexpr int MAX_DEVICES = 64;
 std::atomic<void*> g_scratch_ptr[MAX_DEVICES];      // device address of `scratch` on each GPU, 0 = not asked yet

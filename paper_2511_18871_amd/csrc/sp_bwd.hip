@@ -17,7 +17,9 @@
 #include "sp_common.hpp"
 #include "sp_launch.hpp"
 #include "sp_edge.hpp"
+#include <algorithm>
 #include <type_traits>
+#include <vector>
 
 namespace sp {
 namespace {
@@ -518,7 +520,7 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(BwdArgs a, EdgeArgs 
 //     that one's barriers, first loads, stores and steps without work (other responses' rows) lie under the other's MFMAs.
 //   NW = 8: wave w owns key block w & 3 and the row half w >> 2 of tiles of 64 rows, K and V in LDS, one workgroup per
 //     CU; the two halves' partial sums are added through LDS at the end, in a fixed order.  Half as many steps per
-//     workgroup: for packings with too few workgroups to fill the chip (dkdv_head_split), where the longest one counts.
+//     workgroup: where the longest one counts (dkdv_head_split, and by dkdv_waves()).
 // The LDS addresses of a step's operands are whole sums in registers plus constants (two steps per turn of the loop, one
 // per buffer); left to the compiler they were 25 additions per step, and K did not fit the registers.
 // 8 -> 4 waves with these addresses, one box: 16K prompt with 32 answers 7.67 -> 7.24 ms, 64 groups of a short prompt
@@ -568,7 +570,7 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const TileDesc td, c
     if (hh == 0) dkdv_ldsEnd[32 * kb + c] = e_s;
     const int qt0 = max(s0, row_lo) / BQ, qt1 = (row_end + BQ - 1) / BQ;
     const int rep_all = a.Hq / a.Hkv;
-    const int rep = a.head_split ? 1 : rep_all;        // q heads this workgroup walks
+    const int rep = NW == 8 && a.head_split ? 1 : rep_all;        // q heads this workgroup walks
     const int64_t q_stride = (int64_t)a.Hq * 128;
     const int64_t kv_stride = (int64_t)a.Hkv * 128;
 
@@ -944,7 +946,7 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const TileDesc td, c
 template <int NW>
 __global__ __launch_bounds__(64 * NW, 2) void bwd_dkdv_kernel(BwdArgs a) {
     int tile, kvh, hr_only = 0;
-    if (a.head_split) {
+    if (NW == 8 && a.head_split) {
         int head;
         if (!decode_item(blockIdx.x, a.n_tiles, a.Hq, a.Hkv, tile, head)) return;
         kvh = head / (a.Hq / a.Hkv);
@@ -983,6 +985,82 @@ __global__ __launch_bounds__(256) void dkdv_reduce_kernel(const float* __restric
 }
 
 }  // namespace
+
+// Eight waves walk a key tile 1.2 times as fast as four that have the CU to themselves, but two workgroups of four
+// share a CU at 0.7 of that speed each.  Which shape ends first depends on how the tiles fall onto the CUs: workgroups go
+// round the XCDs and within an XCD round its four shader engines, in order, and a group's first tiles are its longest.
+// The launch is therefore played through on the host, for one XCD (the others get the same mixture), with the times that
+// the two shapes take on an idle chip, us per row tile and q head.
+// Measured on 439 packings of 96 to 2600 workgroups (both shapes; one to 40 groups, 4/4 to 40/8 heads): the shape taken is
+// 0.3 % from the faster one on average (0.4 % on 138 more, drawn afterwards); four waves throughout 10 %, eight waves 2.9 %, a line by the number of
+// workgroups alone up to 24 % (a group of 9152 tokens, 28/4 heads, 288 workgroups: 1592 us with four waves, 1281 with
+// eight; nine groups of 1000, as many workgroups: 292 and 323).
+int dkdv_waves(const Problem& p) {
+    constexpr int SE = 4, CUS = 8;                             // of an XCD
+    const int n_wgs = count_tiles(p, 128) * p.Hkv;
+    if (n_wgs <= 8 * SE * CUS) return 8;                       // no CU gets a second workgroup
+    const bool many = n_wgs > 2048;
+    const int rep = p.Hq / p.Hkv;
+    std::vector<float> w8, w4;                                 // time of each key tile's workgroup
+    double sum = 0.;
+    float longest = 0.f;
+    for (int g = 0; g < p.n_groups; ++g) {
+        const int32_t* e = p.host_table + TAB_HEADER + TAB_GROUP_WORDS * g;
+        const int Lp = e[1], Tg = e[2];
+        const int32_t* roff = p.host_table + e[3];
+        for (int s0 = 0, j = 0; s0 < Tg; s0 += 128) {
+            const int last = (s0 + 128 < Tg ? s0 + 128 : Tg) - 1, from = p.resp_only && Lp > s0 ? Lp : s0;
+            int to = Tg;                                       // one past the last row that sees a key of the tile
+            if (s0 >= Lp) { while (roff[j + 1] <= last) ++j; to = roff[j + 1]; }
+            const int rows = to > from ? to : from;
+            const float t4 = 5.f + 0.77f * (float)(((rows + 31) / 32 - from / 32) * rep);
+            sum += t4;
+            longest = std::max(longest, t4);
+            if (many) continue;
+            w8.push_back(6.f + 1.24f * (float)(((rows + 63) / 64 - from / 64) * rep));
+            w4.push_back(t4);
+        }
+    }
+    // many workgroups: even, unless one is longer than what a CU gets in all
+    if (many) return sum * p.Hkv < 256. * longest ? 8 : 4;
+    std::vector<int> tiles;                                    // of XCD 0, in order
+    for (int bid = 0, n = (int)w8.size(), grid = grid_for_items(n, p.Hkv, p.Hkv); bid < grid; bid += 8) {
+        int tile, kvh;
+        if (decode_item(bid, n, p.Hkv, p.Hkv, tile, kvh)) tiles.push_back(tile);
+    }
+    float end8 = 0.f, end4 = 0.f;
+    for (int se = 0; se < SE; ++se) {
+        float busy[CUS] = {};
+        for (size_t i = se; i < tiles.size(); i += SE) {
+            float* cu = std::min_element(busy, busy + CUS);
+            *cu += w8[tiles[i]];
+            end8 = std::max(end8, *cu);
+        }
+        float left[CUS][2] = {}, now = 0.f;                    // work left of the residents of each CU
+        for (size_t i = se;;) {
+            for (int fill = 0; fill < 2; ++fill)               // an empty CU first
+                for (int c = 0; c < CUS && i < tiles.size(); ++c) {
+                    if (left[c][0] > 0.f && left[c][1] > 0.f) continue;
+                    if (fill == 0 && (left[c][0] > 0.f || left[c][1] > 0.f)) continue;
+                    left[c][left[c][0] > 0.f] = w4[tiles[i]];
+                    i += SE;
+                }
+            float dt = 1e30f;
+            auto speed = [&](int c) { return left[c][0] > 0.f && left[c][1] > 0.f ? 0.7f : 1.f; };
+            for (int c = 0; c < CUS; ++c)
+                for (int k = 0; k < 2; ++k)
+                    if (left[c][k] > 0.f) dt = std::min(dt, left[c][k] / speed(c));
+            if (dt == 1e30f) break;
+            now += dt;
+            for (int c = 0; c < CUS; ++c) {
+                const float done = dt * speed(c) * 1.0001f + 1e-3f;        // the one that sets dt ends in any rounding
+                for (int k = 0; k < 2; ++k) left[c][k] = left[c][k] > done ? left[c][k] - done : 0.f;
+            }
+        }
+        end4 = std::max(end4, now);
+    }
+    return end4 < end8 ? 4 : 8;
+}
 
 hipError_t launch_bwd_bf16(const Problem& p, hipStream_t s) {
     hipError_t e = hipSuccess;
@@ -1026,7 +1104,8 @@ hipError_t launch_bwd_bf16(const Problem& p, hipStream_t s) {
                                n4, p.Hq / p.Hkv, p.scale, a.accumulate);
         } else {
             const int grid = grid_for_items(a.n_tiles, p.Hkv, p.Hkv);
-            hipLaunchKernelGGL(bwd_dkdv_kernel<4>, dim3(grid), dim3(256), 0, s, a);
+            if (dkdv_waves(p) == 8) hipLaunchKernelGGL(bwd_dkdv_kernel<8>, dim3(grid), dim3(512), 0, s, a);
+            else hipLaunchKernelGGL(bwd_dkdv_kernel<4>, dim3(grid), dim3(256), 0, s, a);
         }
         e = hipGetLastError();
     }

@@ -145,7 +145,7 @@ struct Schedule { const TileDesc* tiles256; const TileDesc* tiles128; const int*
 // (blocks are dealt round-robin over the 8 XCDs, each with a private L2) share one
 // kv head, and q heads of the same tile sit next to each other.
 // Returns false when the block has no work.
-__device__ __forceinline__ bool decode_item(int bid, int n_tiles, int Hq, int Hkv,
+__host__ __device__ __forceinline__ bool decode_item(int bid, int n_tiles, int Hq, int Hkv,
                                             int& tile, int& head) {
     const int rep = Hq / Hkv;
     const int per_kv = n_tiles * rep;          // items of one kv head

@@ -139,4 +139,7 @@ inline bool dkdv_head_split(int64_t total_tokens, int n_groups, int Hq, int Hkv)
     return Hq > Hkv && (total_tokens / 128 + n_groups) * Hkv <= 192;
 }
 
+// Waves per workgroup (8 or 4) of a dkdv pass that is not split over the q heads (rule and reasons: sp_bwd.hip).
+int dkdv_waves(const Problem& p);
+
 }  // namespace sp
