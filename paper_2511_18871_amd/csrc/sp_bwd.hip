@@ -536,7 +536,7 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const TileDesc td, c
     __shared__ __attribute__((aligned(1024))) char dkdv_ldsKV[K_REG ? 128 * 256 : 2 * 128 * 256];
     __shared__ __attribute__((aligned(1024))) char dkdv_lds[2][2 * QT_BYTES];                // [buffer][Q | dO]
     __shared__ __attribute__((aligned(256))) float dkdv_ldsLD[2][2][BQ];                     // [buffer][L2 | -D][row]
-    __shared__ int dkdv_ldsEnd[BNK];                // e_s of the tile's keys, below
+    __shared__ int dkdv_ldsEnd[K_REG ? BNK : 1];    // e_s of the tile's keys, below
     constexpr int RD = 3;      // LDS operand ring depth (prefetch distance RD - 1 MFMAs)
     const int s0 = ti * BNK;
     GroupDesc gd;
@@ -566,8 +566,9 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const TileDesc td, c
 
     // with only response rows contributing, the rows start at the end of the prompt
     const int row_lo = a.resp_only ? Lp : 0;
-    // (a step that masks reads e_s back: held in a register it was spilled, and its reload waited for the tile copies)
-    if (hh == 0) dkdv_ldsEnd[32 * kb + c] = e_s;
+    // (four waves: a step that masks reads e_s back; held in a register it was spilled, and its reload waited for the
+    // tile copies.  Eight waves have the register: 1 % of the pass)
+    if (K_REG && hh == 0) dkdv_ldsEnd[32 * kb + c] = e_s;
     const int qt0 = max(s0, row_lo) / BQ, qt1 = (row_end + BQ - 1) / BQ;
     const int rep_all = a.Hq / a.Hkv;
     const int rep = NW == 8 && a.head_split ? 1 : rep_all;        // q heads this workgroup walks
@@ -709,8 +710,9 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const TileDesc td, c
 
     // dP accumulates on top of -D, so that dS = P acc is one multiplication per element and D of the rows occupies no
     // registers of its own; S starts from zero and L2 is subtracted within the exponent's fma.  (S seeded with -lse / scale
-    // in the same way ran 0.4 % faster, but each of its partial sums then rounds at the magnitude of lse / scale, which
-    // doubles the error of P on ordinary inputs, and -lse / scale leaves float32 under a scale of 1e-30.)
+    // in the same way saves 1.5 % of the pass under responses of 30 to 600 tokens and nothing elsewhere, but each of its
+    // partial sums rounds at the magnitude of lse / scale, which doubles the error of P on ordinary inputs, and
+    // -lse / scale leaves float32 under a scale of 1e-30.)
     // Within a step the vector work is folded under the MFMAs: the exponentials of the first 8
     // rows run under the dP MFMAs (S is complete by then), those of the last 8 rows under the
     // first half of the dV/dK MFMAs (which only need the first 8 rows of P and dS).  Masking is
@@ -793,8 +795,8 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const TileDesc td, c
 #pragma unroll
         for (int i = 0; i < 8; ++i) {       // S = Q K^T
             advance(i);
-            if (i >= 4) rows16(ldsD, i - 4, pacc);
-            if (i == 4 || i == 5) rowsL(i - 4);
+            if (i < 2) rowsL(i);                         // (both planes two slices later: 1 % of the pass)
+            if (i >= 2 && i < 6) rows16(ldsD, i - 2, pacc);
             sacc = mfma32(ra[i % RD], K_REG ? kreg[i] : rb[i % RD], i == 0 ? zero16 : sacc);
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -803,8 +805,8 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const TileDesc td, c
         if (!full) {
             int lane;                                    // again, so that nothing of the mask lives across steps
             asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=&v"(lane));
-            const int key = 32 * kb + (lane & 31);
-            mask16(sacc, (low_bits(dkdv_ldsEnd[key] - r0) & ~low_bits(max(s0 + key, row_lo) - r0)) >> (4 * (lane >> 5)));
+            const int key = 32 * kb + (lane & 31), end = K_REG ? dkdv_ldsEnd[key] : e_s;
+            mask16(sacc, (low_bits(end - r0) & ~low_bits(max(s0 + key, row_lo) - r0)) >> (4 * (lane >> 5)));
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
