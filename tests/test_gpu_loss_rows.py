@@ -1,5 +1,7 @@
-"""Rows of the log-probability passes at every cut a row can have: elements ahead of a 16-byte boundary (odd vocabularies), vectors around whole rounds
-of each workgroup size, a tail; prompt rows of a gradient that the call allocates are zero."""
+"""Rows of the log-probability passes at every cut a row can have: elements ahead of a 16-byte boundary (odd vocabularies),
+vectors around whole rounds of each workgroup size (64 threads below 4096 bf16 or 2048 float32 elements, 1024 from 65536 or
+32768 on, 256 between), a tail; masked rows; a gradient too large for the caches, which is stored past them; prompt rows of
+a gradient that the call allocates are zero."""
 import numpy as np
 import pytest
 import torch
@@ -13,7 +15,7 @@ PACK = ([3, 0, 2], [2, 1, 2], [1, 3, 2, 4, 1])
 
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
-@pytest.mark.parametrize("V", [1, 7, 8, 9, 1023, 2048, 4095, 4097, 8192, 16384, 16389, 49157])
+@pytest.mark.parametrize("V", [1, 7, 8, 9, 1023, 2048, 4095, 4097, 8192, 16384, 16389, 49157, 65535, 65536, 65543, 151936])
 def test_rows_of_any_vocabulary(V, dtype):
     pl, Gs, rl = PACK
     T = sum(pl) + sum(rl)
@@ -87,3 +89,35 @@ def test_rows_masked_with_any_low_value(mask, dtype, V):
     err = np.abs(dz[keep] - rdz[keep])
     gtol = 1e-5 * max(1.0, float(np.abs(rdz).max())) if dtype == torch.float32 else 2.0 ** -8 * np.abs(rdz[keep]) + 1e-5
     assert float((err - gtol).max()) <= 0.0
+
+
+@pytest.mark.parametrize("dtype,V", [(torch.bfloat16, 151936), (torch.bfloat16, 151937), (torch.bfloat16, 20001), (torch.float32, 75968),
+                                     (torch.float32, 75971), (torch.float32, 1501)])
+def test_a_gradient_beyond_the_caches(dtype, V):
+    size = 2 if dtype == torch.bfloat16 else 4
+    n = (256 << 20) // (V * size) // 4 + 1               # tokens: 4 n + 14, just over 256 MB
+    pl, Gs, rl = [n, 3], [2, 1], [n, n + 9, n + 2]
+    T = sum(pl) + sum(rl)
+    assert T * V * size > 256 << 20
+    gen = torch.Generator(device="cuda").manual_seed(V)
+    z = torch.empty(T, V, dtype=dtype, device="cuda").normal_(0.0, 3.0, generator=gen)
+    y = torch.randint(0, V, (T,), generator=gen, device="cuda", dtype=torch.int32)
+    g = torch.randn(T, generator=gen, device="cuda")
+    stale = torch.full_like(z, float("nan"))             # what the call's own allocation may hold
+    del stale
+    logp, lse = B.sp_attn_logprob_fwd(z, y, pl, Gs, rl)
+    dz = B.sp_attn_logprob_bwd(z, y, lse, g, pl, Gs, rl)
+    torch.cuda.synchronize()
+    idx = lo.response_index(pl, Gs, rl)
+    assert not dz[torch.from_numpy(idx < 0).cuda()].any()
+    assert torch.isfinite(dz).all()
+    at = np.flatnonzero(idx >= 0)
+    rows = at[np.linspace(0, len(at) - 1, 12).astype(int)]
+    pick = lambda x: x[torch.from_numpy(rows).cuda()].cpu().double().numpy()
+    z64 = pick(z)
+    rlogp, _ = lo.logprob_fwd(z64, y.cpu().numpy()[rows], idx[rows])
+    rdz = lo.logprob_bwd(z64, y.cpu().numpy()[rows], pick(g), idx[rows])
+    assert float(np.abs(pick(logp) - rlogp).max()) <= 2e-5
+    err = np.abs(pick(dz) - rdz)
+    tol = 1e-5 * max(1.0, float(np.abs(rdz).max())) if dtype == torch.float32 else 2.0 ** -8 * np.abs(rdz) + 1e-5
+    assert float((err - tol).max()) <= 0.0
