@@ -148,7 +148,7 @@ sp_status sp_attn_bwd_batched(const void* q, const void* k, const void* v,
  *   SP_BWD_STAGE_DQ      dq      (needs D in the same workspace; o unused).  On the bf16 path it
  *                        also REPLACES D in the workspace by sum_s P*dP, the same quantity
  *                        evaluated in fp32 without the bf16 rounding of o, and writes the dq of rows
- *                        that see at most 64 keys in a separate small kernel (fp32 dS).
+ *                        that see at most 64 keys from fp32 dS (by workgroups of their own in the same launch).
  *   SP_BWD_STAGE_DKDV    dk, dv  (needs D in the same workspace; o unused)
  * Ordering on one workspace: ROWSUM first; then DQ and DKDV one after the other, never concurrently
  * (DQ rewrites the D plane that DKDV reads: overlapping them, e.g. on two streams, is a data race).
@@ -384,10 +384,11 @@ sp_status sp_attn_mfma_ceiling(int32_t lds_operands, const void* a, const void* 
 sp_status sp_attn_probe_atomic_add(float* buf, int64_t rows, int32_t heads, int32_t steps, int32_t n_blocks,
                                    int32_t layout, void* stream);
 
-/* Which workgroup shape a bf16 call on this packing takes for the forward and the dq pass: *rows = 256
- * or 128 (see sp_attn_set_small_shape_steps below for the rule).  Optionally also the number of 64-key
- * steps that the workgroups of either tiling run per q head (the quantities the rule compares; the
- * count for 128-row tiles is in steps of half the rows).  Host arithmetic on the lengths (Section 4.3:
+/* Which workgroup shape a bf16 call on this packing takes for the forward and the dq pass: *rows = 256 (eight waves of
+ * 32 rows) or 128 (four; see sp_attn_set_small_shape_steps below for the rule).  Optionally also the quantities that the
+ * rule compares: the number of 64-key steps of row tiles of 256 and of 128 rows of one q head.  They are the steps that
+ * run where every q head has a kv head of its own; else a workgroup holds rows of several q heads, spans fewer of them
+ * and runs fewer steps.  Host arithmetic on the lengths (Section 4.3:
  * the key ranges of the three terms of its complexity split); no device work; for tools and tests.
  * Errors as the host checks of sp_attn_fwd_batched. */
 sp_status sp_attn_row_tile(int32_t n_groups, const int32_t* prompt_lens, const int32_t* Gs,
@@ -401,12 +402,11 @@ sp_status sp_attn_dkdv_waves(int32_t n_groups, const int32_t* prompt_lens, const
                              int32_t n_q_heads, int32_t n_kv_heads, uint32_t flags, int32_t* waves);
 
 /* Tuning knob, process-wide (no counterpart in the paper).  The bf16 kernels come in two workgroup
- * shapes: 256 query rows with one workgroup per CU, for long key loops, and 128 rows with two
- * workgroups per CU, whose fixed per-workgroup costs overlap and which execute less work that no row of
- * a tile needs, for batches of short or ragged groups.  By default a call (forward, dq pass) takes the
- * small shape when that saves more than 3 % of the executed 64-key steps (host arithmetic on the
- * lengths).  With the knob set, it takes the small shape when a 256-row workgroup of its packing would run
- * fewer than `steps` such steps on average: 0 = always the large shape; a large value = always the small
+ * shapes: eight waves with one workgroup per CU, for long key loops, and four waves with two
+ * workgroups per CU, whose fixed per-workgroup costs overlap, for batches of short or ragged groups.  By default a call
+ * (forward, dq pass) takes the small shape when row tiles of 128 rows need more than 3 % fewer 64-key steps than tiles
+ * of 256 (host arithmetic on the lengths).  With the knob set, it takes the small shape when a 256-row tile of its
+ * packing has fewer than `steps` such steps on average: 0 = always the large shape; a large value = always the small
  * one; negative = back to the default rule.  Results do not depend on the shape beyond rounding order.
  * For measurements and tests; safe to call at any time between calls. */
 void sp_attn_set_small_shape_steps(int32_t steps);

@@ -131,8 +131,8 @@ def sp_attn_segment_table(prompt_lens: Sequence[int], Gs: Sequence[int], resp_le
 
 
 def sp_attn_row_tile(prompt_lens: Sequence[int], Gs: Sequence[int], resp_lens_flat: Sequence[int]):
-    """(rows, steps_256, steps_128): the workgroup shape (256 or 128 query rows) that a bf16 call on this packing
-    takes, and the 64-key steps per q head of either tiling.  Host arithmetic only."""
+    """(rows, steps_256, steps_128): the workgroup shape (256 or 128 query rows, eight or four waves) that a bf16 call on this packing
+    takes, and the 64-key steps of one q head's row tiles of either size.  Host arithmetic only."""
     lib = load_library()
     rows = ctypes.c_int32(0)
     s256, s128 = ctypes.c_int64(0), ctypes.c_int64(0)

@@ -439,7 +439,7 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd_kernel(FwdArgs a) {      // tw
     // loop-invariant, and hoisted above the main loop they would cost it registers (they were spilled)
     int lz = l;
     asm volatile("" : "+v"(lz));
-    {   // P of the last (padded) step and its V tile
+    {   // P of the last step that ran (eight waves: the padded one of an odd count) and its V tile
         const int c16z = (lz >> 4) & 1, j16z = lz & 15, hhz = lz >> 5;
         const char* ldsV = ldsVb[vlast];
         auto ldVz = [&](int i, int half) -> s16x4 {

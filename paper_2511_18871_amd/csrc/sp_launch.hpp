@@ -79,12 +79,12 @@ hipError_t launch_prepare(const int32_t* host_words, int n_words, int* dev_tab, 
                           int tag_mode, bool with_schedule, int n_groups, int64_t total_tokens, int n256, int n128,
                           const Schedule& sched, hipStream_t s);
 
-// Packings whose 256-row workgroups would run fewer 64-key steps than this on average take the kernels'
-// 128-row shape (two workgroups per CU).  SP_ATTN_SMALL_STEPS overrides the default, for measurements.
+// The threshold of sp_attn_set_small_shape_steps(), or < 0: the rule of use_small_shape().
 int small_shape_steps();
 
-// Number of 64-key steps that the workgroups of this packing run with row tiles of `bm` rows (per q head; host
-// arithmetic on the segment table), and the number of such workgroups.
+// Number of (row tile of `bm` rows, 64-key tile) pairs of one q head that hold an allowed pair, and of row tiles (host
+// arithmetic on the segment table).  With one q head per kv head these are the steps and the workgroups that run; with
+// more, a workgroup spans fewer rows (wave_rows() in sp_common.hpp) and skips most of what only other rows see.
 inline void key_steps(const Problem& p, int bm, int64_t& steps, int64_t& tiles) {
     const int32_t* tab = p.host_table;
     steps = 0; tiles = 0;
@@ -107,12 +107,17 @@ inline void key_steps(const Problem& p, int bm, int64_t& steps, int64_t& tiles) 
     }
 }
 
-// Which workgroup shape the forward and the dq pass take.  The 128-row shape executes less work that no row
-// of a tile needs (fewer rows ride along through the key tiles of other responses and past their own
-// diagonal) and overlaps the fixed costs of two workgroups per CU, but pays for it: twice the tile copies per
-// MFMA and a barrier per step.  Measured on packings from 3 K to 270 K tokens the price is about 3 % of
-// the loop, so the small shape is taken when it saves more executed steps than that.  The knob, when set,
-// replaces the rule by a threshold on the mean number of steps of a 256-row workgroup.
+// Which workgroup shape the forward and the dq pass take: four waves where row tiles of 128 rows need more than 3 % fewer
+// steps than tiles of 256.  Those are not the steps that run (with four to seven q heads per kv head the shapes differ by 1 to
+// 3 % of them); the share says how short and ragged a packing's segments are, and with that how much of a workgroup's life is
+// fixed cost, which the four-wave shape hides behind the CU's other workgroup.  Its price is twice the tile copies
+// per MFMA and a barrier per step.  Both shapes timed on 9 workloads and 51 drawn packings, 354 to 265 K tokens, 28/4 to
+// 40/8 and 4/2 heads (time with eight waves over time with four; forward, dq pass):
+//   no more than 3 % saved    0.97 .. 1.01, 1.00 .. 1.03      (16K prompt and short answers 0.971, 0.996)
+//   3 to 8 % saved            0.95 .. 1.34, 1.01 .. 1.32      (response rows under an 8K prompt 0.954, 1.023)
+//   more                      1.02 .. 1.40, 1.02 .. 1.38
+// The shape taken is on average 0.1 % (forward) and 0.04 % (dq) from the faster one, at worst 4.8 % (the response rows).
+// The knob, when set, replaces the rule by a threshold on the mean number of steps of a 256-row tile.
 inline bool use_small_shape(const Problem& p) {
     int64_t s256, t256, s128, t128;
     key_steps(p, 256, s256, t256);
