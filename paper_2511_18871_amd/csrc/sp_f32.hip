@@ -219,7 +219,7 @@ __global__ __launch_bounds__(256) void rowsum_bf16_kernel(const __bf16* __restri
 // each lane first needs a whole row of its own (dot_row: all loads ahead of the sums; the wave's own row x is uniform) and
 // then the wave a row per key, ROWS of them in flight (add_rows; with one in flight a chunk took 5 us).
 // Order of every sum as in the plain loops.  One box, a group of 64 + 4 x 32 tokens, 2 heads of 64, us before -> after:
-// forward 19.6 -> 10.5, dq 23.0 -> 12.6, dkdv 37.1 -> 23.3; backward of 1500 + 5 x 200 tokens, 4 heads of 128,
+// forward 19.6 -> 10.8, dq 23.0 -> 13.0, dkdv 37.1 -> 24.0; backward of 1500 + 5 x 200 tokens, 4 heads of 128,
 // 4.30 -> 3.29 ms (ROWS = 16: 3.56).
 constexpr int ROWS = 32;
 template <int DH>

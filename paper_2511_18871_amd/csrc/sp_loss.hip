@@ -26,7 +26,7 @@ template <> struct Ld<float> { typedef f32x4 vec; static constexpr int N = 4; };
 // vectors in flight.  A workgroup has LT threads: 1024 (few rows open at a time) for rows that fill them eight
 // times, else 256 or 64.  One box, 2048 rows of 151936 bf16 logits under 1024 prompt rows, forward + backward: 256
 // threads 165 + 268 us, 1024 threads 172 + 260, with stores that bypass the caches 98 + 270 (the forward no longer waits
-// for the write-back of the gradient before it; 6.4 and 5.8 TB/s).  Before: 147 + 396, the gradient filled with zeros first.
+// for the write-back of the gradient before it), with exponents of differences (below) 100 + 270 (6.2 and 5.8 TB/s).  Before: 147 + 396, the gradient filled with zeros first.
 constexpr int UNROLL = 2;
 template <typename T>
 struct RowSplit {
