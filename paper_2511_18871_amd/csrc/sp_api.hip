@@ -47,13 +47,14 @@ inline bool misaligned(const void* p) { return ((uintptr_t)p & 15) != 0; }
 
 // Bytes of the schedule region that follows the table: key_lo and row_hi per token, then the tile
 // descriptors (sized by upper bounds on the tile counts, so that it depends on the totals alone).
-struct SchedLayout { size_t key_lo, row_hi, tiles256, tiles128, bytes; };
+struct SchedLayout { size_t key_lo, row_hi, tiles256, tiles128, key_tiles, bytes; };
 SchedLayout sched_layout(int64_t total_tokens, int32_t n_groups) {
     SchedLayout s{};
     const size_t per_tok = align256((size_t)total_tokens * 4);
     const size_t b256 = align256(((size_t)total_tokens / 256 + (size_t)n_groups + 1) * sizeof(sp::TileDesc));
     const size_t b128 = align256(((size_t)total_tokens / 128 + (size_t)n_groups + 1) * sizeof(sp::TileDesc));
-    s.key_lo = 0; s.row_hi = per_tok; s.tiles256 = 2 * per_tok; s.tiles128 = s.tiles256 + b256; s.bytes = s.tiles128 + b128;
+    s.key_lo = 0; s.row_hi = per_tok; s.tiles256 = 2 * per_tok; s.tiles128 = s.tiles256 + b256;
+    s.key_tiles = s.tiles128 + b128; s.bytes = s.key_tiles + b128;
     return s;
 }
 
@@ -192,7 +193,8 @@ sp_status run(bool bwd, const void* q, const void* k, const void* v, const void*
     char* const sched_base = (char*)workspace + TAG_BYTES + align256(L.words.size() * 4);
     const SchedLayout sl = sched_layout(L.total_tokens, n_groups);
     p.sched = sp::Schedule{(const sp::TileDesc*)(sched_base + sl.tiles256), (const sp::TileDesc*)(sched_base + sl.tiles128),
-                           (const int*)(sched_base + sl.key_lo), (const int*)(sched_base + sl.row_hi)};
+                           (const sp::TileDesc*)(sched_base + sl.key_tiles), (const int*)(sched_base + sl.key_lo),
+                           (const int*)(sched_base + sl.row_hi)};
     p.Dbuf = (float*)(sched_base + sl.bytes);
     p.dkdv_partial = (bwd && dtype == SP_BF16 && sp::dkdv_head_split(L.total_tokens, n_groups, Hq, Hkv))
                          ? (float*)((char*)p.Dbuf + align256((size_t)Hq * (size_t)L.total_tokens * 8)) : nullptr;
@@ -212,9 +214,11 @@ sp_status run(bool bwd, const void* q, const void* k, const void* v, const void*
     p.host_table = L.words.data();
 
     p.n_tiles256 = sp::count_tiles(p, 256); p.n_tiles128 = sp::count_tiles(p, 128);
+    const int key_order = bwd && dtype == SP_BF16 && (stages & SP_BWD_STAGE_DKDV) ? sp::key_order(p) : sp::KEYS_AS_PACKED;
+    if (key_order == sp::KEYS_AS_PACKED) p.sched.key_tiles = p.sched.tiles128;
     hipError_t e = sp::launch_prepare(L.words.data(), (int)L.words.size(), table_of(workspace), (uint32_t*)workspace, tag,
                                       keep_tag ? sp::TAG_KEEP : tag_mode, dtype == SP_BF16, n_groups, L.total_tokens,
-                                      p.n_tiles256, p.n_tiles128, p.sched, s);
+                                      p.n_tiles256, p.n_tiles128, p.sched, key_order, s);
     if (e == hipSuccess) {
         if (dtype == SP_BF16) e = bwd ? sp::launch_bwd_bf16(p, s) : sp::launch_fwd_bf16(p, s);
         else e = bwd ? sp::launch_bwd_f32(p, s) : sp::launch_fwd_f32(p, s);
@@ -357,11 +361,12 @@ sp_status sp_attn_fwd_multi(int32_t n_sets, const void* const* q, const void* co
     char* const sched_base = (char*)workspace + TAG_BYTES + align256(L.words.size() * 4);
     const SchedLayout sl = sched_layout(L.total_tokens, n_groups);
     p.sched = sp::Schedule{(const sp::TileDesc*)(sched_base + sl.tiles256), (const sp::TileDesc*)(sched_base + sl.tiles128),
-                           (const int*)(sched_base + sl.key_lo), (const int*)(sched_base + sl.row_hi)};
+                           (const sp::TileDesc*)(sched_base + sl.key_tiles), (const int*)(sched_base + sl.key_lo),
+                           (const int*)(sched_base + sl.row_hi)};
     p.n_tiles256 = sp::count_tiles(p, 256); p.n_tiles128 = sp::count_tiles(p, 128);
     hipError_t e = sp::launch_prepare(L.words.data(), (int)L.words.size(), table_of(workspace), (uint32_t*)workspace,
                                       sp::ReserveTag{}, sp::TAG_CLEAR, dtype == SP_BF16, n_groups, L.total_tokens,
-                                      p.n_tiles256, p.n_tiles128, p.sched, s);
+                                      p.n_tiles256, p.n_tiles128, p.sched, sp::KEYS_AS_PACKED, s);
     if (e == hipSuccess) {
         if (dtype == SP_BF16) {
             p.n_sets = n_sets;
@@ -402,7 +407,7 @@ sp_status rope_call(const void* x, void* y, int32_t H, const void* x2, void* y2,
                     workspace_bytes, need);
     hipStream_t s = (hipStream_t)stream;
     hipError_t e = sp::launch_prepare(L.words.data(), (int)L.words.size(), table_of(workspace), (uint32_t*)workspace,
-                                      sp::ReserveTag{}, sp::TAG_CLEAR, false, n_groups, L.total_tokens, 0, 0, sp::Schedule{}, s);
+                                      sp::ReserveTag{}, sp::TAG_CLEAR, false, n_groups, L.total_tokens, 0, 0, sp::Schedule{}, sp::KEYS_AS_PACKED, s);
     if (e == hipSuccess)
         e = sp::launch_rope(x, y, H, x2, y2, H2, table_of(workspace), L.total_tokens, head_dim, rope_base, inverse != 0,
                             dtype == SP_F32, s);
@@ -445,7 +450,7 @@ sp_status loss_setup(int32_t n_groups, const int32_t* prompt_lens, const int32_t
                     workspace_bytes, need);
     *scratch = (float*)((char*)workspace + TAG_BYTES + align256(L.words.size() * 4));
     hipError_t e = sp::launch_prepare(L.words.data(), (int)L.words.size(), table_of(workspace), (uint32_t*)workspace,
-                                      sp::ReserveTag{}, sp::TAG_CLEAR, false, n_groups, L.total_tokens, 0, 0, sp::Schedule{}, s);
+                                      sp::ReserveTag{}, sp::TAG_CLEAR, false, n_groups, L.total_tokens, 0, 0, sp::Schedule{}, sp::KEYS_AS_PACKED, s);
     if (e != hipSuccess) return fail(SP_ERR_DEVICE, "HIP launch failed: %s", hipGetErrorString(e));
     return SP_OK;
 }

@@ -954,8 +954,7 @@ __global__ __launch_bounds__(64 * NW, 2) void bwd_dkdv_kernel(BwdArgs a) {
         kvh = head / (a.Hq / a.Hkv);
         hr_only = head % (a.Hq / a.Hkv);
     } else if (!decode_item(blockIdx.x, a.n_tiles, a.Hkv, a.Hkv, tile, kvh)) return;
-    // key tiles in ascending order: the first prompt tile is seen by every row (most work)
-    dkdv_body<NW>(a, a.sched.tiles128[tile], kvh, hr_only);
+    dkdv_body<NW>(a, a.sched.key_tiles[tile], kvh, hr_only);
 }
 
 // Second stage of the head-split dkdv pass: dk = scale * sum_hr partial[0][hr], dv = sum_hr
@@ -996,7 +995,9 @@ __global__ __launch_bounds__(256) void dkdv_reduce_kernel(const float* __restric
 // Measured on 439 packings of 96 to 2600 workgroups (both shapes; one to 40 groups, 4/4 to 40/8 heads): the shape taken is
 // 0.3 % from the faster one on average (0.4 % on 138 more, drawn afterwards); four waves throughout 10 %, eight waves 2.9 %, a line by the number of
 // workgroups alone up to 24 % (a group of 9152 tokens, 28/4 heads, 288 workgroups: 1592 us with four waves, 1281 with
-// eight; nine groups of 1000, as many workgroups: 292 and 323).
+// eight; nine groups of 1000, as many workgroups: 292 and 323).  What is played is the packing's order; the launch itself
+// starts prompt tiles first (key_order()), which gains more than the choice of a shape: there, on 75 packings of more than 256
+// workgroups, the shape taken is 1.8 % from the faster one on average, four waves throughout 7.8 %, eight 7.2 %.
 int dkdv_waves(const Problem& p) {
     constexpr int SE = 4, CUS = 8;                             // of an XCD
     const int n_wgs = count_tiles(p, 128) * p.Hkv;

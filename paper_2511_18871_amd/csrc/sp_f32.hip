@@ -29,7 +29,8 @@ __global__ void upload_table_kernel(TabChunk chunk, int* __restrict__ dst, int o
 // One thread per packed token writes its segment bounds, one per work tile its descriptor (see Schedule).
 __device__ __forceinline__ void schedule_body(const int* __restrict__ tab, int n_groups, int64_t T_total, int n256,
                                               int n128, TileDesc* __restrict__ tiles256, TileDesc* __restrict__ tiles128,
-                                              int* __restrict__ key_lo, int* __restrict__ row_hi) {
+                                              TileDesc* __restrict__ key_tiles, int* __restrict__ key_lo,
+                                              int* __restrict__ row_hi, int key_order) {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i < T_total) {
         const GroupDesc gd = load_group(tab, find_group_of_token(tab, i));
@@ -44,24 +45,59 @@ __device__ __forceinline__ void schedule_body(const int* __restrict__ tab, int n
         key_lo[i] = lo;
         row_hi[i] = hi;
     }
-    auto describe = [&](auto bt_tag, int n, TileDesc* out) {
+    auto describe = [&](auto bt_tag, int n, TileDesc* out) -> TileDesc {
         constexpr int BT = decltype(bt_tag)::value;
-        if (i >= n) return;
-        int g, ti;
-        find_tile<BT>(tab, n_groups, (int)i, g, ti);
-        if (g < 0) g = n_groups - 1;                   // cannot happen: n is the exact tile count
-        const GroupDesc gd = load_group(tab, g);
-        out[i] = TileDesc{g, ti, gd.tok_base, gd.Lp, gd.Tg, 0, 0, 0};
+        TileDesc td{0, 0, 0, 0, 0, 0, 0, 0};
+        if (i >= n) return td;
+        find_tile<BT>(tab, n_groups, (int)i, td.g, td.ti);
+        if (td.g < 0) td.g = n_groups - 1;             // cannot happen: n is the exact tile count
+        const GroupDesc gd = load_group(tab, td.g);
+        td.tok_base = gd.tok_base; td.Lp = gd.Lp; td.Tg = gd.Tg;
+        out[i] = td;
+        return td;
     };
     describe(std::integral_constant<int, 256>{}, n256, tiles256);
-    describe(std::integral_constant<int, 128>{}, n128, tiles128);
+    if ((int64_t)blockIdx.x * 256 >= n128) return;     // the whole block
+    const TileDesc td = describe(std::integral_constant<int, 128>{}, n128, tiles128);
+    if (key_order == KEYS_AS_PACKED) return;
+    // place among the key tiles: the number of prompt tiles, and of those ahead of this block's first tile, by a strided
+    // sum over the groups; within the block by a scan
+    __shared__ int part[3][4], first[2];
+    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+    const bool prompt = i < n128 && 128 * td.ti < td.Lp;
+    if (threadIdx.x == 0) { first[0] = td.g; first[1] = min(td.ti, (td.Lp + 127) / 128); }
+    __syncthreads();
+    int before = 0, all = 0;
+    for (int g = threadIdx.x; g < n_groups; g += 256) {
+        const int c = (tab[TAB_HEADER + TAB_GROUP_WORDS * g + 1] + 127) / 128;
+        all += c;
+        before += g < first[0] ? c : 0;
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) { all += __shfl_xor(all, o, 64); before += __shfl_xor(before, o, 64); }
+    const uint64_t mine = __builtin_amdgcn_ballot_w64(prompt);
+    if (l == 0) { part[0][w] = all; part[1][w] = before; part[2][w] = __popcll(mine); }
+    __syncthreads();
+    const int n_prompt = part[0][0] + part[0][1] + part[0][2] + part[0][3];
+    int rank = first[1] + part[1][0] + part[1][1] + part[1][2] + part[1][3] + __popcll(mine & ((1ull << l) - 1));
+    for (int v = 0; v < w; ++v) rank += part[2][v];    // prompt tiles ahead of tile i
+    int at = prompt ? rank : n_prompt + (int)i - rank;
+    if (prompt && key_order == KEYS_BY_ROWS) {         // prompt tiles with more rows, or as many in an earlier group
+        at = 0;
+        for (int g = 0; g < n_groups; ++g) {
+            const int* e = tab + TAB_HEADER + TAB_GROUP_WORDS * g;
+            const int more = e[2] - (td.Tg - 128 * td.ti) + (g < td.g ? 1 : 0);
+            at += min((e[1] + 127) / 128, max(0, (more + 127) / 128));
+        }
+    }
+    if (i < n128) key_tiles[at] = td;
 }
 
 __global__ __launch_bounds__(256) void schedule_kernel(const int* __restrict__ tab, int n_groups, int64_t T_total,
                                                        int n256, int n128, TileDesc* __restrict__ tiles256,
-                                                       TileDesc* __restrict__ tiles128, int* __restrict__ key_lo,
-                                                       int* __restrict__ row_hi) {
-    schedule_body(tab, n_groups, T_total, n256, n128, tiles256, tiles128, key_lo, row_hi);
+                                                       TileDesc* __restrict__ tiles128, TileDesc* __restrict__ key_tiles,
+                                                       int* __restrict__ key_lo, int* __restrict__ row_hi, int key_order) {
+    schedule_body(tab, n_groups, T_total, n256, n128, tiles256, tiles128, key_tiles, key_lo, row_hi, key_order);
 }
 
 // Tag block maintenance, one wave.  See sp_launch.hpp for the modes.  A reserve written for all rows
@@ -91,8 +127,8 @@ __global__ __launch_bounds__(256) void prepare_kernel(PrepChunk chunk, int n_wor
                                                       uint32_t* __restrict__ tag_blk, ReserveTag want, int tag_mode,
                                                       int with_schedule, int n_groups, int64_t T_total, int n256,
                                                       int n128, TileDesc* __restrict__ tiles256,
-                                                      TileDesc* __restrict__ tiles128, int* __restrict__ key_lo,
-                                                      int* __restrict__ row_hi) {
+                                                      TileDesc* __restrict__ tiles128, TileDesc* __restrict__ key_tiles,
+                                                      int* __restrict__ key_lo, int* __restrict__ row_hi, int key_order) {
     __shared__ int tab_s[PREP_WORDS];
     for (int i = threadIdx.x; i < n_words; i += 256) {
         const int x = chunk.w[i];
@@ -101,7 +137,7 @@ __global__ __launch_bounds__(256) void prepare_kernel(PrepChunk chunk, int n_wor
     }
     if (blockIdx.x == 0 && threadIdx.x < 64 && tag_mode != TAG_KEEP) reserve_tag_body(tag_blk, want, tag_mode);
     __syncthreads();
-    if (with_schedule) schedule_body(tab_s, n_groups, T_total, n256, n128, tiles256, tiles128, key_lo, row_hi);
+    if (with_schedule) schedule_body(tab_s, n_groups, T_total, n256, n128, tiles256, tiles128, key_tiles, key_lo, row_hi, key_order);
 }
 
 template <typename T>
@@ -426,9 +462,10 @@ inline int blocks_for_waves(int64_t waves) { return (int)((waves + 3) / 4); }
 // block, else the tag kernel, the table in pieces and the schedule kernel.
 hipError_t launch_prepare(const int32_t* host_words, int n_words, int* dev_tab, uint32_t* tag_block, const ReserveTag& tag,
                           int tag_mode, bool with_schedule, int n_groups, int64_t total_tokens, int n256, int n128,
-                          const Schedule& sched, hipStream_t s) {
+                          const Schedule& sched, int key_order, hipStream_t s) {
     TileDesc* const t256 = (TileDesc*)sched.tiles256;
     TileDesc* const t128 = (TileDesc*)sched.tiles128;
+    TileDesc* const kt = (TileDesc*)sched.key_tiles;
     int* const key_lo = (int*)sched.key_lo;
     int* const row_hi = (int*)sched.row_hi;
     int64_t n = total_tokens;
@@ -440,7 +477,7 @@ hipError_t launch_prepare(const int32_t* host_words, int n_words, int* dev_tab, 
         for (int i = n_words; i < PREP_WORDS; ++i) c.w[i] = 0;
         hipLaunchKernelGGL(prepare_kernel, dim3(with_schedule ? sched_blocks : 1u), dim3(256), 0, s, c, n_words, dev_tab,
                            tag_block, tag, tag_mode, with_schedule ? 1 : 0, n_groups, total_tokens, n256, n128, t256, t128,
-                           key_lo, row_hi);
+                           kt, key_lo, row_hi, key_order);
         return hipGetLastError();
     }
     if (tag_mode != TAG_KEEP) {
@@ -459,7 +496,7 @@ hipError_t launch_prepare(const int32_t* host_words, int n_words, int* dev_tab, 
     }
     if (with_schedule)
         hipLaunchKernelGGL(schedule_kernel, dim3(sched_blocks), dim3(256), 0, s, (const int*)dev_tab, n_groups, total_tokens,
-                           n256, n128, t256, t128, key_lo, row_hi);
+                           n256, n128, t256, t128, kt, key_lo, row_hi, key_order);
     return hipGetLastError();
 }
 

@@ -75,9 +75,25 @@ hipError_t launch_logprob_bwd(const void* z, const int* y, const float* lse, con
 hipError_t launch_grpo(const float* logp, const float* old, const float* ref, const float* adv, float* g,
                        float* J, float* loss, const int* tab, int n_resp, int n_nonempty, float eps_low,
                        float eps_high, float beta, hipStream_t s);
+// Order of the key tiles (Schedule): the packing's, prompt tiles first group by group, or prompt tiles first by the rows that
+// see them, most first.  A dkdv workgroup of a prompt's first tile can run a hundred times as long as one of a response,
+// and in the packing's order the last group's starts when the rest of the launch is nearly through.  Sorted by rows they also
+// pair well on the CUs, but tiles of one group, which stream the same Q / dO rows, no longer run side by side.  dkdv
+// stage of 90 packings (10 to 7000 workgroups), geometric mean over the packing's order: group by group 0.906, by rows 0.896.
+// By rows over group by group: up to 1500 workgroups 0.73 .. 1.03, mean 0.955; 1600 to 2000 0.93 .. 1.07; beyond,
+// 1.00 .. 1.12 (64 groups of 1000 tokens: 28/4 heads, 2048 workgroups 936 and 990 us, packing's order 1178; 32/8 heads, 4096,
+// 1057 and 1183, 1188).  As built, 100 other packings: 0.903.  Four long prompts with 16 answers (32/8) 3690 -> 3556 us, 64
+// short ones (28/4) 4000 -> 3110.  Up to 256 workgroups all start at once, and one group's tiles are in order already.
+constexpr int KEYS_AS_PACKED = 0, KEYS_BY_GROUP = 1, KEYS_BY_ROWS = 2;
+inline int key_order(const Problem& p) {
+    const int64_t wgs = (int64_t)p.n_tiles128 * (p.dkdv_partial ? p.Hq : p.Hkv);
+    if (wgs <= 256 || p.n_groups == 1) return KEYS_AS_PACKED;
+    return wgs <= 1536 && p.n_groups <= 256 ? KEYS_BY_ROWS : KEYS_BY_GROUP;    // (a tile's place by rows is a loop over the groups)
+}
+
 hipError_t launch_prepare(const int32_t* host_words, int n_words, int* dev_tab, uint32_t* tag_block, const ReserveTag& tag,
                           int tag_mode, bool with_schedule, int n_groups, int64_t total_tokens, int n256, int n128,
-                          const Schedule& sched, hipStream_t s);
+                          const Schedule& sched, int key_order, hipStream_t s);
 
 // The threshold of sp_attn_set_small_shape_steps(), or < 0: the rule of use_small_shape().
 int small_shape_steps();
