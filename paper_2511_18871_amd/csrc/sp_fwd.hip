@@ -62,6 +62,12 @@ struct FwdArgs {
 // the buffer ring.  One box, before -> after, us: 64 groups of a short prompt and 16 answers 2674 -> 2349, 64 groups of
 // 1000 tokens 874 -> 789, three sets of eight 2K prompts 7560 -> 7290, four long prompts 1922 -> 1886, one short group
 // 17.9 -> 14.6, 16K prompt with 32 answers 4020 -> 3997.
+// Short key loops are bound by instruction issue, not by memory (64 groups of a short prompt and 16 answers, one wave's life of
+// 37 K cycles: lookups 4.7, first copies 3.4, 5.8 steps of 3.5, last product 1.8, stores 5.8; 2.9 TB/s).  The rows' own
+// segments are therefore walked from their first key on, not from the multiple of 64 below it (a quarter of a step less),
+// and what follows the loop takes its addresses from those of the loop or by one xor each (200 of 900 vector instructions
+// outside the loop).  One box, before -> after, us: that packing 2410 -> 2308, 64 groups of 1000 tokens 805 -> 784, three sets of
+// eight 2K prompts 7222 -> 7128, one short group 14.8 -> 14.0, 16K prompt 3913 -> 3910.
 // NAIVE = the measurement baseline (every tile at or below the packed diagonal, mask applied element by
 // element): a separate instantiation, so that it shows under its own name in kernel traces and its
 // branches cost the product kernel nothing.
@@ -116,19 +122,12 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd_kernel(FwdArgs a) {      // tw
         for (int ks = 0; ks < 8; ++ks) qreg[ks] = *reinterpret_cast<const bf16x8*>(qp + 16 * ks);
     }
 
-    int n1, k2b, k2e;
-    if (NAIVE) {
-        n1 = (t1 + BN - 1) / BN; k2b = k2e = n1;
-    } else {
-        n1 = (min(Lp, t1) + BN - 1) / BN;
-        k2b = k2e = n1;
-        if (t1 > Lp) {
-            k2b = max(n1, b2 / BN);
-            k2e = (t1 + BN - 1) / BN;
-        }
-    }
-    const int total = n1 + (k2e - k2b);
-    auto tile_at = [&](int it) { return it < n1 ? it : k2b + (it - n1); };
+    // key tiles: n1 from the group's first key on, then those of the rows' own segments, from k2 on: the first key of the
+    // first response row's segment, unless the prompt's last tile holds it
+    const int n1 = ((NAIVE ? t1 : min(Lp, t1)) + BN - 1) / BN;
+    const int k2 = max(n1 * BN, b2);
+    const int total = n1 + (NAIVE || t1 <= Lp ? 0 : max(t1 - k2 + BN - 1, 0) / BN);
+    auto key_at = [&](int it) { return it < n1 ? it * BN : k2 + (it - n1) * BN; };
 
     const int kvh = head / (a.Hq / a.Hkv);
     const int64_t kv_stride = (int64_t)a.Hkv * 128;
@@ -154,7 +153,6 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd_kernel(FwdArgs a) {      // tw
                (uint64_t)(unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)b);
     };
     const uint64_t kbase_s = sgpr64(kbase), vbase_s = sgpr64(vbase);
-    const unsigned tile_bytes = BN * stride_b;
     auto lds_u32 = [](char* p) -> unsigned {
         return __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)p);
     };
@@ -164,13 +162,13 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd_kernel(FwdArgs a) {      // tw
     for (int b = 0; b < NB; ++b) { m0K[b] = lds_u32(ldsKb[b]) + chunk0; m0V[b] = lds_u32(ldsVb[b]) + chunk0; }
     auto issue = [&](uint64_t base_s, unsigned m0dst, int it) {
         if (!copier || it >= total) return;
-        const int kt = tile_at(it);
-        const uint64_t tb = base_s + (uint64_t)(unsigned)kt * tile_bytes;
-        if (kt * BN + BN <= Tg) {
+        const int key0 = key_at(it);
+        const uint64_t tb = base_s + (uint64_t)(unsigned)key0 * stride_b;
+        if (key0 + BN <= Tg) {
 #pragma unroll
             for (int u = 0; u < 4; ++u) async_copy16_sm(tb, voff[u], m0dst + 1024u * u);
         } else {
-            const int last = Tg - 1 - kt * BN;
+            const int last = Tg - 1 - key0;
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 const int row = 4 * (4 * (w & 3) + u) + (l >> 4);
@@ -186,7 +184,7 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd_kernel(FwdArgs a) {      // tw
     auto needs_mask = [&](int it) -> bool {
         if (it < n_full) return false;
         if (it >= total || !wave_valid || NAIVE) return true;
-        const int s0 = tile_at(it) * BN;
+        const int s0 = key_at(it);
         return !((s0 + BN - 1 <= tw0) && (s0 + BN <= Lp || s0 >= st_last));
     };
 
@@ -246,7 +244,7 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd_kernel(FwdArgs a) {      // tw
             S[i >> 3] = mfma32(ldK(0, i), qreg[i & 7], (i & 7) == 0 ? zero16 : S[i >> 3]);
     };
     auto mask = [&](int it, f32x16 (&S)[2]) {
-        const int s0 = it < total ? tile_at(it) * BN : 0;
+        const int s0 = it < total ? key_at(it) : 0;
         const int tme = it < total ? tm : -1;
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb) {
@@ -280,7 +278,7 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd_kernel(FwdArgs a) {      // tw
         constexpr int R = decltype(par_tag)::value;
         constexpr bool SECOND = decltype(second_tag)::value, BRIDGE = decltype(bridge_tag)::value;
         constexpr int OFF = SECOND ? 32 % RD : 0;     // ring position of this step's first operand
-        if (needs_mask(j)) mask(j, Scur);
+        if (__builtin_expect(needs_mask(j), 0)) mask(j, Scur);
         __builtin_amdgcn_sched_barrier(0);
         const float mc = m * cs;
         float tsum = 0.f;          // this lane's half of the tile's row sum
@@ -320,7 +318,7 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd_kernel(FwdArgs a) {      // tw
         tsum += pe[31];
         pnew[15] = pack2(pe[30], pe[31]);
         tsr = sum2(pnew[15], tsr);
-        if (__builtin_amdgcn_ballot_w64(!(tsum <= P_LIMIT)) != 0) {
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(tsum <= P_LIMIT)) != 0, 0)) {
             float mx = Scur[0][0];
 #pragma unroll
             for (int e = 1; e < 32; ++e) mx = fmaxf(mx, Scur[e >> 4][e & 15]);
@@ -440,13 +438,12 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd_kernel(FwdArgs a) {      // tw
     int lz = l;
     asm volatile("" : "+v"(lz));
     {   // P of the last step that ran (eight waves: the padded one of an odd count) and its V tile
-        const int c16z = (lz >> 4) & 1, j16z = lz & 15, hhz = lz >> 5;
-        const char* ldsV = ldsVb[vlast];
-        auto ldVz = [&](int i, int half) -> s16x4 {
-            const int col4 = 32 * (i & 3) + 16 * c16z + 4 * (j16z & 3);
-            const int row4 = 32 * (i >> 3) + 16 * ((i >> 2) & 1) + 4 * hhz + (j16z >> 2) + 8 * half;
-            return lds_read_tr4(ldsV, row4, col4);
-        };
+        unsigned tv[4][2];
+#pragma unroll
+        for (int db = 0; db < 4; ++db)
+#pragma unroll
+            for (int half = 0; half < 2; ++half) tv[db][half] = trA[db][half] + TILE_BYTES * vlast;
+        auto ldVz = [&](int i, int half) -> s16x4 { return lds_at_tr4(tv[i & 3][half] + 4096 * (i >> 2)); };
         s16x4 rg[RD][2];
 #pragma unroll
         for (int i = 0; i < RD - 1; ++i) { rg[i][0] = ldVz(i, 0); rg[i][1] = ldVz(i, 1); }
@@ -470,38 +467,61 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd_kernel(FwdArgs a) {      // tw
     // its own 8 KB of LDS (swizzled like the operand tiles: two-way conflicts on the 8-byte writes,
     // which is their minimum, none on the 16-byte reads) and stores whole rows: 16 lanes per row,
     // four rows per instruction.  No workgroup barrier: a wave reads back only what it wrote.
-    char* const stage = ldsKb[0] + 8192 * w;
+    // Addresses: a granule's place is the row's base with the granule and the row's swizzle xored in, one instruction per access.
     const float inv = 1.0f / lrt;
-    auto store_rows = [&, c = lz & 31, hh = lz >> 5, l = lz](__bf16* dst, auto value) {
+    const unsigned stage = lds_u32(ldsKb[0]) + 8192u * w;
+    const unsigned putA = stage + 256u * (lz & 31) + 8u * (lz >> 5) + (swz(lz & 31) << 4);
+    const unsigned getA = stage + 256u * (lz >> 4) + (((lz & 15) ^ ((lz >> 4) << 2)) << 4);
+    const bool whole = tw0 + 32 <= Tg && !(a.resp_only && tw0 < Lp);
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    auto store_rows = [&](__bf16* dst, const unsigned (&x)[32]) {
 #pragma unroll
-        for (int db = 0; db < 4; ++db)
-#pragma unroll
-            for (int gq = 0; gq < 4; ++gq) {
-                bf16x4 x;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) x[e] = value(db, 4 * gq + e);
-                *reinterpret_cast<bf16x4*>(stage + tile_off(c, 4 * db + gq) + 8 * hh) = x;
-            }
+        for (int n = 0; n < 16; ++n)
+            *(__attribute__((address_space(3))) u32x2*)(uintptr_t)(putA ^ (n << 4)) = u32x2{x[2 * n], x[2 * n + 1]};
         // all eight reads first, then the stores (one LDS round trip instead of eight); the rows of one lane lie
         // four rows apart, so one 64-bit address and a constant stride serve all of them
-        bf16x8 x[8];
+        bf16x8 y[8];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) x[i] = lds_read_row8(stage, 4 * i + (l >> 4), l & 15);
+        for (int i = 0; i < 8; ++i) y[i] = lds_at_row8((getA ^ ((i & 3) << 4)) + 1024u * i);
         __builtin_amdgcn_sched_barrier(0);
-        __bf16* const p0 = dst + ((int64_t)(gd.tok_base + tw0 + (l >> 4)) * a.Hq + head) * 128 + 8 * (l & 15);
+        __bf16* const p0 = dst + ((int64_t)(gd.tok_base + tw0 + (lz >> 4)) * a.Hq + head) * 128 + 8 * (lz & 15);
         const int64_t stride = (int64_t)4 * a.Hq * 128;
+        if (whole) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int tr = tw0 + 4 * i + (l >> 4);
-            if (tr < Tg && !(a.resp_only && tr < Lp)) *reinterpret_cast<bf16x8*>(p0 + i * stride) = x[i];
+            for (int i = 0; i < 8; ++i) *reinterpret_cast<bf16x8*>(p0 + i * stride) = y[i];
+        } else {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int tr = tw0 + 4 * i + (lz >> 4);
+                if (tr < Tg && !(a.resp_only && tr < Lp)) *reinterpret_cast<bf16x8*>(p0 + i * stride) = y[i];
+            }
         }
     };
-    store_rows(ao, [&](int db, int r) { return (__bf16)(oacc[db][r] * inv); });
-    if (a.o_lo)              // what the rounding of o dropped: lets the backward form D from an unrounded o
-        store_rows(a.o_lo, [&](int db, int r) {
-            const float x = oacc[db][r] * inv;
-            return (__bf16)(x - (float)(__bf16)x);
-        });
+    unsigned ob[32];         // o in pairs: [8 db + 2 gq + e / 2]
+#pragma unroll
+    for (int n = 0; n < 32; ++n) {
+        f32x16& x = oacc[n >> 3];
+        const int r = 2 * (n & 7);
+        x[r] *= inv; x[r + 1] *= inv;
+        ob[n] = pack2(x[r], x[r + 1]);
+    }
+    store_rows(ao, ob);
+    if (a.o_lo) {            // what the rounding of o dropped: lets the backward form D from an unrounded o
+        // x - bf16(x), which is exact, as one dot product per element: the other half of the pair is multiplied by 0.  The
+        // pairs {-1, 0} and {0, -1} come from scalar registers: as an inline constant the first selects the wrong half
+        typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+        unsigned first_bits = 0xbf80u, second_bits = 0xbf800000u;
+        asm volatile("" : "+s"(first_bits), "+s"(second_bits));
+        const bf16x2 first = __builtin_bit_cast(bf16x2, first_bits), second = __builtin_bit_cast(bf16x2, second_bits);
+#pragma unroll
+        for (int n = 0; n < 32; ++n) {
+            const f32x16& x = oacc[n >> 3];
+            const int r = 2 * (n & 7);
+            const bf16x2 hi = __builtin_bit_cast(bf16x2, ob[n]);
+            ob[n] = pack2(__builtin_amdgcn_fdot2_f32_bf16(hi, first, x[r], false), __builtin_amdgcn_fdot2_f32_bf16(hi, second, x[r + 1], false));
+        }
+        store_rows(a.o_lo, ob);
+    }
     if (valid && !(a.resp_only && t < Lp) && hh == 0)
         alse[(int64_t)head * T_total + gd.tok_base + t] = (m * cs + __log2f(ltot)) * LN2;
 }
