@@ -64,6 +64,10 @@ struct BwdArgs {
 // and D, and dP starts at -D.  One box, before -> after, us: 16K prompt with 32 answers 5440 -> 5190, four long prompts
 // 2750 -> 2515, 64 groups of a short prompt and 16 answers 3640 -> 3110, 64 groups of 1000 tokens 1100 -> 990, response
 // rows under an 8K prompt 630 -> 545.
+// On short key loops a quarter of a wave's life was the prologue: six waits for memory behind one another (descriptor, segment
+// starts, reserve flag, q and dO, o and its residual, first keys), now two, and D by dot products of pairs (64 instructions for
+// 320).  With the forward's key tiles and addresses, us: 64 groups of a short prompt and 16 answers 2782 -> 2679, 64 groups of
+// 1000 tokens 981 -> 957, two small groups 20.6 -> 19.8, four long prompts 2442 -> 2434, 16K prompt 5192 -> 5225.
 template <int NW>
 __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(BwdArgs a, EdgeArgs edge, int short_blocks, int row_blocks) {
     constexpr int BM = 32 * NW, BN = 64;
@@ -73,7 +77,8 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(BwdArgs a, EdgeArgs 
     constexpr int NSLOT = NW == 8 ? 3 : 4;
     constexpr int SLOT_BYTES = NW == 8 ? 2 * TILE_BYTES : TILE_BYTES;       // [K | V] of 64 keys, or of 32
     constexpr int V_OFF = SLOT_BYTES / 2;                                    // where V starts inside a slot
-    __shared__ __attribute__((aligned(1024))) char lds[NSLOT][SLOT_BYTES];
+    // (one slot more than the ring: the rows come in through all but slot 0, into which the first keys are copied meanwhile)
+    __shared__ __attribute__((aligned(1024))) char lds[NSLOT + 1][SLOT_BYTES];
 
     // Workgroups ahead of the row tiles' (a multiple of 8, so that those keep their XCDs) or, NW = 8, behind them: the rows
     // that see at most EDGE_LEN keys, two waves per (segment, q head).  As a launch of their own they had the chip to
@@ -112,11 +117,14 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(BwdArgs a, EdgeArgs 
     const int tm = valid ? t : -1;
     const bool wave_valid = tw0 < Tg;
     const int tw1 = min(tw0 + 31, Tg - 1);
-    // first own-segment key of this lane's row and of the workgroup's first response row (0 on the prompt)
-    const int st = valid ? a.sched.key_lo[gd.tok_base + t] : 0;
-    const int b2 = __builtin_amdgcn_readfirstlane(a.sched.key_lo[gd.tok_base + min(max(t0, Lp), Tg - 1)]);
-    // lanes 0..31 hold the wave's rows in order: the last valid row's start comes from its lane
-    const int st_last = wave_valid ? __builtin_amdgcn_readlane(st, tw1 - tw0) : 0;
+    // What the rows' own words say is loaded ahead of everything and looked at behind the issue of the rows: a wait for each
+    // of them in turn was a quarter of the prologue.
+    const int64_t row_word = (int64_t)head * T_total + gd.tok_base + min(t, Tg - 1);
+    const int st_word = a.sched.key_lo[gd.tok_base + min(t, Tg - 1)];
+    const int b2_word = a.sched.key_lo[gd.tok_base + min(max(t0, Lp), Tg - 1)];
+    const float lse_word = a.lse[row_word], nD_word = a.fused_rowsum ? 0.f : a.nD[row_word];
+    const bool have_lo = a.fused_rowsum && a.o_lo != nullptr;
+    const uint32_t lo_word = have_lo && a.lo_flag != nullptr ? *a.lo_flag : 1u;
 
     auto sgpr64 = [](const void* p) -> uint64_t {
         const uint64_t b = (uint64_t)(uintptr_t)p;
@@ -126,117 +134,6 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(BwdArgs a, EdgeArgs 
     auto lds_u32 = [](char* p) -> unsigned {
         return __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)p);
     };
-
-    // The wave's rows of q and dO (and of o and its residual for the folded rowsum) in MFMA operand layout.
-    // Loaded straight from memory in that layout an instruction touches 32 rows and uses 32 bytes of each,
-    // and the 32 such instructions of a wave are bound by the address unit: a quarter of a 128-row workgroup's
-    // life on short key loops.  They come in like the K/V tiles instead: copied row-contiguous (four whole
-    // rows per instruction) into the wave's own share of the not yet used tile ring, swizzled, and read back
-    // with the operand reads of a K tile.  The share holds TPR tensors of 32 rows at a time.  Rows past the
-    // end of the group read the group's last row: their scores are all masked (P = dS = 0 whatever q and dO
-    // hold, and a non-finite dO there only reaches dq rows that are not stored).
-    constexpr int SHARE = NSLOT * SLOT_BYTES / NW;          // 16 KB (NW = 4), 12 KB (NW = 8)
-    constexpr int TPR = SHARE / 8192;
-    char* const stg = &lds[0][0] + SHARE * w;
-    const int rbase = min(tw0, Tg - 1), rlast = Tg - 1 - rbase;
-    auto stage_rows = [&](const __bf16* tensor, int slot) {
-        const uint64_t sb = sgpr64(tensor + ((int64_t)(gd.tok_base + rbase) * a.Hq + head) * 128);
-        const unsigned m0 = lds_u32(stg) + 8192u * slot;
-        const unsigned row_bytes = (unsigned)a.Hq * 256u;
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int row = 4 * u + (l >> 4);
-            async_copy16_sm(sb, (unsigned)min(row, rlast) * row_bytes + (((l & 15) ^ swz(row)) << 4), m0 + 1024u * u);
-        }
-    };
-    auto read_rows = [&](int slot, bf16x8 (&r)[8]) {
-        asm volatile("" ::: "memory");              // the reads stay behind the wait for the copies
-#pragma unroll
-        for (int ks = 0; ks < 8; ++ks) r[ks] = lds_read_row8(stg + 8192 * slot, c, 2 * ks + hh);
-    };
-    auto lds_reads_done = [] { __builtin_amdgcn_s_waitcnt(0xC07F); };     // lgkmcnt(0): the share may be overwritten
-
-    bf16x8 qreg[8], goreg[8];
-    float Lq = 0.f, Dq = 0.f;
-    {
-        // whether the forward's rounding residual is valid: one word, read ahead of the copies so that its wait
-        // is theirs
-        const bool use_lo = a.fused_rowsum && a.o_lo != nullptr &&
-                            (a.lo_flag == nullptr || __builtin_amdgcn_readfirstlane((int)*a.lo_flag) != 0);
-        float lse_row = 0.f;
-        if (valid) {
-            lse_row = a.lse[(int64_t)head * T_total + gd.tok_base + t];
-            if (!a.fused_rowsum) Dq = -a.nD[(int64_t)head * T_total + gd.tok_base + t];
-        }
-        stage_rows(a.q, 0);
-        if constexpr (TPR == 2) {
-            stage_rows(a.d_o, 1);
-            wait_vm0();
-            read_rows(0, qreg);
-            read_rows(1, goreg);
-        } else {
-            wait_vm0();
-            read_rows(0, qreg);
-            lds_reads_done();
-            stage_rows(a.d_o, 0);
-            wait_vm0();
-            read_rows(0, goreg);
-        }
-        if (a.fused_rowsum) {
-            // The arithmetic of rowsum_bf16_kernel, operation for operation, so that a backward in one call
-            // and a staged one agree bit for bit: that kernel gives a row to 16 lanes of 8 elements each
-            // (lane `sub` = elements 8 sub .. 8 sub + 7, summed in order by fma) and adds the lanes in an
-            // xor-shuffle tree (8, 4, 2, 1).  This lane holds the chunks sub = 2 ks + hh, so the first three
-            // levels are sums inside the lane and the last one is the exchange with the row's other lane.
-            bf16x8 oreg[8], lreg[8];
-            lds_reads_done();
-            stage_rows(a.o, 0);
-            if constexpr (TPR == 2) {
-                if (use_lo) stage_rows(a.o_lo, 1);
-                wait_vm0();
-                read_rows(0, oreg);
-                if (use_lo) read_rows(1, lreg);
-            } else {
-                wait_vm0();
-                read_rows(0, oreg);
-                if (use_lo) {
-                    lds_reads_done();
-                    stage_rows(a.o_lo, 0);
-                    wait_vm0();
-                    read_rows(0, lreg);
-                }
-            }
-            float ch[8];
-#pragma unroll
-            for (int ks = 0; ks < 8; ++ks) {
-                float acc1 = 0.f;
-                if (use_lo) {
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) acc1 = __builtin_fmaf((float)goreg[ks][e], (float)oreg[ks][e] + (float)lreg[ks][e], acc1);
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) acc1 = __builtin_fmaf((float)goreg[ks][e], (float)oreg[ks][e], acc1);
-                }
-                ch[ks] = acc1;
-            }
-            const float x0 = ch[0] + ch[4], x1 = ch[1] + ch[5], x2 = ch[2] + ch[6], x3 = ch[3] + ch[7];
-            const float y0 = x0 + x2, y1 = x1 + x3;
-            Dq = pair_sum(y0 + y1);
-            if (!valid) Dq = 0.f;
-        }
-        Lq = lse_row * LOG2E;
-        if (a.fused_rowsum && valid && hh == 0) a.L2[(int64_t)head * T_total + gd.tok_base + t] = Lq;
-        // the shares overlap the ring slots that the first tile copies (of other waves, too) are about to fill
-        lds_reads_done();
-        __syncthreads();
-    }
-
-    int n1 = (min(Lp, t1) + BN - 1) / BN, k2b = n1, k2e = n1;
-    if (t1 > Lp) {
-        k2b = max(n1, b2 / BN);
-        k2e = (t1 + BN - 1) / BN;
-    }
-    const int total = n1 + (k2e - k2b);
 
     const int kvh = head / (a.Hq / a.Hkv);
     const int64_t kv_stride = (int64_t)a.Hkv * 128;
@@ -262,13 +159,8 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(BwdArgs a, EdgeArgs 
     unsigned m0slot[NSLOT];
 #pragma unroll
     for (int i = 0; i < NSLOT; ++i) m0slot[i] = lds_u32(lds[i]) + 1024u * NCH * (w & 3);
-    auto tile_at = [&](int it) { return it < n1 ? it : k2b + (it - n1); };
-    // NW = 8: `it` counts 64-key tiles; NW = 4: halves of them (32 keys), each into a slot of its own
-    auto issue = [&](int it, int slot) {
-        if (!copier || it >= (NW == 8 ? total : 2 * total)) return;
-        // first key of the slot; the second half of a group's last tile may lie wholly past the group's end: it
-        // is then read from the group's last row on (every offset below stays non-negative)
-        const int key0 = min(NW == 8 ? tile_at(it) * BN : tile_at(it >> 1) * BN + 32 * (it & 1), Tg - 1);
+    // copies a slot's keys, from key0 on
+    auto copy_keys = [&](int key0, int slot) {
         constexpr int ROWS = NW == 8 ? BN : 32;
         const uint64_t off = (uint64_t)(unsigned)key0 * stride_b;
         const unsigned m0 = m0slot[slot];
@@ -287,6 +179,125 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(BwdArgs a, EdgeArgs 
                 async_copy16_sm(vbase_s + off, vo, m0 + V_OFF + 1024u * u);
             }
         }
+    };
+    // the first keys under a prompt are known without a look at the rows' segments
+    const int n1 = (min(Lp, t1) + BN - 1) / BN;
+    if (copier && n1 > 0) copy_keys(0, 0);
+
+    // The wave's rows of q and dO (and of o and its residual for the folded rowsum) in MFMA operand layout.
+    // Loaded straight from memory in that layout an instruction touches 32 rows and uses 32 bytes of each,
+    // and the 32 such instructions of a wave are bound by the address unit: a quarter of a 128-row workgroup's
+    // life on short key loops.  They come in like the K/V tiles instead: copied row-contiguous (four whole
+    // rows per instruction) into the wave's own share of the not yet used tile ring, swizzled, and read back
+    // with the operand reads of a K tile.  The share holds TPR tensors of 32 rows at a time; the others are loaded
+    // meanwhile, row-contiguous too, into registers that the accumulators need only later, and pass through the share
+    // afterwards: the prologue waits for memory once.  Rows past the
+    // end of the group read the group's last row: their scores are all masked (P = dS = 0 whatever q and dO
+    // hold, and a non-finite dO there only reaches dq rows that are not stored).
+    constexpr int SHARE = NSLOT * SLOT_BYTES / NW;          // 16 KB (NW = 4), 12 KB (NW = 8)
+    constexpr int TPR = SHARE / 8192;
+    char* const stg = &lds[1][0] + SHARE * w;
+    const int rbase = min(tw0, Tg - 1), rlast = Tg - 1 - rbase;
+    auto stage_rows = [&](const __bf16* tensor, int slot) {
+        const uint64_t sb = sgpr64(tensor + ((int64_t)(gd.tok_base + rbase) * a.Hq + head) * 128);
+        const unsigned m0 = lds_u32(stg) + 8192u * slot;
+        const unsigned row_bytes = (unsigned)a.Hq * 256u;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int row = 4 * u + (l >> 4);
+            async_copy16_sm(sb, (unsigned)min(row, rlast) * row_bytes + (((l & 15) ^ swz(row)) << 4), m0 + 1024u * u);
+        }
+    };
+    auto load_rows = [&](const __bf16* tensor, i32x4 (&r)[8]) {
+        const char* const p = reinterpret_cast<const char*>(tensor + ((int64_t)(gd.tok_base + rbase) * a.Hq + head) * 128);
+        const unsigned row_bytes = (unsigned)a.Hq * 256u;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int row = 4 * u + (l >> 4);
+            r[u] = *reinterpret_cast<const i32x4*>(p + ((unsigned)min(row, rlast) * row_bytes + (((l & 15) ^ swz(row)) << 4)));
+        }
+    };
+    auto put_rows = [&](const i32x4 (&r)[8], int slot) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) *reinterpret_cast<i32x4*>(stg + 8192 * slot + 1024 * u + 16 * l) = r[u];
+    };
+    auto read_rows = [&](int slot, bf16x8 (&r)[8]) {
+        asm volatile("" ::: "memory");              // the reads stay behind the wait for the copies
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) r[ks] = lds_read_row8(stg + 8192 * slot, c, 2 * ks + hh);
+    };
+    auto lds_reads_done = [] { __builtin_amdgcn_s_waitcnt(0xC07F); };     // lgkmcnt(0): the share may be overwritten
+
+    bf16x8 qreg[8], goreg[8];
+    float Lq = 0.f, Dq = 0.f;
+    {
+        i32x4 gotmp[8], otmp[8], ltmp[8];
+        stage_rows(a.q, 0);
+        if constexpr (TPR == 2) stage_rows(a.d_o, 1);
+        else load_rows(a.d_o, gotmp);
+        if (a.fused_rowsum) load_rows(a.o, otmp);
+        if (have_lo) load_rows(a.o_lo, ltmp);
+        wait_vm0();
+        read_rows(0, qreg);
+        if constexpr (TPR == 2) {
+            read_rows(1, goreg);
+        } else {
+            lds_reads_done();
+            put_rows(gotmp, 0);
+            read_rows(0, goreg);
+        }
+        if (a.fused_rowsum) {
+            // The arithmetic of rowsum_bf16_kernel, operation for operation, so that a backward in one call
+            // and a staged one agree bit for bit: that kernel gives a row to 16 lanes of 8 elements each
+            // (lane `sub` = elements 8 sub .. 8 sub + 7: dO . o, then dO . residual, dot8()) and adds the lanes in an
+            // xor-shuffle tree (8, 4, 2, 1).  This lane holds the chunks sub = 2 ks + hh, so the first three
+            // levels are sums inside the lane and the last one is the exchange with the row's other lane.
+            const bool use_lo = have_lo && __builtin_amdgcn_readfirstlane((int)lo_word) != 0;
+            bf16x8 oreg[8], lreg[8];
+            float ch[8];
+            lds_reads_done();
+            put_rows(otmp, 0);
+            if (TPR == 2 && use_lo) put_rows(ltmp, 1);
+            read_rows(0, oreg);
+#pragma unroll
+            for (int ks = 0; ks < 8; ++ks) ch[ks] = dot8(goreg[ks], oreg[ks], 0.f);
+            if (use_lo) {
+                if constexpr (TPR == 1) {
+                    lds_reads_done();
+                    put_rows(ltmp, 0);
+                }
+                read_rows(TPR - 1, lreg);
+#pragma unroll
+                for (int ks = 0; ks < 8; ++ks) ch[ks] = dot8(goreg[ks], lreg[ks], ch[ks]);
+            }
+            const float x0 = ch[0] + ch[4], x1 = ch[1] + ch[5], x2 = ch[2] + ch[6], x3 = ch[3] + ch[7];
+            const float y0 = x0 + x2, y1 = x1 + x3;
+            Dq = pair_sum(y0 + y1);
+        } else {
+            Dq = -nD_word;
+        }
+        if (!valid) Dq = 0.f;
+        Lq = valid ? lse_word * LOG2E : 0.f;
+        if (a.fused_rowsum && valid && hh == 0) a.L2[row_word] = Lq;
+        // the shares overlap the ring slots that the first tile copies (of other waves, too) are about to fill
+        lds_reads_done();
+        __syncthreads();
+    }
+    // first own-segment key of this lane's row and of the workgroup's first response row (0 on the prompt)
+    const int st = valid ? st_word : 0;
+    const int b2 = __builtin_amdgcn_readfirstlane(b2_word);
+    // lanes 0..31 hold the wave's rows in order: the last valid row's start comes from its lane
+    const int st_last = wave_valid ? __builtin_amdgcn_readlane(st, tw1 - tw0) : 0;
+
+    // key tiles as in the forward: n1 from the group's first key on, then from k2 on
+    const int k2 = max(n1 * BN, b2);
+    const int total = n1 + (t1 <= Lp ? 0 : max(t1 - k2 + BN - 1, 0) / BN);
+    auto key_at = [&](int it) { return it < n1 ? it * BN : k2 + (it - n1) * BN; };
+    // NW = 8: `it` counts 64-key tiles; NW = 4: halves of them (32 keys), each into a slot of its own.  The second half of a
+    // group's last tile may lie wholly past the group's end: it is then read from the group's last row on
+    auto issue = [&](int it, int slot) {
+        if (!copier || it >= (NW == 8 ? total : 2 * total)) return;
+        copy_keys(min(NW == 8 ? key_at(it) : key_at(it >> 1) + 32 * (it & 1), Tg - 1), slot);
     };
 
     f32x16 acc[4];
@@ -312,7 +323,7 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(BwdArgs a, EdgeArgs 
     // pipeline body is the same for every tile; what the last stage computes of the half past the last one is
     // not used.
     const int H = 2 * total;
-    auto s0_of = [&](int h) { return tile_at(h >> 1) * BN + 32 * (h & 1); };
+    auto s0_of = [&](int h) { return key_at(h >> 1) + 32 * (h & 1); };
     auto needs_mask = [&](int h) -> bool {
         if (h >= H) return false;
         if (!wave_valid) return true;
@@ -413,11 +424,13 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(BwdArgs a, EdgeArgs 
 
     f32x16 SA, PA, SB, PB;
     if (total > 0) {
-        issue(0, 0);
+        if (n1 == 0) {
+            issue(0, 0);
+            wait_vm0();
+            __syncthreads();
+        }
         issue(1, 1);
         if constexpr (NW == 4) issue(2, 2);
-        wait_vm0();
-        __syncthreads();
         // M(0) and the first NE1 elements of V(0), unpipelined
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
@@ -438,7 +451,8 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(BwdArgs a, EdgeArgs 
         auto tile_stages = [&](int it, auto slot_tag) {
             constexpr int S = decltype(slot_tag)::value, S1 = (S + 1) % 3, S2 = (S + 2) % 3, HALF = 32 * 256;
             constexpr int A0 = S * SLOT_BYTES, A1 = A0 + HALF, A2 = S1 * SLOT_BYTES;       // halves 2 it, 2 it + 1, 2 it + 2
-            if (it > 0) { wait_vm0(); __syncthreads(); }
+            wait_vm0();
+            __syncthreads();
             prime(A1);
             issue(it + 2, S2);              // into the slot of tile it-1, which every wave has left
             stage(2 * it, SA, PA, SB, PB, std::integral_constant<int, A1>{}, std::integral_constant<int, A0>{},
@@ -461,7 +475,8 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(BwdArgs a, EdgeArgs 
         // vmcnt(0), measured the same: the other workgroup of the CU covers the wait.)
         auto half_stage = [&](int h, auto slot_tag, f32x16& Sc, f32x16& Pc, f32x16& Sn, f32x16& Pn) {
             constexpr int S = decltype(slot_tag)::value, A0 = S * SLOT_BYTES, A1 = ((S + 1) & 3) * SLOT_BYTES;
-            if (h > 0) { wait_vm0(); __syncthreads(); }
+            wait_vm0();
+            __syncthreads();
             prime(A1);
             issue(h + 3, (S + 3) & 3);
             stage(h, Sc, Pc, Sn, Pn, std::integral_constant<int, A1>{}, std::integral_constant<int, A0>{},
@@ -490,24 +505,30 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(BwdArgs a, EdgeArgs 
     int lz = l;
     asm volatile("" : "+v"(lz));
     const uint64_t keep = __builtin_amdgcn_ballot_w64(store && !short_row);        // bit = the row's low lane
+    const unsigned putA = lds_u32(stg) + 256u * (lz & 31) + 8u * (lz >> 5) + (swz(lz & 31) << 4);      // as in the forward
+    const unsigned getA = lds_u32(stg) + 256u * (lz >> 4) + (((lz & 15) ^ ((lz >> 4) << 2)) << 4);
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
     __syncthreads();
 #pragma unroll
-    for (int db = 0; db < 4; ++db)
-#pragma unroll
-        for (int gq = 0; gq < 4; ++gq) {
-            bf16x4 x;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) x[e] = (__bf16)(acc[db][4 * gq + e] * a.scale);
-            *reinterpret_cast<bf16x4*>(stg + tile_off(lz & 31, 4 * db + gq) + 8 * (lz >> 5)) = x;
-        }
+    for (int n = 0; n < 16; ++n) {
+        f32x16& x = acc[n >> 2];
+        const int r = 4 * (n & 3);
+        *(__attribute__((address_space(3))) u32x2*)(uintptr_t)(putA ^ (n << 4)) =
+            u32x2{pack2(x[r] * a.scale, x[r + 1] * a.scale), pack2(x[r + 2] * a.scale, x[r + 3] * a.scale)};
+    }
     bf16x8 x[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) x[i] = lds_read_row8(stg, 4 * i + (lz >> 4), lz & 15);
+    for (int i = 0; i < 8; ++i) x[i] = lds_at_row8((getA ^ ((i & 3) << 4)) + 1024u * i);
     __bf16* const p0 = a.dq + ((int64_t)(gd.tok_base + tw0 + (lz >> 4)) * a.Hq + head) * 128 + 8 * (lz & 15);
     const int64_t stride = (int64_t)4 * a.Hq * 128;
+    if ((unsigned)keep == 0xffffffffu) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
-        if ((keep >> (4 * i + (lz >> 4))) & 1) *reinterpret_cast<bf16x8*>(p0 + i * stride) = x[i];
+        for (int i = 0; i < 8; ++i) *reinterpret_cast<bf16x8*>(p0 + i * stride) = x[i];
+    } else {
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if ((keep >> (4 * i + (lz >> 4))) & 1) *reinterpret_cast<bf16x8*>(p0 + i * stride) = x[i];
+    }
 }
 
 // ------------------------------------------------------------------------------------

@@ -279,6 +279,15 @@ __device__ __forceinline__ bf16x8 pack8(float a0, float a1, float a2, float a3,
     return r;
 }
 
+// acc + the dot product of eight bf16 pairs, two at a time (v_dot2_f32_bf16)
+__device__ __forceinline__ float dot8(bf16x8 a, bf16x8 b, float acc) {
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+    for (int e = 0; e < 8; e += 2)
+        acc = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{a[e], a[e + 1]}, bf16x2{b[e], b[e + 1]}, acc, false);
+    return acc;
+}
+
 __device__ __forceinline__ float xor32(float x) { return __shfl_xor(x, 32, 64); }
 
 // max / sum of x over the lane pair (l, l ^ 32) with one v_permlane32_swap: after the swap

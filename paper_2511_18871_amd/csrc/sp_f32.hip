@@ -215,15 +215,9 @@ __global__ __launch_bounds__(256) void rowsum_bf16_kernel(const __bf16* __restri
         const int64_t off = base + (int64_t)r * 128;
         const bf16x8 a = *reinterpret_cast<const bf16x8*>(d_o + off);
         const bf16x8 b = *reinterpret_cast<const bf16x8*>(o + off);
-        float acc = 0.f;
-        if (HAS_LO && use_lo) {        // o was stored with its rounding residual: D from the unrounded value
-            const bf16x8 c = *reinterpret_cast<const bf16x8*>(o_lo + off);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) acc = __builtin_fmaf((float)a[e], (float)b[e] + (float)c[e], acc);
-        } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) acc = __builtin_fmaf((float)a[e], (float)b[e], acc);
-        }
+        float acc = dot8(a, b, 0.f);
+        // o was stored with its rounding residual: D from the unrounded value
+        if (HAS_LO && use_lo) acc = dot8(a, *reinterpret_cast<const bf16x8*>(o_lo + off), acc);
         return acc;
     };
     auto put = [&](int r, float acc) {
