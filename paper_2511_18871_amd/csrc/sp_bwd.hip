@@ -38,12 +38,14 @@ struct BwdArgs {
     __bf16* dq; __bf16* dk; __bf16* dv;
     const int* tab;
     Schedule sched;      // tile descriptors and per-token segment bounds, written by the schedule kernel of the call
-    int n_tiles, n_groups, Hq, Hkv;
+    ItemMap items;       // of the pass
+    int n_groups, Hq, Hkv;
     float scale, c;      // c = scale * log2(e)
     int resp_only;       // only response rows are computed (dq) / contribute (dk, dv)
     int accumulate;      // dk, dv are added to what the output buffers hold
     // dkdv pass on small problems: one workgroup per (key tile, Q head) instead of per (key tile,
     // kv head); the per-q-head partial sums go to `partial` in fp32 and a second kernel adds them
+    int rep;             // q heads per kv head
     int head_split;
     float* partial;      // [2 (dK, dV)][rep][T_total][Hkv][128] fp32
 };
@@ -96,15 +98,15 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(BwdArgs a, EdgeArgs 
         }
         return;
     }
-    int tile, head;
-    if (!decode_item(rb, a.n_tiles, a.Hq, a.Hkv, tile, head)) return;
-    const TileDesc td = (BM == 256 ? a.sched.tiles256 : a.sched.tiles128)[tile];
+    Item item;
+    if (!decode_item(rb, a.items, item)) return;
+    const TileDesc td = (BM == 256 ? a.sched.tiles256 : a.sched.tiles128)[item.tile];
     GroupDesc gd;
     gd.tok_base = td.tok_base; gd.Lp = td.Lp; gd.Tg = td.Tg; gd.G = 0; gd.roff = nullptr;
     const int Lp = gd.Lp, Tg = gd.Tg;
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
-    const WaveRows wr = wave_rows<NW>(td, head, a.Hq / a.Hkv, w);
-    head = wr.head;
+    const WaveRows wr = wave_rows<NW>(td, item, a.items.rep, w);
+    const int head = wr.head;
     const int t0 = wr.t0, t1 = wr.t1;
     const int64_t T_total = a.tab[1];
     if (t0 >= Tg || (a.resp_only && t1 <= Lp)) return;      // past the group's end, or prompt rows only
@@ -135,7 +137,7 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(BwdArgs a, EdgeArgs 
         return __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)p);
     };
 
-    const int kvh = head / (a.Hq / a.Hkv);
+    const int kvh = item.kvh;
     const int64_t kv_stride = (int64_t)a.Hkv * 128;
     const __bf16* kbase = a.k + ((int64_t)gd.tok_base * a.Hkv + kvh) * 128;
     const __bf16* vbase = a.v + ((int64_t)gd.tok_base * a.Hkv + kvh) * 128;
@@ -591,7 +593,7 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const TileDesc td, c
     // tile copies.  Eight waves have the register: 1 % of the pass)
     if (K_REG && hh == 0) dkdv_ldsEnd[32 * kb + c] = e_s;
     const int qt0 = max(s0, row_lo) / BQ, qt1 = (row_end + BQ - 1) / BQ;
-    const int rep_all = a.Hq / a.Hkv;
+    const int rep_all = a.rep;
     const int rep = NW == 8 && a.head_split ? 1 : rep_all;        // q heads this workgroup walks
     const int64_t q_stride = (int64_t)a.Hq * 128;
     const int64_t kv_stride = (int64_t)a.Hkv * 128;
@@ -968,14 +970,9 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const TileDesc td, c
 
 template <int NW>
 __global__ __launch_bounds__(64 * NW, 2) void bwd_dkdv_kernel(BwdArgs a) {
-    int tile, kvh, hr_only = 0;
-    if (NW == 8 && a.head_split) {
-        int head;
-        if (!decode_item(blockIdx.x, a.n_tiles, a.Hq, a.Hkv, tile, head)) return;
-        kvh = head / (a.Hq / a.Hkv);
-        hr_only = head % (a.Hq / a.Hkv);
-    } else if (!decode_item(blockIdx.x, a.n_tiles, a.Hkv, a.Hkv, tile, kvh)) return;
-    dkdv_body<NW>(a, a.sched.key_tiles[tile], kvh, hr_only);
+    Item item;           // per (key tile, q head) where the pass is split over the q heads, else per (key tile, kv head)
+    if (!decode_item(blockIdx.x, a.items, item)) return;
+    dkdv_body<NW>(a, a.sched.key_tiles[item.tile], item.kvh, item.hr);
 }
 
 // Second stage of the head-split dkdv pass: dk = scale * sum_hr partial[0][hr], dv = sum_hr
@@ -1048,9 +1045,10 @@ int dkdv_waves(const Problem& p) {
     // many workgroups: even, unless one is longer than what a CU gets in all
     if (many) return sum * p.Hkv < 256. * longest ? 8 : 4;
     std::vector<int> tiles;                                    // of XCD 0, in order
-    for (int bid = 0, n = (int)w8.size(), grid = grid_for_items(n, p.Hkv, p.Hkv); bid < grid; bid += 8) {
-        int tile, kvh;
-        if (decode_item(bid, n, p.Hkv, p.Hkv, tile, kvh)) tiles.push_back(tile);
+    const ItemMap items = make_item_map((int)w8.size(), p.Hkv, p.Hkv);
+    for (int bid = 0, grid = grid_for_items((int)w8.size(), p.Hkv, p.Hkv); bid < grid; bid += 8) {
+        Item it;
+        if (decode_item(bid, items, it)) tiles.push_back(it.tile);
     }
     float end8 = 0.f, end4 = 0.f;
     for (int se = 0; se < SE; ++se) {
@@ -1107,8 +1105,8 @@ hipError_t launch_bwd_bf16(const Problem& p, hipStream_t s) {
     if (p.stages & STAGE_DQ) {
         // short key loops: the four-wave shape, two workgroups per CU (the forward's rule, see bwd_dq_kernel)
         const bool small = use_small_shape(p);
-        a.n_tiles = count_tiles(p, small ? 128 : 256);
-        const int grid = grid_for_items(a.n_tiles, p.Hq, p.Hkv);
+        const int n_tiles = count_tiles(p, small ? 128 : 256), grid = grid_for_items(n_tiles, p.Hq, p.Hkv);
+        a.items = make_item_map(n_tiles, p.Hq, p.Hkv);
         const EdgeArgs edge = edge_args(p);
         const int shorts = (edge_blocks(edge, small ? 2 : 3) + 7) & ~7, total = grid + shorts;
         if (small) hipLaunchKernelGGL(bwd_dq_kernel<4>, dim3(total), dim3(256), 0, s, a, edge, shorts, grid);
@@ -1117,17 +1115,20 @@ hipError_t launch_bwd_bf16(const Problem& p, hipStream_t s) {
         if (e != hipSuccess) return e;
     }
     if (p.stages & STAGE_DKDV) {
-        a.n_tiles = count_tiles(p, 128);
+        const int n_tiles = count_tiles(p, 128);
+        a.rep = p.Hq / p.Hkv;
         a.head_split = p.dkdv_partial != nullptr;
         a.partial = p.dkdv_partial;
         if (a.head_split) {
-            const int grid = grid_for_items(a.n_tiles, p.Hq, p.Hkv);
+            const int grid = grid_for_items(n_tiles, p.Hq, p.Hkv);
+            a.items = make_item_map(n_tiles, p.Hq, p.Hkv);
             hipLaunchKernelGGL(bwd_dkdv_kernel<8>, dim3(grid), dim3(512), 0, s, a);
             const int64_t n4 = p.total_tokens * p.Hkv * 32;
             hipLaunchKernelGGL(dkdv_reduce_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, a.partial, a.dk, a.dv,
                                n4, p.Hq / p.Hkv, p.scale, a.accumulate);
         } else {
-            const int grid = grid_for_items(a.n_tiles, p.Hkv, p.Hkv);
+            const int grid = grid_for_items(n_tiles, p.Hkv, p.Hkv);
+            a.items = make_item_map(n_tiles, p.Hkv, p.Hkv);
             if (dkdv_waves(p) == 8) hipLaunchKernelGGL(bwd_dkdv_kernel<8>, dim3(grid), dim3(512), 0, s, a);
             else hipLaunchKernelGGL(bwd_dkdv_kernel<4>, dim3(grid), dim3(256), 0, s, a);
         }

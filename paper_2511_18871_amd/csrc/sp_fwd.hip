@@ -32,7 +32,8 @@ struct FwdArgs {
     int blocks_per_set;
     const int* tab;
     Schedule sched; // tile descriptors and per-token segment bounds, written by the schedule kernel of the call
-    int n_tiles, n_groups, Hq, Hkv;
+    ItemMap items;
+    int n_groups, Hq, Hkv;
     float c;        // softmax_scale * log2(e)
     int naive;
     int resp_only;  // compute and write response rows only
@@ -81,19 +82,20 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd_kernel(FwdArgs a) {      // tw
 
     // blocks are dealt set-major; blocks_per_set is a multiple of 8, so the block -> XCD mapping
     // of a set does not depend on how many sets the launch carries
-    const int set = blockIdx.x / a.blocks_per_set;
+    const int bid = blockIdx.x, bps = a.blocks_per_set, set = (bid >= bps) + (bid >= 2 * bps) + (bid >= 3 * bps);
+    static_assert(MAX_SETS == 4, "sets are counted by comparisons");
     const __bf16* const aq = a.q[set]; const __bf16* const ak = a.k[set]; const __bf16* const av = a.v[set];
     __bf16* const ao = a.o[set]; float* const alse = a.lse[set];
-    int tile, head;
-    if (!decode_item(blockIdx.x - set * a.blocks_per_set, a.n_tiles, a.Hq, a.Hkv, tile, head)) return;
+    Item item;
+    if (!decode_item(bid - set * bps, a.items, item)) return;
     // the tile's descriptor: one 32-byte load instead of a bisection over the groups and the group's entry
-    const TileDesc td = (BM == 256 ? a.sched.tiles256 : a.sched.tiles128)[tile];
+    const TileDesc td = (BM == 256 ? a.sched.tiles256 : a.sched.tiles128)[item.tile];
     GroupDesc gd;
     gd.tok_base = td.tok_base; gd.Lp = td.Lp; gd.Tg = td.Tg; gd.G = 0; gd.roff = nullptr;
     const int Lp = gd.Lp, Tg = gd.Tg;
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
-    const WaveRows wr = wave_rows<NW>(td, head, a.Hq / a.Hkv, w);
-    head = wr.head;
+    const WaveRows wr = wave_rows<NW>(td, item, a.items.rep, w);
+    const int head = wr.head;
     const int t0 = wr.t0, t1 = wr.t1;
     const int T_total = a.tab[1];
     if (t0 >= Tg || (a.resp_only && t1 <= Lp)) return;      // past the group's end, or prompt rows only
@@ -129,7 +131,7 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd_kernel(FwdArgs a) {      // tw
     const int total = n1 + (NAIVE || t1 <= Lp ? 0 : max(t1 - k2 + BN - 1, 0) / BN);
     auto key_at = [&](int it) { return it < n1 ? it * BN : k2 + (it - n1) * BN; };
 
-    const int kvh = head / (a.Hq / a.Hkv);
+    const int kvh = item.kvh;
     const int64_t kv_stride = (int64_t)a.Hkv * 128;
     const __bf16* kbase = ak + ((int64_t)gd.tok_base * a.Hkv + kvh) * 128;
     const __bf16* vbase = av + ((int64_t)gd.tok_base * a.Hkv + kvh) * 128;
@@ -544,8 +546,9 @@ hipError_t launch_fwd_bf16(const Problem& p, hipStream_t s) {
     // the eight-wave shape whatever the packing (its loops are long by construction).
     const bool small = !p.naive && use_small_shape(p);
     const int bm = small ? 128 : 256;
-    a.n_tiles = count_tiles(p, bm);
-    a.blocks_per_set = grid_for_items(a.n_tiles, p.Hq, p.Hkv);
+    const int n_tiles = count_tiles(p, bm);
+    a.items = make_item_map(n_tiles, p.Hq, p.Hkv);
+    a.blocks_per_set = grid_for_items(n_tiles, p.Hq, p.Hkv);
     if (a.blocks_per_set % 8 != 0) a.blocks_per_set += 8 - a.blocks_per_set % 8;
     if (p.naive) hipLaunchKernelGGL((fwd_kernel<8, true>), dim3(a.blocks_per_set * n_sets), dim3(512), 0, s, a);
     else if (small) hipLaunchKernelGGL((fwd_kernel<4, false>), dim3(a.blocks_per_set * n_sets), dim3(256), 0, s, a);
