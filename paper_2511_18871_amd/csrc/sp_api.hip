@@ -385,6 +385,15 @@ sp_status sp_attn_fwd_multi(int32_t n_sets, const void* const* q, const void* co
 }
 
 namespace {
+// The table of a call that needs nothing else prepared: as a kernel argument (nothing is written to the workspace, and a
+// reserve that a forward left there stays valid), or in the workspace.
+hipError_t table_for(const Layout& L, void* workspace, hipStream_t s, sp::TabArg& tab) {
+    tab = sp::make_tab_arg(L.words.data(), L.words.size(), table_of(workspace));
+    if (!tab.dev) return hipSuccess;
+    return sp::launch_prepare(L.words.data(), (int)L.words.size(), table_of(workspace), (uint32_t*)workspace, sp::ReserveTag{},
+                              sp::TAG_CLEAR, false, L.words[0], L.total_tokens, 0, 0, sp::Schedule{}, sp::KEYS_AS_PACKED, s);
+}
+
 sp_status rope_call(const void* x, void* y, int32_t H, const void* x2, void* y2, int32_t H2, int32_t inverse,
                     int32_t n_groups, const int32_t* prompt_lens, const int32_t* Gs, const int32_t* resp_lens_flat,
                     int32_t head_dim, double rope_base, sp_dtype dtype, void* workspace, size_t workspace_bytes,
@@ -406,10 +415,10 @@ sp_status rope_call(const void* x, void* y, int32_t H, const void* x2, void* y2,
         return fail(SP_ERR_WORKSPACE, "workspace %p of %zu bytes; need %zu bytes, 16-byte aligned", workspace,
                     workspace_bytes, need);
     hipStream_t s = (hipStream_t)stream;
-    hipError_t e = sp::launch_prepare(L.words.data(), (int)L.words.size(), table_of(workspace), (uint32_t*)workspace,
-                                      sp::ReserveTag{}, sp::TAG_CLEAR, false, n_groups, L.total_tokens, 0, 0, sp::Schedule{}, sp::KEYS_AS_PACKED, s);
+    sp::TabArg tab;
+    hipError_t e = table_for(L, workspace, s, tab);
     if (e == hipSuccess)
-        e = sp::launch_rope(x, y, H, x2, y2, H2, table_of(workspace), L.total_tokens, head_dim, rope_base, inverse != 0,
+        e = sp::launch_rope(x, y, H, x2, y2, H2, tab, L.total_tokens, head_dim, rope_base, inverse != 0,
                             dtype == SP_F32, s);
     if (e != hipSuccess) return fail(SP_ERR_DEVICE, "HIP launch failed: %s", hipGetErrorString(e));
     return SP_OK;
@@ -439,9 +448,10 @@ size_t sp_attn_loss_workspace_bytes(int64_t total_tokens, int32_t n_groups, int6
 }
 
 namespace {
-// shared front end of the three loss calls: packing -> table in the workspace
+// shared front end of the three loss calls: packing -> table
 sp_status loss_setup(int32_t n_groups, const int32_t* prompt_lens, const int32_t* Gs, const int32_t* resp_lens_flat,
-                     void* workspace, size_t workspace_bytes, hipStream_t s, Layout& L, float** scratch) {
+                     void* workspace, size_t workspace_bytes, hipStream_t s, Layout& L, float** scratch,
+                     sp::TabArg& tab) {
     sp_status st = build_table(n_groups, prompt_lens, Gs, resp_lens_flat, L);
     if (st != SP_OK) return st;
     const size_t need = sp_attn_loss_workspace_bytes(L.total_tokens, n_groups, L.total_responses);
@@ -449,8 +459,7 @@ sp_status loss_setup(int32_t n_groups, const int32_t* prompt_lens, const int32_t
         return fail(SP_ERR_WORKSPACE, "workspace %p of %zu bytes; need %zu bytes, 16-byte aligned", workspace,
                     workspace_bytes, need);
     *scratch = (float*)((char*)workspace + TAG_BYTES + align256(L.words.size() * 4));
-    hipError_t e = sp::launch_prepare(L.words.data(), (int)L.words.size(), table_of(workspace), (uint32_t*)workspace,
-                                      sp::ReserveTag{}, sp::TAG_CLEAR, false, n_groups, L.total_tokens, 0, 0, sp::Schedule{}, sp::KEYS_AS_PACKED, s);
+    hipError_t e = table_for(L, workspace, s, tab);
     if (e != hipSuccess) return fail(SP_ERR_DEVICE, "HIP launch failed: %s", hipGetErrorString(e));
     return SP_OK;
 }
@@ -466,9 +475,10 @@ sp_status sp_attn_logprob_fwd(const void* logits, const int32_t* labels, float* 
     if (vocab < 1) return fail(SP_ERR_INVALID_ARG, "vocab=%lld", (long long)vocab);
     if (dtype != SP_BF16 && dtype != SP_F32) return fail(SP_ERR_UNSUPPORTED, "unknown dtype %d", (int)dtype);
     Layout L; float* scratch = nullptr;
-    sp_status st = loss_setup(n_groups, prompt_lens, Gs, resp_lens_flat, workspace, workspace_bytes, (hipStream_t)stream, L, &scratch);
+    sp::TabArg tab;
+    sp_status st = loss_setup(n_groups, prompt_lens, Gs, resp_lens_flat, workspace, workspace_bytes, (hipStream_t)stream, L, &scratch, tab);
     if (st != SP_OK) return st;
-    hipError_t e = sp::launch_logprob_fwd(logits, labels, logp, lse, table_of(workspace), L.total_tokens, vocab,
+    hipError_t e = sp::launch_logprob_fwd(logits, labels, logp, lse, tab, L.total_tokens, vocab,
                                           dtype == SP_F32, (hipStream_t)stream);
     if (e != hipSuccess) return fail(SP_ERR_DEVICE, "HIP launch failed: %s", hipGetErrorString(e));
     return SP_OK;
@@ -493,9 +503,10 @@ sp_status sp_attn_logprob_bwd_ex(const void* logits, const int32_t* labels, cons
     if (vocab < 1) return fail(SP_ERR_INVALID_ARG, "vocab=%lld", (long long)vocab);
     if (dtype != SP_BF16 && dtype != SP_F32) return fail(SP_ERR_UNSUPPORTED, "unknown dtype %d", (int)dtype);
     Layout L; float* scratch = nullptr;
-    sp_status st = loss_setup(n_groups, prompt_lens, Gs, resp_lens_flat, workspace, workspace_bytes, (hipStream_t)stream, L, &scratch);
+    sp::TabArg tab;
+    sp_status st = loss_setup(n_groups, prompt_lens, Gs, resp_lens_flat, workspace, workspace_bytes, (hipStream_t)stream, L, &scratch, tab);
     if (st != SP_OK) return st;
-    hipError_t e = sp::launch_logprob_bwd(logits, labels, lse, g, dlogits, table_of(workspace), L.total_tokens, vocab,
+    hipError_t e = sp::launch_logprob_bwd(logits, labels, lse, g, dlogits, tab, L.total_tokens, vocab,
                                           dtype == SP_F32, (flags & SP_FLAG_ZERO_PROMPT_ROWS) != 0, (hipStream_t)stream);
     if (e != hipSuccess) return fail(SP_ERR_DEVICE, "HIP launch failed: %s", hipGetErrorString(e));
     return SP_OK;
@@ -510,11 +521,12 @@ sp_status sp_attn_grpo_loss(const float* logp, const float* logp_old, const floa
     if (!(eps_low >= 0.f && eps_low < 1.f) || !(eps_high >= 0.f) || !std::isfinite(eps_high) || !std::isfinite(beta))
         return fail(SP_ERR_INVALID_ARG, "eps_low must lie in [0, 1), eps_high in [0, inf), beta finite");
     Layout L; float* scratch = nullptr;
-    sp_status st = loss_setup(n_groups, prompt_lens, Gs, resp_lens_flat, workspace, workspace_bytes, (hipStream_t)stream, L, &scratch);
+    sp::TabArg tab;
+    sp_status st = loss_setup(n_groups, prompt_lens, Gs, resp_lens_flat, workspace, workspace_bytes, (hipStream_t)stream, L, &scratch, tab);
     if (st != SP_OK) return st;
     int nonempty = 0;
     for (int64_t r = 0; r < L.total_responses; ++r) nonempty += resp_lens_flat[r] > 0;
-    hipError_t e = sp::launch_grpo(logp, logp_old, logp_ref, adv, g, scratch, loss, table_of(workspace),
+    hipError_t e = sp::launch_grpo(logp, logp_old, logp_ref, adv, g, scratch, loss, tab, (uint32_t*)workspace,
                                    (int)L.total_responses, nonempty, eps_low, eps_high, beta, (hipStream_t)stream);
     if (e != hipSuccess) return fail(SP_ERR_DEVICE, "HIP launch failed: %s", hipGetErrorString(e));
     return SP_OK;

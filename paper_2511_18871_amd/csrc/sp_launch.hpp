@@ -1,10 +1,27 @@
 // Internal launcher interface between the C-ABI layer (sp_api.hip) and the kernels.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <cstddef>
 #include <stdint.h>
 #include "sp_common.hpp"
 
 namespace sp {
+
+// Segment table of a call as the FIRST parameter of its kernel: kernels that need nothing else prepared read a table of up to
+// ARG_WORDS words (with the other parameters, under the 4 KB of kernel arguments) from there, larger ones from `dev`.  A launch
+// that only stores the table is 5 us and the gap behind it: rotation of a 16K prompt's q and k 112.0 -> 109.9, loss over a 152K
+// vocabulary 395.8 -> 390.9 (with the objective of up to 16 responses in one launch instead of two).
+constexpr int ARG_WORDS = 768;
+struct TabArg { const int* dev; int32_t words[ARG_WORDS]; };
+inline TabArg make_tab_arg(const int32_t* words, size_t n, const int* dev) {
+    TabArg t;
+    t.dev = n <= (size_t)ARG_WORDS ? nullptr : dev;
+    for (size_t i = 0; i < (size_t)ARG_WORDS; ++i) t.words[i] = !t.dev && i < n ? words[i] : 0;
+    return t;
+}
+__device__ __forceinline__ const int* table_of(const TabArg& t) {
+    return t.dev ? t.dev : (const int*)((uintptr_t)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(TabArg, words));
+}
 
 constexpr unsigned STAGE_ROWSUM = 1u, STAGE_DKDV = 2u, STAGE_DQ = 4u;
 constexpr int MAX_SETS = 4;      // tensor sets that one forward launch can serve
@@ -66,15 +83,15 @@ hipError_t launch_rowsum(const Problem& p, bool f32, hipStream_t s);
 // then do not store.
 constexpr int EDGE_LEN = 64;
 hipError_t launch_short_rows(const Problem& p, hipStream_t s);
-hipError_t launch_rope(const void* x, void* y, int H, const void* x2, void* y2, int H2, const int* tab,
+hipError_t launch_rope(const void* x, void* y, int H, const void* x2, void* y2, int H2, const TabArg& tab,
                        int64_t total_tokens, int d, double base, bool inverse, bool f32, hipStream_t s);
-hipError_t launch_logprob_fwd(const void* z, const int* y, float* logp, float* lse, const int* tab,
+hipError_t launch_logprob_fwd(const void* z, const int* y, float* logp, float* lse, const TabArg& tab,
                               int64_t total_tokens, int64_t V, bool f32, hipStream_t s);
 hipError_t launch_logprob_bwd(const void* z, const int* y, const float* lse, const float* g, void* dz,
-                              const int* tab, int64_t total_tokens, int64_t V, bool f32, bool zero_prompt, hipStream_t s);
+                              const TabArg& tab, int64_t total_tokens, int64_t V, bool f32, bool zero_prompt, hipStream_t s);
 hipError_t launch_grpo(const float* logp, const float* old, const float* ref, const float* adv, float* g,
-                       float* J, float* loss, const int* tab, int n_resp, int n_nonempty, float eps_low,
-                       float eps_high, float beta, hipStream_t s);
+                       float* J, float* loss, const TabArg& tab, uint32_t* tag, int n_resp, int n_nonempty,
+                       float eps_low, float eps_high, float beta, hipStream_t s);
 // Order of the key tiles (Schedule): the packing's, prompt tiles first group by group, or prompt tiles first by the rows that
 // see them, most first.  A dkdv workgroup of a prompt's first tile can run a hundred times as long as one of a response,
 // and in the packing's order the last group's starts when the rest of the launch is nearly through.  Sorted by rows they also

@@ -64,9 +64,9 @@ __device__ __forceinline__ void block_lse(float& m, float& s, float* sh) {
 }
 
 template <typename T, int LT>
-__global__ __launch_bounds__(LT) void logprob_fwd_kernel(const T* __restrict__ z, const int* __restrict__ y,
-                                                         float* __restrict__ logp, float* __restrict__ lse,
-                                                         const int* __restrict__ tab, int64_t V) {
+__global__ __launch_bounds__(LT) void logprob_fwd_kernel(TabArg table, const T* __restrict__ z, const int* __restrict__ y,
+                                                         float* __restrict__ logp, float* __restrict__ lse, int64_t V) {
+    const int* const tab = table_of(table);
     __shared__ float sh[2 * LT / 64];
     const int64_t tok = blockIdx.x;
     const GroupDesc gd = load_group(tab, find_group_of_token(tab, tok));
@@ -128,10 +128,10 @@ __global__ __launch_bounds__(LT) void logprob_fwd_kernel(const T* __restrict__ z
 // zero_prompt: prompt rows of dz are set to zero (otherwise they are not touched).  Rows are taken last first and each
 // from its end: the last 256 MB that the forward read are what the Infinity Cache still holds.
 template <typename T, int LT, bool BYPASS>
-__global__ __launch_bounds__(LT) void logprob_bwd_kernel(const T* __restrict__ z, const int* __restrict__ y,
+__global__ __launch_bounds__(LT) void logprob_bwd_kernel(TabArg table, const T* __restrict__ z, const int* __restrict__ y,
                                                          const float* __restrict__ lse, const float* __restrict__ g,
-                                                         T* __restrict__ dz, const int* __restrict__ tab, int64_t V,
-                                                         int zero_prompt) {
+                                                         T* __restrict__ dz, int64_t V, int zero_prompt) {
+    const int* const tab = table_of(table);
     const int64_t tok = (int64_t)gridDim.x - 1 - blockIdx.x;
     const GroupDesc gd = load_group(tab, find_group_of_token(tab, tok));
     constexpr int N = Ld<T>::N;
@@ -177,15 +177,10 @@ __global__ __launch_bounds__(LT) void logprob_bwd_kernel(const T* __restrict__ z
     if ((int)threadIdx.x < n_loose) out[loose] = value(row[loose], loose);
 }
 
-// one wave per response (global index k over all groups)
-__global__ __launch_bounds__(256) void grpo_kernel(const float* __restrict__ logp, const float* __restrict__ old,
-                                                   const float* __restrict__ ref, const float* __restrict__ adv,
-                                                   float* __restrict__ g, float* __restrict__ J,
-                                                   const int* __restrict__ tab, int n_resp, float eps_low,
-                                                   float eps_high, float beta, float inv_R) {
-    const int k = blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int l = threadIdx.x & 63;
-    if (k >= n_resp) return;
+// objective of response k (global index over all groups), one wave; returns J_k in every lane and writes g of its rows
+__device__ __forceinline__ float grpo_response(const int* tab, int k, int l, const float* __restrict__ logp, const float* __restrict__ old,
+                                               const float* __restrict__ ref, const float* __restrict__ adv,
+                                               float* __restrict__ g, float eps_low, float eps_high, float beta, float inv_R) {
     // Group that holds response k.  Group g's response offsets start at table word e[3] = base + R_g + g,
     // with base the first offset word and R_g the responses in earlier groups, so R_g is read off the
     // group entries and the group is the last one with R_g <= k: a bisection (responses of empty groups
@@ -217,7 +212,42 @@ __global__ __launch_bounds__(256) void grpo_kernel(const float* __restrict__ log
         g[tok] = -inv_len * inv_R * (d_surr - beta * (1.0f - eu));
     }
     for (int o = 32; o >= 1; o >>= 1) acc += __shfl_xor(acc, o, 64);
-    if (l == 0) J[k] = acc * inv_len;
+    return acc * inv_len;
+}
+
+// One wave per response.  J lies in the workspace, whose tag block is cleared as by every call that writes there.
+__global__ __launch_bounds__(256) void grpo_kernel(TabArg table, const float* __restrict__ logp, const float* __restrict__ old,
+                                                   const float* __restrict__ ref, const float* __restrict__ adv,
+                                                   float* __restrict__ g, float* __restrict__ J, uint32_t* __restrict__ tag,
+                                                   int n_resp, float eps_low, float eps_high, float beta, float inv_R) {
+    const int k = blockIdx.x * 4 + (threadIdx.x >> 6), l = threadIdx.x & 63;
+    if (blockIdx.x == 0 && threadIdx.x < 64) tag[l] = 0u;
+    if (k >= n_resp) return;
+    const float j = grpo_response(table_of(table), k, l, logp, old, ref, adv, g, eps_low, eps_high, beta, inv_R);
+    if (l == 0) J[k] = j;
+}
+
+// The same for up to ONE_BLOCK responses, with the sum of grpo_reduce_kernel, in one launch
+constexpr int ONE_BLOCK = 16;
+__global__ __launch_bounds__(64 * ONE_BLOCK) void grpo_small_kernel(TabArg table, const float* __restrict__ logp, const float* __restrict__ old,
+                                                                    const float* __restrict__ ref, const float* __restrict__ adv,
+                                                                    float* __restrict__ g, float* __restrict__ loss, int n_resp,
+                                                                    float eps_low, float eps_high, float beta, float inv_R) {
+    __shared__ float sh[ONE_BLOCK];
+    const int k = threadIdx.x >> 6, l = threadIdx.x & 63;
+    const float j = k < n_resp ? grpo_response(table_of(table), k, l, logp, old, ref, adv, g, eps_low, eps_high, beta, inv_R) : 0.f;
+    if (l == 0) sh[k] = j;
+    __syncthreads();
+    if (threadIdx.x == 0) {          // the tree of grpo_reduce_kernel over the first ONE_BLOCK elements (the others are zero)
+        float x[ONE_BLOCK];
+#pragma unroll
+        for (int i = 0; i < ONE_BLOCK; ++i) x[i] = sh[i];
+#pragma unroll
+        for (int o = ONE_BLOCK / 2; o >= 1; o >>= 1)
+#pragma unroll
+            for (int i = 0; i < o; ++i) x[i] += x[i + o];
+        loss[0] = -x[0] * inv_R;
+    }
 }
 
 // fixed-order sum of J[0..n) by one workgroup: thread i adds J[i], J[i+256], ... then a tree
@@ -249,38 +279,42 @@ void with_row_kernel(int64_t V, bool f32, F f) {
     if (f32) sized(float{}); else sized(__bf16{});
 }
 
-hipError_t launch_logprob_fwd(const void* z, const int* y, float* logp, float* lse, const int* tab,
+hipError_t launch_logprob_fwd(const void* z, const int* y, float* logp, float* lse, const TabArg& tab,
                               int64_t total_tokens, int64_t V, bool f32, hipStream_t s) {
     with_row_kernel(V, f32, [&](auto elem, auto lt) {
         typedef decltype(elem) T;
         hipLaunchKernelGGL((logprob_fwd_kernel<T, decltype(lt)::value>), dim3((unsigned)total_tokens),
-                           dim3(decltype(lt)::value), 0, s, (const T*)z, y, logp, lse, tab, V);
+                           dim3(decltype(lt)::value), 0, s, tab, (const T*)z, y, logp, lse, V);
     });
     return hipGetLastError();
 }
 
 hipError_t launch_logprob_bwd(const void* z, const int* y, const float* lse, const float* g, void* dz,
-                              const int* tab, int64_t total_tokens, int64_t V, bool f32, bool zero_prompt, hipStream_t s) {
+                              const TabArg& tab, int64_t total_tokens, int64_t V, bool f32, bool zero_prompt, hipStream_t s) {
     // a gradient that the Infinity Cache (256 MB) cannot hold for its reader is stored past the caches
     const bool bypass = total_tokens * V * (f32 ? 4 : 2) > (int64_t)256 << 20;
     with_row_kernel(V, f32, [&](auto elem, auto lt) {
         typedef decltype(elem) T;
         constexpr int LT = decltype(lt)::value;
         if (bypass) hipLaunchKernelGGL((logprob_bwd_kernel<T, LT, true>), dim3((unsigned)total_tokens), dim3(LT), 0, s,
-                                       (const T*)z, y, lse, g, (T*)dz, tab, V, (int)zero_prompt);
+                                       tab, (const T*)z, y, lse, g, (T*)dz, V, (int)zero_prompt);
         else hipLaunchKernelGGL((logprob_bwd_kernel<T, LT, false>), dim3((unsigned)total_tokens), dim3(LT), 0, s,
-                                (const T*)z, y, lse, g, (T*)dz, tab, V, (int)zero_prompt);
+                                tab, (const T*)z, y, lse, g, (T*)dz, V, (int)zero_prompt);
     });
     return hipGetLastError();
 }
 
 hipError_t launch_grpo(const float* logp, const float* old, const float* ref, const float* adv, float* g,
-                       float* J, float* loss, const int* tab, int n_resp, int n_nonempty, float eps_low,
-                       float eps_high, float beta, hipStream_t s) {
+                       float* J, float* loss, const TabArg& tab, uint32_t* tag, int n_resp, int n_nonempty,
+                       float eps_low, float eps_high, float beta, hipStream_t s) {
     const float inv_R = n_nonempty > 0 ? 1.0f / (float)n_nonempty : 0.f;
-    if (n_resp > 0)
-        hipLaunchKernelGGL(grpo_kernel, dim3((n_resp + 3) / 4), dim3(256), 0, s, logp, old, ref, adv, g, J, tab, n_resp,
+    if (n_resp <= ONE_BLOCK) {
+        hipLaunchKernelGGL(grpo_small_kernel, dim3(1), dim3(64 * ONE_BLOCK), 0, s, tab, logp, old, ref, adv, g, loss, n_resp,
                            eps_low, eps_high, beta, inv_R);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL(grpo_kernel, dim3((n_resp + 3) / 4), dim3(256), 0, s, tab, logp, old, ref, adv, g, J, tag, n_resp,
+                       eps_low, eps_high, beta, inv_R);
     hipLaunchKernelGGL(grpo_reduce_kernel, dim3(1), dim3(256), 0, s, J, n_resp, inv_R, loss);
     return hipGetLastError();
 }

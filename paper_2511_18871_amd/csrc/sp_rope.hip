@@ -26,9 +26,10 @@ template <> struct Vec8<float> { typedef float type __attribute__((ext_vector_ty
 struct RopeFreq { double theta[64]; };      // theta_i = base^(-2 i / d), i < d / 2 <= 64
 
 template <typename T>
-__global__ __launch_bounds__(256) void rope_kernel(const T* __restrict__ x, T* __restrict__ y, int H,
+__global__ __launch_bounds__(256) void rope_kernel(TabArg table, const T* __restrict__ x, T* __restrict__ y, int H,
                                                    const T* __restrict__ x2, T* __restrict__ y2, int H2,
-                                                   const int* __restrict__ tab, int d, RopeFreq f, int inverse) {
+                                                   int d, RopeFreq f, int inverse) {
+    const int* const tab = table_of(table);
     typedef typename Vec8<T>::type V8;
     const int half = d >> 1;
     const int tpt = half >> 3;                          // threads per token
@@ -74,7 +75,7 @@ __global__ __launch_bounds__(256) void rope_kernel(const T* __restrict__ x, T* _
 
 }  // namespace
 
-hipError_t launch_rope(const void* x, void* y, int H, const void* x2, void* y2, int H2, const int* tab,
+hipError_t launch_rope(const void* x, void* y, int H, const void* x2, void* y2, int H2, const TabArg& tab,
                        int64_t total_tokens, int d, double base, bool inverse, bool f32, hipStream_t s) {
     const int tpt = d / 16;
     const int64_t threads = total_tokens * tpt;
@@ -82,11 +83,11 @@ hipError_t launch_rope(const void* x, void* y, int H, const void* x2, void* y2, 
     RopeFreq f{};
     for (int i = 0; i < d / 2; ++i) f.theta[i] = pow(base, -2.0 * (double)i / (double)d);
     if (f32)
-        hipLaunchKernelGGL(rope_kernel<float>, dim3(grid), dim3(256), 0, s, (const float*)x, (float*)y, H,
-                           (const float*)x2, (float*)y2, H2, tab, d, f, (int)inverse);
+        hipLaunchKernelGGL(rope_kernel<float>, dim3(grid), dim3(256), 0, s, tab, (const float*)x, (float*)y, H,
+                           (const float*)x2, (float*)y2, H2, d, f, (int)inverse);
     else
-        hipLaunchKernelGGL(rope_kernel<__bf16>, dim3(grid), dim3(256), 0, s, (const __bf16*)x, (__bf16*)y, H,
-                           (const __bf16*)x2, (__bf16*)y2, H2, tab, d, f, (int)inverse);
+        hipLaunchKernelGGL(rope_kernel<__bf16>, dim3(grid), dim3(256), 0, s, tab, (const __bf16*)x, (__bf16*)y, H,
+                           (const __bf16*)x2, (__bf16*)y2, H2, d, f, (int)inverse);
     return hipGetLastError();
 }
 
