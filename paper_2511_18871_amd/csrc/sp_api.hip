@@ -84,6 +84,7 @@ struct Layout {
     int64_t total_responses = 0;
     int max_group_tokens = 0;
     int min_prompt_len = 0x7fffffff;
+    int max_responses = 0;            // of a group
 };
 
 sp_status build_table(int32_t n_groups, const int32_t* prompt_lens, const int32_t* Gs,
@@ -94,6 +95,7 @@ sp_status build_table(int32_t n_groups, const int32_t* prompt_lens, const int32_
     for (int g = 0; g < n_groups; ++g) {
         if (Gs[g] < 0) return fail(SP_ERR_INVALID_ARG, "group %d: G=%d is negative", g, Gs[g]);
         nresp += Gs[g];
+        if (Gs[g] > L.max_responses) L.max_responses = Gs[g];
     }
     if (nresp > 0 && !resp_lens_flat) return fail(SP_ERR_INVALID_ARG, "resp_lens is NULL but G > 0");
     if (nresp > (int64_t)1 << 28) return fail(SP_ERR_INVALID_ARG, "too many responses");
@@ -216,7 +218,12 @@ sp_status run(bool bwd, const void* q, const void* k, const void* v, const void*
     p.n_tiles256 = sp::count_tiles(p, 256); p.n_tiles128 = sp::count_tiles(p, 128);
     const int key_order = bwd && dtype == SP_BF16 && (stages & SP_BWD_STAGE_DKDV) ? sp::key_order(p) : sp::KEYS_AS_PACKED;
     if (key_order == sp::KEYS_AS_PACKED) p.sched.key_tiles = p.sched.tiles128;
-    hipError_t e = sp::launch_prepare(L.words.data(), (int)L.words.size(), table_of(workspace), (uint32_t*)workspace, tag,
+    // a backward in stages, or of response rows only, has a rowsum launch of its own, which reads the prepared table
+    const bool one_call = !bwd || (stages == SP_BWD_STAGE_ALL && !resp_only && sp::rowsum_fast_path(p));
+    p.small.on = dtype == SP_BF16 && one_call && key_order == sp::KEYS_AS_PACKED &&
+                 sp::use_small_call(p, L.words.size(), L.max_responses);
+    p.small.tag_mode = tag_mode; p.small.want = tag; p.small.tag = (uint32_t*)workspace;
+    hipError_t e = p.small.on ? hipSuccess : sp::launch_prepare(L.words.data(), (int)L.words.size(), table_of(workspace), (uint32_t*)workspace, tag,
                                       keep_tag ? sp::TAG_KEEP : tag_mode, dtype == SP_BF16, n_groups, L.total_tokens,
                                       p.n_tiles256, p.n_tiles128, p.sched, key_order, s);
     if (e == hipSuccess) {

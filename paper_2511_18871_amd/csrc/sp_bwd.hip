@@ -36,7 +36,8 @@ struct BwdArgs {
     int fused_rowsum;
     const __bf16* o; const __bf16* o_lo; const uint32_t* lo_flag;
     __bf16* dq; __bf16* dk; __bf16* dv;
-    const int* tab;
+    SmallCall small;
+    int64_t T_total;
     Schedule sched;      // tile descriptors and per-token segment bounds, written by the schedule kernel of the call
     ItemMap items;       // of the pass
     int n_groups, Hq, Hkv;
@@ -70,8 +71,8 @@ struct BwdArgs {
 // starts, reserve flag, q and dO, o and its residual, first keys), now two, and D by dot products of pairs (64 instructions for
 // 320).  With the forward's key tiles and addresses, us: 64 groups of a short prompt and 16 answers 2782 -> 2679, 64 groups of
 // 1000 tokens 981 -> 957, two small groups 20.6 -> 19.8, four long prompts 2442 -> 2434, 16K prompt 5192 -> 5225.
-template <int NW>
-__global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(BwdArgs a, EdgeArgs edge, int short_blocks, int row_blocks) {
+template <int NW, bool SMALL>          // SMALL: as in the forward
+__global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(TabArg table, BwdArgs a, EdgeArgs edge, int short_blocks, int row_blocks) {
     constexpr int BM = 32 * NW, BN = 64;
     constexpr int RD = 3;                       // LDS operand ring depth (prefetch distance RD - 1 MFMAs)
     constexpr int NE1 = 5;                      // elements of a half's vector work done under the previous D stage
@@ -92,6 +93,7 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(BwdArgs a, EdgeArgs 
     const int sb = (int)blockIdx.x - (NW == 8 ? row_blocks : 0), rb = (int)blockIdx.x - (NW == 8 ? 0 : short_blocks);
     if (NW == 8 ? sb >= 0 : rb < 0) {
         const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), i = min(w >> 1, PAIRS - 1);
+        if constexpr (SMALL) edge.tab = table_of(table);
         for (int64_t p0 = (int64_t)PAIRS * sb; p0 < edge.n_pairs; p0 += (int64_t)PAIRS * short_blocks) {
             short_rows_body<true>(edge, w < 2 * PAIRS ? p0 + i : edge.n_pairs, w & 1, &lds[0][0] + EDGE_LDS * i);
             __syncthreads();
@@ -100,7 +102,15 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(BwdArgs a, EdgeArgs 
     }
     Item item;
     if (!decode_item(rb, a.items, item)) return;
-    const TileDesc td = (BM == 256 ? a.sched.tiles256 : a.sched.tiles128)[item.tile];
+    TileDesc td;
+    SmallGroup sg;
+    if constexpr (SMALL) {
+        int ti;
+        sg = small_tile<BM>(table_of(table), a.n_groups, item.tile, threadIdx.x & 63, ti);
+        td = TileDesc{0, ti, sg.tok_base, sg.Lp, sg.Tg, 0, 0, 0};
+    } else {
+        td = (BM == 256 ? a.sched.tiles256 : a.sched.tiles128)[item.tile];
+    }
     GroupDesc gd;
     gd.tok_base = td.tok_base; gd.Lp = td.Lp; gd.Tg = td.Tg; gd.G = 0; gd.roff = nullptr;
     const int Lp = gd.Lp, Tg = gd.Tg;
@@ -108,7 +118,7 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(BwdArgs a, EdgeArgs 
     const WaveRows wr = wave_rows<NW>(td, item, a.items.rep, w);
     const int head = wr.head;
     const int t0 = wr.t0, t1 = wr.t1;
-    const int64_t T_total = a.tab[1];
+    const int64_t T_total = a.T_total;
     if (t0 >= Tg || (a.resp_only && t1 <= Lp)) return;      // past the group's end, or prompt rows only
 
     const int c = l & 31, hh = l >> 5, j = l & 15, c16 = (l >> 4) & 1;
@@ -122,11 +132,21 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(BwdArgs a, EdgeArgs 
     // What the rows' own words say is loaded ahead of everything and looked at behind the issue of the rows: a wait for each
     // of them in turn was a quarter of the prologue.
     const int64_t row_word = (int64_t)head * T_total + gd.tok_base + min(t, Tg - 1);
-    const int st_word = a.sched.key_lo[gd.tok_base + min(t, Tg - 1)];
-    const int b2_word = a.sched.key_lo[gd.tok_base + min(max(t0, Lp), Tg - 1)];
+    int st_word, b2_word;
+    if constexpr (SMALL) {
+        const int first = max(t0, Lp);                     // as in the forward
+        int s1, e1;
+        small_segment(sg, hh == 0 ? t : first, s1, e1);
+        b2_word = first < Tg ? __builtin_amdgcn_readlane(s1, 32) : 0;
+        s1 = __shfl(s1, c, 64);
+        st_word = t >= Lp ? s1 : 0;
+    } else {
+        st_word = a.sched.key_lo[gd.tok_base + min(t, Tg - 1)];
+        b2_word = a.sched.key_lo[gd.tok_base + min(max(t0, Lp), Tg - 1)];
+    }
     const float lse_word = a.lse[row_word], nD_word = a.fused_rowsum ? 0.f : a.nD[row_word];
     const bool have_lo = a.fused_rowsum && a.o_lo != nullptr;
-    const uint32_t lo_word = have_lo && a.lo_flag != nullptr ? *a.lo_flag : 1u;
+    const uint32_t lo_word = !have_lo || a.lo_flag == nullptr ? 1u : SMALL ? (uint32_t)reserve_tag_matches(a.small.tag, a.small.want, l) : *a.lo_flag;
 
     auto sgpr64 = [](const void* p) -> uint64_t {
         const uint64_t b = (uint64_t)(uintptr_t)p;
@@ -548,8 +568,8 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(BwdArgs a, EdgeArgs 
 // per buffer); left to the compiler they were 25 additions per step, and K did not fit the registers.
 // 8 -> 4 waves with these addresses, one box: 16K prompt with 32 answers 7.67 -> 7.24 ms, 64 groups of a short prompt
 // and 16 answers 4.44 -> 3.95 ms, 64 groups of 1000 tokens 1.33 -> 1.07 ms, response rows under an 8K prompt 0.77 -> 0.67 ms.
-template <int NW>
-__device__ __forceinline__ void dkdv_body(const BwdArgs& a, const TileDesc td, const int kvh, const int hr_only) {
+template <int NW, bool SMALL>
+__device__ __forceinline__ void dkdv_body(const BwdArgs& a, const SmallGroup& sg, const TileDesc td, const int kvh, const int hr_only) {
     const int ti = td.ti;
     constexpr int BNK = 128, BQ = 8 * NW;
     constexpr bool K_REG = NW == 4;                 // the wave's K rows stay in registers, only V in LDS
@@ -565,7 +585,7 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const TileDesc td, c
     GroupDesc gd;
     gd.tok_base = td.tok_base; gd.Lp = td.Lp; gd.Tg = td.Tg; gd.G = 0; gd.roff = nullptr;
     const int Lp = gd.Lp, Tg = gd.Tg;
-    const int64_t T_total = a.tab[1];
+    const int64_t T_total = a.T_total;
 
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
     const int c = l & 31, hh = l >> 5, j = l & 15, c16 = (l >> 4) & 1;
@@ -580,8 +600,17 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const TileDesc td, c
     const int s1 = min(s0 + BNK, Tg);
     // rows [s, e_s) see this lane's key; row_end: where the rows that see any key of the tile end (the
     // group's end if the tile holds a prompt key, else the end of its last key's response)
-    const int e_s = valid ? a.sched.row_hi[gd.tok_base + s] : 0;
-    const int row_end = __builtin_amdgcn_readfirstlane(s0 < Lp ? Tg : a.sched.row_hi[gd.tok_base + s1 - 1]);
+    int e_s, row_end;
+    if constexpr (SMALL) {
+        int b1, e1;
+        small_segment(sg, hh == 0 ? s : s1 - 1, b1, e1);
+        row_end = s0 < Lp ? Tg : __builtin_amdgcn_readlane(e1, 32);
+        e1 = __shfl(e1, c, 64);
+        e_s = !valid ? 0 : s < Lp ? Tg : e1;
+    } else {
+        e_s = valid ? a.sched.row_hi[gd.tok_base + s] : 0;
+        row_end = __builtin_amdgcn_readfirstlane(s0 < Lp ? Tg : a.sched.row_hi[gd.tok_base + s1 - 1]);
+    }
     // smallest / largest row bound e_s over the wave's keys (prompt keys: Tg; response keys: the
     // end of their response, non-decreasing in s); lanes 0..31 hold the wave's keys in order
     const int e_min = !wave_valid ? 0 : (ws1 < Lp ? Tg : __builtin_amdgcn_readlane(e_s, max(ws0, Lp) - ws0));
@@ -968,11 +997,22 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const TileDesc td, c
     }
 }
 
-template <int NW>
-__global__ __launch_bounds__(64 * NW, 2) void bwd_dkdv_kernel(BwdArgs a) {
+template <int NW, bool SMALL>
+__global__ __launch_bounds__(64 * NW, 2) void bwd_dkdv_kernel(TabArg table, BwdArgs a) {
+    if (SMALL && blockIdx.x == 0 && threadIdx.x < 64 && a.small.tag_mode != TAG_KEEP)       // (the dq pass is through)
+        reserve_tag_body(a.small.tag, a.small.want, a.small.tag_mode, threadIdx.x);
     Item item;           // per (key tile, q head) where the pass is split over the q heads, else per (key tile, kv head)
     if (!decode_item(blockIdx.x, a.items, item)) return;
-    dkdv_body<NW>(a, a.sched.key_tiles[item.tile], item.kvh, item.hr);
+    TileDesc td;
+    SmallGroup sg;
+    if constexpr (SMALL) {
+        int ti;
+        sg = small_tile<128>(table_of(table), a.n_groups, item.tile, threadIdx.x & 63, ti);
+        td = TileDesc{0, ti, sg.tok_base, sg.Lp, sg.Tg, 0, 0, 0};
+    } else {
+        td = a.sched.key_tiles[item.tile];
+    }
+    dkdv_body<NW, SMALL>(a, sg, td, item.kvh, item.hr);
 }
 
 // Second stage of the head-split dkdv pass: dk = scale * sum_hr partial[0][hr], dv = sum_hr
@@ -1100,8 +1140,9 @@ hipError_t launch_bwd_bf16(const Problem& p, hipStream_t s) {
     a.q = (const __bf16*)p.q; a.k = (const __bf16*)p.k; a.v = (const __bf16*)p.v; a.d_o = (const __bf16*)p.d_o;
     a.lse = p.lse; a.nD = p.Dbuf; a.L2 = p.Dbuf + (int64_t)p.Hq * p.total_tokens;
     a.dq = (__bf16*)p.dq; a.dk = (__bf16*)p.dk; a.dv = (__bf16*)p.dv;
-    a.tab = p.tab; a.sched = p.sched; a.n_groups = p.n_groups; a.Hq = p.Hq; a.Hkv = p.Hkv; a.scale = p.scale; a.c = p.scale * LOG2E;
+    a.small = p.small; a.T_total = p.total_tokens; a.sched = p.sched; a.n_groups = p.n_groups; a.Hq = p.Hq; a.Hkv = p.Hkv; a.scale = p.scale; a.c = p.scale * LOG2E;
     a.resp_only = p.resp_only; a.accumulate = p.accumulate;
+    const TabArg table = small_table(p);
     if (p.stages & STAGE_DQ) {
         // short key loops: the four-wave shape, two workgroups per CU (the forward's rule, see bwd_dq_kernel)
         const bool small = use_small_shape(p);
@@ -1109,12 +1150,24 @@ hipError_t launch_bwd_bf16(const Problem& p, hipStream_t s) {
         a.items = make_item_map(n_tiles, p.Hq, p.Hkv);
         const EdgeArgs edge = edge_args(p);
         const int shorts = (edge_blocks(edge, small ? 2 : 3) + 7) & ~7, total = grid + shorts;
-        if (small) hipLaunchKernelGGL(bwd_dq_kernel<4>, dim3(total), dim3(256), 0, s, a, edge, shorts, grid);
-        else hipLaunchKernelGGL(bwd_dq_kernel<8>, dim3(total), dim3(512), 0, s, a, edge, shorts, grid);
+        auto launch = [&](auto small_call) {
+            constexpr bool S = decltype(small_call)::value;
+            if (small) hipLaunchKernelGGL((bwd_dq_kernel<4, S>), dim3(total), dim3(256), 0, s, table, a, edge, shorts, grid);
+            else hipLaunchKernelGGL((bwd_dq_kernel<8, S>), dim3(total), dim3(512), 0, s, table, a, edge, shorts, grid);
+        };
+        if (p.small.on) launch(std::true_type{}); else launch(std::false_type{});
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     if (p.stages & STAGE_DKDV) {
+        auto launch = [&](int waves, int grid) {
+            auto go = [&](auto small_call) {
+                constexpr bool S = decltype(small_call)::value;
+                if (waves == 8) hipLaunchKernelGGL((bwd_dkdv_kernel<8, S>), dim3(grid), dim3(512), 0, s, table, a);
+                else hipLaunchKernelGGL((bwd_dkdv_kernel<4, S>), dim3(grid), dim3(256), 0, s, table, a);
+            };
+            if (p.small.on) go(std::true_type{}); else go(std::false_type{});
+        };
         const int n_tiles = count_tiles(p, 128);
         a.rep = p.Hq / p.Hkv;
         a.head_split = p.dkdv_partial != nullptr;
@@ -1122,15 +1175,14 @@ hipError_t launch_bwd_bf16(const Problem& p, hipStream_t s) {
         if (a.head_split) {
             const int grid = grid_for_items(n_tiles, p.Hq, p.Hkv);
             a.items = make_item_map(n_tiles, p.Hq, p.Hkv);
-            hipLaunchKernelGGL(bwd_dkdv_kernel<8>, dim3(grid), dim3(512), 0, s, a);
+            launch(8, grid);
             const int64_t n4 = p.total_tokens * p.Hkv * 32;
             hipLaunchKernelGGL(dkdv_reduce_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, a.partial, a.dk, a.dv,
                                n4, p.Hq / p.Hkv, p.scale, a.accumulate);
         } else {
             const int grid = grid_for_items(n_tiles, p.Hkv, p.Hkv);
             a.items = make_item_map(n_tiles, p.Hkv, p.Hkv);
-            if (dkdv_waves(p) == 8) hipLaunchKernelGGL(bwd_dkdv_kernel<8>, dim3(grid), dim3(512), 0, s, a);
-            else hipLaunchKernelGGL(bwd_dkdv_kernel<4>, dim3(grid), dim3(256), 0, s, a);
+            launch(dkdv_waves(p), grid);
         }
         e = hipGetLastError();
     }

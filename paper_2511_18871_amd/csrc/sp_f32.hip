@@ -100,22 +100,8 @@ __global__ __launch_bounds__(256) void schedule_kernel(const int* __restrict__ t
     schedule_body(tab, n_groups, T_total, n256, n128, tiles256, tiles128, key_tiles, key_lo, row_hi, key_order);
 }
 
-// Tag block maintenance, one wave.  See sp_launch.hpp for the modes.  A reserve written for all rows
-// (word 10 = 0) also serves a backward over response rows only (want word 10 = 1), not the reverse.
-__device__ __forceinline__ void reserve_tag_body(uint32_t* __restrict__ blk, const ReserveTag& want, int mode) {
-    const int i = threadIdx.x;                  // one whole wave: lanes 0..63
-    if (mode == TAG_CLEAR) { blk[i] = 0u; return; }
-    if (mode == TAG_WRITE) { blk[i] = i < TAG_WORDS ? want.w[i] : 0u; return; }
-    const uint32_t have = blk[i];
-    bool same = i >= TAG_WORDS || have == want.w[i];
-    if (i == 10) same = have == want.w[10] || have == 0u;
-    const bool ok = __builtin_amdgcn_ballot_w64(!same) == 0;
-    if (i < TAG_WORDS && !ok) blk[i] = 0u;
-    if (i == TAG_FLAG_WORD) blk[i] = ok ? 1u : 0u;
-}
-
 __global__ __launch_bounds__(64) void reserve_tag_kernel(uint32_t* __restrict__ blk, ReserveTag want, int mode) {
-    reserve_tag_body(blk, want, mode);
+    reserve_tag_body(blk, want, mode, threadIdx.x);
 }
 
 // Everything a call does ahead of its attention kernels, in one launch, for segment tables that fit one
@@ -135,7 +121,7 @@ __global__ __launch_bounds__(256) void prepare_kernel(PrepChunk chunk, int n_wor
         tab_s[i] = x;
         if (blockIdx.x == 0) dev_tab[i] = x;
     }
-    if (blockIdx.x == 0 && threadIdx.x < 64 && tag_mode != TAG_KEEP) reserve_tag_body(tag_blk, want, tag_mode);
+    if (blockIdx.x == 0 && threadIdx.x < 64 && tag_mode != TAG_KEEP) reserve_tag_body(tag_blk, want, tag_mode, threadIdx.x);
     __syncthreads();
     if (with_schedule) schedule_body(tab_s, n_groups, T_total, n256, n128, tiles256, tiles128, key_tiles, key_lo, row_hi, key_order);
 }

@@ -30,13 +30,13 @@ struct FwdArgs {
     const __bf16* q[MAX_SETS]; const __bf16* k[MAX_SETS]; const __bf16* v[MAX_SETS];
     __bf16* o[MAX_SETS]; float* lse[MAX_SETS];
     int blocks_per_set;
-    const int* tab;
     Schedule sched; // tile descriptors and per-token segment bounds, written by the schedule kernel of the call
     ItemMap items;
-    int n_groups, Hq, Hkv;
+    int n_groups, T_total, Hq, Hkv;
     float c;        // softmax_scale * log2(e)
     int naive;
     int resp_only;  // compute and write response rows only
+    SmallCall small;
     __bf16* o_lo;   // optional (single-set launches): o_fp32 - bf16(o), rounded to bf16, same layout as o
 };
 
@@ -72,8 +72,9 @@ struct FwdArgs {
 // NAIVE = the measurement baseline (every tile at or below the packed diagonal, mask applied element by
 // element): a separate instantiation, so that it shows under its own name in kernel traces and its
 // branches cost the product kernel nothing.
-template <int NW, bool NAIVE>
-__global__ __launch_bounds__(NW * 64, 2) void fwd_kernel(FwdArgs a) {      // two waves per SIMD in either shape
+// SMALL = a call whose kernels look everything up themselves (SmallCall); as a run-time branch it cost the others 0.5 to 1 %.
+template <int NW, bool NAIVE, bool SMALL>
+__global__ __launch_bounds__(NW * 64, 2) void fwd_kernel(TabArg table, FwdArgs a) {      // two waves per SIMD in either shape
     constexpr int BM = 32 * NW;
     constexpr int NB = NW == 8 ? 4 : 2;            // K buffers = V buffers
     constexpr int RD = 3;      // LDS operand ring depth (prefetch distance RD - 1 MFMAs)
@@ -86,10 +87,20 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd_kernel(FwdArgs a) {      // tw
     static_assert(MAX_SETS == 4, "sets are counted by comparisons");
     const __bf16* const aq = a.q[set]; const __bf16* const ak = a.k[set]; const __bf16* const av = a.v[set];
     __bf16* const ao = a.o[set]; float* const alse = a.lse[set];
+    if (SMALL && bid == 0 && threadIdx.x < 64 && a.small.tag_mode != TAG_KEEP)
+        reserve_tag_body(a.small.tag, a.small.want, a.small.tag_mode, threadIdx.x);
     Item item;
     if (!decode_item(bid - set * bps, a.items, item)) return;
     // the tile's descriptor: one 32-byte load instead of a bisection over the groups and the group's entry
-    const TileDesc td = (BM == 256 ? a.sched.tiles256 : a.sched.tiles128)[item.tile];
+    TileDesc td;
+    SmallGroup sg;
+    if constexpr (SMALL) {
+        int ti;
+        sg = small_tile<BM>(table_of(table), a.n_groups, item.tile, threadIdx.x & 63, ti);
+        td = TileDesc{0, ti, sg.tok_base, sg.Lp, sg.Tg, 0, 0, 0};
+    } else {
+        td = (BM == 256 ? a.sched.tiles256 : a.sched.tiles128)[item.tile];
+    }
     GroupDesc gd;
     gd.tok_base = td.tok_base; gd.Lp = td.Lp; gd.Tg = td.Tg; gd.G = 0; gd.roff = nullptr;
     const int Lp = gd.Lp, Tg = gd.Tg;
@@ -97,7 +108,7 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd_kernel(FwdArgs a) {      // tw
     const WaveRows wr = wave_rows<NW>(td, item, a.items.rep, w);
     const int head = wr.head;
     const int t0 = wr.t0, t1 = wr.t1;
-    const int T_total = a.tab[1];
+    const int T_total = a.T_total;
     if (t0 >= Tg || (a.resp_only && t1 <= Lp)) return;      // past the group's end, or prompt rows only
 
     const int c = l & 31, hh = l >> 5, j16 = l & 15, c16 = (l >> 4) & 1;
@@ -109,8 +120,18 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd_kernel(FwdArgs a) {      // tw
     const bool wave_valid = tw0 < Tg;
     const int tw1 = min(tw0 + 31, Tg - 1);
     // first own-segment key of this lane's row and of the workgroup's first response row (0 on the prompt)
-    const int st = valid ? a.sched.key_lo[gd.tok_base + t] : 0;
-    const int b2 = __builtin_amdgcn_readfirstlane(a.sched.key_lo[gd.tok_base + min(max(t0, Lp), Tg - 1)]);
+    int st = 0, b2;
+    if constexpr (SMALL) {
+        const int first = max(t0, Lp);                     // as a lane's token, so that one search serves both
+        int s1, e1;
+        small_segment(sg, hh == 0 ? t : first, s1, e1);
+        b2 = first < Tg ? __builtin_amdgcn_readlane(s1, 32) : 0;
+        s1 = __shfl(s1, c, 64);
+        st = valid && t >= Lp ? s1 : 0;
+    } else {
+        st = valid ? a.sched.key_lo[gd.tok_base + t] : 0;
+        b2 = __builtin_amdgcn_readfirstlane(a.sched.key_lo[gd.tok_base + min(max(t0, Lp), Tg - 1)]);
+    }
     // lanes 0..31 hold the wave's rows in order: the last valid row's start comes from its lane
     const int st_last = wave_valid ? __builtin_amdgcn_readlane(st, tw1 - tw0) : 0;
 
@@ -539,7 +560,8 @@ hipError_t launch_fwd_bf16(const Problem& p, hipStream_t s) {
         a.v[i] = (const __bf16*)(multi ? p.vs[i] : p.v);
         a.o[i] = (__bf16*)(multi ? p.os[i] : p.o_out); a.lse[i] = multi ? p.lses[i] : p.lse_out;
     }
-    a.tab = p.tab; a.n_groups = p.n_groups; a.sched = p.sched;
+    a.n_groups = p.n_groups; a.T_total = (int)p.total_tokens; a.sched = p.sched; a.small = p.small;
+    const TabArg table = small_table(p);
     a.Hq = p.Hq; a.Hkv = p.Hkv; a.c = p.scale * LOG2E; a.naive = p.naive; a.resp_only = p.resp_only;
     a.o_lo = n_sets == 1 ? (__bf16*)p.o_lo_out : nullptr;
     // Short key loops: the four-wave shape, two workgroups per CU (see fwd_kernel).  The naive baseline keeps
@@ -550,9 +572,14 @@ hipError_t launch_fwd_bf16(const Problem& p, hipStream_t s) {
     a.items = make_item_map(n_tiles, p.Hq, p.Hkv);
     a.blocks_per_set = grid_for_items(n_tiles, p.Hq, p.Hkv);
     if (a.blocks_per_set % 8 != 0) a.blocks_per_set += 8 - a.blocks_per_set % 8;
-    if (p.naive) hipLaunchKernelGGL((fwd_kernel<8, true>), dim3(a.blocks_per_set * n_sets), dim3(512), 0, s, a);
-    else if (small) hipLaunchKernelGGL((fwd_kernel<4, false>), dim3(a.blocks_per_set * n_sets), dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((fwd_kernel<8, false>), dim3(a.blocks_per_set * n_sets), dim3(512), 0, s, a);
+    const dim3 grid(a.blocks_per_set * n_sets);
+    auto launch = [&](auto small_call) {
+        constexpr bool S = decltype(small_call)::value;
+        if (p.naive) hipLaunchKernelGGL((fwd_kernel<8, true, S>), grid, dim3(512), 0, s, table, a);
+        else if (small) hipLaunchKernelGGL((fwd_kernel<4, false, S>), grid, dim3(256), 0, s, table, a);
+        else hipLaunchKernelGGL((fwd_kernel<8, false, S>), grid, dim3(512), 0, s, table, a);
+    };
+    if (p.small.on) launch(std::true_type{}); else launch(std::false_type{});
     return hipGetLastError();
 }
 

@@ -39,6 +39,66 @@ struct ReserveTag { uint32_t w[TAG_WORDS]; };
 constexpr int TAG_CLEAR = 0, TAG_WRITE = 1, TAG_CHECK = 2;
 constexpr int TAG_KEEP = -1;      // for launch_prepare: leave the tag block as it is
 
+// What the attention kernels of a small call do themselves instead of the preparation launch: the table comes as a kernel
+// argument, a wave looks its tile and its tokens' segments up in registers, and the tag block is kept by the kernels
+// (forward: written by the first workgroup; backward: compared by each workgroup of the dq pass, updated by the dkdv pass).
+// us, before -> after: one short group's forward 17.8 -> 15.4, two small groups' training pass 69.8 -> 66.8, one 1K prompt
+// 248.9 -> 244.9, one group of 9000 tokens, 28/4 heads (1988 tiles times heads), 2419.7 -> 2411.5.  Larger calls would not notice.
+struct SmallCall { int on; int tag_mode; ReserveTag want; uint32_t* tag; };
+// Tag block maintenance by one wave (lane i = word i).  A reserve written for all rows (word 10 = 0) also serves a backward
+// over response rows only (want word 10 = 1), not the reverse.
+__device__ __forceinline__ bool reserve_tag_matches(const uint32_t* blk, const ReserveTag& want, int i) {
+    const uint32_t have = blk[i];
+    uint32_t w = 0;
+#pragma unroll
+    for (int k = 0; k < TAG_WORDS; ++k) if (i == k) w = want.w[k];
+    bool same = i >= TAG_WORDS || have == w;
+    if (i == 10) same = same || have == 0u;
+    return __builtin_amdgcn_ballot_w64(!same) == 0;
+}
+__device__ __forceinline__ void reserve_tag_body(uint32_t* blk, const ReserveTag& want, int mode, int i) {
+    if (mode == TAG_CLEAR) { blk[i] = 0u; return; }
+    if (mode == TAG_WRITE) {
+        uint32_t w = 0;
+#pragma unroll
+        for (int k = 0; k < TAG_WORDS; ++k) if (i == k) w = want.w[k];
+        blk[i] = w;
+        return;
+    }
+    const bool ok = reserve_tag_matches(blk, want, i);
+    if (i < TAG_WORDS && !ok) blk[i] = 0u;
+    if (i == TAG_FLAG_WORD) blk[i] = ok ? 1u : 0u;
+}
+
+// Lookups of a whole wave in a table of at most 64 groups of at most 63 responses each: a lane holds a group, or a response
+// offset of the tile's group, and the searches are ballots and lane exchanges, not chains of loads.
+constexpr int SMALL_CALL_TILES = 2048;      // 128-row tiles times q heads
+constexpr int SMALL_GROUPS = 64, SMALL_RESPONSES = 63;
+struct SmallGroup { int tok_base, Lp, Tg, G, off; };      // off: response offset `lane` of the group (lanes 0 .. G)
+template <int BT>
+__device__ __forceinline__ SmallGroup small_tile(const int* tab, int n_groups, int tile, int l, int& ti) {
+    SmallGroup g;
+    const int* e = tab + TAB_HEADER + TAB_GROUP_WORDS * min(l, n_groups - 1);
+    const int tok = e[0], Lp = e[1], Tg = e[2], roff = e[3], G = e[4], before = e[BT == 256 ? TAB_TILES256 : TAB_TILES128];
+    const int n = 63 - __clzll((long long)__builtin_amdgcn_ballot_w64(l < n_groups && before <= tile));   // before[0] = 0
+    g.tok_base = __builtin_amdgcn_readlane(tok, n); g.Lp = __builtin_amdgcn_readlane(Lp, n);
+    g.Tg = __builtin_amdgcn_readlane(Tg, n); g.G = __builtin_amdgcn_readlane(G, n);
+    ti = tile - __builtin_amdgcn_readlane(before, n);
+    g.off = tab[__builtin_amdgcn_readlane(roff, n) + min(l, g.G)];
+    return g;
+}
+// the response that holds token t >= Lp (its start and end by lane): the last offset ahead of the end that is at most t
+__device__ __forceinline__ void small_segment(const SmallGroup& g, int t, int& st, int& en) {
+    int pos = 0;
+#pragma unroll
+    for (int step = 32; step >= 1; step >>= 1) {
+        const int at = pos + step, x = __shfl(g.off, at & 63, 64);
+        if (at < g.G && x <= t) pos = at;
+    }
+    st = __shfl(g.off, pos, 64);
+    en = __shfl(g.off, pos + 1, 64);
+}
+
 struct Problem {
     const void* q; const void* k; const void* v;
     const void* o; const float* lse; const void* d_o;     // backward inputs (o also fwd output)
@@ -70,6 +130,7 @@ struct Problem {
     float* dkdv_partial;                                  // bf16 backward on small problems: fp32 per-q-head partials
     // host copies of the per-group token counts and of the whole segment table, for grid sizing and
     // for choosing kernel shapes
+    SmallCall small;
     const int* host_group_tokens;
     const int32_t* host_table;
 };
@@ -114,6 +175,16 @@ hipError_t launch_prepare(const int32_t* host_words, int n_words, int* dev_tab, 
 
 // The threshold of sp_attn_set_small_shape_steps(), or < 0: the rule of use_small_shape().
 int small_shape_steps();
+
+inline TabArg small_table(const Problem& p) {
+    return p.small.on ? make_tab_arg(p.host_table, (size_t)p.host_table[2], nullptr) : make_tab_arg(p.host_table, 0, nullptr);
+}
+
+// Calls whose kernels look everything up themselves (SmallCall)
+inline bool use_small_call(const Problem& p, size_t words, int max_responses) {
+    return words <= (size_t)ARG_WORDS && p.n_groups <= SMALL_GROUPS && max_responses <= SMALL_RESPONSES &&
+           (int64_t)p.n_tiles128 * p.Hq <= SMALL_CALL_TILES;
+}
 
 // Number of (row tile of `bm` rows, 64-key tile) pairs of one q head that hold an allowed pair, and of row tiles (host
 // arithmetic on the segment table).  With one q head per kv head these are the steps and the workgroups that run; with
