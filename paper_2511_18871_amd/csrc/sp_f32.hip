@@ -1,9 +1,8 @@
 // float32 plain-ALU debug path of shared-prompt attention, the segment-table upload
 // and the backward preprocess D = rowsum(dO * O).
 //
-// The debug kernels give one wavefront a single (row, head) or (key, kv head) and walk
-// the allowed keys / rows of the Section 4.3 mask in chunks of 64, one per lane.  No
-// MFMA, no LDS: they exist to cross-check the MFMA path and to serve float32 callers.
+// The debug kernels give one wavefront, or the eight of a workgroup, a single (row, head) or (key, kv head) and walk
+// the allowed keys / rows of the Section 4.3 mask in chunks.  No MFMA: they exist to cross-check the MFMA path and to serve float32 callers.
 #include "sp_common.hpp"
 #include "sp_launch.hpp"
 #include <type_traits>
@@ -231,32 +230,47 @@ __global__ __launch_bounds__(256) void rowsum_bf16_kernel(const __bf16* __restri
     }
 }
 
-// The float32 kernels are bound by latency, not by arithmetic: a wave walks its keys (rows) in chunks of 64, and per chunk
-// each lane first needs a whole row of its own (dot_row: all loads ahead of the sums; the wave's own row x is uniform) and
-// then the wave a row per key, ROWS of them in flight (add_rows; with one in flight a chunk took 5 us).
-// Order of every sum as in the plain loops.  One box, a group of 64 + 4 x 32 tokens, 2 heads of 64, us before -> after:
-// forward 19.6 -> 10.8, dq 23.0 -> 13.0, dkdv 37.1 -> 24.0; backward of 1500 + 5 x 200 tokens, 4 heads of 128,
-// 4.30 -> 3.29 ms (ROWS = 16: 3.56).
-constexpr int ROWS = 32;
-template <int DH>
-__device__ __forceinline__ float dot_row(const float* __restrict__ x, const float* __restrict__ y) {
-    f32x4 v[DH / 4];
+// The float32 kernels are bound by latency, not by arithmetic: a wave takes keys (rows) in chunks, and per chunk it needs one
+// batch of loads for the scores and one (rows 32 at a time, lanes along a row) for the sums.  Two shapes:
+//   WIDE, where there are few (row, head) or (key, kv head): a workgroup of eight waves per one of them, every wave takes
+//     each eighth chunk of 32 keys, two lanes per key.  The waves' sums meet in LDS, in a fixed order.
+//   else a wave per one of them and chunks of 64 keys, a lane per key, the wave's own row in scalar registers.
+// With the rowsum within the dq kernel and the table as an argument, a training pass of 64 + 4 x 32 tokens, 2 heads of 64: 54.0 ->
+// 33.0 us; 300 + 5 x 100, 4 / 2 heads of 64: 321 -> 222.
+constexpr int F32_WAVES = 8;
+template <bool WIDE> constexpr int CHUNK = WIDE ? 32 : 64;
+template <bool WIDE> constexpr int F32_BLOCK = WIDE ? 64 * F32_WAVES : 256;
+// dot product of two rows in the lane, or (WIDE) half of it in each lane of the pair (l, l ^ 32)
+template <int DH, bool WIDE>
+__device__ __forceinline__ float dot_row(const float* __restrict__ x, const float* __restrict__ y, int l) {
+    constexpr int N = WIDE ? DH / 8 : DH / 4;
+    const int at = WIDE ? DH / 2 * (l >> 5) : 0;
+    f32x4 v[N];
 #pragma unroll
-    for (int i = 0; i < DH / 4; ++i) v[i] = *reinterpret_cast<const f32x4*>(y + 4 * i);
+    for (int i = 0; i < N; ++i) v[i] = *reinterpret_cast<const f32x4*>(y + at + 4 * i);
     float acc = 0.f;
+    if constexpr (WIDE) {
+        f32x4 u[N];
 #pragma unroll
-    for (int i = 0; i < DH; ++i) acc = __builtin_fmaf(x[i], v[i >> 2][i & 3], acc);
+        for (int i = 0; i < N; ++i) u[i] = *reinterpret_cast<const f32x4*>(x + at + 4 * i);
+#pragma unroll
+        for (int i = 0; i < 4 * N; ++i) acc = __builtin_fmaf(u[i >> 2][i & 3], v[i >> 2][i & 3], acc);
+        return pair_sum(acc);
+    }
+#pragma unroll
+    for (int i = 0; i < 4 * N; ++i) acc = __builtin_fmaf(x[i], v[i >> 2][i & 3], acc);
     return acc;
 }
 __device__ __forceinline__ float lane_value(float x, int lane) {      // of a wave-uniform lane
     return __uint_as_float((unsigned)__builtin_amdgcn_readlane((int)__float_as_uint(x), lane));
 }
 // acc[e] += sum over j < n of lane j's p * row j's element l + 64 e; p is 0 in the lanes from n on.  Row j at base + j * stride.
-// The last ROWS rows may run past n: they repeat row n - 1 with weight 0, which is nothing unless that row holds an
+// The rows of a batch past n repeat row n - 1 with weight 0, which is nothing unless that row holds an
 // infinity (0 * inf).  A sum that became NaN is therefore taken once more over the n rows alone, one by one; excluding the
-// repeated rows with a select per row instead cost the tiny group above 52.8 -> 60.3 us a training pass.
+// repeated rows with a select per row instead costs a tenth of the kernel.
 template <int PER>
 __device__ __forceinline__ void add_rows(float (&acc)[PER], float p, const float* __restrict__ base, int64_t stride, int n, int l) {
+    constexpr int ROWS = 32;
     float start[PER];
 #pragma unroll
     for (int e = 0; e < PER; ++e) start[e] = acc[e];
@@ -289,22 +303,38 @@ __device__ __forceinline__ void add_rows(float (&acc)[PER], float p, const float
         }
     }
 }
+// The chunks of keys that row t sees: those of the prompt, then those of its response from its first token on.
+template <int C>
+struct KeyChunks {
+    int n1, n, end1, st, end;
+    __device__ __forceinline__ KeyChunks(const GroupDesc& gd, int t) {
+        st = seg_start(gd, t);
+        end1 = min(gd.Lp, t + 1);
+        end = t + 1;
+        n1 = (end1 + C - 1) / C;
+        n = n1 + (t >= gd.Lp ? (end - st + C - 1) / C : 0);
+    }
+    __device__ __forceinline__ int first(int i) const { return i < n1 ? C * i : st + C * (i - n1); }
+    __device__ __forceinline__ int count(int i) const { return min(C, (i < n1 ? end1 : end) - first(i)); }
+};
 
-template <int DH>
-__global__ __launch_bounds__(256) void fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
-                                                      const float* __restrict__ v, float* __restrict__ o,
-                                                      float* __restrict__ lse, const int* __restrict__ tab,
-                                                      int Hq, int Hkv, float scale, int resp_only) {
+template <int DH, bool WIDE>
+__global__ __launch_bounds__(F32_BLOCK<WIDE>) void fwd_f32_kernel(TabArg table, const float* __restrict__ q, const float* __restrict__ k,
+                                                                 const float* __restrict__ v, float* __restrict__ o,
+                                                                 float* __restrict__ lse, int64_t T_total, int Hq, int Hkv,
+                                                                 float scale, int resp_only) {
     constexpr int PER = DH / 64;
-    const int64_t T_total = tab[1];
-    const int64_t gw = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int l = threadIdx.x & 63;
-    if (gw >= T_total * Hq) return;
-    const int tok = (int)(gw / Hq), h = (int)(gw % Hq);
+    __shared__ float sh_m[F32_WAVES], sh_l[F32_WAVES], sh_acc[WIDE ? F32_WAVES : 1][DH];
+    const int* const tab = table_of(table);
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
+    const int64_t item = WIDE ? blockIdx.x : (int64_t)blockIdx.x * 4 + w;
+    if (item >= T_total * Hq) return;
+    const int tok = (int)(item / Hq), h = (int)(item % Hq);
     const GroupDesc gd = load_group(tab, find_group_of_token(tab, tok));
     const int t = tok - gd.tok_base;
     if (resp_only && t < gd.Lp) return;
-    const int st = seg_start(gd, t);
+    constexpr int C = CHUNK<WIDE>;
+    const KeyChunks<C> ch(gd, t);
     const int kvh = h / (Hq / Hkv);
     const float* qrow = q + ((int64_t)tok * Hq + h) * DH;
     const float* kb = k + ((int64_t)gd.tok_base * Hkv + kvh) * DH;
@@ -314,123 +344,178 @@ __global__ __launch_bounds__(256) void fwd_f32_kernel(const float* __restrict__ 
     float m = -INFINITY, lsum = 0.f, acc[PER];
 #pragma unroll
     for (int e = 0; e < PER; ++e) acc[e] = 0.f;
-    for (int s0 = 0; s0 <= t; s0 += 64) {
-        if (s0 >= gd.Lp && s0 + 64 <= st) continue;        // wholly inside other responses
-        const int s = s0 + l;
-        const bool ok = s <= t && (s < gd.Lp || s >= st);
-        const float sc = ok ? scale * dot_row<DH>(qrow, kb + (int64_t)s * kvs) : -INFINITY;
+    for (int i = WIDE ? w : 0; i < ch.n; i += WIDE ? F32_WAVES : 1) {
+        const int s0 = ch.first(i), nk = ch.count(i), key = l & (C - 1);
+        const bool ok = key < nk;
+        const float dot = dot_row<DH, WIDE>(qrow, kb + (int64_t)(s0 + min(key, nk - 1)) * kvs, l);
+        const float sc = ok ? scale * dot : -INFINITY;
         const float mnew = fmaxf(m, wave_max(sc));
         if (mnew == -INFINITY) continue;
         const float alpha = expf(m - mnew);
         const float p = ok ? expf(sc - mnew) : 0.f;
-        lsum = lsum * alpha + wave_sum(p);
+        lsum = lsum * alpha + wave_sum(l < C ? p : 0.f);
         m = mnew;
-        const int nk = min(64, t + 1 - s0);
 #pragma unroll
         for (int e = 0; e < PER; ++e) acc[e] *= alpha;
         add_rows<PER>(acc, p, vb + (int64_t)s0 * kvs, kvs, nk, l);
     }
-    float* orow = o + ((int64_t)tok * Hq + h) * DH;
+    if constexpr (!WIDE) {
+        float* const orow = o + ((int64_t)tok * Hq + h) * DH;
 #pragma unroll
-    for (int e = 0; e < PER; ++e) orow[l + 64 * e] = acc[e] / lsum;
-    if (l == 0) lse[(int64_t)h * T_total + tok] = m + logf(lsum);
+        for (int e = 0; e < PER; ++e) orow[l + 64 * e] = acc[e] / lsum;
+        if (l == 0) lse[(int64_t)h * T_total + tok] = m + logf(lsum);
+        return;
+    }
+    if (l == 0) { sh_m[w] = m; sh_l[w] = lsum; }
+#pragma unroll
+    for (int e = 0; e < PER; ++e) sh_acc[w][l + 64 * e] = acc[e];
+    __syncthreads();
+    if ((int)threadIdx.x >= DH) return;
+    float mt = sh_m[0];
+#pragma unroll
+    for (int i = 1; i < F32_WAVES; ++i) mt = fmaxf(mt, sh_m[i]);
+    float ls = 0.f, x = 0.f;
+#pragma unroll
+    for (int i = 0; i < F32_WAVES; ++i) {
+        if (sh_m[i] == -INFINITY) continue;              // a wave without a key (or with scores of -inf only)
+        const float f = expf(sh_m[i] - mt);
+        ls = __builtin_fmaf(sh_l[i], f, ls);
+        x = __builtin_fmaf(sh_acc[i][threadIdx.x], f, x);
+    }
+    o[((int64_t)tok * Hq + h) * DH + threadIdx.x] = x / ls;
+    if (threadIdx.x == 0) lse[(int64_t)h * T_total + tok] = mt + logf(ls);
 }
 
 // dQ[t,h] = scale * sum_s dS[t,s] K[s],  dS = P * (dP - D)
-template <int DH>
-__global__ __launch_bounds__(256) void bwd_dq_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
-                                                         const float* __restrict__ v, const float* __restrict__ d_o,
-                                                         const float* __restrict__ lse, const float* __restrict__ D,
-                                                         float* __restrict__ dq, const int* __restrict__ tab,
-                                                         int Hq, int Hkv, float scale, int resp_only) {
+// `o` (a call that runs the rowsum stage too): D is formed here, with the arithmetic of rowsum_kernel, and written for the
+// dkdv kernel.  `tag`: cleared (a call without a preparation launch).
+template <int DH, bool WIDE>
+__global__ __launch_bounds__(F32_BLOCK<WIDE>, WIDE && DH == 64 ? 4 : 1) void bwd_dq_f32_kernel(TabArg table, const float* __restrict__ q, const float* __restrict__ k,
+                                                                    const float* __restrict__ v, const float* __restrict__ d_o,
+                                                                    const float* __restrict__ o, const float* __restrict__ lse,
+                                                                    float* __restrict__ D, float* __restrict__ dq, uint32_t* __restrict__ tag,
+                                                                    int64_t T_total, int Hq, int Hkv, float scale, int resp_only) {
     constexpr int PER = DH / 64;
-    const int64_t T_total = tab[1];
-    const int64_t gw = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int l = threadIdx.x & 63;
-    if (gw >= T_total * Hq) return;
-    const int tok = (int)(gw / Hq), h = (int)(gw % Hq);
+    __shared__ float sh_acc[WIDE ? F32_WAVES : 1][DH];
+    const int* const tab = table_of(table);
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
+    const int64_t item = WIDE ? blockIdx.x : (int64_t)blockIdx.x * 4 + w;
+    if (item >= T_total * Hq) return;
+    const int tok = (int)(item / Hq), h = (int)(item % Hq);
+    if (tag && blockIdx.x == 0 && w == 0) tag[l] = 0u;
     const GroupDesc gd = load_group(tab, find_group_of_token(tab, tok));
     const int t = tok - gd.tok_base;
     if (resp_only && t < gd.Lp) return;
-    const int st = seg_start(gd, t);
+    constexpr int C = CHUNK<WIDE>;
+    const KeyChunks<C> ch(gd, t);
     const int kvh = h / (Hq / Hkv);
-    const float* qrow = q + ((int64_t)tok * Hq + h) * DH;
-    const float* gorow = d_o + ((int64_t)tok * Hq + h) * DH;
+    const int64_t row = (int64_t)tok * Hq + h, word = (int64_t)h * T_total + tok;
     const float* kb = k + ((int64_t)gd.tok_base * Hkv + kvh) * DH;
     const float* vb = v + ((int64_t)gd.tok_base * Hkv + kvh) * DH;
     const int64_t kvs = (int64_t)Hkv * DH;
-    const float L = lse[(int64_t)h * T_total + tok];
-    const float Dt = D[(int64_t)h * T_total + tok];
+    const float L = lse[word];
+    float Dt;
+    if (o) {
+        Dt = 0.f;
+#pragma unroll
+        for (int e = 0; e < PER; ++e) Dt += d_o[row * DH + l + 64 * e] * o[row * DH + l + 64 * e];
+        Dt = wave_sum(Dt);
+        if ((WIDE ? (int)threadIdx.x : l) == 0) D[word] = Dt;
+    } else {
+        Dt = D[word];
+    }
 
     float acc[PER];
 #pragma unroll
     for (int e = 0; e < PER; ++e) acc[e] = 0.f;
-    for (int s0 = 0; s0 <= t; s0 += 64) {
-        if (s0 >= gd.Lp && s0 + 64 <= st) continue;
-        const int s = s0 + l;
-        const bool ok = s <= t && (s < gd.Lp || s >= st);
-        float ds = 0.f;
-        if (ok) {
-            const float p = expf(scale * dot_row<DH>(qrow, kb + (int64_t)s * kvs) - L);
-            ds = p * (dot_row<DH>(gorow, vb + (int64_t)s * kvs) - Dt);
-        }
-        const int nk = min(64, t + 1 - s0);
+    for (int i = WIDE ? w : 0; i < ch.n; i += WIDE ? F32_WAVES : 1) {
+        const int s0 = ch.first(i), nk = ch.count(i), key = l & (C - 1);
+        const int64_t at = (int64_t)(s0 + min(key, nk - 1)) * kvs;
+        const float dot = dot_row<DH, WIDE>(q + row * DH, kb + at, l);
+        if (WIDE) __builtin_amdgcn_sched_barrier(0);       // (a second row in flight beside these spills)
+        const float dp = dot_row<DH, WIDE>(d_o + row * DH, vb + at, l);
+        const float ds = key < nk ? expf(scale * dot - L) * (dp - Dt) : 0.f;
         add_rows<PER>(acc, ds, kb + (int64_t)s0 * kvs, kvs, nk, l);
     }
-    float* out = dq + ((int64_t)tok * Hq + h) * DH;
+    if constexpr (!WIDE) {
 #pragma unroll
-    for (int e = 0; e < PER; ++e) out[l + 64 * e] = scale * acc[e];
+        for (int e = 0; e < PER; ++e) dq[row * DH + l + 64 * e] = scale * acc[e];
+        return;
+    }
+#pragma unroll
+    for (int e = 0; e < PER; ++e) sh_acc[w][l + 64 * e] = acc[e];
+    __syncthreads();
+    if ((int)threadIdx.x >= DH) return;
+    float x = 0.f;
+#pragma unroll
+    for (int i = 0; i < F32_WAVES; ++i) x += sh_acc[i][threadIdx.x];
+    dq[row * DH + threadIdx.x] = scale * x;
 }
 
 // dK[s,g] = scale * sum_{h in g} sum_t dS[t,s] Q[t,h];  dV[s,g] = sum_{h in g} sum_t P[t,s] dO[t,h].
 // The rows that see key s are contiguous: [s, Tg) for a prompt key (later prompt rows and
 // every row of every response), [s, end of its response) otherwise.
-template <int DH>
-__global__ __launch_bounds__(256) void bwd_dkdv_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
-                                                           const float* __restrict__ v, const float* __restrict__ d_o,
-                                                           const float* __restrict__ lse, const float* __restrict__ D,
-                                                           float* __restrict__ dk, float* __restrict__ dv,
-                                                           const int* __restrict__ tab, int Hq, int Hkv, float scale,
-                                                           int resp_only, int accumulate) {
+template <int DH, bool WIDE>
+__global__ __launch_bounds__(F32_BLOCK<WIDE>) void bwd_dkdv_f32_kernel(TabArg table, const float* __restrict__ q, const float* __restrict__ k,
+                                                                      const float* __restrict__ v, const float* __restrict__ d_o,
+                                                                      const float* __restrict__ lse, const float* __restrict__ D,
+                                                                      float* __restrict__ dk, float* __restrict__ dv,
+                                                                      int64_t T_total, int Hq, int Hkv, float scale,
+                                                                      int resp_only, int accumulate) {
     constexpr int PER = DH / 64;
-    const int64_t T_total = tab[1];
-    const int64_t gw = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int l = threadIdx.x & 63;
-    if (gw >= T_total * Hkv) return;
-    const int tok = (int)(gw / Hkv), kvh = (int)(gw % Hkv);
+    __shared__ float sh_acc[2][WIDE ? F32_WAVES : 1][DH];
+    constexpr int C = CHUNK<WIDE>;
+    const int* const tab = table_of(table);
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
+    const int64_t item = WIDE ? blockIdx.x : (int64_t)blockIdx.x * 4 + w;
+    if (item >= T_total * Hkv) return;
+    const int tok = (int)(item / Hkv), kvh = (int)(item % Hkv);
     const GroupDesc gd = load_group(tab, find_group_of_token(tab, tok));
     const int s = tok - gd.tok_base;
-    const int row_end = s < gd.Lp ? gd.Tg : seg_end(gd, s);
-    const int rep = Hq / Hkv;
+    const int row_end = s < gd.Lp ? gd.Tg : seg_end(gd, s), row_lo = resp_only ? max(s, gd.Lp) : s;
+    const int rep = Hq / Hkv, n = (row_end - row_lo + C - 1) / C;
     const float* krow = k + ((int64_t)tok * Hkv + kvh) * DH;
     const float* vrow = v + ((int64_t)tok * Hkv + kvh) * DH;
 
     float ak[PER], av[PER];
 #pragma unroll
     for (int e = 0; e < PER; ++e) { ak[e] = 0.f; av[e] = 0.f; }
-    for (int hr = 0; hr < rep; ++hr) {
-        const int h = kvh * rep + hr;
-        for (int r0 = resp_only ? max(s, gd.Lp) : s; r0 < row_end; r0 += 64) {
-            const int t = r0 + l;
-            float p = 0.f, ds = 0.f;
-            if (t < row_end) {
-                const int64_t row = ((int64_t)(gd.tok_base + t) * Hq + h) * DH;
-                const int64_t sidx = (int64_t)h * T_total + gd.tok_base + t;
-                p = expf(scale * dot_row<DH>(q + row, krow) - lse[sidx]);
-                ds = p * (dot_row<DH>(d_o + row, vrow) - D[sidx]);
-            }
-            const int nr = min(64, row_end - r0);
-            const int64_t row0 = ((int64_t)(gd.tok_base + r0) * Hq + h) * DH;
-            add_rows<PER>(av, p, d_o + row0, (int64_t)Hq * DH, nr, l);
-            add_rows<PER>(ak, ds, q + row0, (int64_t)Hq * DH, nr, l);
+    for (int hr = 0, i = WIDE ? w : 0; hr < rep; ++hr, i -= n) {      // chunk i of the n * rep, counted within the head
+        for (; i < n; i += WIDE ? F32_WAVES : 1) {
+            const int h = kvh * rep + hr, r0 = row_lo + C * i, nr = min(C, row_end - r0), r = l & (C - 1);
+            const int64_t row0 = ((int64_t)(gd.tok_base + r0) * Hq + h) * DH, rs = (int64_t)Hq * DH;
+            const int64_t at = row0 + min(r, nr - 1) * rs, word = (int64_t)h * T_total + gd.tok_base + r0 + min(r, nr - 1);
+            const float L = lse[word], Dt = D[word];
+            const float dot = dot_row<DH, WIDE>(krow, q + at, l);
+            if (WIDE && DH == 128) __builtin_amdgcn_sched_barrier(0);
+            const float dp = dot_row<DH, WIDE>(vrow, d_o + at, l);
+            const float p = r < nr ? expf(scale * dot - L) : 0.f, ds = r < nr ? p * (dp - Dt) : 0.f;
+            if (WIDE && DH == 128) __builtin_amdgcn_sched_barrier(0);
+            add_rows<PER>(av, p, d_o + row0, rs, nr, l);
+            if (WIDE && DH == 128) __builtin_amdgcn_sched_barrier(0);
+            add_rows<PER>(ak, ds, q + row0, rs, nr, l);
         }
     }
-    float* okr = dk + ((int64_t)tok * Hkv + kvh) * DH;
-    float* ovr = dv + ((int64_t)tok * Hkv + kvh) * DH;
+    if constexpr (!WIDE) {
+        float* const okr = dk + ((int64_t)tok * Hkv + kvh) * DH;
+        float* const ovr = dv + ((int64_t)tok * Hkv + kvh) * DH;
 #pragma unroll
-    for (int e = 0; e < PER; ++e) {
-        okr[l + 64 * e] = scale * ak[e] + (accumulate ? okr[l + 64 * e] : 0.f);
-        ovr[l + 64 * e] = av[e] + (accumulate ? ovr[l + 64 * e] : 0.f);
+        for (int e = 0; e < PER; ++e) {
+            okr[l + 64 * e] = scale * ak[e] + (accumulate ? okr[l + 64 * e] : 0.f);
+            ovr[l + 64 * e] = av[e] + (accumulate ? ovr[l + 64 * e] : 0.f);
+        }
+        return;
+    }
+#pragma unroll
+    for (int e = 0; e < PER; ++e) { sh_acc[0][w][l + 64 * e] = ak[e]; sh_acc[1][w][l + 64 * e] = av[e]; }
+    __syncthreads();
+    for (int i = threadIdx.x; i < 2 * DH; i += 64 * F32_WAVES) {
+        const int which = i / DH, e = i - which * DH;
+        float x = 0.f;
+#pragma unroll
+        for (int j = 0; j < F32_WAVES; ++j) x += sh_acc[which][j][e];
+        float* const out = (which == 0 ? dk : dv) + ((int64_t)tok * Hkv + kvh) * DH + e;
+        *out = (which == 0 ? scale * x : x) + (accumulate ? *out : 0.f);
     }
 }
 
@@ -508,35 +593,54 @@ hipError_t launch_rowsum(const Problem& p, bool f32, hipStream_t s) {
     return hipGetLastError();
 }
 
+// Calls f(head dimension, shape, ...) with the faster shape.  us, narrow and WIDE, of one group, half of it prompt, five answers:
+//   heads of 64    T Hq = 768: forward 14.0, 11.9, dq 17.2, 15.7, dkdv 27.4, 17.9; 4800: 112, 105, 177, 174, 250, 231; 6400:
+//                  180, 169, 289, 286, 378, 386; four q heads on two kv heads, 2400 tokens: dkdv 1000, 820
+//   heads of 128   T Hq = 400: 12.8, 10.2, 18.6, 13.2, 28.5, 24.4; 768: 18.7, 17.5, 26.9, 22.9, 43.5, 45.3; 1024: 23.0, 23.7, 32.4,
+//                  31.6, 55.6, 66.7 (here WIDE spills in the dkdv kernel); four q on two kv heads, 1600 T Hkv: dkdv 313, 306
+// (`items` of the dkdv kernel: T Hkv over the q heads per kv head, which a wave would walk behind one another.)
+template <typename F>
+void with_f32_shape(const Problem& p, int64_t n, int64_t items, int limit128, F f) {
+    auto sized = [&](auto dh) {
+        if (items <= (decltype(dh)::value == 64 ? 5000 : limit128)) f(dh, std::true_type{}, dim3((unsigned)n), dim3(F32_BLOCK<true>));
+        else f(dh, std::false_type{}, dim3((unsigned)((n + 3) / 4)), dim3(F32_BLOCK<false>));
+    };
+    if (p.head_dim == 64) sized(std::integral_constant<int, 64>{}); else sized(std::integral_constant<int, 128>{});
+}
+inline TabArg f32_table(const Problem& p) {
+    return make_tab_arg(p.host_table, p.small.on ? (size_t)p.host_table[2] : (size_t)ARG_WORDS + 1, p.tab);
+}
+
 hipError_t launch_fwd_f32(const Problem& p, hipStream_t s) {
-    const int grid = blocks_for_waves(p.total_tokens * p.Hq);
-    if (p.head_dim == 64)
-        hipLaunchKernelGGL(fwd_f32_kernel<64>, dim3(grid), dim3(256), 0, s, (const float*)p.q, (const float*)p.k,
-                           (const float*)p.v, (float*)p.o_out, p.lse_out, p.tab, p.Hq, p.Hkv, p.scale, p.resp_only);
-    else
-        hipLaunchKernelGGL(fwd_f32_kernel<128>, dim3(grid), dim3(256), 0, s, (const float*)p.q, (const float*)p.k,
-                           (const float*)p.v, (float*)p.o_out, p.lse_out, p.tab, p.Hq, p.Hkv, p.scale, p.resp_only);
+    const int64_t n = p.total_tokens * p.Hq;
+    with_f32_shape(p, n, n, 800, [&](auto dh, auto wide, dim3 grid, dim3 block) {
+        hipLaunchKernelGGL((fwd_f32_kernel<decltype(dh)::value, decltype(wide)::value>), grid, block, 0, s, f32_table(p),
+                           (const float*)p.q, (const float*)p.k, (const float*)p.v, (float*)p.o_out, p.lse_out, p.total_tokens,
+                           p.Hq, p.Hkv, p.scale, p.resp_only);
+    });
     return hipGetLastError();
 }
 
 hipError_t launch_bwd_f32(const Problem& p, hipStream_t s) {
-    if (p.stages & STAGE_ROWSUM) {
+    const bool fused = (p.stages & STAGE_ROWSUM) && (p.stages & STAGE_DQ) && !p.resp_only;      // rowsum within the dq kernel
+    if ((p.stages & STAGE_ROWSUM) && !fused) {
         hipError_t e = launch_rowsum(p, true, s);
         if (e != hipSuccess) return e;
     }
-    const int gq = blocks_for_waves(p.total_tokens * p.Hq);
-    const int gk = blocks_for_waves(p.total_tokens * p.Hkv);
-#define SP_F32_BWD(DH)                                                                                      \
-    if (p.stages & STAGE_DQ)                                                                               \
-    hipLaunchKernelGGL(bwd_dq_f32_kernel<DH>, dim3(gq), dim3(256), 0, s, (const float*)p.q, (const float*)p.k, \
-                       (const float*)p.v, (const float*)p.d_o, p.lse, p.Dbuf, (float*)p.dq, p.tab, p.Hq,   \
-                       p.Hkv, p.scale, p.resp_only);                                                       \
-    if (p.stages & STAGE_DKDV)                                                                             \
-    hipLaunchKernelGGL(bwd_dkdv_f32_kernel<DH>, dim3(gk), dim3(256), 0, s, (const float*)p.q,              \
-                       (const float*)p.k, (const float*)p.v, (const float*)p.d_o, p.lse, p.Dbuf,           \
-                       (float*)p.dk, (float*)p.dv, p.tab, p.Hq, p.Hkv, p.scale, p.resp_only, p.accumulate);
-    if (p.head_dim == 64) { SP_F32_BWD(64) } else { SP_F32_BWD(128) }
-#undef SP_F32_BWD
+    const int64_t nq = p.total_tokens * p.Hq, nk = p.total_tokens * p.Hkv;
+    if (p.stages & STAGE_DQ)
+        with_f32_shape(p, nq, nq, 800, [&](auto dh, auto wide, dim3 grid, dim3 block) {
+            hipLaunchKernelGGL((bwd_dq_f32_kernel<decltype(dh)::value, decltype(wide)::value>), grid, block, 0, s, f32_table(p),
+                               (const float*)p.q, (const float*)p.k, (const float*)p.v, (const float*)p.d_o,
+                               fused ? (const float*)p.o : nullptr, p.lse, p.Dbuf, (float*)p.dq,
+                               p.small.on ? p.small.tag : nullptr, p.total_tokens, p.Hq, p.Hkv, p.scale, p.resp_only);
+        });
+    if (p.stages & STAGE_DKDV)
+        with_f32_shape(p, nk, nk * p.Hkv / p.Hq, 600, [&](auto dh, auto wide, dim3 grid, dim3 block) {
+            hipLaunchKernelGGL((bwd_dkdv_f32_kernel<decltype(dh)::value, decltype(wide)::value>), grid, block, 0, s, f32_table(p),
+                               (const float*)p.q, (const float*)p.k, (const float*)p.v, (const float*)p.d_o, p.lse, p.Dbuf,
+                               (float*)p.dk, (float*)p.dv, p.total_tokens, p.Hq, p.Hkv, p.scale, p.resp_only, p.accumulate);
+        });
     return hipGetLastError();
 }
 
