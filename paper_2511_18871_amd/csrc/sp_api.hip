@@ -218,8 +218,8 @@ sp_status run(bool bwd, const void* q, const void* k, const void* v, const void*
     p.n_tiles256 = sp::count_tiles(p, 256); p.n_tiles128 = sp::count_tiles(p, 128);
     const int key_order = bwd && dtype == SP_BF16 && (stages & SP_BWD_STAGE_DKDV) ? sp::key_order(p) : sp::KEYS_AS_PACKED;
     if (key_order == sp::KEYS_AS_PACKED) p.sched.key_tiles = p.sched.tiles128;
-    // a backward in stages, or of response rows only, has a rowsum launch of its own, which reads the prepared table
-    const bool one_call = !bwd || (stages == SP_BWD_STAGE_ALL && !resp_only && (dtype == SP_F32 || sp::rowsum_fast_path(p)));
+    // a backward in stages has a rowsum launch of its own, which reads the prepared table
+    const bool one_call = !bwd || (stages == SP_BWD_STAGE_ALL && (dtype == SP_F32 || sp::rowsum_fast_path(p)));
     // (float32: the table alone; a forward then writes nothing to the workspace)
     p.small.on = dtype == SP_F32 ? one_call && L.words.size() <= (size_t)sp::ARG_WORDS
                                  : one_call && key_order == sp::KEYS_AS_PACKED && sp::use_small_call(p, L.words.size(), L.max_responses);

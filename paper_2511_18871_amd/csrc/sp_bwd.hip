@@ -298,9 +298,20 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(TabArg table, BwdArg
         } else {
             Dq = -nD_word;
         }
-        if (!valid) Dq = 0.f;
-        Lq = valid ? lse_word * LOG2E : 0.f;
-        if (a.fused_rowsum && valid && hh == 0) a.L2[row_word] = Lq;
+        // in response-rows mode what prompt rows hold takes no part; the dkdv pass, which loads the planes of the 64 rows around
+        // the prompt's end, gets zeros
+        const bool idle = a.resp_only && t < Lp;
+        if (!valid || idle) Dq = 0.f;
+        Lq = valid && !idle ? lse_word * LOG2E : 0.f;
+        if (a.fused_rowsum && hh == 0) {
+            if (valid) a.L2[row_word] = Lq;
+            if (valid && idle) a.nD[row_word] = 0.f;
+            if (a.resp_only && (tw0 & 32) && tw0 <= Lp && Lp < tw0 + 32) {      // first half of those 64 rows: of another workgroup
+                const int64_t before = (int64_t)head * T_total + gd.tok_base + t - 32;
+                a.L2[before] = 0.f;
+                a.nD[before] = 0.f;
+            }
+        }
         // the shares overlap the ring slots that the first tile copies (of other waves, too) are about to fill
         lds_reads_done();
         __syncthreads();
@@ -1127,10 +1138,9 @@ int dkdv_waves(const Problem& p) {
 hipError_t launch_bwd_bf16(const Problem& p, hipStream_t s) {
     hipError_t e = hipSuccess;
     // A call that runs both the rowsum and the dq stage folds the first into the second (the dq pass has
-    // the dO rows in registers anyway): one pass over o and dO less.  Not in response-rows mode, where the
-    // dq pass skips the prompt's tiles and the dkdv pass still needs finite planes for every row it loads,
-    // and not for head counts that the layout of rowsum_bf16_kernel (whose arithmetic the fold repeats) does not take.
-    const bool fused = (p.stages & STAGE_ROWSUM) && (p.stages & STAGE_DQ) && !p.resp_only && rowsum_fast_path(p);
+    // the dO rows in registers anyway): one pass over o and dO less (in response-rows mode, where the separate pass read the prompt rows too: 2560 rows under an 8K prompt, forward and backward 1707 -> 1632 us).  Not
+    // for head counts that the layout of rowsum_bf16_kernel (whose arithmetic the fold repeats) does not take.
+    const bool fused = (p.stages & STAGE_ROWSUM) && (p.stages & STAGE_DQ) && rowsum_fast_path(p);
     if ((p.stages & STAGE_ROWSUM) && !fused) {
         e = launch_rowsum(p, false, s);
         if (e != hipSuccess) return e;

@@ -622,7 +622,7 @@ hipError_t launch_fwd_f32(const Problem& p, hipStream_t s) {
 }
 
 hipError_t launch_bwd_f32(const Problem& p, hipStream_t s) {
-    const bool fused = (p.stages & STAGE_ROWSUM) && (p.stages & STAGE_DQ) && !p.resp_only;      // rowsum within the dq kernel
+    const bool fused = (p.stages & STAGE_ROWSUM) && (p.stages & STAGE_DQ);      // rowsum within the dq kernel
     if ((p.stages & STAGE_ROWSUM) && !fused) {
         hipError_t e = launch_rowsum(p, true, s);
         if (e != hipSuccess) return e;
