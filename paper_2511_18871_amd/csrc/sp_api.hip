@@ -136,7 +136,7 @@ sp_status run(bool bwd, const void* q, const void* k, const void* v, const void*
               int32_t n_groups, const int32_t* prompt_lens, const int32_t* Gs, const int32_t* resp_lens_flat,
               int32_t Hq, int32_t Hkv, int32_t d, float scale, sp_dtype dtype, sp_schedule schedule,
               unsigned stages, unsigned flags, void* workspace, size_t workspace_bytes, void* stream,
-              void* o_lo = nullptr) {
+              void* o_lo = nullptr, bool fixed_workspace = false) {
     g_err[0] = 0;
     if (o_lo && misaligned(o_lo)) return fail(SP_ERR_INVALID_ARG, "o_lo pointer %p is not 16-byte aligned", o_lo);
     if (o_lo && dtype != SP_BF16) return fail(SP_ERR_UNSUPPORTED, "o_lo is a bf16 option (fp32 outputs are not rounded)");
@@ -159,7 +159,13 @@ sp_status run(bool bwd, const void* q, const void* k, const void* v, const void*
     Layout L;
     st = build_table(n_groups, prompt_lens, Gs, resp_lens_flat, L);
     if (st != SP_OK) return st;
-    const size_t need = sp_attn_workspace_bytes(bwd, L.total_tokens, n_groups, L.total_responses, Hq, Hkv, d, dtype);
+    size_t need = sp_attn_workspace_bytes(bwd, L.total_tokens, n_groups, L.total_responses, Hq, Hkv, d, dtype);
+    // (a workspace of fixed size takes what fits with one row part per key tile)
+    int parts = bwd && dtype == SP_BF16 ? sp::dkdv_max_parts(L.total_tokens, n_groups, Hq, Hkv) : 1;
+    if (fixed_workspace && parts == 2 && workspace_bytes < need) {
+        need -= align256((size_t)2 * (Hq / Hkv) * (size_t)L.total_tokens * Hkv * 128 * 4);
+        parts = 1;
+    }
     if (!workspace || misaligned(workspace) || workspace_bytes < need)
         return fail(SP_ERR_WORKSPACE, "workspace %p of %zu bytes; need %zu bytes, 16-byte aligned", workspace,
                     workspace_bytes, need);
@@ -214,6 +220,7 @@ sp_status run(bool bwd, const void* q, const void* k, const void* v, const void*
     p.accumulate = (flags & SP_FLAG_ACCUMULATE_DKDV) != 0;
     p.host_group_tokens = L.group_tokens.data();
     p.host_table = L.words.data();
+    p.dkdv_parts = parts == 2 ? sp::dkdv_parts(p) : 1;
 
     p.n_tiles256 = sp::count_tiles(p, 256); p.n_tiles128 = sp::count_tiles(p, 128);
     const int key_order = bwd && dtype == SP_BF16 && (stages & SP_BWD_STAGE_DKDV) ? sp::key_order(p) : sp::KEYS_AS_PACKED;
@@ -247,7 +254,7 @@ size_t sp_attn_workspace_bytes(int is_bwd, int64_t total_tokens, int32_t n_group
     if (is_bwd) bytes += align256((size_t)n_q_heads * (size_t)total_tokens * 8);   // D and scaled LSE
     if (is_bwd && dtype == SP_BF16 && n_kv_heads > 0 && n_q_heads % n_kv_heads == 0 &&
         sp::dkdv_head_split(total_tokens, n_groups, n_q_heads, n_kv_heads))       // per-q-head dK, dV partials
-        bytes += align256((size_t)2 * (n_q_heads / n_kv_heads) * (size_t)total_tokens * n_kv_heads * 128 * 4);
+        bytes += sp::dkdv_max_parts(total_tokens, n_groups, n_q_heads, n_kv_heads) * align256((size_t)2 * (n_q_heads / n_kv_heads) * (size_t)total_tokens * n_kv_heads * 128 * 4);
     return bytes;
 }
 
@@ -624,7 +631,7 @@ sp_status sp_attn_bwd_batched_static(const void* q, const void* k, const void* v
     // workspace check of the common path before anything is enqueued.
     sp_status st = run(true, q, k, v, o, lse, d_o, nullptr, nullptr, dq, dk, dv, n_groups, prompt_lens, Gs,
                        resp_lens_flat, n_q_heads, n_kv_heads, head_dim, softmax_scale, dtype, SP_SCHED_SHARED,
-                       SP_BWD_STAGE_ALL, 0u, ws, SP_STATIC_SCRATCH_BYTES, stream);
+                       SP_BWD_STAGE_ALL, 0u, ws, SP_STATIC_SCRATCH_BYTES, stream, nullptr, true);
     if (st == SP_ERR_WORKSPACE) {
         char msg[sizeof(g_err)];
         snprintf(msg, sizeof(msg), "%s", g_err);

@@ -47,7 +47,8 @@ struct BwdArgs {
     // dkdv pass on small problems: one workgroup per (key tile, Q head) instead of per (key tile,
     // kv head); the per-q-head partial sums go to `partial` in fp32 and a second kernel adds them
     int rep;             // q heads per kv head
-    int head_split;
+    Div kv_heads;
+    int head_split;      // row parts of a key tile: 0 (not split), 1 or 2
     float* partial;      // [2 (dK, dV)][rep][T_total][Hkv][128] fp32
 };
 
@@ -579,8 +580,11 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(TabArg table, BwdArg
 // per buffer); left to the compiler they were 25 additions per step, and K did not fit the registers.
 // 8 -> 4 waves with these addresses, one box: 16K prompt with 32 answers 7.67 -> 7.24 ms, 64 groups of a short prompt
 // and 16 answers 4.44 -> 3.95 ms, 64 groups of 1000 tokens 1.33 -> 1.07 ms, response rows under an 8K prompt 0.77 -> 0.67 ms.
+// Row parts of a key tile of `steps` 64-row tiles in the head-split pass (see dkdv_parts())
+__device__ __forceinline__ int row_parts(const BwdArgs& a, int steps) { return a.head_split == 2 && steps >= PART_STEPS ? 2 : 1; }
+
 template <int NW, bool SMALL>
-__device__ __forceinline__ void dkdv_body(const BwdArgs& a, const SmallGroup& sg, const TileDesc td, const int kvh, const int hr_only) {
+__device__ __forceinline__ void dkdv_body(const BwdArgs& a, const SmallGroup& sg, const TileDesc td, const int kvh, const int hr_only, const int part) {
     const int ti = td.ti;
     constexpr int BNK = 128, BQ = 8 * NW;
     constexpr bool K_REG = NW == 4;                 // the wave's K rows stay in registers, only V in LDS
@@ -632,7 +636,12 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const SmallGroup& sg
     // (four waves: a step that masks reads e_s back; held in a register it was spilled, and its reload waited for the
     // tile copies.  Eight waves have the register: 1 % of the pass)
     if (K_REG && hh == 0) dkdv_ldsEnd[32 * kb + c] = e_s;
-    const int qt0 = max(s0, row_lo) / BQ, qt1 = (row_end + BQ - 1) / BQ;
+    int qt0 = max(s0, row_lo) / BQ, qt1 = (row_end + BQ - 1) / BQ;
+    if (NW == 8 && a.head_split) {                     // this workgroup's row part, the later rows first
+        const int parts = row_parts(a, qt1 - qt0), mid = (qt0 + qt1) / 2;
+        if (part >= parts) return;
+        if (parts == 2) { if (part == 0) qt0 = mid; else qt1 = mid; }
+    }
     const int rep_all = a.rep;
     const int rep = NW == 8 && a.head_split ? 1 : rep_all;        // q heads this workgroup walks
     const int64_t q_stride = (int64_t)a.Hq * 128;
@@ -991,10 +1000,10 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const SmallGroup& sg
                 for (int gq = 0; gq < 4; ++gq) {
                     const f32x4 y = *reinterpret_cast<const f32x4*>(xch + (db * 4 + gq) * 256);
                     if (a.head_split) {      // fp32 partial sum of this q head; scaled and rounded by the reduce kernel
-                        float* part = a.partial + ((int64_t)pass * rep_all + hr_only) * T_total * a.Hkv * 128;
+                        float* sums = a.partial + (((int64_t)pass * a.head_split + part) * rep_all + hr_only) * T_total * a.Hkv * 128;
                         const f32x4 z = {acc[db][4 * gq] + y[0], acc[db][4 * gq + 1] + y[1], acc[db][4 * gq + 2] + y[2],
                                          acc[db][4 * gq + 3] + y[3]};
-                        *reinterpret_cast<f32x4*>(part + orow + 32 * db + 8 * gq) = z;
+                        *reinterpret_cast<f32x4*>(sums + orow + 32 * db + 8 * gq) = z;
                         continue;
                     }
                     bf16x4 x;
@@ -1023,7 +1032,8 @@ __global__ __launch_bounds__(64 * NW, 2) void bwd_dkdv_kernel(TabArg table, BwdA
     } else {
         td = a.sched.key_tiles[item.tile];
     }
-    dkdv_body<NW, SMALL>(a, sg, td, item.kvh, item.hr);
+    const int two = NW == 8 && a.head_split == 2 ? 1 : 0;          // (q head, row part)
+    dkdv_body<NW, SMALL>(a, sg, td, item.kvh, item.hr >> two, item.hr & two);
 }
 
 // Second stage of the head-split dkdv pass: dk = scale * sum_hr partial[0][hr], dv = sum_hr
@@ -1051,6 +1061,52 @@ __global__ __launch_bounds__(256) void dkdv_reduce_kernel(const float* __restric
 #pragma unroll
         for (int e = 0; e < 4; ++e) r[e] = (__bf16)(acc[e] * mul + (float)old[e]);
         *reinterpret_cast<bf16x4*>(out) = r;
+    }
+}
+
+// The same where key tiles may have two row parts: over the parts of the key's tile and the q heads.  Looking the tile up costs
+// 1.7 us, so a pass without row parts takes the kernel above.  A workgroup takes RK keys of a tile and one kv head, a thread 4 consecutive elements.
+constexpr int RK = 8;
+template <bool SMALL>
+__global__ __launch_bounds__(256) void dkdv_reduce_parts_kernel(TabArg table, BwdArgs a) {
+    const int part = blockIdx.x & (128 / RK - 1);
+    unsigned kvh;
+    const int tile = (int)divmod(blockIdx.x / (128 / RK), a.kv_heads, kvh);
+    SmallGroup sg;
+    TileDesc td;
+    int row_end;
+    if constexpr (SMALL) {
+        int ti, b1, e1;
+        sg = small_tile<128>(table_of(table), a.n_groups, tile, threadIdx.x & 63, ti);
+        td = TileDesc{0, ti, sg.tok_base, sg.Lp, sg.Tg, 0, 0, 0};
+        small_segment(sg, min(128 * ti + 128, td.Tg) - 1, b1, e1);
+        row_end = 128 * ti < td.Lp ? td.Tg : e1;
+    } else {
+        td = a.sched.key_tiles[tile];
+        row_end = 128 * td.ti < td.Lp ? td.Tg : a.sched.row_hi[td.tok_base + min(128 * td.ti + 128, td.Tg) - 1];
+    }
+    row_end = __builtin_amdgcn_readfirstlane(row_end);
+    const int s0 = 128 * td.ti;
+    const int parts = row_parts(a, (row_end + 63) / 64 - max(s0, a.resp_only ? td.Lp : 0) / 64);
+    const int s = s0 + RK * part + (threadIdx.x >> 5);
+    if (s >= td.Tg) return;
+    const int64_t plane = a.T_total * a.Hkv * 128, i = ((int64_t)(td.tok_base + s) * a.Hkv + kvh) * 128 + 4 * (threadIdx.x & 31);
+#pragma unroll
+    for (int pass = 0; pass < 2; ++pass) {
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        for (int n = 0; n < parts * a.rep; ++n) {
+            const f32x4 x = *reinterpret_cast<const f32x4*>(a.partial + ((int64_t)pass * a.head_split * a.rep + n) * plane + i);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[e] += x[e];
+        }
+        __bf16* out = (pass == 0 ? a.dk : a.dv) + i;
+        const float mul = pass == 0 ? a.scale : 1.0f;
+        bf16x4 old = {0, 0, 0, 0};
+        if (a.accumulate) old = *reinterpret_cast<const bf16x4*>(out);
+        bf16x4 y;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) y[e] = (__bf16)(acc[e] * mul + (float)old[e]);
+        *reinterpret_cast<bf16x4*>(out) = y;
     }
 }
 
@@ -1180,15 +1236,20 @@ hipError_t launch_bwd_bf16(const Problem& p, hipStream_t s) {
         };
         const int n_tiles = count_tiles(p, 128);
         a.rep = p.Hq / p.Hkv;
-        a.head_split = p.dkdv_partial != nullptr;
+        a.head_split = p.dkdv_partial ? p.dkdv_parts : 0;
         a.partial = p.dkdv_partial;
         if (a.head_split) {
-            const int grid = grid_for_items(n_tiles, p.Hq, p.Hkv);
-            a.items = make_item_map(n_tiles, p.Hq, p.Hkv);
-            launch(8, grid);
+            const int items = p.Hq * p.dkdv_parts;
+            a.items = make_item_map(n_tiles, items, p.Hkv);
+            a.kv_heads = make_div(p.Hkv);
+            launch(8, grid_for_items(n_tiles, items, p.Hkv));
             const int64_t n4 = p.total_tokens * p.Hkv * 32;
-            hipLaunchKernelGGL(dkdv_reduce_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, a.partial, a.dk, a.dv,
-                               n4, p.Hq / p.Hkv, p.scale, a.accumulate);
+            const dim3 rg((unsigned)(n_tiles * p.Hkv * (128 / RK)));
+            if (p.dkdv_parts == 1)
+                hipLaunchKernelGGL(dkdv_reduce_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, a.partial, a.dk, a.dv,
+                                   n4, p.Hq / p.Hkv, p.scale, a.accumulate);
+            else if (p.small.on) hipLaunchKernelGGL(dkdv_reduce_parts_kernel<true>, rg, dim3(256), 0, s, table, a);
+            else hipLaunchKernelGGL(dkdv_reduce_parts_kernel<false>, rg, dim3(256), 0, s, table, a);
         } else {
             const int grid = grid_for_items(n_tiles, p.Hkv, p.Hkv);
             a.items = make_item_map(n_tiles, p.Hkv, p.Hkv);

@@ -127,6 +127,7 @@ struct Problem {
     const void* o_lo;                                     // backward (bf16): optional residual for D
     const uint32_t* o_lo_flag;                            // device word: o_lo may be used only if it is non-zero (NULL: always)
     int accumulate;                                       // backward: dk, dv += instead of =
+    int dkdv_parts;                                       // row parts of a key tile in the head-split pass
     float* dkdv_partial;                                  // bf16 backward on small problems: fp32 per-q-head partials
     // host copies of the per-group token counts and of the whole segment table, for grid sizing and
     // for choosing kernel shapes
@@ -246,6 +247,29 @@ inline int count_tiles(const Problem& p, int bm) {
 // partial sums in the workspace.  Both the workspace size and the launch use this rule.
 inline bool dkdv_head_split(int64_t total_tokens, int n_groups, int Hq, int Hkv) {
     return Hq > Hkv && (total_tokens / 128 + n_groups) * Hkv <= 192;
+}
+
+// Where it is split over the q heads, the pass is over when the workgroup of the first key tile is, which walks every row of
+// its group.  Packings that leave CUs idle all the same have room in the workspace for a second set of partial sums; whether
+// tiles of at least eight steps (512 rows) are cut into two row parts as well is then decided by the longest tile's
+// steps: what is gained is half of them, what is paid is a workgroup's fixed cost (five steps) and the sums.  Training passes, us, one part
+// and two (workgroups, longest tile's steps):
+//   56, 14   66.4  60.6      104, 24   99.9  88.7      168, 24  107.8 102.3      208, 52  193.3 173.7      188, 22  105.1 105.3
+//   196, 13  76.2  82.7      256, 14   83.4  89.7      280, 19   88.1  95.4      308, 22  105.6 116.9       76, 3    44.5  46.0
+inline int64_t head_split_wgs(int64_t total_tokens, int n_groups, int Hq) { return (total_tokens / 128 + n_groups) * Hq; }
+inline int dkdv_max_parts(int64_t total_tokens, int n_groups, int Hq, int Hkv) {
+    return dkdv_head_split(total_tokens, n_groups, Hq, Hkv) && head_split_wgs(total_tokens, n_groups, Hq) <= 224 ? 2 : 1;
+}
+constexpr int PART_STEPS = 8;
+inline int dkdv_parts(const Problem& p) {
+    if (dkdv_max_parts(p.total_tokens, p.n_groups, p.Hq, p.Hkv) < 2) return 1;
+    int most = 0;                                              // of a group's first tile: no other has more
+    for (int g = 0; g < p.n_groups; ++g) {
+        const int32_t* e = p.host_table + TAB_HEADER + TAB_GROUP_WORDS * g;
+        const int steps = (e[2] + 63) / 64 - (p.resp_only ? e[1] / 64 : 0);
+        if (steps > most) most = steps;
+    }
+    return most >= PART_STEPS && head_split_wgs(p.total_tokens, p.n_groups, p.Hq) <= 9 * most ? 2 : 1;
 }
 
 // Waves per workgroup (8 or 4) of a dkdv pass that is not split over the q heads (rule and reasons: sp_bwd.hip).
