@@ -19,8 +19,11 @@ inline TabArg make_tab_arg(const int32_t* words, size_t n, const int* dev) {
     for (size_t i = 0; i < (size_t)ARG_WORDS; ++i) t.words[i] = !t.dev && i < n ? words[i] : 0;
     return t;
 }
+// (in the constant address space, which the compiler follows: as a generic pointer it made flat loads of what scalar loads
+// serve, 0.5 ns per row of the loss, 15 % of 62 K rows of 3328 logits)
 __device__ __forceinline__ const int* table_of(const TabArg& t) {
-    return t.dev ? t.dev : (const int*)((uintptr_t)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(TabArg, words));
+    const uint64_t at = t.dev ? (uint64_t)(uintptr_t)t.dev : (uint64_t)(uintptr_t)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(TabArg, words);
+    return (const int*)(const __attribute__((address_space(4))) int*)at;
 }
 
 constexpr unsigned STAGE_ROWSUM = 1u, STAGE_DKDV = 2u, STAGE_DQ = 4u;
