@@ -47,15 +47,22 @@ inline bool misaligned(const void* p) { return ((uintptr_t)p & 15) != 0; }
 
 // Bytes of the schedule region that follows the table: key_lo and row_hi per token, then the tile
 // descriptors (sized by upper bounds on the tile counts, so that it depends on the totals alone).
-struct SchedLayout { size_t key_lo, row_hi, tiles256, tiles128, key_tiles, bytes; };
+struct SchedLayout { size_t key_lo, row_hi, tiles256, tiles128, bytes; };
 SchedLayout sched_layout(int64_t total_tokens, int32_t n_groups) {
     SchedLayout s{};
     const size_t per_tok = align256((size_t)total_tokens * 4);
     const size_t b256 = align256(((size_t)total_tokens / 256 + (size_t)n_groups + 1) * sizeof(sp::TileDesc));
     const size_t b128 = align256(((size_t)total_tokens / 128 + (size_t)n_groups + 1) * sizeof(sp::TileDesc));
-    s.key_lo = 0; s.row_hi = per_tok; s.tiles256 = 2 * per_tok; s.tiles128 = s.tiles256 + b256;
-    s.key_tiles = s.tiles128 + b128; s.bytes = s.key_tiles + b128;
+    s.key_lo = 0; s.row_hi = per_tok; s.tiles256 = 2 * per_tok; s.tiles128 = s.tiles256 + b256; s.bytes = s.tiles128 + b128;
     return s;
+}
+
+// The key tiles in the order of the dkdv pass and one row part's partial sums (bf16 backward, behind everything else)
+size_t key_tile_bytes(int64_t total_tokens, int32_t n_groups) {
+    return align256(((size_t)total_tokens / 128 + (size_t)n_groups + 1) * sizeof(sp::TileDesc));
+}
+size_t partial_bytes(int64_t total_tokens, int32_t Hq, int32_t Hkv) {
+    return align256((size_t)2 * (Hq / Hkv) * (size_t)total_tokens * Hkv * 128 * 4);
 }
 
 size_t table_words(int32_t n_groups, int64_t total_responses) {
@@ -160,11 +167,15 @@ sp_status run(bool bwd, const void* q, const void* k, const void* v, const void*
     st = build_table(n_groups, prompt_lens, Gs, resp_lens_flat, L);
     if (st != SP_OK) return st;
     size_t need = sp_attn_workspace_bytes(bwd, L.total_tokens, n_groups, L.total_responses, Hq, Hkv, d, dtype);
-    // (a workspace of fixed size takes what fits with one row part per key tile)
     int parts = bwd && dtype == SP_BF16 ? sp::dkdv_max_parts(L.total_tokens, n_groups, Hq, Hkv) : 1;
-    if (fixed_workspace && parts == 2 && workspace_bytes < need) {
-        need -= align256((size_t)2 * (Hq / Hkv) * (size_t)L.total_tokens * Hkv * 128 * 4);
+    bool ordered = bwd && dtype == SP_BF16;            // room for the key tiles in an order of their own
+    if (fixed_workspace && parts == 2 && workspace_bytes < need) {     // takes what fits without either
+        need -= partial_bytes(L.total_tokens, Hq, Hkv);
         parts = 1;
+    }
+    if (fixed_workspace && ordered && workspace_bytes < need) {
+        need -= key_tile_bytes(L.total_tokens, n_groups);
+        ordered = false;
     }
     if (!workspace || misaligned(workspace) || workspace_bytes < need)
         return fail(SP_ERR_WORKSPACE, "workspace %p of %zu bytes; need %zu bytes, 16-byte aligned", workspace,
@@ -201,8 +212,7 @@ sp_status run(bool bwd, const void* q, const void* k, const void* v, const void*
     char* const sched_base = (char*)workspace + TAG_BYTES + align256(L.words.size() * 4);
     const SchedLayout sl = sched_layout(L.total_tokens, n_groups);
     p.sched = sp::Schedule{(const sp::TileDesc*)(sched_base + sl.tiles256), (const sp::TileDesc*)(sched_base + sl.tiles128),
-                           (const sp::TileDesc*)(sched_base + sl.key_tiles), (const int*)(sched_base + sl.key_lo),
-                           (const int*)(sched_base + sl.row_hi)};
+                           nullptr, (const int*)(sched_base + sl.key_lo), (const int*)(sched_base + sl.row_hi)};
     p.Dbuf = (float*)(sched_base + sl.bytes);
     p.dkdv_partial = (bwd && dtype == SP_BF16 && sp::dkdv_head_split(L.total_tokens, n_groups, Hq, Hkv))
                          ? (float*)((char*)p.Dbuf + align256((size_t)Hq * (size_t)L.total_tokens * 8)) : nullptr;
@@ -223,8 +233,11 @@ sp_status run(bool bwd, const void* q, const void* k, const void* v, const void*
     p.dkdv_parts = parts == 2 ? sp::dkdv_parts(p) : 1;
 
     p.n_tiles256 = sp::count_tiles(p, 256); p.n_tiles128 = sp::count_tiles(p, 128);
-    const int key_order = bwd && dtype == SP_BF16 && (stages & SP_BWD_STAGE_DKDV) ? sp::key_order(p) : sp::KEYS_AS_PACKED;
-    if (key_order == sp::KEYS_AS_PACKED) p.sched.key_tiles = p.sched.tiles128;
+    const int key_order = ordered && (stages & SP_BWD_STAGE_DKDV) ? sp::key_order(p) : sp::KEYS_AS_PACKED;
+    p.sched.key_tiles = p.sched.tiles128;
+    if (key_order != sp::KEYS_AS_PACKED)
+        p.sched.key_tiles = (const sp::TileDesc*)((char*)p.Dbuf + align256((size_t)Hq * (size_t)L.total_tokens * 8) +
+                                                  (p.dkdv_partial ? parts * partial_bytes(L.total_tokens, Hq, Hkv) : 0));
     // a backward in stages has a rowsum launch of its own, which reads the prepared table
     const bool one_call = !bwd || (stages == SP_BWD_STAGE_ALL && (dtype == SP_F32 || sp::rowsum_fast_path(p)));
     // (float32: the table alone; a forward then writes nothing to the workspace)
@@ -254,7 +267,8 @@ size_t sp_attn_workspace_bytes(int is_bwd, int64_t total_tokens, int32_t n_group
     if (is_bwd) bytes += align256((size_t)n_q_heads * (size_t)total_tokens * 8);   // D and scaled LSE
     if (is_bwd && dtype == SP_BF16 && n_kv_heads > 0 && n_q_heads % n_kv_heads == 0 &&
         sp::dkdv_head_split(total_tokens, n_groups, n_q_heads, n_kv_heads))       // per-q-head dK, dV partials
-        bytes += sp::dkdv_max_parts(total_tokens, n_groups, n_q_heads, n_kv_heads) * align256((size_t)2 * (n_q_heads / n_kv_heads) * (size_t)total_tokens * n_kv_heads * 128 * 4);
+        bytes += sp::dkdv_max_parts(total_tokens, n_groups, n_q_heads, n_kv_heads) * partial_bytes(total_tokens, n_q_heads, n_kv_heads);
+    if (is_bwd && dtype == SP_BF16) bytes += key_tile_bytes(total_tokens, n_groups);
     return bytes;
 }
 
@@ -376,8 +390,7 @@ sp_status sp_attn_fwd_multi(int32_t n_sets, const void* const* q, const void* co
     char* const sched_base = (char*)workspace + TAG_BYTES + align256(L.words.size() * 4);
     const SchedLayout sl = sched_layout(L.total_tokens, n_groups);
     p.sched = sp::Schedule{(const sp::TileDesc*)(sched_base + sl.tiles256), (const sp::TileDesc*)(sched_base + sl.tiles128),
-                           (const sp::TileDesc*)(sched_base + sl.key_tiles), (const int*)(sched_base + sl.key_lo),
-                           (const int*)(sched_base + sl.row_hi)};
+                           nullptr, (const int*)(sched_base + sl.key_lo), (const int*)(sched_base + sl.row_hi)};
     p.n_tiles256 = sp::count_tiles(p, 256); p.n_tiles128 = sp::count_tiles(p, 128);
     hipError_t e = sp::launch_prepare(L.words.data(), (int)L.words.size(), table_of(workspace), (uint32_t*)workspace,
                                       sp::ReserveTag{}, sp::TAG_CLEAR, dtype == SP_BF16, n_groups, L.total_tokens,

@@ -69,3 +69,11 @@ def test_static_scratch_rejects_problems_beyond_its_size():
     assert b"built-in scratch" in lib.sp_attn_last_error()
     torch.cuda.synchronize()
     assert float(x.float().abs().sum()) == 0.0
+
+
+@pytest.mark.parametrize("prompt", [500, 3000])            # partial sums in two row parts; one set of them only
+def test_static_scratch_with_row_parts(prompt):
+    w = W.Workload("static_parts", [W.Group(prompt, [300, 64, 0, 200])], 8, 2, 128, torch.bfloat16, 73)
+    t, dev, packing, want = _case(w)
+    for a, b in zip(_run_static(dev, packing), want):
+        assert torch.equal(a, b)
