@@ -638,9 +638,11 @@ sp_status sp_attn_bwd_batched_static(const void* q, const void* k, const void* v
             return fail(SP_ERR_DEVICE, "hipGetSymbolAddress(scratch) failed on device %d: %s", dev, hipGetErrorString(e));
         g_scratch_ptr[dev].store(ws, std::memory_order_release);
     }
-    // Everything the kernels read from the scratch is written earlier in the same call (table by the
-    // upload, D / scaled LSE by the rowsum stage, partial sums by the dkdv pass for every key), so
-    // nothing has to be cleared; a problem that needs more than the array is rejected by the
+    // Nothing has to be cleared, for every word that the kernels read from the scratch was written earlier in the same call:
+    // table and schedule by the preparation (a small call reads neither), both planes by the dq pass (all rows of its
+    // workgroups; in response-rows mode, which skips those of a prompt alone, zeros for the prompt rows of the row tile that the
+    // prompt's end cuts, the only ones that the dkdv pass loads) or by the rowsum launch, partial sums by the dkdv pass for every
+    // key.  A problem that needs more than the array is rejected by the
     // workspace check of the common path before anything is enqueued.
     sp_status st = run(true, q, k, v, o, lse, d_o, nullptr, nullptr, dq, dk, dv, n_groups, prompt_lens, Gs,
                        resp_lens_flat, n_q_heads, n_kv_heads, head_dim, softmax_scale, dtype, SP_SCHED_SHARED,

@@ -636,7 +636,9 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const SmallGroup& sg
     // (four waves: a step that masks reads e_s back; held in a register it was spilled, and its reload waited for the
     // tile copies.  Eight waves have the register: 1 % of the pass)
     if (K_REG && hh == 0) dkdv_ldsEnd[32 * kb + c] = e_s;
-    int qt0 = max(s0, row_lo) / BQ, qt1 = (row_end + BQ - 1) / BQ;
+    // (no tile at all under a prompt without response rows: the one that its end cuts holds no row that takes part, and nothing
+    // writes L2 and -D of its rows)
+    int qt0 = max(s0, row_lo) / BQ, qt1 = row_end > row_lo ? (row_end + BQ - 1) / BQ : qt0;
     if (NW == 8 && a.head_split) {                     // this workgroup's row part, the later rows first
         const int parts = row_parts(a, qt1 - qt0), mid = (qt0 + qt1) / 2;
         if (part >= parts) return;
@@ -974,6 +976,7 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const SmallGroup& sg
         }
         return;
     }
+    wait_vm0();                                // the K and V copies of a workgroup without steps
     // add the two row halves: waves 4..7 park their partial sums in LDS (the Q/dO buffers,
     // 16 KB per wave), waves 0..3 add them and write the result.  dK first, then dV.
     float* xch = reinterpret_cast<float*>(&dkdv_lds[0][0]) + (size_t)kb * 4096 + l * 4;
@@ -1087,7 +1090,8 @@ __global__ __launch_bounds__(256) void dkdv_reduce_parts_kernel(TabArg table, Bw
     }
     row_end = __builtin_amdgcn_readfirstlane(row_end);
     const int s0 = 128 * td.ti;
-    const int parts = row_parts(a, (row_end + 63) / 64 - max(s0, a.resp_only ? td.Lp : 0) / 64);
+    const int row_lo = a.resp_only ? td.Lp : 0;
+    const int parts = row_parts(a, row_end > row_lo ? (row_end + 63) / 64 - max(s0, row_lo) / 64 : 0);
     const int s = s0 + RK * part + (threadIdx.x >> 5);
     if (s >= td.Tg) return;
     const int64_t plane = a.T_total * a.Hkv * 128, i = ((int64_t)(td.tok_base + s) * a.Hkv + kvh) * 128 + 4 * (threadIdx.x & 31);
@@ -1140,12 +1144,12 @@ int dkdv_waves(const Problem& p) {
             const int last = (s0 + 128 < Tg ? s0 + 128 : Tg) - 1, from = p.resp_only && Lp > s0 ? Lp : s0;
             int to = Tg;                                       // one past the last row that sees a key of the tile
             if (s0 >= Lp) { while (roff[j + 1] <= last) ++j; to = roff[j + 1]; }
-            const int rows = to > from ? to : from;
-            const float t4 = 5.f + 0.77f * (float)(((rows + 31) / 32 - from / 32) * rep);
+            const int n32 = to > from ? (to + 31) / 32 - from / 32 : 0, n64 = to > from ? (to + 63) / 64 - from / 64 : 0;
+            const float t4 = 5.f + 0.77f * (float)(n32 * rep);
             sum += t4;
             longest = std::max(longest, t4);
             if (many) continue;
-            w8.push_back(6.f + 1.24f * (float)(((rows + 63) / 64 - from / 64) * rep));
+            w8.push_back(6.f + 1.24f * (float)(n64 * rep));
             w4.push_back(t4);
         }
     }

@@ -272,7 +272,7 @@ inline int dkdv_parts(const Problem& p) {
     int most = 0;                                              // of a group's first tile: no other has more
     for (int g = 0; g < p.n_groups; ++g) {
         const int32_t* e = p.host_table + TAB_HEADER + TAB_GROUP_WORDS * g;
-        const int steps = (e[2] + 63) / 64 - (p.resp_only ? e[1] / 64 : 0);
+        const int steps = p.resp_only && e[1] == e[2] ? 0 : (e[2] + 63) / 64 - (p.resp_only ? e[1] / 64 : 0);
         if (steps > most) most = steps;
     }
     return most >= PART_STEPS && head_split_wgs(p.total_tokens, p.n_groups, p.Hq) <= 9 * most ? 2 : 1;
