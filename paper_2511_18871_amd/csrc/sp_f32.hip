@@ -350,7 +350,10 @@ __global__ __launch_bounds__(F32_BLOCK<WIDE>) void fwd_f32_kernel(TabArg table, 
         const float dot = dot_row<DH, WIDE>(qrow, kb + (int64_t)(s0 + min(key, nk - 1)) * kvs, l);
         const float sc = ok ? scale * dot : -INFINITY;
         const float mnew = fmaxf(m, wave_max(sc));
-        if (mnew == -INFINITY) continue;
+        // (nothing but masked keys and scores of -inf so far.  A NaN, which the maximum ignores, goes on: both sums become NaN)
+        unsigned bits = __float_as_uint(sc);
+        asm volatile("" : "+v"(bits));
+        if (mnew == -INFINITY && !__builtin_amdgcn_ballot_w64((bits & 0x7fffffffu) > 0x7f800000u)) continue;
         const float alpha = expf(m - mnew);
         const float p = ok ? expf(sc - mnew) : 0.f;
         lsum = lsum * alpha + wave_sum(l < C ? p : 0.f);
@@ -377,7 +380,7 @@ __global__ __launch_bounds__(F32_BLOCK<WIDE>) void fwd_f32_kernel(TabArg table, 
     float ls = 0.f, x = 0.f;
 #pragma unroll
     for (int i = 0; i < F32_WAVES; ++i) {
-        if (sh_m[i] == -INFINITY) continue;              // a wave without a key (or with scores of -inf only)
+        if (__float_as_uint(sh_l[i]) == 0u) continue;    // a wave without a key (or with scores of -inf only)
         const float f = expf(sh_m[i] - mt);
         ls = __builtin_fmaf(sh_l[i], f, ls);
         x = __builtin_fmaf(sh_acc[i][threadIdx.x], f, x);

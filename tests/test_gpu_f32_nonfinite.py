@@ -28,3 +28,32 @@ def test_an_infinite_last_row_stays_infinite(T, d):
     _, _, dv = B.sp_attn_bwd(q.cuda(), k.cuda(), finite.cuda(), o.nan_to_num(0, 0, 0), lse, d_o.cuda(), *args)
     torch.cuda.synchronize()
     assert torch.all(dv == float("inf"))
+
+
+# a NaN among the keys reaches every row that sees it, also where it is alone in a chunk of keys, and no other row
+@pytest.mark.parametrize("d,heads", [(64, 2), (64, 56), (128, 2), (128, 12)])         # eight waves per row, one wave
+@pytest.mark.parametrize("key", [0, 31, 63, 64, 65, 104])
+def test_a_nan_key_reaches_the_rows_that_see_it(key, d, heads):
+    prompt, resp = 64, [1, 40]
+    T, gen = prompt + sum(resp), torch.Generator().manual_seed(key)
+    q, k, v = (torch.randn(T, heads, d, generator=gen) for _ in range(3))
+    args = (prompt, resp, d ** -0.5)
+    clean, _ = B.sp_attn_fwd(q.cuda(), k.cuda(), v.cuda(), *args)
+    k[key] = float("nan")
+    o, lse = B.sp_attn_fwd(q.cuda(), k.cuda(), v.cuda(), *args)
+    torch.cuda.synchronize()
+    t = torch.arange(T)
+    start = torch.where(t < prompt, 0, torch.where(t < prompt + resp[0], prompt, prompt + resp[0]))
+    sees = ((key <= t) & ((key < prompt) | (key >= start))).cuda()
+    assert o[sees].isnan().all() and lse[:, sees].isnan().all()
+    assert torch.equal(o[~sees], clean[~sees]) and lse[:, ~sees].isfinite().all()
+
+
+@pytest.mark.parametrize("d,heads", [(64, 2), (64, 56), (128, 2), (128, 12)])
+def test_a_chunk_of_nan_keys_is_not_passed_over(d, heads):
+    T, gen = 200, torch.Generator().manual_seed(d)
+    q, k, v = (torch.randn(T, heads, d, generator=gen) for _ in range(3))
+    k[:64] = float("nan")
+    o, lse = B.sp_attn_fwd(q.cuda(), k.cuda(), v.cuda(), T, [], d ** -0.5)
+    torch.cuda.synchronize()
+    assert o.isnan().all() and lse.isnan().all()
