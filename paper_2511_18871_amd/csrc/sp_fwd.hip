@@ -530,18 +530,13 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd_kernel(TabArg table, FwdArgs a
     }
     store_rows(ao, ob);
     if (a.o_lo) {            // what the rounding of o dropped: lets the backward form D from an unrounded o
-        // x - bf16(x), which is exact, as one dot product per element: the other half of the pair is multiplied by 0.  The
-        // pairs {-1, 0} and {0, -1} come from scalar registers: as an inline constant the first selects the wrong half
-        typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-        unsigned first_bits = 0xbf80u, second_bits = 0xbf800000u;
-        asm volatile("" : "+s"(first_bits), "+s"(second_bits));
-        const bf16x2 first = __builtin_bit_cast(bf16x2, first_bits), second = __builtin_bit_cast(bf16x2, second_bits);
+        // x - bf16(x), which is exact, element by element: as dot products of the pair with {-1, 0} and {0, -1}, half the
+        // instructions, an infinite o made its neighbour's residual NaN
 #pragma unroll
         for (int n = 0; n < 32; ++n) {
             const f32x16& x = oacc[n >> 3];
             const int r = 2 * (n & 7);
-            const bf16x2 hi = __builtin_bit_cast(bf16x2, ob[n]);
-            ob[n] = pack2(__builtin_amdgcn_fdot2_f32_bf16(hi, first, x[r], false), __builtin_amdgcn_fdot2_f32_bf16(hi, second, x[r + 1], false));
+            ob[n] = pack2(x[r] - __uint_as_float(ob[n] << 16), x[r + 1] - __uint_as_float(ob[n] & 0xffff0000u));
         }
         store_rows(a.o_lo, ob);
     }

@@ -113,3 +113,26 @@ def test_binding_hands_the_forward_workspace_to_the_backward():
     rdq, rdk, rdv, _, _ = oracle_bwd(w, t)
     for name, a, r in (("dQ", dq, rdq), ("dK", dk, rdk), ("dV", dv, rdv)):
         print(gate(name, to64(a), r, w.dtype))
+
+
+@pytest.mark.parametrize("shape", [0, 1 << 20])
+@pytest.mark.parametrize("column", [0, 1, 126, 127])
+def test_an_infinite_output_leaves_its_neighbours_residual_alone(column, shape):
+    """One column of v infinite: o is infinite there, and the residual of every other column is what it is without."""
+    w, t, (q, k, v, _), pk = _setup(seed=84)
+    v[0, 0, column] = 0                              # token 0: a prompt token, seen by all rows of its group
+    group, rep = w.groups[0].total, w.n_q_heads // w.n_kv_heads
+    B.set_small_shape_steps(shape)
+    try:
+        lo = [torch.zeros_like(q) for _ in range(2)]
+        want, _ = B.sp_attn_fwd_batched_ex(q, k, v, *pk, 0, o_lo=lo[0])
+        v[0, 0, column] = float("inf")
+        got, _ = B.sp_attn_fwd_batched_ex(q, k, v, *pk, 0, o_lo=lo[1])
+        torch.cuda.synchronize()
+    finally:
+        B.set_small_shape_steps(-1)
+    assert not got[:group, :rep, column].isfinite().any()
+    for x, y in ((got, want), (lo[1], lo[0])):
+        x[:group, :rep, column] = 0
+        y[:group, :rep, column] = 0
+        assert torch.equal(x, y)
