@@ -52,7 +52,8 @@ typedef enum {
     SP_ERR_INVALID_ARG = 1,   /* null/misaligned pointer, negative length, empty group,
                                  n_q_heads % n_kv_heads != 0, scale not finite or <= 0 */
     SP_ERR_UNSUPPORTED = 2,   /* head_dim or dtype the kernels do not implement */
-    SP_ERR_WORKSPACE = 3,     /* workspace NULL or smaller than sp_attn_workspace_bytes() */
+    SP_ERR_WORKSPACE = 3,     /* workspace NULL, misaligned, or smaller than the call cannot do without
+                                 (sp_attn_workspace_bytes() is always enough) */
     SP_ERR_DEVICE = 4         /* the HIP runtime reported a launch error */
 } sp_status;
 
@@ -72,7 +73,10 @@ typedef enum { SP_SCHED_SHARED = 0, SP_SCHED_NAIVE_CAUSAL = 1 } sp_schedule;
 /* Bytes of device workspace a call needs (Section 4.3 has no counterpart: this is
  * where the segment table and, for the backward, D = rowsum(dO * O) live).
  * total_tokens = sum over groups of prompt_len + sum(resp_lens); total_responses =
- * sum of G over groups.  Returns 0 for arguments no call would accept. */
+ * sum of G over groups.  Returns 0 for arguments no call would accept.  A larger workspace
+ * serves as well, so one may serve several packings.  The size grows with tokens, groups and responses, but for
+ * one step: a bf16 backward with n_q_heads > n_kv_heads needs room for partial sums while
+ * (total_tokens / 128 + n_groups) * n_kv_heads <= 192, and not beyond. */
 size_t sp_attn_workspace_bytes(int is_bwd, int64_t total_tokens, int32_t n_groups,
                                int64_t total_responses, int32_t n_q_heads,
                                int32_t n_kv_heads, int32_t head_dim, sp_dtype dtype);
@@ -92,6 +96,14 @@ size_t sp_attn_workspace_bytes(int is_bwd, int64_t total_tokens, int32_t n_group
  * _ex entry points does the same through caller memory and takes precedence.  Not written by
  * sp_attn_fwd_multi or by the naive baseline schedule. */
 size_t sp_attn_reserve_bytes(int64_t total_tokens, int32_t n_q_heads, int32_t head_dim, sp_dtype dtype);
+
+/* Room for row parts (0 where no packing of these totals uses it).  A bf16 backward of few tokens leaves CUs idle; given
+ * a workspace of at least
+ *     sp_attn_workspace_bytes(1, ...) + sp_attn_reserve_bytes(...) + sp_attn_row_parts_bytes(...)
+ * bytes it may cut the rows of long key tiles in two, which changes the order in which dk and dv are summed.  With less it
+ * runs without. */
+size_t sp_attn_row_parts_bytes(int64_t total_tokens, int32_t n_groups, int32_t n_q_heads, int32_t n_kv_heads,
+                               sp_dtype dtype);
 
 /* Forward for one group (Section 4.3, modifications 1 and 3): writes
  * o [T, n_q_heads, head_dim] and lse [n_q_heads, T], T = prompt_len + sum(resp_lens).
@@ -176,12 +188,13 @@ sp_status sp_attn_bwd_batched_stages(const void* q, const void* k, const void* v
 
 /* sp_attn_bwd_batched for callers that cannot allocate or hand over device memory: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments and results
- * (bitwise) as sp_attn_bwd_batched, without the workspace: the segment table, D and the other
+ * (bitwise) as sp_attn_bwd_batched with a workspace of sp_attn_workspace_bytes(1, ...) bytes, without it: the segment table, D and the other
  * intermediates live in an array of SP_STATIC_SCRATCH_BYTES bytes that is part of the library's
  * device image (every GPU the library is used on holds its own copy until the process ends).  The
  * call allocates and frees nothing, on the host's HIP side or through any library.
- *   - A problem whose sp_attn_workspace_bytes(1, ...) exceeds SP_STATIC_SCRATCH_BYTES is rejected with
- *     SP_ERR_WORKSPACE before anything is enqueued (bf16: about n_q_heads * T_total <= 4e6).
+ *   - A problem that needs more than SP_STATIC_SCRATCH_BYTES (all of sp_attn_workspace_bytes(1, ...) but the key
+ *     tiles' order) is rejected with SP_ERR_WORKSPACE before anything is enqueued (bf16: about n_q_heads * T_total <= 4e6;
+ *     with partial sums, n_q_heads * T_total <= 32000).
  *   - All calls on one GPU share that GPU's array: calls that overlap in time on one GPU (different
  *     streams, or host threads) race on it.  Calls ordered on one stream are safe; every call
  *     rewrites all it reads, so nothing carries over from one call to the next.

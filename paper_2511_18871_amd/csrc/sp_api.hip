@@ -57,7 +57,7 @@ SchedLayout sched_layout(int64_t total_tokens, int32_t n_groups) {
     return s;
 }
 
-// The key tiles in the order of the dkdv pass and one row part's partial sums (bf16 backward, behind everything else)
+// The key tiles in the order of the dkdv pass, and one row part's partial sums (bf16 backward)
 size_t key_tile_bytes(int64_t total_tokens, int32_t n_groups) {
     return align256(((size_t)total_tokens / 128 + (size_t)n_groups + 1) * sizeof(sp::TileDesc));
 }
@@ -67,6 +67,17 @@ size_t partial_bytes(int64_t total_tokens, int32_t Hq, int32_t Hkv) {
 
 size_t table_words(int32_t n_groups, int64_t total_responses) {
     return (size_t)sp::TAB_HEADER + (size_t)sp::TAB_GROUP_WORDS * n_groups + (size_t)total_responses + n_groups;
+}
+
+// What a call cannot do without.  Behind it, as far as a backward's workspace has room: the forward's reserve, the key tiles in
+// their own order, the second row part's partial sums, each only where those before it fit.  So the reserve lies where
+// the forward left it whatever else fits, and a workspace sized for a larger packing serves a smaller one.
+size_t needed_bytes(bool bwd, int64_t total_tokens, int32_t n_groups, int64_t total_responses, int32_t Hq, int32_t Hkv, sp_dtype dtype) {
+    size_t bytes = TAG_BYTES + align256(table_words(n_groups, total_responses) * 4) + sched_layout(total_tokens, n_groups).bytes;
+    if (bwd) bytes += align256((size_t)Hq * (size_t)total_tokens * 8);             // D and scaled LSE
+    if (bwd && dtype == SP_BF16 && Hkv > 0 && Hq % Hkv == 0 && sp::dkdv_head_split(total_tokens, n_groups, Hq, Hkv))
+        bytes += partial_bytes(total_tokens, Hq, Hkv);                             // per-q-head dK, dV partials
+    return bytes;
 }
 
 sp_status check_geometry(int32_t Hq, int32_t Hkv, int32_t d, float scale, sp_dtype dtype) {
@@ -143,7 +154,7 @@ sp_status run(bool bwd, const void* q, const void* k, const void* v, const void*
               int32_t n_groups, const int32_t* prompt_lens, const int32_t* Gs, const int32_t* resp_lens_flat,
               int32_t Hq, int32_t Hkv, int32_t d, float scale, sp_dtype dtype, sp_schedule schedule,
               unsigned stages, unsigned flags, void* workspace, size_t workspace_bytes, void* stream,
-              void* o_lo = nullptr, bool fixed_workspace = false) {
+              void* o_lo = nullptr, bool own_scratch = false) {
     g_err[0] = 0;
     if (o_lo && misaligned(o_lo)) return fail(SP_ERR_INVALID_ARG, "o_lo pointer %p is not 16-byte aligned", o_lo);
     if (o_lo && dtype != SP_BF16) return fail(SP_ERR_UNSUPPORTED, "o_lo is a bf16 option (fp32 outputs are not rounded)");
@@ -166,26 +177,22 @@ sp_status run(bool bwd, const void* q, const void* k, const void* v, const void*
     Layout L;
     st = build_table(n_groups, prompt_lens, Gs, resp_lens_flat, L);
     if (st != SP_OK) return st;
-    size_t need = sp_attn_workspace_bytes(bwd, L.total_tokens, n_groups, L.total_responses, Hq, Hkv, d, dtype);
-    int parts = bwd && dtype == SP_BF16 ? sp::dkdv_max_parts(L.total_tokens, n_groups, Hq, Hkv) : 1;
-    bool ordered = bwd && dtype == SP_BF16;            // room for the key tiles in an order of their own
-    if (fixed_workspace && parts == 2 && workspace_bytes < need) {     // takes what fits without either
-        need -= partial_bytes(L.total_tokens, Hq, Hkv);
-        parts = 1;
-    }
-    if (fixed_workspace && ordered && workspace_bytes < need) {
-        need -= key_tile_bytes(L.total_tokens, n_groups);
-        ordered = false;
-    }
+    const size_t need = needed_bytes(bwd, L.total_tokens, n_groups, L.total_responses, Hq, Hkv, dtype);
     if (!workspace || misaligned(workspace) || workspace_bytes < need)
         return fail(SP_ERR_WORKSPACE, "workspace %p of %zu bytes; need %zu bytes, 16-byte aligned", workspace,
                     workspace_bytes, need);
 
-    // The reserve sits behind everything a backward of this problem keeps in the workspace, so the
-    // forward and its backward find it at the same offset.
-    const size_t reserve_off = align256(sp_attn_workspace_bytes(1, L.total_tokens, n_groups, L.total_responses, Hq, Hkv, d, dtype));
+    // The reserve sits behind what a backward of this problem cannot do without, so the forward and its backward find it at
+    // the same offset.  (The library's own scratch holds none: it has no forward.)
+    const size_t reserve_off = needed_bytes(true, L.total_tokens, n_groups, L.total_responses, Hq, Hkv, dtype);
     const size_t reserve_len = sp_attn_reserve_bytes(L.total_tokens, Hq, d, dtype);
-    const bool reserve_fits = reserve_len > 0 && workspace_bytes >= reserve_off + reserve_len;
+    const bool reserve_fits = !own_scratch && reserve_len > 0 && workspace_bytes >= reserve_off + reserve_len;
+    const size_t key_tiles_off = reserve_off + (reserve_fits ? reserve_len : 0);
+    const size_t parts_off = key_tiles_off + key_tile_bytes(L.total_tokens, n_groups);
+    const bool ordered = bwd && dtype == SP_BF16 && workspace_bytes >= parts_off;
+    // row parts change the order of sums: they go with the reserve, so that of the calls without one none has them
+    const bool two_parts = ordered && reserve_fits && sp::dkdv_max_parts(L.total_tokens, n_groups, Hq, Hkv) == 2 &&
+                           workspace_bytes >= parts_off + partial_bytes(L.total_tokens, Hq, Hkv);
     void* const reserve = (char*)workspace + reserve_off;
     const bool resp_only = (flags & SP_FLAG_RESPONSE_ROWS) != 0;
     sp::ReserveTag tag{};
@@ -200,10 +207,6 @@ sp_status run(bool bwd, const void* q, const void* k, const void* v, const void*
         tag.w[10] = resp_only ? 1u : 0u;        // a reserve written for response rows only serves only such a backward
         tag_mode = bwd ? sp::TAG_CHECK : sp::TAG_WRITE;
     }
-    // gradient stages enqueued on their own run on the workspace that their ROWSUM stage prepared (and
-    // checked): the tag is left as it is
-    const bool keep_tag = bwd && !(stages & SP_BWD_STAGE_ROWSUM);
-
     hipStream_t s = (hipStream_t)stream;
     sp::Problem p{};
     p.q = q; p.k = k; p.v = v; p.o = o; p.lse = lse; p.d_o = d_o;
@@ -230,14 +233,16 @@ sp_status run(bool bwd, const void* q, const void* k, const void* v, const void*
     p.accumulate = (flags & SP_FLAG_ACCUMULATE_DKDV) != 0;
     p.host_group_tokens = L.group_tokens.data();
     p.host_table = L.words.data();
-    p.dkdv_parts = parts == 2 ? sp::dkdv_parts(p) : 1;
+    p.dkdv_parts = two_parts ? sp::dkdv_parts(p) : 1;
+    p.dkdv_partial2 = p.dkdv_parts == 2 ? (float*)((char*)workspace + parts_off) : nullptr;
 
     p.n_tiles256 = sp::count_tiles(p, 256); p.n_tiles128 = sp::count_tiles(p, 128);
     const int key_order = ordered && (stages & SP_BWD_STAGE_DKDV) ? sp::key_order(p) : sp::KEYS_AS_PACKED;
     p.sched.key_tiles = p.sched.tiles128;
-    if (key_order != sp::KEYS_AS_PACKED)
-        p.sched.key_tiles = (const sp::TileDesc*)((char*)p.Dbuf + align256((size_t)Hq * (size_t)L.total_tokens * 8) +
-                                                  (p.dkdv_partial ? parts * partial_bytes(L.total_tokens, Hq, Hkv) : 0));
+    if (key_order != sp::KEYS_AS_PACKED) p.sched.key_tiles = (const sp::TileDesc*)((char*)workspace + key_tiles_off);
+    // gradient stages enqueued on their own run on the workspace that their ROWSUM stage prepared (and checked): the tag is
+    // left as it is, unless they write where a larger workspace would have held a reserve
+    const bool keep_tag = bwd && !(stages & SP_BWD_STAGE_ROWSUM) && (reserve_fits || key_order == sp::KEYS_AS_PACKED);
     // a backward in stages has a rowsum launch of its own, which reads the prepared table
     const bool one_call = !bwd || (stages == SP_BWD_STAGE_ALL && (dtype == SP_F32 || sp::rowsum_fast_path(p)));
     // (float32: the table alone; a forward then writes nothing to the workspace)
@@ -263,11 +268,7 @@ size_t sp_attn_workspace_bytes(int is_bwd, int64_t total_tokens, int32_t n_group
                                int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim, sp_dtype dtype) {
     (void)head_dim;
     if (total_tokens < 1 || n_groups < 1 || total_responses < 0 || n_q_heads < 1) return 0;
-    size_t bytes = TAG_BYTES + align256(table_words(n_groups, total_responses) * 4) + sched_layout(total_tokens, n_groups).bytes;
-    if (is_bwd) bytes += align256((size_t)n_q_heads * (size_t)total_tokens * 8);   // D and scaled LSE
-    if (is_bwd && dtype == SP_BF16 && n_kv_heads > 0 && n_q_heads % n_kv_heads == 0 &&
-        sp::dkdv_head_split(total_tokens, n_groups, n_q_heads, n_kv_heads))       // per-q-head dK, dV partials
-        bytes += sp::dkdv_max_parts(total_tokens, n_groups, n_q_heads, n_kv_heads) * partial_bytes(total_tokens, n_q_heads, n_kv_heads);
+    size_t bytes = needed_bytes(is_bwd != 0, total_tokens, n_groups, total_responses, n_q_heads, n_kv_heads, dtype);
     if (is_bwd && dtype == SP_BF16) bytes += key_tile_bytes(total_tokens, n_groups);
     return bytes;
 }
@@ -275,6 +276,11 @@ size_t sp_attn_workspace_bytes(int is_bwd, int64_t total_tokens, int32_t n_group
 size_t sp_attn_reserve_bytes(int64_t total_tokens, int32_t n_q_heads, int32_t head_dim, sp_dtype dtype) {
     if (total_tokens < 1 || n_q_heads < 1 || head_dim < 1 || dtype != SP_BF16) return 0;
     return align256((size_t)total_tokens * (size_t)n_q_heads * (size_t)head_dim * 2);
+}
+
+size_t sp_attn_row_parts_bytes(int64_t total_tokens, int32_t n_groups, int32_t n_q_heads, int32_t n_kv_heads, sp_dtype dtype) {
+    if (total_tokens < 1 || n_groups < 1 || n_q_heads < 1 || n_kv_heads < 1 || n_q_heads % n_kv_heads != 0 || dtype != SP_BF16) return 0;
+    return sp::dkdv_max_parts(total_tokens, n_groups, n_q_heads, n_kv_heads) == 2 ? partial_bytes(total_tokens, n_q_heads, n_kv_heads) : 0;
 }
 
 sp_status sp_attn_fwd(const void* q, const void* k, const void* v, void* o, float* lse, int32_t prompt_len,

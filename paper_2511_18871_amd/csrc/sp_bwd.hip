@@ -49,7 +49,8 @@ struct BwdArgs {
     int rep;             // q heads per kv head
     Div kv_heads;
     int head_split;      // row parts of a key tile: 0 (not split), 1 or 2
-    float* partial;      // [2 (dK, dV)][rep][T_total][Hkv][128] fp32
+    float* partial;      // [2 (dK, dV)][rep][T_total][Hkv][128] fp32 of the first row part
+    float* partial2;     // the same of the second
 };
 
 // ------------------------------------------------------------------------------------
@@ -1003,7 +1004,7 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const SmallGroup& sg
                 for (int gq = 0; gq < 4; ++gq) {
                     const f32x4 y = *reinterpret_cast<const f32x4*>(xch + (db * 4 + gq) * 256);
                     if (a.head_split) {      // fp32 partial sum of this q head; scaled and rounded by the reduce kernel
-                        float* sums = a.partial + (((int64_t)pass * a.head_split + part) * rep_all + hr_only) * T_total * a.Hkv * 128;
+                        float* sums = (part == 0 ? a.partial : a.partial2) + ((int64_t)pass * rep_all + hr_only) * T_total * a.Hkv * 128;
                         const f32x4 z = {acc[db][4 * gq] + y[0], acc[db][4 * gq + 1] + y[1], acc[db][4 * gq + 2] + y[2],
                                          acc[db][4 * gq + 3] + y[3]};
                         *reinterpret_cast<f32x4*>(sums + orow + 32 * db + 8 * gq) = z;
@@ -1098,10 +1099,13 @@ __global__ __launch_bounds__(256) void dkdv_reduce_parts_kernel(TabArg table, Bw
 #pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-        for (int n = 0; n < parts * a.rep; ++n) {
-            const f32x4 x = *reinterpret_cast<const f32x4*>(a.partial + ((int64_t)pass * a.head_split * a.rep + n) * plane + i);
+        for (int n = 0; n < parts; ++n) {
+            const float* const sums = (n == 0 ? a.partial : a.partial2) + (int64_t)pass * a.rep * plane + i;
+            for (int hr = 0; hr < a.rep; ++hr) {
+                const f32x4 x = *reinterpret_cast<const f32x4*>(sums + hr * plane);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) acc[e] += x[e];
+                for (int e = 0; e < 4; ++e) acc[e] += x[e];
+            }
         }
         __bf16* out = (pass == 0 ? a.dk : a.dv) + i;
         const float mul = pass == 0 ? a.scale : 1.0f;
@@ -1241,7 +1245,7 @@ hipError_t launch_bwd_bf16(const Problem& p, hipStream_t s) {
         const int n_tiles = count_tiles(p, 128);
         a.rep = p.Hq / p.Hkv;
         a.head_split = p.dkdv_partial ? p.dkdv_parts : 0;
-        a.partial = p.dkdv_partial;
+        a.partial = p.dkdv_partial; a.partial2 = p.dkdv_partial2;
         if (a.head_split) {
             const int items = p.Hq * p.dkdv_parts;
             a.items = make_item_map(n_tiles, items, p.Hkv);

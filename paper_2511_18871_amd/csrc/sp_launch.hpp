@@ -132,6 +132,7 @@ struct Problem {
     int accumulate;                                       // backward: dk, dv += instead of =
     int dkdv_parts;                                       // row parts of a key tile in the head-split pass
     float* dkdv_partial;                                  // bf16 backward on small problems: fp32 per-q-head partials
+    float* dkdv_partial2;                                 // the second row part's
     // host copies of the per-group token counts and of the whole segment table, for grid sizing and
     // for choosing kernel shapes
     SmallCall small;
@@ -253,15 +254,14 @@ inline bool dkdv_head_split(int64_t total_tokens, int n_groups, int Hq, int Hkv)
 }
 
 // Where it is split over the q heads, the pass is over when the workgroup of the first key tile is, which walks every row of
-// its group.  Packings that leave CUs idle all the same have room in the workspace for a second set of partial sums; whether
+// its group.  Packings that leave CUs idle all the same can use a second set of partial sums (sp_attn_row_parts_bytes()); whether
 // tiles of at least eight steps (512 rows) are cut into two row parts as well is then decided by the longest tile's
 // steps: what is gained is half of them, what is paid is a workgroup's fixed cost (five steps) and the sums.  Training passes, us, one part
 // and two (workgroups, longest tile's steps):
 //   56, 14   66.4  60.6      104, 24   99.9  88.7      168, 24  107.8 102.3      116, 57  194.1 163.9      188, 22  105.1 105.3
 //   196, 13  76.2  82.7      256, 14   83.4  89.7      280, 19   88.1  95.4      308, 22  105.6 116.9       76, 3    44.5  46.0
 inline int64_t head_split_wgs(int64_t total_tokens, int n_groups, int Hq) { return (total_tokens / 128 + n_groups) * Hq; }
-// (more groups never need less; and both sets fit the library's own 32 MB, so that the entry point without a workspace, whose
-// results are those of the others bit for bit, has room for them too)
+// (By the totals alone, as callers size workspaces by them; both sets within 30 MB, the range that was measured.)
 inline int dkdv_max_parts(int64_t total_tokens, int n_groups, int Hq, int Hkv) {
     return dkdv_head_split(total_tokens, n_groups, Hq, Hkv) && head_split_wgs(total_tokens, 1, Hq) <= 224 &&
            2 * 2 * (int64_t)Hq * total_tokens * 128 * 4 <= (int64_t)30 << 20 ? 2 : 1;

@@ -136,3 +136,42 @@ def test_an_infinite_output_leaves_its_neighbours_residual_alone(column, shape):
         x[:group, :rep, column] = 0
         y[:group, :rep, column] = 0
         assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("tokens", [700, 1500, 1900, 1921])
+def test_a_workspace_of_a_larger_packing_serves_a_smaller_one(tokens):
+    """One workspace, sized for 2500 tokens: smaller packings run on it, reserve included.  And one with not a byte more than
+    the call cannot do without, which has no room for an order of the key tiles."""
+    w, t, (q, k, v, d_o), pk = _setup(seed=85, groups=[W.Group(tokens - 400, [130, 170]), W.Group(60, [40])])
+    size = lambda T: B.workspace_bytes(True, T, 2, 3, 8, 2, 128, B.SP_BF16)
+    large = size(2500) + B.reserve_bytes(2500, 8, 128, B.SP_BF16)
+    o_lo = torch.empty_like(q)
+    o, lse = B.sp_attn_fwd_batched_ex(q, k, v, *pk, 0, o_lo=o_lo)
+    want = B.sp_attn_bwd_batched_ex(q, k, v, o, lse, d_o, *pk, 0, o_lo=o_lo, workspace=_ws(large))
+    ws = _ws(large)
+    o1, lse1 = B.sp_attn_fwd_batched(q, k, v, *pk, workspace=ws)
+    got = B.sp_attn_bwd_batched(q, k, v, o1, lse1, d_o, *pk, workspace=ws)
+    plain = B.sp_attn_bwd_batched(q, k, v, o, lse, d_o, *pk, workspace=_ws(size(tokens)))
+    least = size(tokens) - ((tokens // 128 + 2 + 1) * 32 + 255) // 256 * 256
+    tight = B.sp_attn_bwd_batched(q, k, v, o, lse, d_o, *pk, workspace=_ws(least))
+    with pytest.raises(B.SpAttnError) as e:
+        B.sp_attn_bwd_batched(q, k, v, o, lse, d_o, *pk, workspace=_ws(least - 1))
+    torch.cuda.synchronize()
+    assert e.value.status == B.SP_ERR_WORKSPACE
+    for a, b in ((got, want), (tight, plain)):
+        assert all(torch.equal(x, y) for x, y in zip(a, b))
+    assert not torch.equal(got[0], plain[0])                           # the reserve was used
+    for name, x, ref in zip(("dQ", "dK", "dV"), got, oracle_bwd(w, t)):
+        gate(name, to64(x), ref, w.dtype)
+
+
+def test_without_room_for_an_order_the_key_tiles_run_as_packed():
+    groups = [W.Group(100 + 40 * (i % 7), [90, 30, 64]) for i in range(40)]
+    w, t, (q, k, v, d_o), pk = _setup(seed=86, groups=groups, heads=(8, 8))
+    o, lse = B.sp_attn_fwd_batched(q, k, v, *pk)
+    need = B.workspace_bytes(True, w.total_tokens, 40, 120, 8, 8, 128, B.SP_BF16)
+    want = B.sp_attn_bwd_batched(q, k, v, o, lse, d_o, *pk, workspace=_ws(need))
+    least = need - ((w.total_tokens // 128 + 40 + 1) * 32 + 255) // 256 * 256
+    got = B.sp_attn_bwd_batched(q, k, v, o, lse, d_o, *pk, workspace=_ws(least))
+    torch.cuda.synchronize()
+    assert all(torch.equal(x, y) for x, y in zip(got, want))

@@ -290,3 +290,20 @@ def test_row_tile_rule_on_the_bench_workloads_and_the_knob():
     assert shape(W.config(5)) == 256
     with pytest.raises(B.SpAttnError):
         B.sp_attn_row_tile([-1], [1], [5])               # a negative prompt length
+
+
+@pytest.mark.parametrize("heads", [(8, 2), (4, 2), (28, 4), (40, 8), (8, 8)])
+def test_a_workspace_for_more_tokens_or_groups_serves_fewer(lib, heads):
+    """What a backward asks for never falls while tokens or groups grow, on either side of the line up to which it is split over
+    the q heads; the room for row parts comes on top and only while it is split."""
+    split = lambda T, n: heads[0] > heads[1] and (T // 128 + n) * heads[1] <= 192
+    for sizes in ([(T, 3) for T in range(3, 14000, 37)], [(1024, n) for n in range(1, 300)]):
+        last = {}
+        for T, n in sizes:
+            need = B.workspace_bytes(True, T, n, 40, *heads, 128, B.SP_BF16)
+            assert need >= last.get(split(T, n), 0), (T, n)
+            last[split(T, n)] = need
+            parts = B.row_parts_bytes(T, n, *heads, B.SP_BF16)
+            assert parts == 0 or (split(T, n) and parts == 2 * 4 * 128 * heads[0] * T)
+    assert B.row_parts_bytes(1000, 2, *heads, B.SP_F32) == 0 and B.row_parts_bytes(0, 1, *heads, B.SP_BF16) == 0
+    assert B.row_parts_bytes(1000, 2, 5, 2, B.SP_BF16) == 0

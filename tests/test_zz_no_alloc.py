@@ -71,7 +71,7 @@ def test_static_scratch_rejects_problems_beyond_its_size():
     assert float(x.float().abs().sum()) == 0.0
 
 
-@pytest.mark.parametrize("prompt", [500, 3000])            # partial sums in two row parts; one set of them only
+@pytest.mark.parametrize("prompt", [500, 3000])            # room for a second set of partial sums in the scratch, which it does not use; none
 def test_static_scratch_with_row_parts(prompt):
     w = W.Workload("static_parts", [W.Group(prompt, [300, 64, 0, 200])], 8, 2, 128, torch.bfloat16, 73)
     t, dev, packing, want = _case(w)
