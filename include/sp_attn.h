@@ -89,10 +89,12 @@ size_t sp_attn_workspace_bytes(int is_bwd, int64_t total_tokens, int32_t n_group
  * unchanged), and a backward that is handed THE SAME workspace, not used by any other call in
  * between, forms D from o plus that residual.  Nothing else changes hands: same arguments, same
  * outputs.  The reserve is protected by a tag at the head of the workspace, naming the o / lse
- * pointers and the shape it belongs to; every call of this library rewrites or re-validates the tag
- * on the device before it writes to a workspace, so a backward that is given a smaller, another,
- * or a since-reused workspace finds no valid reserve and computes D from the bf16 o alone (the
- * result is then what it is without the reserve, never worse).  The explicit o_lo tensor of the
+ * pointers and the shape it belongs to.  A call that writes to a workspace rewrites or re-validates the
+ * tag on the device within its own launches (in stream order; a call that writes nothing there leaves it),
+ * so when it is through, the tag vouches for no reserve that the call may have overwritten: a backward that
+ * is given a smaller, another, or a since-reused workspace finds no valid reserve and computes D from the
+ * bf16 o alone (the result is then what it is without the reserve, never worse).  A call that ends with
+ * SP_ERR_DEVICE may have run in part: its workspace holds no reserve to rely on until the next forward.  The explicit o_lo tensor of the
  * _ex entry points does the same through caller memory and takes precedence.  Not written by
  * sp_attn_fwd_multi or by the naive baseline schedule. */
 size_t sp_attn_reserve_bytes(int64_t total_tokens, int32_t n_q_heads, int32_t head_dim, sp_dtype dtype);
@@ -168,8 +170,8 @@ sp_status sp_attn_bwd_batched(const void* q, const void* k, const void* v,
  * accurate one when no reserve is used, and the only one whose results are bitwise repeatable from
  * run to run.  To overlap the two gradient passes, give each its own workspace and run ROWSUM on
  * both.  Output pointers of stages that are not requested may be NULL.
- * A bf16 call that holds both ROWSUM and DQ (and is not in response-rows mode) runs no separate
- * rowsum kernel: the dq pass, which loads every row of d_o anyway, forms D and lse * log2(e) in its
+ * A bf16 call that holds both ROWSUM and DQ runs no separate rowsum kernel, in response-rows mode neither
+ * (for head counts up to 512): the dq pass, which loads every row of d_o anyway, forms D and lse * log2(e) in its
  * prologue, with the same operations in the same order, so that the results equal those of the
  * stages enqueued one by one bit for bit.
  * sp_attn_bwd_batched(...) is this call with SP_BWD_STAGE_ALL. */
@@ -399,9 +401,9 @@ sp_status sp_attn_probe_atomic_add(float* buf, int64_t rows, int32_t heads, int3
 
 /* Which workgroup shape a bf16 call on this packing takes for the forward and the dq pass: *rows = 256 (eight waves of
  * 32 rows) or 128 (four; see sp_attn_set_small_shape_steps below for the rule).  Optionally also the quantities that the
- * rule compares: the number of 64-key steps of row tiles of 256 and of 128 rows of one q head.  They are the steps that
- * run where every q head has a kv head of its own; else a workgroup holds rows of several q heads, spans fewer of them
- * and runs fewer steps.  Host arithmetic on the lengths (Section 4.3:
+ * rule compares: the number of 64-key steps of row tiles of 256 and of 128 rows of one q head, all rows and key tiles from
+ * multiples of 64.  A call may run fewer: a response's keys are walked from its first one on, response-rows mode
+ * leaves the prompt's rows out, and with several q heads per kv head a workgroup spans fewer rows.  Host arithmetic on the lengths (Section 4.3:
  * the key ranges of the three terms of its complexity split); no device work; for tools and tests.
  * Errors as the host checks of sp_attn_fwd_batched. */
 sp_status sp_attn_row_tile(int32_t n_groups, const int32_t* prompt_lens, const int32_t* Gs,

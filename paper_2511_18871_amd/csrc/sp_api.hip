@@ -39,8 +39,10 @@ inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // Every workspace starts with a tag block of TAG_BYTES; the segment table follows it.  The tag says
 // whether the workspace holds a forward's reserve (the part of o that its rounding to bf16 dropped) and for
-// which outputs; every call rewrites or re-validates it before it writes anything else, so a reserve
-// that some other call may have overwritten is never trusted.
+// which outputs.  A call that writes to the workspace rewrites or re-validates it in its preparation launch, which comes first,
+// or, without one, in the attention kernels themselves: a forward and a float32 backward beside their other writes, a bf16
+// backward in its last pass (its dq pass only compares), the objective beside its sums.  The next call, behind it on the stream,
+// therefore never trusts a reserve that this one may have overwritten.  Calls that write nothing there leave it.
 constexpr size_t TAG_BYTES = 256;
 inline int* table_of(void* workspace) { return (int*)((char*)workspace + TAG_BYTES); }
 inline bool misaligned(const void* p) { return ((uintptr_t)p & 15) != 0; }

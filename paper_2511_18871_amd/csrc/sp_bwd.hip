@@ -581,6 +581,7 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(TabArg table, BwdArg
 // per buffer); left to the compiler they were 25 additions per step, and K did not fit the registers.
 // 8 -> 4 waves with these addresses, one box: 16K prompt with 32 answers 7.67 -> 7.24 ms, 64 groups of a short prompt
 // and 16 answers 4.44 -> 3.95 ms, 64 groups of 1000 tokens 1.33 -> 1.07 ms, response rows under an 8K prompt 0.77 -> 0.67 ms.
+
 // Row parts of a key tile of `steps` 64-row tiles in the head-split pass (see dkdv_parts())
 __device__ __forceinline__ int row_parts(const BwdArgs& a, int steps) { return a.head_split == 2 && steps >= PART_STEPS ? 2 : 1; }
 

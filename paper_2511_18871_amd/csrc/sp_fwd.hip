@@ -67,8 +67,8 @@ struct FwdArgs {
 // 37 K cycles: lookups 4.7, first copies 3.4, 5.8 steps of 3.5, last product 1.8, stores 5.8; 2.9 TB/s).  The rows' own
 // segments are therefore walked from their first key on, not from the multiple of 64 below it (a quarter of a step less),
 // and what follows the loop takes its addresses from those of the loop or by one xor each (200 of 900 vector instructions
-// outside the loop).  One box, before -> after, us: that packing 2410 -> 2308, 64 groups of 1000 tokens 805 -> 784, three sets of
-// eight 2K prompts 7222 -> 7128, one short group 14.8 -> 14.0, 16K prompt 3913 -> 3910.
+// outside the loop).  One box, before -> after, us: that packing 2410 -> 2308, 64 groups of 1000 tokens 805 -> 784, one short group
+// 14.8 -> 14.0; three sets of eight 2K prompts and the 16K prompt within what runs differ.
 // NAIVE = the measurement baseline (every tile at or below the packed diagonal, mask applied element by
 // element): a separate instantiation, so that it shows under its own name in kernel traces and its
 // branches cost the product kernel nothing.

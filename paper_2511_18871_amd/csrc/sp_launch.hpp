@@ -46,7 +46,9 @@ constexpr int TAG_KEEP = -1;      // for launch_prepare: leave the tag block as 
 // argument, a wave looks its tile and its tokens' segments up in registers, and the tag block is kept by the kernels
 // (forward: written by the first workgroup; backward: compared by each workgroup of the dq pass, updated by the dkdv pass).
 // us, before -> after: one short group's forward 17.8 -> 15.4, two small groups' training pass 69.8 -> 66.8, one 1K prompt
-// 248.9 -> 244.9, one group of 9000 tokens, 28/4 heads (1988 tiles times heads), 2419.7 -> 2411.5.  Larger calls would not notice.
+// 248.9 -> 244.9, one group of 9000 tokens, 28/4 heads (1988 tiles times heads), 2419.7 -> 2411.5.  The line is at 2048 of them, beyond
+// which a training pass no longer shows it (forward; training pass): 40 groups of 300, 3360 tiles times heads, 82.5 -> 80.6; 298.8 ->
+// 299.1; one group of 12000, 2632, 863.6 -> 858.6; 4178.6 -> 4174.4; one of 20000, 4396, 2267 -> 2249; 9987 -> 9964.
 struct SmallCall { int on; int tag_mode; ReserveTag want; uint32_t* tag; };
 // Tag block maintenance by one wave (lane i = word i).  A reserve written for all rows (word 10 = 0) also serves a backward
 // over response rows only (want word 10 = 1), not the reverse.
@@ -193,7 +195,9 @@ inline bool use_small_call(const Problem& p, size_t words, int max_responses) {
 
 // Number of (row tile of `bm` rows, 64-key tile) pairs of one q head that hold an allowed pair, and of row tiles (host
 // arithmetic on the segment table).  With one q head per kv head these are the steps and the workgroups that run; with
-// more, a workgroup spans fewer rows (wave_rows() in sp_common.hpp) and skips most of what only other rows see.
+// more, a workgroup spans fewer rows (wave_rows() in sp_common.hpp) and skips most of what only other rows see.  Key tiles are
+// counted from multiples of 64, where the kernels walk a response from its first key on, and rows of the prompt are counted
+// in response-rows mode too, which does not run them: it is a measure of the packing, not of the call.
 inline void key_steps(const Problem& p, int bm, int64_t& steps, int64_t& tiles) {
     const int32_t* tab = p.host_table;
     steps = 0; tiles = 0;
