@@ -127,7 +127,7 @@ __global__ __launch_bounds__(LT) void logprob_fwd_kernel(TabArg table, const T* 
 
 // zero_prompt: prompt rows of dz are set to zero (otherwise they are not touched).  Rows are taken last first and each
 // from its end: the last 256 MB that the forward read are what the Infinity Cache still holds.
-template <typename T, int LT, bool BYPASS>
+template <typename T, int LT, bool LAST, bool BYPASS>       // LAST: the logits are read past the caches, BYPASS: the gradient is stored past them
 __global__ __launch_bounds__(LT) void logprob_bwd_kernel(TabArg table, const T* __restrict__ z, const int* __restrict__ y,
                                                          const float* __restrict__ lse, const float* __restrict__ g,
                                                          T* __restrict__ dz, int64_t V, int zero_prompt) {
@@ -158,6 +158,10 @@ __global__ __launch_bounds__(LT) void logprob_bwd_kernel(TabArg table, const T* 
     const Vec* const rv = reinterpret_cast<const Vec*>(row + rs.head);
     const float L = lse[tok], gt = g[tok];
     const int64_t label = y[tok];
+    auto vec = [&](int64_t i) -> Vec {
+        if constexpr (LAST) return __builtin_nontemporal_load(&rv[i]);
+        else return rv[i];
+    };
     auto value = [&](T x, int64_t k) { return (T)(gt * ((k == label ? 1.f : 0.f) - __expf((float)x - L))); };
     auto put = [&](const Vec& x, int64_t i) {
         Vec d;
@@ -169,11 +173,11 @@ __global__ __launch_bounds__(LT) void logprob_bwd_kernel(TabArg table, const T* 
     for (; i - (UNROLL - 1) * LT >= 0; i -= UNROLL * LT) {
         Vec x[UNROLL];
 #pragma unroll
-        for (int u = 0; u < UNROLL; ++u) x[u] = rv[i - u * LT];
+        for (int u = 0; u < UNROLL; ++u) x[u] = vec(i - u * LT);
 #pragma unroll
         for (int u = 0; u < UNROLL; ++u) put(x[u], i - u * LT);
     }
-    for (; i >= 0; i -= LT) put(rv[i], i);
+    for (; i >= 0; i -= LT) put(vec(i), i);
     if ((int)threadIdx.x < n_loose) out[loose] = value(row[loose], loose);
 }
 
@@ -291,15 +295,23 @@ hipError_t launch_logprob_fwd(const void* z, const int* y, float* logp, float* l
 
 hipError_t launch_logprob_bwd(const void* z, const int* y, const float* lse, const float* g, void* dz,
                               const TabArg& tab, int64_t total_tokens, int64_t V, bool f32, bool zero_prompt, hipStream_t s) {
-    // a gradient that the Infinity Cache (256 MB) cannot hold for its reader is stored past the caches
-    const bool bypass = total_tokens * V * (f32 ? 4 : 2) > (int64_t)256 << 20;
+    // A gradient that the Infinity Cache (256 MB) cannot hold for its reader is stored past the caches.  Where the logits fill a
+    // third of it, they are read past them: nothing after this pass reads them, and what they would displace is the part of them that
+    // the forward left.  Not where rows are short and share cache lines, which would be read twice.  Forward + backward, us, cached
+    // reads -> not: 101 MB of logits 49.4 -> 46.2, 131 MB 62.0 -> 57.2, 180 MB (9000) 98 -> 86, 144 MB (6000) 73.9 -> 71.2, 311 MB 136 -> 124, 933 MB 392 -> 384; but
+    // 67 MB (vocabulary 4096) 32.8 -> 33.7, and with a vocabulary of 1003 60 MB 36 -> 42, 201 MB 112.5 -> 114.5.
+    const int64_t row = V * (f32 ? 4 : 2), bytes = total_tokens * row, cache = (int64_t)256 << 20;
     with_row_kernel(V, f32, [&](auto elem, auto lt) {
         typedef decltype(elem) T;
         constexpr int LT = decltype(lt)::value;
-        if (bypass) hipLaunchKernelGGL((logprob_bwd_kernel<T, LT, true>), dim3((unsigned)total_tokens), dim3(LT), 0, s,
-                                       tab, (const T*)z, y, lse, g, (T*)dz, V, (int)zero_prompt);
-        else hipLaunchKernelGGL((logprob_bwd_kernel<T, LT, false>), dim3((unsigned)total_tokens), dim3(LT), 0, s,
-                                tab, (const T*)z, y, lse, g, (T*)dz, V, (int)zero_prompt);
+        auto launch = [&](auto last, auto bypass) {
+            hipLaunchKernelGGL((logprob_bwd_kernel<T, LT, decltype(last)::value, decltype(bypass)::value>), dim3((unsigned)total_tokens),
+                               dim3(LT), 0, s, tab, (const T*)z, y, lse, g, (T*)dz, V, (int)zero_prompt);
+        };
+        auto with_last = [&](auto last) {
+            if (bytes > cache) launch(last, std::true_type{}); else launch(last, std::false_type{});
+        };
+        if (3 * bytes > cache && (row >= 8192 || row % 128 == 0)) with_last(std::true_type{}); else with_last(std::false_type{});
     });
     return hipGetLastError();
 }
