@@ -148,10 +148,10 @@ def main():
     o = torch.empty_like(q)
     lse = torch.empty(Hq, T, dtype=torch.float32, device=dev)
     dq, dk, dv = torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)
-    # one workspace for the forward and the backward, with room for the forward-to-backward reserve and for row parts
-    ws = torch.empty(B.workspace_bytes(True, T, len(pl), len(rl), Hq, Hkv, d, code)
-                     + (0 if args.no_reserve else B.reserve_bytes(T, Hq, d, code) + B.row_parts_bytes(T, len(pl), Hq, Hkv, code)),
-                     dtype=torch.uint8, device=dev)
+    # one workspace for the forward and the backward, with room for the forward-to-backward reserve and all else they can use
+    size = B.workspace_bytes(True, T, len(pl), len(rl), Hq, Hkv, d, code) if args.no_reserve else \
+        B.full_workspace_bytes(T, len(pl), len(rl), Hq, Hkv, d, code)
+    ws = torch.empty(size, dtype=torch.uint8, device=dev)
     do_bwd = w.backward
 
     # the backward as two stage calls (what one sp_attn_bwd_batched call runs, split so that each pass can be

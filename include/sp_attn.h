@@ -107,6 +107,14 @@ size_t sp_attn_reserve_bytes(int64_t total_tokens, int32_t n_q_heads, int32_t he
 size_t sp_attn_row_parts_bytes(int64_t total_tokens, int32_t n_groups, int32_t n_q_heads, int32_t n_kv_heads,
                                sp_dtype dtype);
 
+/* Bytes of a workspace with which a forward and its backward can do all that they know:
+ *     sp_attn_workspace_bytes(1, ...) + sp_attn_reserve_bytes(...) + sp_attn_row_parts_bytes(...)
+ * and behind them room for pieces of key tiles (bf16, up to 640 key tiles of 128, at most 48 MB): where few key tiles are seen by many
+ * rows, a backward then gives the rows and q heads of such a tile to several workgroups, which changes the order in which dk
+ * and dv are summed.  With less it runs without. */
+size_t sp_attn_full_workspace_bytes(int64_t total_tokens, int32_t n_groups, int64_t total_responses, int32_t n_q_heads,
+                                    int32_t n_kv_heads, int32_t head_dim, sp_dtype dtype);
+
 /* Forward for one group (Section 4.3, modifications 1 and 3): writes
  * o [T, n_q_heads, head_dim] and lse [n_q_heads, T], T = prompt_len + sum(resp_lens).
  * resp_lens: HOST array of G >= 0 entries (may be NULL when G == 0). */

@@ -21,7 +21,7 @@ SP_SCHED_SHARED, SP_SCHED_NAIVE_CAUSAL = 0, 1
 SP_BWD_STAGE_ROWSUM, SP_BWD_STAGE_DKDV, SP_BWD_STAGE_DQ, SP_BWD_STAGE_ALL = 1, 2, 4, 7
 SP_FLAG_RESPONSE_ROWS, SP_FLAG_ACCUMULATE_DKDV, SP_FLAG_ZERO_PROMPT_ROWS = 1, 2, 4
 
-EXPORTS = ("sp_attn_workspace_bytes", "sp_attn_reserve_bytes", "sp_attn_row_parts_bytes", "sp_attn_fwd", "sp_attn_bwd", "sp_attn_fwd_batched",
+EXPORTS = ("sp_attn_workspace_bytes", "sp_attn_reserve_bytes", "sp_attn_row_parts_bytes", "sp_attn_full_workspace_bytes", "sp_attn_fwd", "sp_attn_bwd", "sp_attn_fwd_batched",
            "sp_attn_bwd_batched", "sp_attn_bwd_batched_static", "sp_attn_bwd_batched_stages", "sp_attn_fwd_multi", "sp_attn_rope", "sp_attn_rope_qk", "sp_attn_fwd_batched_ex", "sp_attn_bwd_batched_ex",
            "sp_attn_loss_workspace_bytes", "sp_attn_logprob_fwd", "sp_attn_logprob_bwd", "sp_attn_logprob_bwd_ex", "sp_attn_grpo_loss",
            "sp_attn_segment_table", "sp_attn_row_tile", "sp_attn_dkdv_waves", "sp_attn_mfma_ceiling", "sp_attn_probe_atomic_add", "sp_attn_set_small_shape_steps", "sp_attn_last_error", "sp_attn_version")
@@ -52,6 +52,8 @@ def load_library() -> ctypes.CDLL:
     lib.sp_attn_reserve_bytes.argtypes = [i64, i32, i32, ctypes.c_int]
     lib.sp_attn_row_parts_bytes.restype = sz
     lib.sp_attn_row_parts_bytes.argtypes = [i64, i32, i32, i32, ctypes.c_int]
+    lib.sp_attn_full_workspace_bytes.restype = sz
+    lib.sp_attn_full_workspace_bytes.argtypes = [i64, i32, i64, i32, i32, i32, ctypes.c_int]
     lib.sp_attn_fwd.restype = ctypes.c_int
     lib.sp_attn_fwd.argtypes = [vp, vp, vp, vp, vp, i32, ip, i32, i32, i32, i32, f32, ctypes.c_int, vp, sz, vp]
     lib.sp_attn_bwd.restype = ctypes.c_int
@@ -184,9 +186,15 @@ def row_parts_bytes(total_tokens: int, n_groups: int, n_q_heads: int, n_kv_heads
     return load_library().sp_attn_row_parts_bytes(total_tokens, n_groups, n_q_heads, n_kv_heads, dtype_code)
 
 
+def full_workspace_bytes(total_tokens: int, n_groups: int, total_responses: int, n_q_heads: int, n_kv_heads: int, head_dim: int,
+                         dtype_code: int) -> int:
+    return load_library().sp_attn_full_workspace_bytes(total_tokens, n_groups, total_responses, n_q_heads, n_kv_heads, head_dim,
+                                                       dtype_code)
+
+
 def _workspace(is_bwd, q, n_groups, n_resp, n_kv_heads, workspace, o=None, reserve=False):
     """The workspace tensor of a call.  When the caller passes none: a forward allocates one that also has
-    room for the forward-to-backward reserve (and for row parts) and hangs it on the output tensor it returns (attribute
+    room for the forward-to-backward reserve (and for row parts and pieces of key tiles) and hangs it on the output tensor it returns (attribute
     ``_sp_workspace``); the backward that is given that output finds it there and passes it on, which is
     all the library needs to use the reserve.  A backward with a residual of its own allocates the same.  Plumbing only:
     what the reserve is and whether it is valid is decided by the library."""
@@ -195,9 +203,8 @@ def _workspace(is_bwd, q, n_groups, n_resp, n_kv_heads, workspace, o=None, reser
         return workspace
     if is_bwd and o is not None and getattr(o, "_sp_workspace", None) is not None:
         return o._sp_workspace
-    need = workspace_bytes(is_bwd or reserve, T, n_groups, n_resp, Hq, n_kv_heads, d, _dtype_code(q))
-    if reserve:
-        need += reserve_bytes(T, Hq, d, _dtype_code(q)) + row_parts_bytes(T, n_groups, Hq, n_kv_heads, _dtype_code(q))
+    need = (full_workspace_bytes(T, n_groups, n_resp, Hq, n_kv_heads, d, _dtype_code(q)) if reserve else
+            workspace_bytes(is_bwd, T, n_groups, n_resp, Hq, n_kv_heads, d, _dtype_code(q)))
     workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=q.device)
     if reserve and not is_bwd and o is not None:
         o._sp_workspace = workspace        # sized for the backward too

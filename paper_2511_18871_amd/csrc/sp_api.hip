@@ -4,6 +4,7 @@
 #include "sp_common.hpp"
 #include "sp_launch.hpp"
 
+#include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <cstdarg>
@@ -195,6 +196,10 @@ sp_status run(bool bwd, const void* q, const void* k, const void* v, const void*
     // row parts change the order of sums: they go with the reserve, so that of the calls without one none has them
     const bool two_parts = ordered && reserve_fits && sp::dkdv_max_parts(L.total_tokens, n_groups, Hq, Hkv) == 2 &&
                            workspace_bytes >= parts_off + partial_bytes(L.total_tokens, Hq, Hkv);
+    // pieces of key tiles, likewise
+    const size_t pieces_off = parts_off + sp_attn_row_parts_bytes(L.total_tokens, n_groups, Hq, Hkv, dtype);
+    const size_t pieces_len = sp::piece_bytes(L.total_tokens, n_groups, Hq, Hkv);
+    const bool pieces_fit = ordered && reserve_fits && pieces_len > 0 && workspace_bytes >= pieces_off + pieces_len;
     void* const reserve = (char*)workspace + reserve_off;
     const bool resp_only = (flags & SP_FLAG_RESPONSE_ROWS) != 0;
     sp::ReserveTag tag{};
@@ -239,7 +244,15 @@ sp_status run(bool bwd, const void* q, const void* k, const void* v, const void*
     p.dkdv_partial2 = p.dkdv_parts == 2 ? (float*)((char*)workspace + parts_off) : nullptr;
 
     p.n_tiles256 = sp::count_tiles(p, 256); p.n_tiles128 = sp::count_tiles(p, 128);
-    const int key_order = ordered && (stages & SP_BWD_STAGE_DKDV) ? sp::key_order(p) : sp::KEYS_AS_PACKED;
+    const bool small_call = dtype == SP_BF16 && (!bwd || (stages == SP_BWD_STAGE_ALL && sp::rowsum_fast_path(p))) &&
+                            sp::use_small_call(p, L.words.size(), L.max_responses);
+    sp::KeyPieces pieces;
+    if (pieces_fit && (stages & SP_BWD_STAGE_DKDV)) {
+        pieces = sp::plan_key_pieces(p, sp::piece_slots(L.total_tokens, n_groups, Hq, Hkv),
+                                     (size_t)sp::ARG_WORDS - (small_call ? L.words.size() : 0));
+        if (!pieces.words.empty()) { p.pieces = &pieces; p.piece_sums = (float*)((char*)workspace + pieces_off); }
+    }
+    const int key_order = !p.pieces && ordered && (stages & SP_BWD_STAGE_DKDV) ? sp::key_order(p) : sp::KEYS_AS_PACKED;
     p.sched.key_tiles = p.sched.tiles128;
     if (key_order != sp::KEYS_AS_PACKED) p.sched.key_tiles = (const sp::TileDesc*)((char*)workspace + key_tiles_off);
     // gradient stages enqueued on their own run on the workspace that their ROWSUM stage prepared (and checked): the tag is
@@ -249,7 +262,7 @@ sp_status run(bool bwd, const void* q, const void* k, const void* v, const void*
     const bool one_call = !bwd || (stages == SP_BWD_STAGE_ALL && (dtype == SP_F32 || sp::rowsum_fast_path(p)));
     // (float32: the table alone; a forward then writes nothing to the workspace)
     p.small.on = dtype == SP_F32 ? one_call && L.words.size() <= (size_t)sp::ARG_WORDS
-                                 : one_call && key_order == sp::KEYS_AS_PACKED && sp::use_small_call(p, L.words.size(), L.max_responses);
+                                 : key_order == sp::KEYS_AS_PACKED && small_call;
     p.small.tag_mode = tag_mode; p.small.want = tag; p.small.tag = (uint32_t*)workspace;
     hipError_t e = p.small.on ? hipSuccess : sp::launch_prepare(L.words.data(), (int)L.words.size(), table_of(workspace), (uint32_t*)workspace, tag,
                                       keep_tag ? sp::TAG_KEEP : tag_mode, dtype == SP_BF16, n_groups, L.total_tokens,
@@ -283,6 +296,15 @@ size_t sp_attn_reserve_bytes(int64_t total_tokens, int32_t n_q_heads, int32_t he
 size_t sp_attn_row_parts_bytes(int64_t total_tokens, int32_t n_groups, int32_t n_q_heads, int32_t n_kv_heads, sp_dtype dtype) {
     if (total_tokens < 1 || n_groups < 1 || n_q_heads < 1 || n_kv_heads < 1 || n_q_heads % n_kv_heads != 0 || dtype != SP_BF16) return 0;
     return sp::dkdv_max_parts(total_tokens, n_groups, n_q_heads, n_kv_heads) == 2 ? partial_bytes(total_tokens, n_q_heads, n_kv_heads) : 0;
+}
+
+size_t sp_attn_full_workspace_bytes(int64_t total_tokens, int32_t n_groups, int64_t total_responses, int32_t n_q_heads,
+                                    int32_t n_kv_heads, int32_t head_dim, sp_dtype dtype) {
+    const size_t need = sp_attn_workspace_bytes(1, total_tokens, n_groups, total_responses, n_q_heads, n_kv_heads, head_dim, dtype);
+    if (need == 0 || n_kv_heads < 1) return need;
+    return need + sp_attn_reserve_bytes(total_tokens, n_q_heads, head_dim, dtype) +
+           sp_attn_row_parts_bytes(total_tokens, n_groups, n_q_heads, n_kv_heads, dtype) +
+           (dtype == SP_BF16 ? sp::piece_bytes(total_tokens, n_groups, n_q_heads, n_kv_heads) : 0);
 }
 
 sp_status sp_attn_fwd(const void* q, const void* k, const void* v, void* o, float* lse, int32_t prompt_len,

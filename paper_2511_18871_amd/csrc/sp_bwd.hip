@@ -18,6 +18,7 @@
 #include "sp_launch.hpp"
 #include "sp_edge.hpp"
 #include <algorithm>
+#include <functional>
 #include <type_traits>
 #include <vector>
 
@@ -47,10 +48,13 @@ struct BwdArgs {
     // dkdv pass on small problems: one workgroup per (key tile, Q head) instead of per (key tile,
     // kv head); the per-q-head partial sums go to `partial` in fp32 and a second kernel adds them
     int rep;             // q heads per kv head
-    Div kv_heads;
+    Div kv_heads, rep_div;
     int head_split;      // row parts of a key tile: 0 (not split), 1 or 2
     float* partial;      // [2 (dK, dV)][rep][T_total][Hkv][128] fp32 of the first row part
     float* partial2;     // the same of the second
+    int pieces_at;       // dkdv pass in pieces: word of the table argument at which their list starts
+    int n_slots;         // pieces of tiles with several parts
+    float* piece_sums;   // [kv head][slot][dK, dV][128 keys][128]
 };
 
 // ------------------------------------------------------------------------------------
@@ -585,8 +589,10 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(TabArg table, BwdArg
 // Row parts of a key tile of `steps` 64-row tiles in the head-split pass (see dkdv_parts())
 __device__ __forceinline__ int row_parts(const BwdArgs& a, int steps) { return a.head_split == 2 && steps >= PART_STEPS ? 2 : 1; }
 
-template <int NW, bool SMALL>
-__device__ __forceinline__ void dkdv_body(const BwdArgs& a, const SmallGroup& sg, const TileDesc td, const int kvh, const int hr_only, const int part) {
+// PIECES: part `part` of `parts` of the tile's steps (row tile, q head); the sums go to `sums` where there are several
+template <int NW, bool SMALL, bool PIECES>
+__device__ __forceinline__ void dkdv_body(const BwdArgs& a, const SmallGroup& sg, const TileDesc td, const int kvh, const int hr_only, const int part,
+                                          const int parts, float* const sums) {
     const int ti = td.ti;
     constexpr int BNK = 128, BQ = 8 * NW;
     constexpr bool K_REG = NW == 4;                 // the wave's K rows stay in registers, only V in LDS
@@ -641,13 +647,13 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const SmallGroup& sg
     // (no tile at all under a prompt without response rows: the one that its end cuts holds no row that takes part, and nothing
     // writes L2 and -D of its rows)
     int qt0 = max(s0, row_lo) / BQ, qt1 = row_end > row_lo ? (row_end + BQ - 1) / BQ : qt0;
-    if (NW == 8 && a.head_split) {                     // this workgroup's row part, the later rows first
-        const int parts = row_parts(a, qt1 - qt0), mid = (qt0 + qt1) / 2;
-        if (part >= parts) return;
-        if (parts == 2) { if (part == 0) qt0 = mid; else qt1 = mid; }
+    if (NW == 8 && !PIECES && a.head_split) {          // this workgroup's row part, the later rows first
+        const int n = row_parts(a, qt1 - qt0), mid = (qt0 + qt1) / 2;
+        if (part >= n) return;
+        if (n == 2) { if (part == 0) qt0 = mid; else qt1 = mid; }
     }
     const int rep_all = a.rep;
-    const int rep = NW == 8 && a.head_split ? 1 : rep_all;        // q heads this workgroup walks
+    const int rep = NW == 8 && !PIECES && a.head_split ? 1 : rep_all;        // q heads this workgroup walks
     const int64_t q_stride = (int64_t)a.Hq * 128;
     const int64_t kv_stride = (int64_t)a.Hkv * 128;
 
@@ -808,9 +814,16 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const SmallGroup& sg
         if (LO) v = bf16x2{(__bf16)(x - (float)v[0]), (__bf16)(y - (float)v[1])};
         return __builtin_bit_cast(unsigned, v);
     };
-    const int n_steps = max(q_hi - q_lo, 0) * rep;
+    int n_steps = max(q_hi - q_lo, 0) * rep;
     int qt = q_hi - 1, hr = 0;                // step 0
-    int qt_n = qt, hr_n = 1;                  // step 1
+    if constexpr (PIECES) {
+        const int from = n_steps * part / parts;
+        n_steps = n_steps * (part + 1) / parts - from;
+        unsigned r;
+        qt -= (int)divmod((unsigned)from, a.rep_div, r);
+        hr = (int)r;
+    }
+    int qt_n = qt, hr_n = hr + 1;             // step 1
     if (hr_n == rep) { hr_n = 0; --qt_n; }
     if (n_steps > 0) issue_tile(qt, hr, 0);
     auto step = [&](const int it, auto buf_tag) {
@@ -1004,7 +1017,13 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const SmallGroup& sg
 #pragma unroll
                 for (int gq = 0; gq < 4; ++gq) {
                     const f32x4 y = *reinterpret_cast<const f32x4*>(xch + (db * 4 + gq) * 256);
-                    if (a.head_split) {      // fp32 partial sum of this q head; scaled and rounded by the reduce kernel
+                    if (PIECES && parts > 1) {
+                        const f32x4 z = {acc[db][4 * gq] + y[0], acc[db][4 * gq + 1] + y[1], acc[db][4 * gq + 2] + y[2],
+                                         acc[db][4 * gq + 3] + y[3]};
+                        *reinterpret_cast<f32x4*>(sums + (pass * 128 + 32 * kb + c) * 128 + 4 * hh + 32 * db + 8 * gq) = z;
+                        continue;
+                    }
+                    if (!PIECES && a.head_split) {      // fp32 partial sum of this q head; scaled and rounded by the reduce kernel
                         float* sums = (part == 0 ? a.partial : a.partial2) + ((int64_t)pass * rep_all + hr_only) * T_total * a.Hkv * 128;
                         const f32x4 z = {acc[db][4 * gq] + y[0], acc[db][4 * gq + 1] + y[1], acc[db][4 * gq + 2] + y[2],
                                          acc[db][4 * gq + 3] + y[3]};
@@ -1022,7 +1041,7 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const SmallGroup& sg
     }
 }
 
-template <int NW, bool SMALL>
+template <int NW, bool SMALL, bool PIECES>
 __global__ __launch_bounds__(64 * NW, 2) void bwd_dkdv_kernel(TabArg table, BwdArgs a) {
     if (SMALL && blockIdx.x == 0 && threadIdx.x < 64 && a.small.tag_mode != TAG_KEEP)       // (the dq pass is through)
         reserve_tag_body(a.small.tag, a.small.want, a.small.tag_mode, threadIdx.x);
@@ -1030,15 +1049,23 @@ __global__ __launch_bounds__(64 * NW, 2) void bwd_dkdv_kernel(TabArg table, BwdA
     if (!decode_item(blockIdx.x, a.items, item)) return;
     TileDesc td;
     SmallGroup sg;
+    unsigned piece = (unsigned)item.tile;
+    if constexpr (PIECES) piece = (unsigned)table_of(table)[a.pieces_at + item.tile];
+    const int tile = PIECES ? (int)(piece & 0xffff) : item.tile;
     if constexpr (SMALL) {
         int ti;
-        sg = small_tile<128>(table_of(table), a.n_groups, item.tile, threadIdx.x & 63, ti);
+        sg = small_tile<128>(table_of(table), a.n_groups, tile, threadIdx.x & 63, ti);
         td = TileDesc{0, ti, sg.tok_base, sg.Lp, sg.Tg, 0, 0, 0};
     } else {
-        td = a.sched.key_tiles[item.tile];
+        td = a.sched.key_tiles[tile];
+    }
+    if constexpr (PIECES) {
+        dkdv_body<NW, SMALL, true>(a, sg, td, item.kvh, 0, (int)(piece >> 16 & 0xff), (int)(piece >> 24),
+                                   a.piece_sums + ((int64_t)item.kvh * a.n_slots + item.tile) * (int64_t)(PIECE_SLOT_BYTES / 4));
+        return;
     }
     const int two = NW == 8 && a.head_split == 2 ? 1 : 0;          // (q head, row part)
-    dkdv_body<NW, SMALL>(a, sg, td, item.kvh, item.hr >> two, item.hr & two);
+    dkdv_body<NW, SMALL, false>(a, sg, td, item.kvh, item.hr >> two, item.hr & two, 1, nullptr);
 }
 
 // Second stage of the head-split dkdv pass: dk = scale * sum_hr partial[0][hr], dv = sum_hr
@@ -1115,6 +1142,41 @@ __global__ __launch_bounds__(256) void dkdv_reduce_parts_kernel(TabArg table, Bw
         bf16x4 y;
 #pragma unroll
         for (int e = 0; e < 4; ++e) y[e] = (__bf16)(acc[e] * mul + (float)old[e]);
+        *reinterpret_cast<bf16x4*>(out) = y;
+    }
+}
+
+// The same for key tiles in pieces: a workgroup adds up PK keys of a tile with several parts and one kv head, a thread 4
+// consecutive elements of dK and of dV, parts in order.
+struct PieceSums { uint32_t w[2 * PIECE_SLOTS]; };
+constexpr int PK = 8;
+__global__ __launch_bounds__(256) void dkdv_pieces_kernel(PieceSums tiles, BwdArgs a) {
+    unsigned kvh;
+    const unsigned n = divmod(blockIdx.x / (128 / PK), a.kv_heads, kvh);
+    const uint32_t w = tiles.w[2 * n];
+    const int first = (int)(w & 0xffff), parts = (int)(w >> 16 & 0xff), keys = (int)(w >> 24) + 1;
+    const int key = PK * (int)(blockIdx.x & (128 / PK - 1)) + (int)(threadIdx.x >> 5);
+    if (key >= keys) return;
+    const float* const sums = a.piece_sums + ((int64_t)kvh * a.n_slots + first) * (int64_t)(PIECE_SLOT_BYTES / 4) + 128 * key + 4 * (threadIdx.x & 31);
+    const int64_t i = (((int64_t)tiles.w[2 * n + 1] + key) * a.Hkv + kvh) * 128 + 4 * (threadIdx.x & 31);
+    f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll 4
+    for (int p = 0; p < parts; ++p)
+#pragma unroll
+        for (int pass = 0; pass < 2; ++pass) {
+            const f32x4 x = *reinterpret_cast<const f32x4*>(sums + (int64_t)p * (int64_t)(PIECE_SLOT_BYTES / 4) + pass * 128 * 128);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[pass][e] += x[e];
+        }
+#pragma unroll
+    for (int pass = 0; pass < 2; ++pass) {
+        __bf16* const out = (pass == 0 ? a.dk : a.dv) + i;
+        const float mul = pass == 0 ? a.scale : 1.0f;
+        bf16x4 old = {0, 0, 0, 0};
+        if (a.accumulate) old = *reinterpret_cast<const bf16x4*>(out);
+        bf16x4 y;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) y[e] = (__bf16)(acc[pass][e] * mul + (float)old[e]);
         *reinterpret_cast<bf16x4*>(out) = y;
     }
 }
@@ -1200,6 +1262,99 @@ int dkdv_waves(const Problem& p) {
     return end4 < end8 ? 4 : 8;
 }
 
+// Key tiles in pieces.  The pass ends with its longest workgroup, and a prompt's first key tile is seen by every row of its group: few
+// groups, and short prompts above all, left most CUs waiting for it.  Tiles longer than some length are therefore cut into equal parts
+// (of their row tiles and q heads), and that length is the one at which a launch of pieces, longest first, each to the CU that is
+// free first, is through soonest.  Whole tiles (or, where the pass is split over the q heads, those) are played in the same way; they stay
+// where pieces do not gain a tenth on them (four waves to a workgroup walk whole tiles faster than is played here), and are
+// not played at all where the longest is within a quarter of an even share.  Backward passes, us, before -> after (prompt x answers, q / kv heads): 2 x (60 + 26 x 85), 32/8 (two sweeps,
+// as prompts are short) 436 -> 132; 100 + 10 x 400, 4/2 117 -> 52; 2 x (560 + 27 x 840), 28/4 4757 -> 2552; 35 + 22 x 470,
+// 32/8 2121 -> 516; 1024 + 8 x 256, 28/4 182 -> 170 (sums of prompt tiles only); 650 + 4 x (9 x 84), 32/8 258 -> 234; on 52 drawn
+// packings of 1e8 to 2e11 operations 1.17 times as fast on average, on 18 larger ones 1.20, at worst 0.98.
+KeyPieces plan_key_pieces(const Problem& p, int slots, size_t max_words) {
+    // steps' worth of time: of a workgroup without steps, of storing partial sums, of the launch that adds them up
+    constexpr int FIXED = 5, STORE = 2, SUM_STEPS = 3;
+    KeyPieces out;
+    const int rep = p.Hq / p.Hkv;
+    struct Tile { int steps, id, tok, keys; };
+    std::vector<Tile> tiles;
+    tiles.reserve((size_t)p.n_tiles128);
+    int longest = 0;
+    int64_t all = 0;
+    for (int g = 0; g < p.n_groups; ++g) {
+        const int32_t* e = p.host_table + TAB_HEADER + TAB_GROUP_WORDS * g;
+        const int Lp = e[1], Tg = e[2];
+        const int32_t* roff = p.host_table + e[3];
+        for (int s0 = 0, j = 0; s0 < Tg; s0 += 128) {
+            const int s1 = std::min(s0 + 128, Tg), from = p.resp_only && Lp > s0 ? Lp : s0;
+            int to = Tg;
+            if (s0 >= Lp) { while (roff[j + 1] < s1) ++j; to = roff[j + 1]; }
+            const int q0 = from / 64, q1 = to > (p.resp_only ? Lp : 0) ? (to + 63) / 64 : q0;
+            const int lo = std::max((Lp >= EDGE_LEN ? std::min(q1, 1) : q1) - q0, 0);
+            const int steps = rep * (std::max(q1 - q0, 0) + lo);
+            tiles.push_back(Tile{steps, (int)tiles.size(), e[0] + s0, s1 - s0});
+            longest = std::max(longest, steps);
+            all += steps + FIXED;
+        }
+    }
+    const bool by_xcd = p.Hkv % 8 == 0 || 8 % p.Hkv == 0;
+    const int bins = !by_xcd ? 256 : p.Hkv % 8 == 0 ? 32 : 32 * (8 / p.Hkv), copies = !by_xcd ? p.Hkv : p.Hkv % 8 == 0 ? p.Hkv / 8 : 1;
+    const double even = (double)copies * (double)all / bins;
+    if (longest + FIXED <= 1.25 * even) return out;
+    // when workgroups of `lens` steps, longest first, are through: each goes to the CU that is free first
+    auto through = [&](std::vector<int>& lens) {
+        std::sort(lens.begin(), lens.end(), std::greater<int>());
+        std::vector<int> cu((size_t)bins, 0);                  // a heap, the least on top
+        for (int n : lens)
+            for (int c = 0; c < copies; ++c) {
+                std::pop_heap(cu.begin(), cu.end(), std::greater<int>());
+                cu.back() += n + FIXED;
+                std::push_heap(cu.begin(), cu.end(), std::greater<int>());
+            }
+        return *std::max_element(cu.begin(), cu.end());
+    };
+    auto parts_of = [&](int steps, int len) { return steps <= len ? 1 : std::min((steps + len - 1) / len, 255); };
+    std::vector<int> lens;
+    auto cut = [&](int max_len, int each) {                    // (each: a tile's workgroups of equal share, whatever its length)
+        lens.clear();
+        int64_t n_slots = 0;
+        for (const Tile& t : tiles) {
+            const int parts = max_len ? parts_of(t.steps, max_len) : each * (each > 1 && t.steps / rep >= PART_STEPS ? p.dkdv_parts : 1);
+            if (parts > 1) n_slots += parts;
+            if (max_len && (n_slots > slots || lens.size() + parts > max_words)) return false;
+            for (int i = 0; i < parts; ++i) lens.push_back((t.steps + parts - 1) / parts + (parts > 1 ? STORE : 0));
+        }
+        return max_len == 0 || n_slots > 0;
+    };
+    // whole tiles, or one workgroup per q head and row part, then pieces of falling length
+    cut(0, p.dkdv_partial ? rep : 1);
+    int best = through(lens) - (p.dkdv_partial ? 0 : SUM_STEPS), len = 0;
+    if (!p.dkdv_partial) best = best * 9 / 10;
+    for (int l = longest * 3 / 4; l >= 3; l = std::min(l * 7 / 8, l - 1)) {
+        if (!cut(l, 1)) break;
+        const int end = through(lens);
+        if (end < best) { best = end - best / 50; len = l; }
+        if (l + FIXED < 0.5 * even) break;
+    }
+    if (len == 0) return out;
+    std::sort(tiles.begin(), tiles.end(), [&](const Tile& a, const Tile& b) {
+        const int pa = parts_of(a.steps, len), pb = parts_of(b.steps, len);
+        if ((pa > 1) != (pb > 1)) return pa > 1;
+        const int64_t x = (int64_t)a.steps * pb, y = (int64_t)b.steps * pa;
+        return x != y ? x > y : a.id < b.id;
+    });
+    for (const Tile& t : tiles) {
+        const int parts = parts_of(t.steps, len);
+        if (parts > 1) {
+            out.sums.push_back((uint32_t)out.words.size() | (uint32_t)parts << 16 | (uint32_t)(t.keys - 1) << 24);
+            out.sums.push_back((uint32_t)t.tok);
+            out.n_slots += parts;
+        }
+        for (int i = 0; i < parts; ++i) out.words.push_back((uint32_t)t.id | (uint32_t)i << 16 | (uint32_t)parts << 24);
+    }
+    return out;
+}
+
 hipError_t launch_bwd_bf16(const Problem& p, hipStream_t s) {
     hipError_t e = hipSuccess;
     // A call that runs both the rowsum and the dq stage folds the first into the second (the dq pass has
@@ -1238,19 +1393,34 @@ hipError_t launch_bwd_bf16(const Problem& p, hipStream_t s) {
         auto launch = [&](int waves, int grid) {
             auto go = [&](auto small_call) {
                 constexpr bool S = decltype(small_call)::value;
-                if (waves == 8) hipLaunchKernelGGL((bwd_dkdv_kernel<8, S>), dim3(grid), dim3(512), 0, s, table, a);
-                else hipLaunchKernelGGL((bwd_dkdv_kernel<4, S>), dim3(grid), dim3(256), 0, s, table, a);
+                if (p.pieces) {
+                    TabArg list = table;
+                    for (size_t i = 0; i < p.pieces->words.size(); ++i) list.words[a.pieces_at + i] = (int32_t)p.pieces->words[i];
+                    hipLaunchKernelGGL((bwd_dkdv_kernel<8, S, true>), dim3(grid), dim3(512), 0, s, list, a);
+                } else if (waves == 8) hipLaunchKernelGGL((bwd_dkdv_kernel<8, S, false>), dim3(grid), dim3(512), 0, s, table, a);
+                else hipLaunchKernelGGL((bwd_dkdv_kernel<4, S, false>), dim3(grid), dim3(256), 0, s, table, a);
             };
             if (p.small.on) go(std::true_type{}); else go(std::false_type{});
         };
         const int n_tiles = count_tiles(p, 128);
         a.rep = p.Hq / p.Hkv;
-        a.head_split = p.dkdv_partial ? p.dkdv_parts : 0;
+        a.rep_div = make_div(a.rep);
+        a.kv_heads = make_div(p.Hkv);
+        a.head_split = p.dkdv_partial && !p.pieces ? p.dkdv_parts : 0;
         a.partial = p.dkdv_partial; a.partial2 = p.dkdv_partial2;
-        if (a.head_split) {
+        if (p.pieces) {
+            const int n = (int)p.pieces->words.size();
+            a.pieces_at = p.small.on ? p.host_table[2] : 0;
+            a.n_slots = p.pieces->n_slots;
+            a.piece_sums = p.piece_sums;
+            a.items = make_item_map(n, p.Hkv, p.Hkv);
+            launch(8, grid_for_items(n, p.Hkv, p.Hkv));
+            PieceSums sums{};
+            std::copy(p.pieces->sums.begin(), p.pieces->sums.end(), sums.w);
+            hipLaunchKernelGGL(dkdv_pieces_kernel, dim3((unsigned)(p.pieces->sums.size() / 2 * p.Hkv * (128 / PK))), dim3(256), 0, s, sums, a);
+        } else if (a.head_split) {
             const int items = p.Hq * p.dkdv_parts;
             a.items = make_item_map(n_tiles, items, p.Hkv);
-            a.kv_heads = make_div(p.Hkv);
             launch(8, grid_for_items(n_tiles, items, p.Hkv));
             const int64_t n4 = p.total_tokens * p.Hkv * 32;
             const dim3 rg((unsigned)(n_tiles * p.Hkv * (128 / RK)));

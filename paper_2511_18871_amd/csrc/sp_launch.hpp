@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <cstddef>
 #include <stdint.h>
+#include <vector>
 #include "sp_common.hpp"
 
 namespace sp {
@@ -133,6 +134,8 @@ struct Problem {
     const uint32_t* o_lo_flag;                            // device word: o_lo may be used only if it is non-zero (NULL: always)
     int accumulate;                                       // backward: dk, dv += instead of =
     int dkdv_parts;                                       // row parts of a key tile in the head-split pass
+    const struct KeyPieces* pieces;                       // bf16 backward: the dkdv pass in pieces of key tiles (null: not)
+    float* piece_sums;                                    // their partial sums
     float* dkdv_partial;                                  // bf16 backward on small problems: fp32 per-q-head partials
     float* dkdv_partial2;                                 // the second row part's
     // host copies of the per-group token counts and of the whole segment table, for grid sizing and
@@ -270,7 +273,7 @@ inline int dkdv_max_parts(int64_t total_tokens, int n_groups, int Hq, int Hkv) {
     return dkdv_head_split(total_tokens, n_groups, Hq, Hkv) && head_split_wgs(total_tokens, 1, Hq) <= 224 &&
            2 * 2 * (int64_t)Hq * total_tokens * 128 * 4 <= (int64_t)30 << 20 ? 2 : 1;
 }
-constexpr int PART_STEPS = 8;
+constexpr int PART_STEPS = 8, PIECE_STEPS = 8;
 inline int dkdv_parts(const Problem& p) {
     if (dkdv_max_parts(p.total_tokens, p.n_groups, p.Hq, p.Hkv) < 2) return 1;
     int most = 0;                                              // of a group's first tile: no other has more
@@ -281,6 +284,26 @@ inline int dkdv_parts(const Problem& p) {
     }
     return most >= PART_STEPS && head_split_wgs(p.total_tokens, p.n_groups, p.Hq) <= 9 * most ? 2 : 1;
 }
+
+// Key tiles in pieces: of the packings that use it, the dkdv pass takes a list of (tile, part of its row tiles and q heads), sorted by length,
+// from the kernel arguments behind the table.  word: tile | part << 16 | parts << 24.  Pieces of a tile with several parts lie next
+// to one another ahead of all others and leave partial sums in the slot of their place in the list; a second launch adds them (sums: two
+// words for each such tile, its first slot | parts << 16 | keys - 1 << 24 and its first packed token).
+constexpr int PIECE_TILES = 640, PIECE_SLOTS = 384;       // most key tiles; most slots, all kv heads
+constexpr size_t PIECE_SLOT_BYTES = 2 * 128 * 128 * 4;    // dK and dV of a key tile, float32
+struct KeyPieces { std::vector<uint32_t> words, sums; int n_slots = 0; };
+// slots of a kv head that a call can use, by its totals
+inline int piece_slots(int64_t total_tokens, int n_groups, int Hq, int Hkv) {
+    const int64_t tiles = total_tokens / 128 + n_groups, rows = total_tokens / 64 + n_groups;
+    if (tiles > PIECE_TILES || Hkv < 1 || Hq % Hkv != 0) return 0;
+    const int64_t by_work = tiles * rows * (Hq / Hkv) / PIECE_STEPS, cap = PIECE_SLOTS / Hkv;
+    return (int)(by_work < cap ? by_work : cap);
+}
+inline size_t piece_bytes(int64_t total_tokens, int n_groups, int Hq, int Hkv) {
+    return (size_t)piece_slots(total_tokens, n_groups, Hq, Hkv) * Hkv * PIECE_SLOT_BYTES;
+}
+// the pieces of a call (none where whole key tiles are as good), at most `slots` with partial sums
+KeyPieces plan_key_pieces(const Problem& p, int slots, size_t max_words);
 
 // Waves per workgroup (8 or 4) of a dkdv pass that is not split over the q heads (rule and reasons: sp_bwd.hip).
 int dkdv_waves(const Problem& p);
