@@ -35,3 +35,28 @@ def test_short_rows_in_one_call_and_in_stages(heads, groups, steps):
     for name, got, also, ref in zip(("dQ", "dK", "dV"), one, apart, oracle_bwd(w, t)):
         gate(name, to64(got), ref, w.dtype)
         assert torch.equal(got, also), name
+
+
+@pytest.mark.parametrize("heads", [1, 8])
+@pytest.mark.parametrize("responses", [300, 4000])       # 4000: more row tiles than the second sweep of the dkdv pass lists
+def test_prompt_gradients_under_many_short_responses(responses, heads):
+    """A prompt of 10 tokens under responses of 35, whose every row sees fewer than 64 keys, against batched per-sample attention."""
+    Lp, n, d = 10, 35, 128
+    gen = torch.Generator(device="cuda").manual_seed(responses)
+    T = Lp + responses * n
+    q, k, v, d_o = (torch.randn(T, heads, d, generator=gen, device="cuda").to(torch.bfloat16) for _ in range(4))
+    pack, sc = ([Lp], [responses], [n] * responses), d ** -0.5
+    o, lse = B.sp_attn_fwd_batched(q, k, v, *pack, sc)
+    dq, dk, dv = B.sp_attn_bwd_batched(q, k, v, o, lse, d_o, *pack, sc)
+    torch.cuda.synchronize()
+    idx = torch.cat([torch.arange(Lp).expand(responses, Lp), Lp + torch.arange(responses * n).view(responses, n)], 1).cuda()
+    mask = torch.ones(Lp + n, Lp + n, device="cuda").tril().bool()
+    for h in {0, heads - 1}:
+        Q, K, V = (x[:, h].float()[idx].contiguous().requires_grad_() for x in (q, k, v))
+        G = d_o[:, h].float()[idx].contiguous()
+        G[1:, :Lp] = 0                                    # the prompt's own rows count once
+        S = (Q * sc) @ K.transpose(1, 2).contiguous()
+        (torch.softmax(S.masked_fill(~mask, float("-inf")), -1) @ V).backward(G)
+        for name, got, x in (("dQ", dq, Q), ("dK", dk, K), ("dV", dv, V)):
+            ref = torch.zeros(T, d, dtype=torch.float64, device="cuda").index_add_(0, idx.reshape(-1), x.grad.double().view(-1, d))
+            gate(f"{name} head {h}", to64(got[:, h]), to64(ref), torch.bfloat16)
