@@ -199,7 +199,7 @@ sp_status run(bool bwd, const void* q, const void* k, const void* v, const void*
     // pieces of key tiles, likewise
     const size_t pieces_off = parts_off + sp_attn_row_parts_bytes(L.total_tokens, n_groups, Hq, Hkv, dtype);
     const size_t pieces_len = sp::piece_bytes(L.total_tokens, n_groups, Hq, Hkv);
-    const bool pieces_fit = ordered && reserve_fits && pieces_len > 0 && workspace_bytes >= pieces_off + pieces_len;
+    const bool pieces_fit = dtype == SP_BF16 && reserve_fits && pieces_len > 0 && workspace_bytes >= pieces_off + pieces_len;
     void* const reserve = (char*)workspace + reserve_off;
     const bool resp_only = (flags & SP_FLAG_RESPONSE_ROWS) != 0;
     sp::ReserveTag tag{};
@@ -247,10 +247,18 @@ sp_status run(bool bwd, const void* q, const void* k, const void* v, const void*
     const bool small_call = dtype == SP_BF16 && (!bwd || (stages == SP_BWD_STAGE_ALL && sp::rowsum_fast_path(p))) &&
                             sp::use_small_call(p, L.words.size(), L.max_responses);
     sp::KeyPieces pieces;
-    if (pieces_fit && (stages & SP_BWD_STAGE_DKDV)) {
-        pieces = sp::plan_key_pieces(p, sp::piece_slots(L.total_tokens, n_groups, Hq, Hkv),
-                                     (size_t)sp::ARG_WORDS - (small_call ? L.words.size() : 0));
-        if (!pieces.words.empty()) { p.pieces = &pieces; p.piece_sums = (float*)((char*)workspace + pieces_off); }
+    sp::RowPieces row_pieces;
+    if (pieces_fit) {
+        const size_t list_words = (size_t)sp::ARG_WORDS - (small_call ? L.words.size() : 0);
+        p.piece_sums = (float*)((char*)workspace + pieces_off);
+        if (bwd && (stages & SP_BWD_STAGE_DKDV)) {
+            pieces = sp::plan_key_pieces(p, sp::piece_slots(L.total_tokens, n_groups, Hq, Hkv), list_words);
+            if (!pieces.words.empty()) p.pieces = &pieces;
+        }
+        if ((!bwd && !p.naive) || (bwd && (stages & SP_BWD_STAGE_DQ))) {
+            row_pieces = sp::plan_row_pieces(p, pieces_len / sp::ROW_SLOT_BYTES / Hkv, list_words);
+            if (!row_pieces.words.empty()) p.row_pieces = &row_pieces;
+        }
     }
     const int key_order = !p.pieces && ordered && (stages & SP_BWD_STAGE_DKDV) ? sp::key_order(p) : sp::KEYS_AS_PACKED;
     p.sched.key_tiles = p.sched.tiles128;

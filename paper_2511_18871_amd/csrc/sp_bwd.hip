@@ -52,10 +52,14 @@ struct BwdArgs {
     int head_split;      // row parts of a key tile: 0 (not split), 1 or 2
     float* partial;      // [2 (dK, dV)][rep][T_total][Hkv][128] fp32 of the first row part
     float* partial2;     // the same of the second
+    RowPieceArgs rows;   // dq pass with key loops in parts
     int pieces_at;       // dkdv pass in pieces: word of the table argument at which their list starts
     int n_slots;         // pieces of tiles with several parts
     float* piece_sums;   // [kv head][slot][dK, dV][128 keys][128]
 };
+
+static_assert(sizeof(TabArg) + sizeof(BwdArgs) + sizeof(EdgeArgs) + 8 <= 4096 && sizeof(RowSums) + sizeof(BwdArgs) <= 4096 &&
+              2 * PIECE_SLOTS * 4 + sizeof(BwdArgs) <= 4096, "kernel arguments");
 
 // ------------------------------------------------------------------------------------
 // dq pass
@@ -77,7 +81,7 @@ struct BwdArgs {
 // starts, reserve flag, q and dO, o and its residual, first keys), now two, and D by dot products of pairs (64 instructions for
 // 320).  With the forward's key tiles and addresses, us: 64 groups of a short prompt and 16 answers 2782 -> 2679, 64 groups of
 // 1000 tokens 981 -> 957, two small groups 20.6 -> 19.8, four long prompts 2442 -> 2434, 16K prompt 5192 -> 5225.
-template <int NW, bool SMALL>          // SMALL: as in the forward
+template <int NW, bool SMALL, bool PIECES>          // SMALL, PIECES: as in the forward
 __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(TabArg table, BwdArgs a, EdgeArgs edge, int short_blocks, int row_blocks) {
     constexpr int BM = 32 * NW, BN = 64;
     constexpr int RD = 3;                       // LDS operand ring depth (prefetch distance RD - 1 MFMAs)
@@ -108,6 +112,8 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(TabArg table, BwdArg
     }
     Item item;
     if (!decode_item(rb, a.items, item)) return;
+    RowPiece piece{item.tile, item.hr, 0, 1, 0};
+    if constexpr (PIECES) { piece = row_piece(table_of(table), a.rows, item); item.hr = piece.hr; item.tile = piece.tile; }
     TileDesc td;
     SmallGroup sg;
     if constexpr (SMALL) {
@@ -121,7 +127,7 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(TabArg table, BwdArg
     gd.tok_base = td.tok_base; gd.Lp = td.Lp; gd.Tg = td.Tg; gd.G = 0; gd.roff = nullptr;
     const int Lp = gd.Lp, Tg = gd.Tg;
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
-    const WaveRows wr = wave_rows<NW>(td, item, a.items.rep, w);
+    const WaveRows wr = wave_rows<NW>(td, item, PIECES ? a.rows.rep : a.items.rep, w);
     const int head = wr.head;
     const int t0 = wr.t0, t1 = wr.t1;
     const int64_t T_total = a.T_total;
@@ -210,7 +216,8 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(TabArg table, BwdArg
     };
     // the first keys under a prompt are known without a look at the rows' segments
     const int n1 = (min(Lp, t1) + BN - 1) / BN;
-    if (copier && n1 > 0) copy_keys(0, 0);
+    const bool early = n1 > 0 && (!PIECES || piece.part == 0);
+    if (copier && early) copy_keys(0, 0);
 
     // The wave's rows of q and dO (and of o and its residual for the folded rowsum) in MFMA operand layout.
     // Loaded straight from memory in that layout an instruction touches 32 rows and uses 32 bytes of each,
@@ -309,7 +316,7 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(TabArg table, BwdArg
         const bool idle = a.resp_only && t < Lp;
         if (!valid || idle) Dq = 0.f;
         Lq = valid && !idle ? lse_word * LOG2E : 0.f;
-        if (a.fused_rowsum && hh == 0) {
+        if (a.fused_rowsum && hh == 0 && (!PIECES || piece.part == 0)) {
             if (valid) a.L2[row_word] = Lq;
             if (valid && idle) a.nD[row_word] = 0.f;
             if (a.resp_only && (tw0 & 32) && tw0 <= Lp && Lp < tw0 + 32) {      // first half of those 64 rows: of another workgroup
@@ -330,8 +337,10 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(TabArg table, BwdArg
 
     // key tiles as in the forward: n1 from the group's first key on, then from k2 on
     const int k2 = max(n1 * BN, b2);
-    const int total = n1 + (t1 <= Lp ? 0 : max(t1 - k2 + BN - 1, 0) / BN);
-    auto key_at = [&](int it) { return it < n1 ? it * BN : k2 + (it - n1) * BN; };
+    const int tiles = n1 + (t1 <= Lp ? 0 : max(t1 - k2 + BN - 1, 0) / BN);
+    const int from = PIECES ? tiles * piece.part / piece.parts : 0;       // this workgroup's first tile, and how many it walks
+    const int total = (PIECES ? tiles * (piece.part + 1) / piece.parts : tiles) - from;
+    auto key_at = [&](int it) { return it + from < n1 ? (it + from) * BN : k2 + (it + from - n1) * BN; };
     // NW = 8: `it` counts 64-key tiles; NW = 4: halves of them (32 keys), each into a slot of its own.  The second half of a
     // group's last tile may lie wholly past the group's end: it is then read from the group's last row on
     auto issue = [&](int it, int slot) {
@@ -463,7 +472,7 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(TabArg table, BwdArg
 
     f32x16 SA, PA, SB, PB;
     if (total > 0) {
-        if (n1 == 0) {
+        if (!early) {
             issue(0, 0);
             wait_vm0();
             __syncthreads();
@@ -537,6 +546,16 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(TabArg table, BwdArg
     const bool store = valid && !(a.resp_only && t < Lp);
     // rows that see at most EDGE_LEN keys are written by the workgroups above (fp32 dS): not stored here
     const bool short_row = (t < Lp ? 0 : Lp) + t - st + 1 <= EDGE_LEN;
+    if constexpr (PIECES)
+        if (piece.parts > 1) {
+            float* const slot = a.rows.slots + ((int64_t)item.kvh * a.rows.n_slots + piece.slot) * (int64_t)(ROW_SLOT_BYTES / 4) + w * (ROW_SLOT_BYTES / 16);
+#pragma unroll
+            for (int n = 0; n < 16; ++n)
+                *reinterpret_cast<f32x4*>(slot + 128 * c + 32 * (n >> 2) + 8 * (n & 3) + 4 * hh) =
+                    f32x4{acc[n >> 2][4 * (n & 3)], acc[n >> 2][4 * (n & 3) + 1], acc[n >> 2][4 * (n & 3) + 2], acc[n >> 2][4 * (n & 3) + 3]};
+            if (hh == 0) *reinterpret_cast<f32x4*>(slot + 4096 + 4 * c) = f32x4{dsum, Dq, 0.f, store && !short_row ? 1.f : 0.f};
+            return;
+        }
     if (store && !short_row && hh == 0) a.nD[(int64_t)head * T_total + gd.tok_base + t] = -(Dq + dsum);
     // dQ leaves in whole rows: staged in the wave's share of the ring (every wave has left it), 16 lanes to a row, four rows
     // per instruction; stored from the accumulators an instruction touched 32 rows (64 groups of a short prompt and 16
@@ -568,6 +587,34 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(TabArg table, BwdArg
         for (int i = 0; i < 8; ++i)
             if ((keep >> (4 * i + (lz >> 4))) & 1) *reinterpret_cast<bf16x8*>(p0 + i * stride) = x[i];
     }
+}
+
+// Adds up the parts of an item's dQ (32 rows of one q head) and of what D lacks: a workgroup per item, 8 threads to a row, 16 columns each.
+__global__ __launch_bounds__(256) void dq_pieces_kernel(RowSums list, BwdArgs a) {
+    const RowItem it = row_item(list, a.rows);
+    const float* const slot = row_slot(a.rows, it);
+    const int r = threadIdx.x >> 3, d0 = 16 * (threadIdx.x & 7);
+    if (slot[4096 + 4 * r + 3] == 0.f) return;             // not a row to store
+    float dsum = 0.f, x[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) x[e] = 0.f;
+    for (int p = 0; p < it.parts; ++p) {
+        const float* const s = slot + p * (int64_t)(ROW_SLOT_BYTES / 4);
+        dsum += s[4096 + 4 * r];
+#pragma unroll
+        for (int n = 0; n < 4; ++n) {
+            const f32x4 y = *reinterpret_cast<const f32x4*>(s + 128 * r + d0 + 4 * n);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[4 * n + e] += y[e];
+        }
+    }
+    bf16x8 y[2];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) y[e >> 3][e & 7] = (__bf16)(x[e] * a.scale);
+    __bf16* const out = a.dq + ((int64_t)(it.tok + r) * a.Hq + it.head) * 128 + d0;
+    *reinterpret_cast<bf16x8*>(out) = y[0];
+    *reinterpret_cast<bf16x8*>(out + 8) = y[1];
+    if (d0 == 0) a.nD[(int64_t)it.head * a.T_total + it.tok + r] = -(slot[4096 + 4 * r + 1] + dsum);
 }
 
 // ------------------------------------------------------------------------------------
@@ -1316,6 +1363,32 @@ int dkdv_waves(const Problem& p) {
 // as prompts are short) 436 -> 132; 100 + 10 x 400, 4/2 117 -> 52; 2 x (560 + 27 x 840), 28/4 4757 -> 2552; 35 + 22 x 470,
 // 32/8 2121 -> 516; 1024 + 8 x 256, 28/4 182 -> 170 (sums of prompt tiles only); 650 + 4 x (9 x 84), 32/8 258 -> 234; on 52 drawn
 // packings of 1e8 to 2e11 operations 1.17 times as fast on average, on 18 larger ones 1.20, at worst 0.98.
+namespace {
+// When workgroups of `lens` steps and `fixed` more, `copies` of each, longest first, are through: each goes to the place that is free first.
+int play(std::vector<int>& lens, int places, int copies, int fixed, double* half = nullptr) {
+    std::sort(lens.begin(), lens.end(), std::greater<int>());
+    std::vector<int> at((size_t)places, 0);                    // a heap, the least on top
+    for (int n : lens)
+        for (int c = 0; c < copies; ++c) {
+            std::pop_heap(at.begin(), at.end(), std::greater<int>());
+            at.back() += n + fixed;
+            std::push_heap(at.begin(), at.end(), std::greater<int>());
+        }
+    const int end = *std::max_element(at.begin(), at.end());
+    if (half) {
+        std::nth_element(at.begin(), at.begin() + places / 2, at.end());
+        *half = at[(size_t)places / 2];
+    }
+    return end;
+}
+// CUs over which the workgroups of a kv head go, and kv heads that share them (ItemMap)
+void cus_of(const Problem& p, int& cus, int& copies) {
+    const bool by_xcd = p.Hkv % 8 == 0 || 8 % p.Hkv == 0;
+    cus = !by_xcd ? 256 : p.Hkv % 8 == 0 ? 32 : 32 * (8 / p.Hkv);
+    copies = !by_xcd ? p.Hkv : p.Hkv % 8 == 0 ? p.Hkv / 8 : 1;
+}
+}  // namespace
+
 KeyPieces plan_key_pieces(const Problem& p, int slots, size_t max_words) {
     // steps' worth of time: of a workgroup without steps, of storing partial sums, of the launch that adds them up
     constexpr int FIXED = 5, STORE = 2, SUM_STEPS = 3;
@@ -1352,22 +1425,11 @@ KeyPieces plan_key_pieces(const Problem& p, int slots, size_t max_words) {
             all += steps + FIXED;
         }
     }
-    const bool by_xcd = p.Hkv % 8 == 0 || 8 % p.Hkv == 0;
-    const int bins = !by_xcd ? 256 : p.Hkv % 8 == 0 ? 32 : 32 * (8 / p.Hkv), copies = !by_xcd ? p.Hkv : p.Hkv % 8 == 0 ? p.Hkv / 8 : 1;
+    int bins, copies;
+    cus_of(p, bins, copies);
     const double even = (double)copies * (double)all / bins;
     if (longest + FIXED <= 1.25 * even) return out;
-    // when workgroups of `lens` steps, longest first, are through: each goes to the CU that is free first
-    auto through = [&](std::vector<int>& lens) {
-        std::sort(lens.begin(), lens.end(), std::greater<int>());
-        std::vector<int> cu((size_t)bins, 0);                  // a heap, the least on top
-        for (int n : lens)
-            for (int c = 0; c < copies; ++c) {
-                std::pop_heap(cu.begin(), cu.end(), std::greater<int>());
-                cu.back() += n + FIXED;
-                std::push_heap(cu.begin(), cu.end(), std::greater<int>());
-            }
-        return *std::max_element(cu.begin(), cu.end());
-    };
+    auto through = [&](std::vector<int>& lens) { return play(lens, bins, copies, FIXED); };
     auto parts_of = [&](int steps, int len) { return steps <= len ? 1 : std::min((steps + len - 1) / len, 255); };
     std::vector<int> lens;
     auto cut = [&](int max_len, int each) {                    // (each: a tile's workgroups of equal share, whatever its length)
@@ -1410,6 +1472,109 @@ KeyPieces plan_key_pieces(const Problem& p, int slots, size_t max_words) {
     return out;
 }
 
+// Key loops of the forward and the dq pass in parts, planned in the same way for four-wave workgroups, two to a CU.  Few rows under
+// long prompts leave CUs without a workgroup, or a last round of workgroups that are half as many as the places.  Either all workgroups
+// longer than some length are cut into equal parts, or only those that no full round takes, whichever is through sooner; neither unless it
+// gains a twentieth and the launch that brings the sums together, which up to LEAST steps cannot be.  Forward and dq pass, us, whole -> in parts
+// (prompt x answers, response rows only, q / kv heads): 3 x (10500 + 17 x 40), 4/2 259 -> 66 and 310 -> 77; 2 x (2260 + 58), 28/4
+// 51 -> 26; 8192 + 16 x 160, 40/8 (760 workgroups in 512 places) 439 -> 400 and 568 -> 553; on 66 drawn packings forward and backward
+// 1.06 times as fast on average.  Two waves of one workgroup to an item, without a second launch, walked in step and took 13 to 30 % longer.
+RowPieces plan_row_pieces(const Problem& p, size_t slots, size_t max_words) {
+    // steps' worth of time: of a workgroup without steps, of storing sums, of the launch that brings them together
+    constexpr int FIXED = 4, STORE = 1, SUM_STEPS = 8, LEAST = 16;       // (up to LEAST steps there is nothing to gain)
+    RowPieces out;
+    const int rep = p.Hq / p.Hkv;
+    int places, copies;
+    cus_of(p, places, copies);
+    places *= 2;
+    if (p.n_tiles128 > ROW_PIECE_TILES || rep > 64 || (size_t)p.n_tiles128 * rep > max_words) return out;
+    struct Wg { int steps, word, tok, i; };
+    std::vector<Wg> wgs;
+    wgs.reserve((size_t)p.n_tiles128 * rep);
+    int longest = 0, tile = 0;
+    int64_t all = 0;
+    for (int g = 0; g < p.n_groups; ++g) {
+        const int32_t* e = p.host_table + TAB_HEADER + TAB_GROUP_WORDS * g;
+        const int Lp = e[1], Tg = e[2];
+        const int32_t* roff = p.host_table + e[3];
+        const int n = (Tg + 127) / 128;
+        for (int ti = 0; ti < n; ++ti, ++tile) {
+            const int base = (n - 1 - ti) * 128;               // as wave_rows()
+            for (int hr = 0; hr < rep; ++hr) {
+                const int i = rep - 1 - hr, t0 = base + 32 * (4 * i / rep), t1 = std::min(base + 32 * ((4 * i + 3) / rep) + 32, Tg);
+                if (t0 >= Tg || (p.resp_only && t1 <= Lp)) continue;
+                const int n1 = (std::min(Lp, t1) + 63) / 64;
+                int steps = n1;
+                if (t1 > Lp) {
+                    const int32_t* const after = std::upper_bound(roff, roff + e[4], std::max(t0, Lp));      // behind the row's segment start
+                    steps += std::max(t1 - std::max(n1 * 64, (int)after[-1]) + 63, 0) / 64;
+                }
+                wgs.push_back(Wg{steps, tile | hr << 10, e[0] + base, i});
+                longest = std::max(longest, steps);
+                all += steps + FIXED;
+            }
+        }
+    }
+    const double even = (double)copies * (double)all / places;
+    if (8 * longest < even || longest <= LEAST) return out;
+    std::sort(wgs.begin(), wgs.end(), [](const Wg& a, const Wg& b) { return a.steps != b.steps ? a.steps > b.steps : a.word < b.word; });
+    // the `whole` longest stay whole, others longer than `len` are cut
+    auto parts_of = [&](size_t n, int whole, int len) {
+        const int steps = wgs[n].steps;
+        return (int)n < whole || steps <= len ? 1 : std::min((steps + len - 1) / len, 255);
+    };
+    std::vector<int> lens;
+    auto end_of = [&](int whole, int len) {
+        lens.clear();
+        size_t n_slots = 0, n_sums = 0;
+        for (size_t n = 0; n < wgs.size(); ++n) {
+            const int parts = parts_of(n, whole, len);
+            if (parts > 1) { n_slots += parts; ++n_sums; }
+            if (n_slots > slots || n_sums > (size_t)ROW_SUMS || lens.size() + parts > max_words) return 1e30;
+            for (int i = 0; i < parts; ++i) lens.push_back((wgs[n].steps + parts - 1) / parts + (parts > 1 ? STORE : 0));
+        }
+        double half;               // when half of the places are empty: from then on workgroups are alone on their CUs, 1.44 times as fast
+        const double end = play(lens, places, copies, FIXED, &half);
+        return half + 0.69 * (end - half) + (n_slots ? SUM_STEPS : 0);
+    };
+    const int n_wgs = (int)wgs.size(), rounds = n_wgs - n_wgs % std::max(places / copies, 1);
+    double best = 0.95 * end_of(n_wgs, longest);
+    int whole = 0, len = 0;
+    for (const int w : {0, rounds}) {
+        if (w == n_wgs || (w == 0 && rounds == 0 && whole)) continue;
+        for (const int q : {2, 3, 4, 6, 8, 12, 16}) {
+            const int l = (wgs[w].steps + q - 1) / q;
+            if (l < 3) break;
+            const double end = end_of(w, l);
+            if (end < best) { best = 0.98 * end; whole = w; len = l; }
+        }
+        if (rounds == 0) break;
+    }
+    if (len == 0) return out;
+    // longest first, pieces next to one another
+    const int cut = (wgs[whole].steps + parts_of(whole, whole, len) - 1) / parts_of(whole, whole, len);
+    auto put = [&](auto which) {
+        for (size_t n = 0; n < wgs.size(); ++n) {
+            const int parts = parts_of(n, whole, len);
+            if (which(parts, wgs[n].steps))
+                for (int i = 0; i < parts; ++i) out.words.push_back((uint32_t)wgs[n].word | (uint32_t)i << 16 | (uint32_t)parts << 24);
+        }
+    };
+    put([&](int parts, int steps) { return parts == 1 && steps >= cut; });
+    out.first_slot = (int)out.words.size();
+    put([](int parts, int) { return parts > 1; });
+    put([&](int parts, int steps) { return parts == 1 && steps < cut; });
+    for (size_t n = 0; n < wgs.size(); ++n) {
+        const int parts = parts_of(n, whole, len);
+        if (parts == 1) continue;
+        out.sums.push_back((uint32_t)out.n_slots | (uint32_t)parts << 16);
+        out.sums.push_back((uint32_t)wgs[n].tok);
+        out.sums.push_back((uint32_t)wgs[n].i);
+        out.n_slots += parts;
+    }
+    return out;
+}
+
 hipError_t launch_bwd_bf16(const Problem& p, hipStream_t s) {
     hipError_t e = hipSuccess;
     // A call that runs both the rowsum and the dq stage folds the first into the second (the dq pass has
@@ -1430,17 +1595,22 @@ hipError_t launch_bwd_bf16(const Problem& p, hipStream_t s) {
     const TabArg table = small_table(p);
     if (p.stages & STAGE_DQ) {
         // short key loops: the four-wave shape, two workgroups per CU (the forward's rule, see bwd_dq_kernel)
-        const bool small = use_small_shape(p);
-        const int n_tiles = count_tiles(p, small ? 128 : 256), grid = grid_for_items(n_tiles, p.Hq, p.Hkv);
-        a.items = make_item_map(n_tiles, p.Hq, p.Hkv);
+        const RowPieces* const pieces = p.row_pieces;
+        const bool small = pieces || use_small_shape(p);
+        const int n_tiles = pieces ? (int)pieces->words.size() : count_tiles(p, small ? 128 : 256), per_kv = pieces ? p.Hkv : p.Hq;
+        const int grid = grid_for_items(n_tiles, per_kv, p.Hkv);
+        a.items = make_item_map(n_tiles, per_kv, p.Hkv);
+        if (pieces) a.rows = row_piece_args(p);
         const EdgeArgs edge = edge_args(p);
         const int shorts = (edge_blocks(edge, small ? 2 : 3) + 7) & ~7, total = grid + shorts;
         auto launch = [&](auto small_call) {
             constexpr bool S = decltype(small_call)::value;
-            if (small) hipLaunchKernelGGL((bwd_dq_kernel<4, S>), dim3(total), dim3(256), 0, s, table, a, edge, shorts, grid);
-            else hipLaunchKernelGGL((bwd_dq_kernel<8, S>), dim3(total), dim3(512), 0, s, table, a, edge, shorts, grid);
+            if (pieces) hipLaunchKernelGGL((bwd_dq_kernel<4, S, true>), dim3(total), dim3(256), 0, s, with_list(table, p, pieces->words), a, edge, shorts, grid);
+            else if (small) hipLaunchKernelGGL((bwd_dq_kernel<4, S, false>), dim3(total), dim3(256), 0, s, table, a, edge, shorts, grid);
+            else hipLaunchKernelGGL((bwd_dq_kernel<8, S, false>), dim3(total), dim3(512), 0, s, table, a, edge, shorts, grid);
         };
         if (p.small.on) launch(std::true_type{}); else launch(std::false_type{});
+        if (pieces) hipLaunchKernelGGL(dq_pieces_kernel, dim3((unsigned)(pieces->sums.size() / 3 * p.Hkv * 4)), dim3(256), 0, s, row_sums(*pieces), a);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -1449,9 +1619,7 @@ hipError_t launch_bwd_bf16(const Problem& p, hipStream_t s) {
             auto go = [&](auto small_call) {
                 constexpr bool S = decltype(small_call)::value;
                 if (p.pieces) {
-                    TabArg list = table;
-                    for (size_t i = 0; i < p.pieces->words.size(); ++i) list.words[a.pieces_at + i] = (int32_t)p.pieces->words[i];
-                    hipLaunchKernelGGL((bwd_dkdv_kernel<8, S, true>), dim3(grid), dim3(512), 0, s, list, a);
+                    hipLaunchKernelGGL((bwd_dkdv_kernel<8, S, true>), dim3(grid), dim3(512), 0, s, with_list(table, p, p.pieces->words), a);
                 } else if (waves == 8) hipLaunchKernelGGL((bwd_dkdv_kernel<8, S, false>), dim3(grid), dim3(512), 0, s, table, a);
                 else hipLaunchKernelGGL((bwd_dkdv_kernel<4, S, false>), dim3(grid), dim3(256), 0, s, table, a);
             };

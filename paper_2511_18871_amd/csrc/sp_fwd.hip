@@ -23,7 +23,6 @@ namespace {
 constexpr int BN = 64;                 // keys per LDS tile
 constexpr float P_LIMIT = 16384.0f;     // bound on a lane's per-tile sum of exponentials (2^14)
 constexpr int TILE_BYTES = BN * 256;   // 64 rows x 128 bf16
-constexpr float M_NONE = -1.0e30f;     // reference point of a row that has not seen a key yet (finite on purpose)
 
 struct FwdArgs {
     // one entry per tensor set; the sets share the packing, the schedule and the launch
@@ -34,11 +33,15 @@ struct FwdArgs {
     ItemMap items;
     int n_groups, T_total, Hq, Hkv;
     float c;        // softmax_scale * log2(e)
+    float m_none;   // reference point of a row that has not seen a key yet: finite, as is its product with c, -1e30 where float32 holds that
     int naive;
     int resp_only;  // compute and write response rows only
     SmallCall small;
+    RowPieceArgs pieces;
     __bf16* o_lo;   // optional (single-set launches): o_fp32 - bf16(o), rounded to bf16, same layout as o
 };
+
+static_assert(sizeof(TabArg) + sizeof(FwdArgs) <= 4096 && sizeof(RowSums) + sizeof(FwdArgs) <= 4096, "kernel arguments");
 
 // ------------------------------------------------------------------------------------
 // Hand-scheduled software-pipelined forward.  Step j of a wave holds the MFMAs of two tiles and
@@ -73,7 +76,8 @@ struct FwdArgs {
 // element): a separate instantiation, so that it shows under its own name in kernel traces and its
 // branches cost the product kernel nothing.
 // SMALL = a call whose kernels look everything up themselves (SmallCall); as a run-time branch it cost the others 0.5 to 1 %.
-template <int NW, bool NAIVE, bool SMALL>
+// PIECES = key loops in parts (RowPieces): a workgroup walks part of its key tiles and leaves unnormalised sums to fwd_pieces_kernel.
+template <int NW, bool NAIVE, bool SMALL, bool PIECES>
 __global__ __launch_bounds__(NW * 64, 2) void fwd_kernel(TabArg table, FwdArgs a) {      // two waves per SIMD in either shape
     constexpr int BM = 32 * NW;
     constexpr int NB = NW == 8 ? 4 : 2;            // K buffers = V buffers
@@ -91,6 +95,8 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd_kernel(TabArg table, FwdArgs a
         reserve_tag_body(a.small.tag, a.small.want, a.small.tag_mode, threadIdx.x);
     Item item;
     if (!decode_item(bid - set * bps, a.items, item)) return;
+    RowPiece piece{item.tile, item.hr, 0, 1, 0};
+    if constexpr (PIECES) { piece = row_piece(table_of(table), a.pieces, item); item.hr = piece.hr; item.tile = piece.tile; }
     // the tile's descriptor: one 32-byte load instead of a bisection over the groups and the group's entry
     TileDesc td;
     SmallGroup sg;
@@ -105,7 +111,7 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd_kernel(TabArg table, FwdArgs a
     gd.tok_base = td.tok_base; gd.Lp = td.Lp; gd.Tg = td.Tg; gd.G = 0; gd.roff = nullptr;
     const int Lp = gd.Lp, Tg = gd.Tg;
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
-    const WaveRows wr = wave_rows<NW>(td, item, a.items.rep, w);
+    const WaveRows wr = wave_rows<NW>(td, item, PIECES ? a.pieces.rep : a.items.rep, w);
     const int head = wr.head;
     const int t0 = wr.t0, t1 = wr.t1;
     const int T_total = a.T_total;
@@ -149,8 +155,10 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd_kernel(TabArg table, FwdArgs a
     // first response row's segment, unless the prompt's last tile holds it
     const int n1 = ((NAIVE ? t1 : min(Lp, t1)) + BN - 1) / BN;
     const int k2 = max(n1 * BN, b2);
-    const int total = n1 + (NAIVE || t1 <= Lp ? 0 : max(t1 - k2 + BN - 1, 0) / BN);
-    auto key_at = [&](int it) { return it < n1 ? it * BN : k2 + (it - n1) * BN; };
+    const int tiles = n1 + (NAIVE || t1 <= Lp ? 0 : max(t1 - k2 + BN - 1, 0) / BN);
+    const int from = PIECES ? tiles * piece.part / piece.parts : 0;       // this workgroup's first tile, and how many it walks
+    const int total = (PIECES ? tiles * (piece.part + 1) / piece.parts : tiles) - from;
+    auto key_at = [&](int it) { return it + from < n1 ? (it + from) * BN : k2 + (it + from - n1) * BN; };
 
     const int kvh = item.kvh;
     const int64_t kv_stride = (int64_t)a.Hkv * 128;
@@ -205,7 +213,7 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd_kernel(TabArg table, FwdArgs a
     // the first n_full tiles (whole prompt tiles at or below the wave's first row) never need it
     const int n_full = (!wave_valid || NAIVE) ? 0 : __builtin_amdgcn_readfirstlane(min(min(Lp, tw0 + 1) / BN, n1));
     auto needs_mask = [&](int it) -> bool {
-        if (it < n_full) return false;
+        if (it + from < n_full && (!PIECES || it < total)) return false;
         if (it >= total || !wave_valid || NAIVE) return true;
         const int s0 = key_at(it);
         return !((s0 + BN - 1 <= tw0) && (s0 + BN <= Lp || s0 >= st_last));
@@ -398,12 +406,12 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd_kernel(TabArg table, FwdArgs a
 #pragma unroll
         for (int e = 1; e < 32; ++e) mx = fmaxf(mx, sA[e >> 4][e & 15]);
         mx = pair_max(mx);
-        // A row that sees nothing in this tile (possible only without a prompt: a later response's
-        // rows against the first response's keys) starts from a finite sentinel far below any score:
+        // A row that sees nothing in this tile (without a prompt: a later response's rows against the first
+        // response's keys; PIECES: any row whose keys end ahead of the piece's) starts from a finite sentinel far below any score:
         // the first tile in which it does see a key then overflows the after-check and takes that
         // tile's exact maximum.  (Starting from 0 would let a row whose scores all lie below about
         // -126 / log2(e) underflow to a zero sum.)
-        m = (mx == -INFINITY) ? M_NONE : mx;
+        m = (mx == -INFINITY) ? a.m_none : mx;
     }
     int vlast = NB - 1;        // buffer of the last step's V tile
     if constexpr (NB == 4) {
@@ -484,6 +492,17 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd_kernel(TabArg table, FwdArgs a
     // LSE uses the unrounded sum.
     const float ltot = pair_sum(lsum);
     const float lrt = pair_sum(lsr);
+    const bool store = valid && !(a.resp_only && t < Lp);
+    if constexpr (PIECES)
+        if (piece.parts > 1) {
+            float* const slot = a.pieces.slots + ((int64_t)item.kvh * a.pieces.n_slots + piece.slot) * (int64_t)(ROW_SLOT_BYTES / 4) + w * (ROW_SLOT_BYTES / 16);
+#pragma unroll
+            for (int n = 0; n < 16; ++n)
+                *reinterpret_cast<f32x4*>(slot + 128 * c + 32 * (n >> 2) + 8 * (n & 3) + 4 * hh) =
+                    f32x4{oacc[n >> 2][4 * (n & 3)], oacc[n >> 2][4 * (n & 3) + 1], oacc[n >> 2][4 * (n & 3) + 2], oacc[n >> 2][4 * (n & 3) + 3]};
+            if (hh == 0) *reinterpret_cast<f32x4*>(slot + 4096 + 4 * c) = f32x4{m, ltot, lrt, store ? 1.f : 0.f};
+            return;
+        }
     // The K buffers are free from here on (every wave has passed the last barrier and only the last V buffer
     // is still read).  A lane holds 16 pieces of 8 bytes of its row; written to memory directly, one
     // store instruction would touch 32 rows.  Each wave therefore stages its own 32 rows x 256 B in
@@ -540,8 +559,49 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd_kernel(TabArg table, FwdArgs a
         }
         store_rows(a.o_lo, ob);
     }
-    if (valid && !(a.resp_only && t < Lp) && hh == 0)
+    if (store && hh == 0)
         alse[(int64_t)head * T_total + gd.tok_base + t] = (m * cs + __log2f(ltot)) * LN2;
+}
+
+// Brings the parts of an item's sums (32 rows of one q head) to one reference point, as a workgroup without parts ends: a workgroup per item, 8 threads to a
+// row, 16 columns each.
+__global__ __launch_bounds__(256) void fwd_pieces_kernel(RowSums list, FwdArgs a) {
+    const RowItem it = row_item(list, a.pieces);
+    const float* const slot = row_slot(a.pieces, it);
+    const int r = threadIdx.x >> 3, d0 = 16 * (threadIdx.x & 7);
+    float m = -INFINITY, l = 0.f, lr = 0.f, x[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) x[e] = 0.f;
+    if (slot[4096 + 4 * r + 3] == 0.f) return;             // not a row to store
+    for (int p = 0; p < it.parts; ++p) m = fmaxf(m, slot[p * (int64_t)(ROW_SLOT_BYTES / 4) + 4096 + 4 * r]);
+    for (int p = 0; p < it.parts; ++p) {
+        const float* const s = slot + p * (int64_t)(ROW_SLOT_BYTES / 4);
+        const f32x4 st = *reinterpret_cast<const f32x4*>(s + 4096 + 4 * r);
+        const float f = __builtin_amdgcn_exp2f((st[0] - m) * a.c);
+        l += st[1] * f;
+        lr += st[2] * f;
+#pragma unroll
+        for (int n = 0; n < 4; ++n) {
+            const f32x4 y = *reinterpret_cast<const f32x4*>(s + 128 * r + d0 + 4 * n);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[4 * n + e] += y[e] * f;
+        }
+    }
+    const float inv = 1.0f / lr;
+    const int64_t at = ((int64_t)(it.tok + r) * a.Hq + it.head) * 128 + d0;
+    bf16x8 o[2], lo[2];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+        x[e] *= inv;
+        o[e >> 3][e & 7] = (__bf16)x[e];
+        lo[e >> 3][e & 7] = (__bf16)(x[e] - (float)o[e >> 3][e & 7]);
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        *reinterpret_cast<bf16x8*>(a.o[0] + at + 8 * i) = o[i];
+        if (a.o_lo) *reinterpret_cast<bf16x8*>(a.o_lo + at + 8 * i) = lo[i];
+    }
+    if (d0 == 0) a.lse[0][(int64_t)it.head * a.T_total + it.tok + r] = (m * a.c + __log2f(l)) * LN2;
 }
 
 }  // namespace
@@ -557,24 +617,28 @@ hipError_t launch_fwd_bf16(const Problem& p, hipStream_t s) {
     }
     a.n_groups = p.n_groups; a.T_total = (int)p.total_tokens; a.sched = p.sched; a.small = p.small;
     const TabArg table = small_table(p);
-    a.Hq = p.Hq; a.Hkv = p.Hkv; a.c = p.scale * LOG2E; a.naive = p.naive; a.resp_only = p.resp_only;
+    a.Hq = p.Hq; a.Hkv = p.Hkv; a.c = p.scale * LOG2E; a.m_none = fmaxf(-1e30f / a.c, -3e38f); a.naive = p.naive; a.resp_only = p.resp_only;
     a.o_lo = n_sets == 1 ? (__bf16*)p.o_lo_out : nullptr;
     // Short key loops: the four-wave shape, two workgroups per CU (see fwd_kernel).  The naive baseline keeps
     // the eight-wave shape whatever the packing (its loops are long by construction).
-    const bool small = !p.naive && use_small_shape(p);
+    const RowPieces* const pieces = p.row_pieces;
+    const bool small = !p.naive && (pieces || use_small_shape(p));
     const int bm = small ? 128 : 256;
-    const int n_tiles = count_tiles(p, bm);
-    a.items = make_item_map(n_tiles, p.Hq, p.Hkv);
-    a.blocks_per_set = grid_for_items(n_tiles, p.Hq, p.Hkv);
+    const int n_tiles = pieces ? (int)pieces->words.size() : count_tiles(p, bm), per_kv = pieces ? p.Hkv : p.Hq;
+    a.items = make_item_map(n_tiles, per_kv, p.Hkv);
+    a.blocks_per_set = grid_for_items(n_tiles, per_kv, p.Hkv);
+    if (pieces) a.pieces = row_piece_args(p);
     if (a.blocks_per_set % 8 != 0) a.blocks_per_set += 8 - a.blocks_per_set % 8;
     const dim3 grid(a.blocks_per_set * n_sets);
     auto launch = [&](auto small_call) {
         constexpr bool S = decltype(small_call)::value;
-        if (p.naive) hipLaunchKernelGGL((fwd_kernel<8, true, S>), grid, dim3(512), 0, s, table, a);
-        else if (small) hipLaunchKernelGGL((fwd_kernel<4, false, S>), grid, dim3(256), 0, s, table, a);
-        else hipLaunchKernelGGL((fwd_kernel<8, false, S>), grid, dim3(512), 0, s, table, a);
+        if (p.naive) hipLaunchKernelGGL((fwd_kernel<8, true, S, false>), grid, dim3(512), 0, s, table, a);
+        else if (pieces) hipLaunchKernelGGL((fwd_kernel<4, false, S, true>), grid, dim3(256), 0, s, with_list(table, p, pieces->words), a);
+        else if (small) hipLaunchKernelGGL((fwd_kernel<4, false, S, false>), grid, dim3(256), 0, s, table, a);
+        else hipLaunchKernelGGL((fwd_kernel<8, false, S, false>), grid, dim3(512), 0, s, table, a);
     };
     if (p.small.on) launch(std::true_type{}); else launch(std::false_type{});
+    if (pieces) hipLaunchKernelGGL(fwd_pieces_kernel, dim3((unsigned)(pieces->sums.size() / 3 * p.Hkv * 4)), dim3(256), 0, s, row_sums(*pieces), a);
     return hipGetLastError();
 }
 

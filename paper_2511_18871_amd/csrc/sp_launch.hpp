@@ -135,7 +135,8 @@ struct Problem {
     int accumulate;                                       // backward: dk, dv += instead of =
     int dkdv_parts;                                       // row parts of a key tile in the head-split pass
     const struct KeyPieces* pieces;                       // bf16 backward: the dkdv pass in pieces of key tiles (null: not)
-    float* piece_sums;                                    // their partial sums
+    const struct RowPieces* row_pieces;                   // the forward and the dq pass with key loops in parts (null: not)
+    float* piece_sums;                                    // the partial sums of either
     float* dkdv_partial;                                  // bf16 backward on small problems: fp32 per-q-head partials
     float* dkdv_partial2;                                 // the second row part's
     // host copies of the per-group token counts and of the whole segment table, for grid sizing and
@@ -304,6 +305,49 @@ inline size_t piece_bytes(int64_t total_tokens, int n_groups, int Hq, int Hkv) {
 }
 // the pieces of a call (none where whole key tiles are as good), at most `slots` with partial sums
 KeyPieces plan_key_pieces(const Problem& p, int slots, size_t max_words);
+
+// Key loops of the forward and the dq pass in parts: of the packings that use it, both take a list of (tile of 128 rows, workgroup of the tile,
+// part of its key tiles) from the kernel arguments behind the table, one of four-wave workgroups, longest first.  Workgroups with
+// several parts leave unnormalised float32 sums in slots, in the order of the list, where they lie next to one another from first_slot on, and a second
+// launch brings them together.  word: tile | workgroup << 10 | part << 16 | parts << 24; sums: three words for each such
+// workgroup, its first slot | parts << 16, the packed token of its tile's first row, and its number within the tile, counted from the first rows.
+constexpr int ROW_PIECE_TILES = 1024, ROW_SUMS = 240;     // most tiles (and 64 q heads per kv head); most workgroups with parts, per kv head
+constexpr size_t ROW_SLOT_BYTES = 4 * (32 * 128 + 32 * 4) * 4;        // four items: 32 rows of 128 columns, four numbers per row
+struct RowPieces { std::vector<uint32_t> words, sums; int first_slot = 0, n_slots = 0; };
+struct RowSums { uint32_t w[3 * ROW_SUMS]; };
+struct RowPieceArgs { int at, first_slot, n_slots; float* slots; Div rep, kv_heads; };      // at: word of the table argument at which the list starts
+struct RowPiece { int tile, hr, part, parts, slot; };
+__device__ __forceinline__ RowPiece row_piece(const int* tab, const RowPieceArgs& a, const Item& it) {
+    const unsigned w = (unsigned)tab[a.at + it.tile];
+    return RowPiece{(int)(w & 1023), (int)(w >> 10 & 63), (int)(w >> 16 & 255), (int)(w >> 24), it.tile - a.first_slot};
+}
+struct RowItem { int first, parts, kvh, w, tok, head; };
+__device__ __forceinline__ RowItem row_item(const RowSums& list, const RowPieceArgs& a) {
+    unsigned kvh, h;
+    const unsigned n = divmod(blockIdx.x >> 2, a.kv_heads, kvh);
+    RowItem it{(int)(list.w[3 * n] & 0xffff), (int)(list.w[3 * n] >> 16), (int)kvh, (int)(blockIdx.x & 3), 0, 0};
+    it.tok = (int)list.w[3 * n + 1] + 32 * (int)divmod(4 * list.w[3 * n + 2] + it.w, a.rep, h);       // as wave_rows()
+    it.head = (int)(kvh * a.rep.d + h);
+    return it;
+}
+__device__ __forceinline__ const float* row_slot(const RowPieceArgs& a, const RowItem& it) {
+    return a.slots + ((int64_t)it.kvh * a.n_slots + it.first) * (int64_t)(ROW_SLOT_BYTES / 4) + it.w * (int)(ROW_SLOT_BYTES / 16);
+}
+RowPieces plan_row_pieces(const Problem& p, size_t slots, size_t max_words);
+inline RowPieceArgs row_piece_args(const Problem& p) {
+    return RowPieceArgs{p.small.on ? p.host_table[2] : 0, p.row_pieces->first_slot, p.row_pieces->n_slots, p.piece_sums, make_div(p.Hq / p.Hkv), make_div(p.Hkv)};
+}
+inline RowSums row_sums(const RowPieces& r) {
+    RowSums s{};
+    for (size_t i = 0; i < r.sums.size(); ++i) s.w[i] = r.sums[i];
+    return s;
+}
+// the table argument with a list behind the table
+inline TabArg with_list(TabArg t, const Problem& p, const std::vector<uint32_t>& list) {
+    const size_t at = p.small.on ? (size_t)p.host_table[2] : 0;
+    for (size_t i = 0; i < list.size(); ++i) t.words[at + i] = (int32_t)list[i];
+    return t;
+}
 
 // Waves per workgroup (8 or 4) of a dkdv pass that is not split over the q heads (rule and reasons: sp_bwd.hip).
 int dkdv_waves(const Problem& p);

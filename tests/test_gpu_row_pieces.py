@@ -1,0 +1,112 @@
+"""The forward and the dq pass with key loops in parts: few rows under long prompts, response rows only and all rows, ragged ends of
+keys, rows that see no key of a part, all ways in which kv heads fall onto the chip; the gradients of stages and of a second call bit for
+bit, and what a workspace without the room gives."""
+import pytest
+import torch
+
+from paper_2511_18871_amd import binding as B
+from paper_2511_18871_amd import workloads as W
+from parity import gate, gate_lse, oracle_bwd, to64
+
+pytestmark = pytest.mark.gpu
+
+PACKS = {
+    "two_prompts": [W.Group(1400, [20, 5, 0, 33]), W.Group(1089, [1, 70])],
+    "prompt_alone": [W.Group(1601, [])],
+    "long_response": [W.Group(3, [1500]), W.Group(40, [30])],
+    "no_prompt": [W.Group(0, [64, 1300, 40])],
+}
+
+
+def _setup(name, heads, seed, resp_only=False):
+    w = W.Workload(name, PACKS[name], *heads, 128, torch.bfloat16, seed)
+    t = W.make_tensors(w)
+    resp, at = torch.ones(w.total_tokens, dtype=torch.bool), 0
+    for g in w.groups:
+        resp[at:at + g.prompt_len] = False
+        at += g.total
+    if resp_only:
+        t.d_o[~resp] = 0
+    return w, t, resp, (w.prompt_lens(), w.Gs(), w.resp_lens_flat(), w.softmax_scale)
+
+
+@pytest.mark.parametrize("heads", [(4, 2), (28, 4), (8, 8), (6, 3), (8, 1)])
+@pytest.mark.parametrize("name", list(PACKS))
+def test_all_rows(name, heads):
+    w, t, _, pk = _setup(name, heads, 790)
+    q, k, v, d_o = t.q.cuda(), t.k.cuda(), t.v.cuda(), t.d_o.cuda()
+    o, lse = B.sp_attn_fwd_batched(q, k, v, *pk)
+    nan = lambda: [torch.full_like(x, float("nan")) for x in (q, k, v)]
+    one, again, staged = nan(), nan(), nan()
+    B.sp_attn_bwd_batched_ex(q, k, v, o, lse, d_o, *pk, 0, *one)
+    B.sp_attn_bwd_batched_ex(q, k, v, o, lse, d_o, *pk, 0, *again)
+    for stage in (1, 4, 2):
+        B.sp_attn_bwd_batched_ex(q, k, v, o, lse, d_o, *pk, 0, *staged, stages=stage)
+    torch.cuda.synchronize()
+    for x, y, z in zip(one, again, staged):
+        assert torch.equal(x, y) and torch.equal(x, z)
+    *grads, ro, rlse = oracle_bwd(w, t)
+    gate("O", to64(o), ro, w.dtype)
+    gate_lse(to64(lse), rlse, w.dtype)
+    for what, got, ref in zip(("dQ", "dK", "dV"), one, grads):
+        gate(what, to64(got), ref, w.dtype)
+
+
+@pytest.mark.parametrize("heads", [(4, 2), (8, 8), (28, 4)])
+@pytest.mark.parametrize("name", ["two_prompts", "long_response"])
+def test_response_rows_only(name, heads):
+    w, t, resp, pk = _setup(name, heads, 791, True)
+    q, k, v, d_o = t.q.cuda(), t.k.cuda(), t.v.cuda(), t.d_o.cuda()
+    fl = B.SP_FLAG_RESPONSE_ROWS
+    o, lse = B.sp_attn_fwd_batched_ex(q, k, v, *pk, fl, o=torch.full_like(q, 7.0), lse=torch.full((heads[0], w.total_tokens), 7.0, device="cuda"))
+    dq, dk, dv = B.sp_attn_bwd_batched_ex(q, k, v, o, lse, d_o, *pk, fl, dq=torch.full_like(q, 7.0))
+    torch.cuda.synchronize()
+    rdq, rdk, rdv, ro, rlse = oracle_bwd(w, t)
+    idle = ~resp.cuda()
+    assert (o[idle] == 7).all() and (lse[:, idle] == 7).all() and (dq[idle] == 7).all()
+    gate("O", to64(o)[resp], ro[resp], w.dtype)
+    gate_lse(to64(lse)[:, resp], rlse[:, resp], w.dtype)
+    gate("dQ", to64(dq)[resp], rdq[resp], w.dtype)
+    gate("dK", to64(dk), rdk, w.dtype)
+    gate("dV", to64(dv), rdv, w.dtype)
+
+
+@pytest.mark.parametrize("name", ["two_prompts", "long_response", "no_prompt"])
+def test_sums_stay_in_their_room(name):
+    heads = (4, 2)
+    w, t, _, pk = _setup(name, heads, 792)
+    q, k, v = t.q.cuda(), t.k.cuda(), t.v.cuda()
+    n, r, T = len(w.groups), len(pk[2]), w.total_tokens
+    behind = (B.workspace_bytes(True, T, n, r, *heads, 128, B.SP_BF16) + B.reserve_bytes(T, heads[0], 128, B.SP_BF16)
+              + B.row_parts_bytes(T, n, *heads, B.SP_BF16))
+    full = B.full_workspace_bytes(T, n, r, *heads, 128, B.SP_BF16)
+    ws = torch.full((full + 4096,), 255, dtype=torch.uint8, device="cuda")
+    o, lse = B.sp_attn_fwd_batched(q, k, v, *pk, workspace=ws[:full])
+    torch.cuda.synchronize()
+    assert (ws[behind:full] != 255).any() and (ws[full:] == 255).all()
+    ws[:] = 255
+    whole, wlse = B.sp_attn_fwd_batched(q, k, v, *pk, workspace=ws[:full - 1])
+    torch.cuda.synchronize()
+    assert (ws[behind:] == 255).all()
+    assert float((o.float() - whole.float()).norm() / whole.float().norm()) < 4e-3      # weights rounded to bf16 against other references
+    assert float((lse - wlse).abs().max()) < 2e-5
+
+
+@pytest.mark.parametrize("log2_scale", [-118, 100])
+@pytest.mark.parametrize("name", ["two_prompts", "no_prompt"])
+def test_extreme_scales(name, log2_scale):
+    """Rows that see no key of a part start from a reference point that stays finite, times the scale too (as test_gpu_scales.py)."""
+    w, t, _, pk = _setup(name, (4, 2), 793)
+    e = -3 - log2_scale
+    fq, fk = 2.0 ** (e // 2), 2.0 ** (e - e // 2)
+    q, k, v, d_o = (t.q * fq).cuda(), (t.k * fk).cuda(), t.v.cuda(), t.d_o.cuda()
+    o, lse = B.sp_attn_fwd_batched(q, k, v, *pk[:3], 2.0 ** log2_scale)
+    dq, dk, dv = B.sp_attn_bwd_batched(q, k, v, o, lse, d_o, *pk[:3], 2.0 ** log2_scale)
+    torch.cuda.synchronize()
+    w.scale = 2.0 ** -3
+    rdq, rdk, rdv, ro, rlse = oracle_bwd(w, t)
+    gate("O", to64(o), ro, w.dtype)
+    gate_lse(to64(lse), rlse, w.dtype)
+    gate("dQ", to64(dq) * fq, rdq, w.dtype)
+    gate("dK", to64(dk) * fk, rdk, w.dtype)
+    gate("dV", to64(dv), rdv, w.dtype)
