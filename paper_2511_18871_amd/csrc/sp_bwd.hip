@@ -398,12 +398,12 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(TabArg table, BwdArg
                 asm volatile("" : "+v"(trA[db][part]));
             }
     }
-    // operand of slice i of a stage: 0..15 those of M, K rows then V rows; 16..23 those of D, slice 16 + i of D: db = i / 2,
-    // 16-key step i % 2 (read transposed).  They pass through one ring of RD registers, read RD - 1 slices ahead.
+    // operand of slice i of a stage: 0..15 those of M, K rows then V rows; 16..23 those of D, slice 16 + i of D: db = i % 4,
+    // 16-key step i / 4 (read transposed; four MFMAs in a row share their operand of dS, as in the forward).  They pass through one ring of RD registers, read RD - 1 slices ahead.
     auto fetch = [&](int atM, int atD, int i) -> bf16x8 {
         if (i < 16) return lds_at_row8(rowA[i & 7] + atM + ((i & 8) ? V_OFF : 0));
-        const int n = i - 16, at = atD + 4096 * (n & 1);
-        return cat4(lds_at_tr4(trA[n >> 1][0] + at), lds_at_tr4(trA[n >> 1][1] + at));
+        const int n = i - 16, at = atD + 4096 * (n >> 2);
+        return cat4(lds_at_tr4(trA[n & 3][0] + at), lds_at_tr4(trA[n & 3][1] + at));
     };
     bf16x8 ring[RD];
     auto pack2 = [&](float x, float y) -> unsigned {
@@ -460,7 +460,7 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_kernel(TabArg table, BwdArg
         for (int i = 0; i < 8; ++i) {
             if (i + RD - 1 < 8) ring[(16 + i + RD - 1 + OFF) % RD] = fetch(atM, atD, 16 + i + RD - 1);
             else if (NEXT >= 0) ring[(16 + i + RD - 1 + OFF) % RD] = fetch(NEXT, 0, i + RD - 1 - 8);
-            acc[i >> 1] = mfma32(ring[(16 + i + OFF) % RD], db8[i & 1], acc[i >> 1]);
+            acc[i & 3] = mfma32(ring[(16 + i + OFF) % RD], db8[i >> 2], acc[i & 3]);
             float tcur = 0.f;
             if (i < NE1) { tcur = v_issue(Sn, i); asm volatile("" : "+v"(tcur)); }
             if (i >= 1 && i - 1 < NE1) v_consume(Sn, Pn, i - 1, tprev);
