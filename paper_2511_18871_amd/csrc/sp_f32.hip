@@ -1,8 +1,8 @@
-// float32 plain-ALU debug path of shared-prompt attention, the segment-table upload
+// float32 path of shared-prompt attention, the segment-table upload
 // and the backward preprocess D = rowsum(dO * O).
 //
-// The debug kernels give one wavefront, or the eight of a workgroup, a single (row, head) or (key, kv head) and walk
-// the allowed keys / rows of the Section 4.3 mask in chunks.  No MFMA: they exist to cross-check the MFMA path and to serve float32 callers.
+// These kernels give the eight wavefronts of a workgroup a single (row, head) or (key, kv head), or 16 of them, and walk
+// the allowed keys / rows of the Section 4.3 mask in chunks, in float32 throughout: they exist to cross-check the bf16 path and to serve float32 callers.
 #include "sp_common.hpp"
 #include "sp_launch.hpp"
 #include <type_traits>
@@ -230,13 +230,12 @@ __global__ __launch_bounds__(256) void rowsum_bf16_kernel(const __bf16* __restri
     }
 }
 
-// The float32 kernels are bound by latency, not by arithmetic: a wave takes keys (rows) in chunks, and per chunk it needs one
-// batch of loads for the scores and one (rows 32 at a time, lanes along a row) for the sums.  Two shapes:
-//   WIDE, where there are few (row, head) or (key, kv head): a workgroup of eight waves per one of them, every wave takes
-//     each eighth chunk of 32 keys, two lanes per key.  The waves' sums meet in LDS, in a fixed order.
-//   else a wave per one of them and chunks of 64 keys, a lane per key, the wave's own row in scalar registers.
+// Few rows (keys): a workgroup of eight waves per (row, head) or (key, kv head), bound by latency: every wave takes each eighth chunk
+// of 32 keys, two lanes per key, with one batch of loads for the scores and one (rows 32 at a time, lanes along a row) for
+// the sums.  The waves' sums meet in LDS, in a fixed order.  (WIDE; else one wave and chunks of 64 keys, a lane per key, the wave's
+// own row in scalar registers: for single rows of the blocks below.)
 // With the rowsum within the dq kernel and the table as an argument, a training pass of 64 + 4 x 32 tokens, 2 heads of 64: 54.0 ->
-// 33.0 us; 300 + 5 x 100, 4 / 2 heads of 64: 321 -> 222.
+// 33.0 us.
 constexpr int F32_WAVES = 8;
 template <bool WIDE> constexpr int CHUNK = WIDE ? 32 : 64;
 template <bool WIDE> constexpr int F32_BLOCK = WIDE ? 64 * F32_WAVES : 256;
@@ -318,19 +317,13 @@ struct KeyChunks {
     __device__ __forceinline__ int count(int i) const { return min(C, (i < n1 ? end1 : end) - first(i)); }
 };
 
+// One row of one head: by one wave, or (WIDE) by the workgroup's eight
 template <int DH, bool WIDE>
-__global__ __launch_bounds__(F32_BLOCK<WIDE>) void fwd_f32_kernel(TabArg table, const float* __restrict__ q, const float* __restrict__ k,
-                                                                 const float* __restrict__ v, float* __restrict__ o,
-                                                                 float* __restrict__ lse, int64_t T_total, int Hq, int Hkv,
-                                                                 float scale, int resp_only) {
+__device__ __forceinline__ void fwd_f32_row(const GroupDesc& gd, int tok, int h, int w, int l, const float* __restrict__ q, const float* __restrict__ k,
+                                            const float* __restrict__ v, float* __restrict__ o, float* __restrict__ lse, int64_t T_total,
+                                            int Hq, int Hkv, float scale, int resp_only) {
     constexpr int PER = DH / 64;
     __shared__ float sh_m[F32_WAVES], sh_l[F32_WAVES], sh_acc[WIDE ? F32_WAVES : 1][DH];
-    const int* const tab = table_of(table);
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
-    const int64_t item = WIDE ? blockIdx.x : (int64_t)blockIdx.x * 4 + w;
-    if (item >= T_total * Hq) return;
-    const int tok = (int)(item / Hq), h = (int)(item % Hq);
-    const GroupDesc gd = load_group(tab, find_group_of_token(tab, tok));
     const int t = tok - gd.tok_base;
     if (resp_only && t < gd.Lp) return;
     constexpr int C = CHUNK<WIDE>;
@@ -389,24 +382,27 @@ __global__ __launch_bounds__(F32_BLOCK<WIDE>) void fwd_f32_kernel(TabArg table, 
     if (threadIdx.x == 0) lse[(int64_t)h * T_total + tok] = mt + logf(ls);
 }
 
+template <int DH>
+__global__ __launch_bounds__(F32_BLOCK<true>) void fwd_f32_kernel(TabArg table, const float* __restrict__ q, const float* __restrict__ k,
+                                                                 const float* __restrict__ v, float* __restrict__ o,
+                                                                 float* __restrict__ lse, int64_t T_total, int Hq, int Hkv,
+                                                                 float scale, int resp_only) {
+    const int* const tab = table_of(table);
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
+    const int tok = (int)(blockIdx.x / (unsigned)Hq), h = (int)(blockIdx.x % (unsigned)Hq);
+    fwd_f32_row<DH, true>(load_group(tab, find_group_of_token(tab, tok)), tok, h, w, l, q, k, v, o, lse, T_total, Hq, Hkv, scale, resp_only);
+}
+
 // dQ[t,h] = scale * sum_s dS[t,s] K[s],  dS = P * (dP - D)
 // `o` (a call that runs the rowsum stage too): D is formed here, with the arithmetic of rowsum_kernel, and written for the
 // dkdv kernel.  `tag`: cleared (a call without a preparation launch).
 template <int DH, bool WIDE>
-__global__ __launch_bounds__(F32_BLOCK<WIDE>, WIDE && DH == 64 ? 4 : 1) void bwd_dq_f32_kernel(TabArg table, const float* __restrict__ q, const float* __restrict__ k,
-                                                                    const float* __restrict__ v, const float* __restrict__ d_o,
-                                                                    const float* __restrict__ o, const float* __restrict__ lse,
-                                                                    float* __restrict__ D, float* __restrict__ dq, uint32_t* __restrict__ tag,
-                                                                    int64_t T_total, int Hq, int Hkv, float scale, int resp_only) {
+__device__ __forceinline__ void dq_f32_row(const GroupDesc& gd, int tok, int h, int w, int l, const float* __restrict__ q, const float* __restrict__ k,
+                                           const float* __restrict__ v, const float* __restrict__ d_o, const float* __restrict__ o,
+                                           const float* __restrict__ lse, float* __restrict__ D, float* __restrict__ dq,
+                                           int64_t T_total, int Hq, int Hkv, float scale, int resp_only) {
     constexpr int PER = DH / 64;
     __shared__ float sh_acc[WIDE ? F32_WAVES : 1][DH];
-    const int* const tab = table_of(table);
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
-    const int64_t item = WIDE ? blockIdx.x : (int64_t)blockIdx.x * 4 + w;
-    if (item >= T_total * Hq) return;
-    const int tok = (int)(item / Hq), h = (int)(item % Hq);
-    if (tag && blockIdx.x == 0 && w == 0) tag[l] = 0u;
-    const GroupDesc gd = load_group(tab, find_group_of_token(tab, tok));
     const int t = tok - gd.tok_base;
     if (resp_only && t < gd.Lp) return;
     constexpr int C = CHUNK<WIDE>;
@@ -455,25 +451,30 @@ __global__ __launch_bounds__(F32_BLOCK<WIDE>, WIDE && DH == 64 ? 4 : 1) void bwd
     dq[row * DH + threadIdx.x] = scale * x;
 }
 
+template <int DH>
+__global__ __launch_bounds__(F32_BLOCK<true>, DH == 64 ? 4 : 1) void bwd_dq_f32_kernel(TabArg table, const float* __restrict__ q, const float* __restrict__ k,
+                                                                    const float* __restrict__ v, const float* __restrict__ d_o,
+                                                                    const float* __restrict__ o, const float* __restrict__ lse,
+                                                                    float* __restrict__ D, float* __restrict__ dq, uint32_t* __restrict__ tag,
+                                                                    int64_t T_total, int Hq, int Hkv, float scale, int resp_only) {
+    const int* const tab = table_of(table);
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
+    const int tok = (int)(blockIdx.x / (unsigned)Hq), h = (int)(blockIdx.x % (unsigned)Hq);
+    if (tag && blockIdx.x == 0 && w == 0) tag[l] = 0u;
+    dq_f32_row<DH, true>(load_group(tab, find_group_of_token(tab, tok)), tok, h, w, l, q, k, v, d_o, o, lse, D, dq, T_total, Hq, Hkv, scale, resp_only);
+}
+
 // dK[s,g] = scale * sum_{h in g} sum_t dS[t,s] Q[t,h];  dV[s,g] = sum_{h in g} sum_t P[t,s] dO[t,h].
 // The rows that see key s are contiguous: [s, Tg) for a prompt key (later prompt rows and
 // every row of every response), [s, end of its response) otherwise.
 template <int DH, bool WIDE>
-__global__ __launch_bounds__(F32_BLOCK<WIDE>) void bwd_dkdv_f32_kernel(TabArg table, const float* __restrict__ q, const float* __restrict__ k,
-                                                                      const float* __restrict__ v, const float* __restrict__ d_o,
-                                                                      const float* __restrict__ lse, const float* __restrict__ D,
-                                                                      float* __restrict__ dk, float* __restrict__ dv,
-                                                                      int64_t T_total, int Hq, int Hkv, float scale,
-                                                                      int resp_only, int accumulate) {
+__device__ __forceinline__ void dkdv_f32_key(const GroupDesc& gd, int tok, int kvh, int w, int l, const float* __restrict__ q, const float* __restrict__ k,
+                                             const float* __restrict__ v, const float* __restrict__ d_o, const float* __restrict__ lse,
+                                             const float* __restrict__ D, float* __restrict__ dk, float* __restrict__ dv,
+                                             int64_t T_total, int Hq, int Hkv, float scale, int resp_only, int accumulate) {
     constexpr int PER = DH / 64;
     __shared__ float sh_acc[2][WIDE ? F32_WAVES : 1][DH];
     constexpr int C = CHUNK<WIDE>;
-    const int* const tab = table_of(table);
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
-    const int64_t item = WIDE ? blockIdx.x : (int64_t)blockIdx.x * 4 + w;
-    if (item >= T_total * Hkv) return;
-    const int tok = (int)(item / Hkv), kvh = (int)(item % Hkv);
-    const GroupDesc gd = load_group(tab, find_group_of_token(tab, tok));
     const int s = tok - gd.tok_base;
     const int row_end = s < gd.Lp ? gd.Tg : seg_end(gd, s), row_lo = resp_only ? max(s, gd.Lp) : s;
     const int rep = Hq / Hkv, n = (row_end - row_lo + C - 1) / C;
@@ -520,6 +521,365 @@ __global__ __launch_bounds__(F32_BLOCK<WIDE>) void bwd_dkdv_f32_kernel(TabArg ta
         float* const out = (which == 0 ? dk : dv) + ((int64_t)tok * Hkv + kvh) * DH + e;
         *out = (which == 0 ? scale * x : x) + (accumulate ? *out : 0.f);
     }
+}
+
+template <int DH>
+__global__ __launch_bounds__(F32_BLOCK<true>) void bwd_dkdv_f32_kernel(TabArg table, const float* __restrict__ q, const float* __restrict__ k,
+                                                                      const float* __restrict__ v, const float* __restrict__ d_o,
+                                                                      const float* __restrict__ lse, const float* __restrict__ D,
+                                                                      float* __restrict__ dk, float* __restrict__ dv,
+                                                                      int64_t T_total, int Hq, int Hkv, float scale,
+                                                                      int resp_only, int accumulate) {
+    const int* const tab = table_of(table);
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
+    const int tok = (int)(blockIdx.x / (unsigned)Hkv), kvh = (int)(blockIdx.x % (unsigned)Hkv);
+    dkdv_f32_key<DH, true>(load_group(tab, find_group_of_token(tab, tok)), tok, kvh, w, l, q, k, v, d_o, lse, D, dk, dv, T_total, Hq, Hkv, scale,
+                           resp_only, accumulate);
+}
+
+// ------------------------------------------------------------------------------------
+// Matrix instructions: 16 rows (keys) to a workgroup of eight waves, each of which takes every eighth chunk of 64 keys (rows).
+// ------------------------------------------------------------------------------------
+// A row per wave read every key's row for itself: L2 traffic bound, 1 MB for a row of 1000 keys.  v_mfma_f32_16x16x4_f32 multiplies in
+// float32 and takes operands straight from the rows: lane (i, g) = (l % 16, l / 16) holds elements 16 j + 4 g + e of row i, and the sums
+// of 16 x 16 tiles, element 4 g + e of column i, are the operand of the product that follows (of key 4 g + e, row i).
+// Where a masked key or row holds an infinity, its weight 0 makes a NaN of the sums; a row with a NaN is computed again by
+// itself, which takes no masked key.
+constexpr int BLK = 16;
+__device__ __forceinline__ f32x4 mfma16(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+template <int DH>
+__device__ __forceinline__ void row16(const float* __restrict__ p, int g, f32x4 (&x)[DH / 16]) {
+#pragma unroll
+    for (int j = 0; j < DH / 16; ++j) x[j] = *reinterpret_cast<const f32x4*>(p + 16 * j + 4 * g);
+}
+// tiles[n] = products of rows 16 n + i (of `rows`, the last one n_rows - 1) with the lanes' row x
+template <int DH>
+__device__ __forceinline__ void dots16(const float* __restrict__ rows, int64_t stride, int n_rows, int i, int g, const f32x4 (&x)[DH / 16], f32x4 (&tiles)[4]) {
+#pragma unroll
+    for (int n = 0; n < 4; ++n) tiles[n] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int n = 0; n < 4; ++n) {
+        if (16 * n >= n_rows) break;
+        f32x4 y[DH / 16];
+        row16<DH>(rows + min(16 * n + i, n_rows - 1) * stride, g, y);
+        f32x4 part[4];                             // four short sums are closer to the exact one than a long one (and do not wait for each other)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) part[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < DH / 16; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) part[e] = mfma16(y[j][e], x[j][e], part[e]);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) tiles[n][r] = (part[0][r] + part[1][r]) + (part[2][r] + part[3][r]);
+    }
+}
+// acc[db] += sum over rows j of p (element 4 g + e of tile n is row 16 n + 4 g + e's weight) * row j's elements 16 db + i
+template <int DH>
+__device__ __forceinline__ void sums16(const float* __restrict__ rows, int64_t stride, int n_rows, int i, int g, const f32x4 (&p)[4], f32x4 (&acc)[DH / 16]) {
+    // a step is one row of each lane group; the next step's row is loaded ahead of this one's products
+    float x[2][DH / 16];
+    auto load = [&](int step, float (&y)[DH / 16]) {
+        const float* const r = rows + min(16 * (step >> 2) + 4 * g + (step & 3), n_rows - 1) * stride + i;
+#pragma unroll
+        for (int db = 0; db < DH / 16; ++db) y[db] = r[16 * db];
+    };
+    load(0, x[0]);
+#pragma unroll
+    for (int step = 0; step < 16; ++step) {
+        if ((step & 3) == 0 && 4 * step >= n_rows) break;
+        if (step + 1 < 16) load(step + 1, x[(step + 1) & 1]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int db = 0; db < DH / 16; ++db) acc[db] = mfma16(x[step & 1][db], p[step >> 2][step & 3], acc[db]);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+__device__ __forceinline__ float max4(float x) { x = fmaxf(x, __shfl_xor(x, 16, 64)); return fmaxf(x, __shfl_xor(x, 32, 64)); }
+__device__ __forceinline__ float sum4(float x) { x += __shfl_xor(x, 16, 64); return x + __shfl_xor(x, 32, 64); }
+__device__ __forceinline__ bool is_nan_bits(float x) {       // by its bits: the build takes float comparisons to see no NaN
+    unsigned b = __float_as_uint(x);
+    asm volatile("" : "+v"(b));
+    return (b & 0x7fffffffu) > 0x7f800000u;
+}
+// The chunks of 64 keys that any of the rows t0 .. t0 + rows - 1 sees: those of the prompt, then those of the rows' own segments from
+// the first response row's first token on.
+struct RowsChunks {
+    int n1, n, end1, k2, end;
+    __device__ __forceinline__ RowsChunks(const GroupDesc& gd, int t0, int rows) {
+        end = t0 + rows;
+        end1 = min(gd.Lp, end);
+        n1 = (end1 + 63) / 64;
+        k2 = end > gd.Lp ? seg_start(gd, max(t0, gd.Lp)) : end;
+        n = n1 + (end - k2 + 63) / 64;
+    }
+    __device__ __forceinline__ int first(int i) const { return i < n1 ? 64 * i : k2 + 64 * (i - n1); }
+    __device__ __forceinline__ int count(int i) const { return min(64, (i < n1 ? end1 : end) - first(i)); }
+};
+// calls f(group, first token, number) for the 16 tokens of a workgroup, group by group
+template <typename F>
+__device__ __forceinline__ void for_tokens(const int* tab, int64_t first, int64_t T_total, F f) {
+    const int64_t end = min(first + BLK, T_total);
+    for (int64_t tok = first; tok < end;) {
+        const GroupDesc gd = load_group(tab, find_group_of_token(tab, tok));
+        const int n = (int)min(end - tok, (int64_t)gd.tok_base + gd.Tg - tok);
+        f(gd, (int)tok, n);
+        tok += n;
+    }
+}
+
+template <int DH>
+__global__ __launch_bounds__(64 * F32_WAVES) void fwd_f32_block_kernel(TabArg table, const float* __restrict__ q, const float* __restrict__ k,
+                                                                       const float* __restrict__ v, float* __restrict__ o,
+                                                                       float* __restrict__ lse, int64_t T_total, int Hq, int Hkv,
+                                                                       float scale, int resp_only) {
+    constexpr int NB = DH / 16, PAD = DH + 4;
+    __shared__ float sh_m[F32_WAVES][BLK], sh_l[F32_WAVES][BLK];
+    __shared__ int sh_bad[BLK];
+    __shared__ __attribute__((aligned(16))) float sh_acc[F32_WAVES][BLK][PAD];
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63, i = l & 15, g = l >> 4;
+    const int h = (int)(blockIdx.x % (unsigned)Hq), kvh = h / (Hq / Hkv);
+    for_tokens(table_of(table), (int64_t)(blockIdx.x / (unsigned)Hq) * BLK, T_total, [&](const GroupDesc& gd, int tok, int rows) {
+        const int t0 = tok - gd.tok_base;
+        if (resp_only && t0 + rows <= gd.Lp) return;
+        const RowsChunks ch(gd, t0, rows);
+        const int64_t kvs = (int64_t)Hkv * DH, qs = (int64_t)Hq * DH;
+        const float* const kb = k + ((int64_t)gd.tok_base * Hkv + kvh) * DH;
+        const float* const vb = v + ((int64_t)gd.tok_base * Hkv + kvh) * DH;
+        const int t = t0 + min(i, rows - 1), st = seg_start(gd, t);
+        f32x4 qr[NB], acc[NB];
+        row16<DH>(q + (int64_t)(gd.tok_base + t) * qs + h * DH, g, qr);
+#pragma unroll
+        for (int db = 0; db < NB; ++db) acc[db] = f32x4{0.f, 0.f, 0.f, 0.f};
+        float m = -INFINITY, lsum = 0.f;
+        for (int c = w; c < ch.n; c += F32_WAVES) {
+            const int s0 = ch.first(c), nk = ch.count(c), lo = c < ch.n1 ? 0 : st - s0, hi = min(nk, t + 1 - s0);
+            f32x4 S[4];
+            dots16<DH>(kb + (int64_t)s0 * kvs, kvs, nk, i, g, qr, S);
+            float mx = -INFINITY;
+            bool nan = false;
+#pragma unroll
+            for (int n = 0; n < 4; ++n)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int key = 16 * n + 4 * g + e;
+                    S[n][e] = key >= lo && key < hi ? scale * S[n][e] : -INFINITY;
+                    nan |= is_nan_bits(S[n][e]);
+                    mx = fmaxf(mx, S[n][e]);
+                }
+            const float mnew = fmaxf(m, max4(mx));
+            const uint64_t nans = __builtin_amdgcn_ballot_w64(nan);
+            // (nothing but masked keys and scores of -inf so far; a NaN goes on: the sums become NaN)
+            const bool none = mnew == -INFINITY && ((nans >> i) & 0x0001000100010001ull) == 0;
+            const float alpha = none ? 1.f : expf(m - mnew);
+            if (!none) m = mnew;
+            lsum *= alpha;
+#pragma unroll
+            for (int n = 0; n < 4; ++n)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int key = 16 * n + 4 * g + e;
+                    S[n][e] = !none && key >= lo && key < hi ? expf(S[n][e] - mnew) : 0.f;
+                    lsum += S[n][e];
+                }
+#pragma unroll
+            for (int db = 0; db < NB; ++db)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[db][e] *= alpha;
+            sums16<DH>(vb + (int64_t)s0 * kvs, kvs, nk, i, g, S, acc);
+        }
+        lsum = sum4(lsum);
+        __syncthreads();                           // (the sums of the tokens of another group are read)
+        if (g == 0) { sh_m[w][i] = m; sh_l[w][i] = lsum; }
+        if (threadIdx.x < BLK) sh_bad[threadIdx.x] = 0;
+#pragma unroll
+        for (int db = 0; db < NB; ++db) *reinterpret_cast<f32x4*>(&sh_acc[w][i][16 * db + 4 * g]) = acc[db];
+        __syncthreads();
+        const int r = (int)threadIdx.x >> 5;
+        const bool mine = r < rows && !(resp_only && t0 + r < gd.Lp);
+        bool bad = false;
+        if (mine) {
+            float mt = sh_m[0][r];
+#pragma unroll
+            for (int x = 1; x < F32_WAVES; ++x) mt = fmaxf(mt, sh_m[x][r]);
+            float ls = 0.f, f[F32_WAVES];
+#pragma unroll
+            for (int x = 0; x < F32_WAVES; ++x) {        // a wave without a key (or with scores of -inf only) has no part
+                f[x] = __float_as_uint(sh_l[x][r]) == 0u ? 0.f : expf(sh_m[x][r] - mt);
+                ls = __builtin_fmaf(sh_l[x][r], f[x], ls);
+            }
+#pragma unroll
+            for (int n = 0; n < DH / 32; ++n) {
+                const int d = (threadIdx.x & 31) + 32 * n;
+                float x = 0.f;
+#pragma unroll
+                for (int u = 0; u < F32_WAVES; ++u) x = __builtin_fmaf(sh_acc[u][r][d], f[u], x);
+                x /= ls;
+                bad |= is_nan_bits(x);
+                o[(int64_t)(tok + r) * qs + h * DH + d] = x;
+            }
+            if ((threadIdx.x & 31) == 0) lse[(int64_t)h * T_total + tok + r] = mt + logf(ls);
+        }
+        if (bad) sh_bad[r] = 1;
+        if (__syncthreads_or(bad))
+            for (int x = w; x < rows; x += F32_WAVES)
+                if (sh_bad[x]) fwd_f32_row<DH, false>(gd, tok + x, h, w, l, q, k, v, o, lse, T_total, Hq, Hkv, scale, resp_only);
+    });
+}
+
+template <int DH>
+__global__ __launch_bounds__(64 * F32_WAVES) void bwd_dq_f32_block_kernel(TabArg table, const float* __restrict__ q, const float* __restrict__ k,
+                                                                          const float* __restrict__ v, const float* __restrict__ d_o,
+                                                                          const float* __restrict__ o, const float* __restrict__ lse,
+                                                                          float* __restrict__ D, float* __restrict__ dq, uint32_t* __restrict__ tag,
+                                                                          int64_t T_total, int Hq, int Hkv, float scale, int resp_only) {
+    constexpr int NB = DH / 16, PAD = DH + 4, PER = DH / 64;
+    __shared__ float sh_D[BLK];
+    __shared__ int sh_bad[BLK];
+    __shared__ __attribute__((aligned(16))) float sh_acc[F32_WAVES][BLK][PAD];
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63, i = l & 15, g = l >> 4;
+    if (tag && blockIdx.x == 0 && w == 0) tag[l] = 0u;
+    const int h = (int)(blockIdx.x % (unsigned)Hq), kvh = h / (Hq / Hkv);
+    for_tokens(table_of(table), (int64_t)(blockIdx.x / (unsigned)Hq) * BLK, T_total, [&](const GroupDesc& gd, int tok, int rows) {
+        const int t0 = tok - gd.tok_base;
+        if (resp_only && t0 + rows <= gd.Lp) return;
+        const RowsChunks ch(gd, t0, rows);
+        const int64_t kvs = (int64_t)Hkv * DH, qs = (int64_t)Hq * DH, row0 = (int64_t)tok * qs + h * DH, word = (int64_t)h * T_total + tok;
+        const float* const kb = k + ((int64_t)gd.tok_base * Hkv + kvh) * DH;
+        const float* const vb = v + ((int64_t)gd.tok_base * Hkv + kvh) * DH;
+        __syncthreads();                           // (the sums of the tokens of another group are read)
+        for (int x = w; x < rows; x += F32_WAVES) {                   // D, as in dq_f32_row()
+            float Dt = 0.f;
+            if (o) {
+#pragma unroll
+                for (int e = 0; e < PER; ++e) Dt += d_o[row0 + x * qs + l + 64 * e] * o[row0 + x * qs + l + 64 * e];
+                Dt = wave_sum(Dt);
+                if (l == 0 && !(resp_only && t0 + x < gd.Lp)) D[word + x] = Dt;
+            } else {
+                Dt = D[word + x];
+            }
+            if (l == 0) { sh_D[x] = Dt; sh_bad[x] = 0; }
+        }
+        const int n0 = min(i, rows - 1), t = t0 + n0, st = seg_start(gd, t);
+        const float L = lse[word + n0];
+        f32x4 qr[NB], gr[NB], acc[NB];
+        row16<DH>(q + row0 + n0 * qs, g, qr);
+        row16<DH>(d_o + row0 + n0 * qs, g, gr);
+#pragma unroll
+        for (int db = 0; db < NB; ++db) acc[db] = f32x4{0.f, 0.f, 0.f, 0.f};
+        __syncthreads();
+        const float Dt = sh_D[n0];
+        for (int c = w; c < ch.n; c += F32_WAVES) {
+            const int s0 = ch.first(c), nk = ch.count(c), lo = c < ch.n1 ? 0 : st - s0, hi = min(nk, t + 1 - s0);
+            f32x4 S[4], P[4];
+            dots16<DH>(kb + (int64_t)s0 * kvs, kvs, nk, i, g, qr, S);
+            dots16<DH>(vb + (int64_t)s0 * kvs, kvs, nk, i, g, gr, P);
+#pragma unroll
+            for (int n = 0; n < 4; ++n)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int key = 16 * n + 4 * g + e;
+                    S[n][e] = key >= lo && key < hi ? expf(scale * S[n][e] - L) * (P[n][e] - Dt) : 0.f;
+                }
+            sums16<DH>(kb + (int64_t)s0 * kvs, kvs, nk, i, g, S, acc);
+        }
+#pragma unroll
+        for (int db = 0; db < NB; ++db) *reinterpret_cast<f32x4*>(&sh_acc[w][i][16 * db + 4 * g]) = acc[db];
+        __syncthreads();
+        const int r = (int)threadIdx.x >> 5;
+        bool bad = false;
+        if (r < rows && !(resp_only && t0 + r < gd.Lp))
+#pragma unroll
+            for (int n = 0; n < DH / 32; ++n) {
+                const int d = (threadIdx.x & 31) + 32 * n;
+                float x = 0.f;
+#pragma unroll
+                for (int u = 0; u < F32_WAVES; ++u) x += sh_acc[u][r][d];
+                bad |= is_nan_bits(x);
+                dq[row0 + r * qs + d] = scale * x;
+            }
+        if (bad) sh_bad[r] = 1;
+        if (__syncthreads_or(bad))
+            for (int x = w; x < rows; x += F32_WAVES)
+                if (sh_bad[x]) dq_f32_row<DH, false>(gd, tok + x, h, w, l, q, k, v, d_o, o, lse, D, dq, T_total, Hq, Hkv, scale, resp_only);
+    });
+}
+
+template <int DH>
+__global__ __launch_bounds__(64 * F32_WAVES) void bwd_dkdv_f32_block_kernel(TabArg table, const float* __restrict__ q, const float* __restrict__ k,
+                                                                            const float* __restrict__ v, const float* __restrict__ d_o,
+                                                                            const float* __restrict__ lse, const float* __restrict__ D,
+                                                                            float* __restrict__ dk, float* __restrict__ dv,
+                                                                            int64_t T_total, int Hq, int Hkv, float scale,
+                                                                            int resp_only, int accumulate) {
+    constexpr int NB = DH / 16, PAD = DH + 4;
+    __shared__ int sh_bad[BLK];
+    __shared__ __attribute__((aligned(16))) float sh_acc[F32_WAVES][BLK][PAD];
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63, i = l & 15, g = l >> 4;
+    const int kvh = (int)(blockIdx.x % (unsigned)Hkv);
+    for_tokens(table_of(table), (int64_t)(blockIdx.x / (unsigned)Hkv) * BLK, T_total, [&](const GroupDesc& gd, int tok, int keys) {
+        const int s0 = tok - gd.tok_base, rep = Hq / Hkv;
+        const int64_t kvs = (int64_t)Hkv * DH, qs = (int64_t)Hq * DH, key0 = (int64_t)tok * kvs + kvh * DH;
+        // rows first .. end - 1 see the lane's key; row_lo .. row_end - 1 see one of the block's
+        const int n0 = min(i, keys - 1), s = s0 + n0, last = s0 + keys - 1, first = resp_only ? max(s, gd.Lp) : s;
+        const int end = i < keys ? (s < gd.Lp ? gd.Tg : seg_end(gd, s)) : 0;
+        const int row_lo = resp_only ? max(s0, gd.Lp) : s0, row_end = s0 < gd.Lp ? gd.Tg : seg_end(gd, last);
+        const int n = max(row_end - row_lo + 63, 0) / 64;
+        f32x4 kr[NB], vr[NB], ak[NB], av[NB];
+        row16<DH>(k + key0 + n0 * kvs, g, kr);
+        row16<DH>(v + key0 + n0 * kvs, g, vr);
+#pragma unroll
+        for (int db = 0; db < NB; ++db) { ak[db] = f32x4{0.f, 0.f, 0.f, 0.f}; av[db] = f32x4{0.f, 0.f, 0.f, 0.f}; }
+        for (int hr = 0, c = w; hr < rep; ++hr, c -= n) {              // chunk c of the n * rep, counted within the head
+            for (; c < n; c += F32_WAVES) {
+                const int h = kvh * rep + hr, r0 = row_lo + 64 * c, nr = min(64, row_end - r0), lo = first - r0, hi = min(nr, end - r0);
+                const int64_t rows = (int64_t)(gd.tok_base + r0) * qs + h * DH, word = (int64_t)h * T_total + gd.tok_base + r0;
+                f32x4 P[4], S[4];
+                dots16<DH>(q + rows, qs, nr, i, g, kr, P);
+                dots16<DH>(d_o + rows, qs, nr, i, g, vr, S);
+#pragma unroll
+                for (int x = 0; x < 4; ++x)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int row = 16 * x + 4 * g + e, at = min(row, nr - 1);
+                        const bool ok = row >= lo && row < hi;
+                        P[x][e] = ok ? expf(scale * P[x][e] - lse[word + at]) : 0.f;
+                        S[x][e] = ok ? P[x][e] * (S[x][e] - D[word + at]) : 0.f;
+                    }
+                sums16<DH>(d_o + rows, qs, nr, i, g, P, av);
+                sums16<DH>(q + rows, qs, nr, i, g, S, ak);
+            }
+        }
+        const int r = (int)threadIdx.x >> 5;
+        float x[2][DH / 32];
+        bool bad = false;
+#pragma unroll
+        for (int which = 0; which < 2; ++which) {
+            __syncthreads();                       // (the sums before these are read)
+            if (which == 0 && threadIdx.x < BLK) sh_bad[threadIdx.x] = 0;
+#pragma unroll
+            for (int db = 0; db < NB; ++db) *reinterpret_cast<f32x4*>(&sh_acc[w][i][16 * db + 4 * g]) = which == 0 ? ak[db] : av[db];
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < DH / 32; ++u) {
+                x[which][u] = 0.f;
+#pragma unroll
+                for (int y = 0; y < F32_WAVES; ++y) x[which][u] += sh_acc[y][r][(threadIdx.x & 31) + 32 * u];
+                bad |= r < keys && is_nan_bits(x[which][u]);
+            }
+        }
+        if (bad) sh_bad[r] = 1;
+        if (__syncthreads_or(bad))
+            for (int y = w; y < keys; y += F32_WAVES)
+                if (sh_bad[y]) dkdv_f32_key<DH, false>(gd, tok + y, kvh, w, l, q, k, v, d_o, lse, D, dk, dv, T_total, Hq, Hkv, scale, resp_only, accumulate);
+        if (r >= keys || sh_bad[r]) return;
+#pragma unroll
+        for (int which = 0; which < 2; ++which)
+#pragma unroll
+            for (int u = 0; u < DH / 32; ++u) {
+                float* const out = (which == 0 ? dk : dv) + key0 + r * kvs + (threadIdx.x & 31) + 32 * u;
+                *out = (which == 0 ? scale * x[0][u] : x[1][u]) + (accumulate ? *out : 0.f);
+            }
+    });
 }
 
 inline int blocks_for_waves(int64_t waves) { return (int)((waves + 3) / 4); }
@@ -596,17 +956,21 @@ hipError_t launch_rowsum(const Problem& p, bool f32, hipStream_t s) {
     return hipGetLastError();
 }
 
-// Calls f(head dimension, shape, ...) with the faster shape.  us, narrow and WIDE, of one group, half of it prompt, five answers:
-//   heads of 64    T Hq = 768: forward 14.0, 11.9, dq 17.2, 15.7, dkdv 27.4, 17.9; 4800: 112, 105, 177, 174, 250, 231; 6400:
-//                  180, 169, 289, 286, 378, 386; four q heads on two kv heads, 2400 tokens: dkdv 1000, 820
-//   heads of 128   T Hq = 400: 12.8, 10.2, 18.6, 13.2, 28.5, 24.4; 768: 18.7, 17.5, 26.9, 22.9, 43.5, 45.3; 1024: 23.0, 23.7, 32.4,
-//                  31.6, 55.6, 66.7 (here WIDE spills in the dkdv kernel); four q on two kv heads, 1600 T Hkv: dkdv 313, 306
-// (`items` of the dkdv kernel: T Hkv over the q heads per kv head, which a wave would walk behind one another.)
-template <typename F>
-void with_f32_shape(const Problem& p, int64_t n, int64_t items, int limit128, F f) {
+// Calls f(head dimension, grid, workgroup) for few rows (keys) times heads, else block().  us, row by row and in blocks, one group, half of
+// it prompt, five answers, 4 / 2 heads:
+//   heads of 64    191 tokens: forward 9.2, 11.2, dq 13.5, 14.2, dkdv 16.4, 22.1; 253: 10.4, 11.1, 15.9, 14.3, 21.3, 24.6; 382: 19.5,
+//                  11.5, 27.7, 14.8, 40.1, 32.9; 800: 57, 16.6, 84, 20.9, 137, 59
+//   heads of 128   93 tokens: 9.2, 12.0, 12.2, 16.0, 13.3, 26.8; 150: 14.7, 13.9, 18.8, 18.6, 18.2, 34.0; 382: 38.9, 14.9, 54.3, 20.3,
+//                  53.6, 54.0; 800: 122, 23.6, 183, 32.4, 186, 100
+// Before, with one wave per row or key instead of blocks: forward and backward of 5 x (80 + 2 x 200) tokens, 4 / 4 heads of 128 161 -> 45
+// and 615 -> 157; 955 tokens, 4 / 2 80 -> 22 and 409 -> 101; 873, 43 -> 15 and 401 -> 127; 1759, 4 / 4 heads of 64 62 -> 23 and 211 -> 73.  Errors against float64 (o, dq, dk, dv, 1e-7): 955 tokens, heads of 128 3.4, 5.1, 7.6, 7.0 -> 1.8, 3.2,
+// 3.6, 3.2; 1152, heads of 64 1.7, 3.2, 3.6, 3.4 -> 1.6, 3.1, 3.5, 3.3.
+template <typename F, typename G>
+void with_f32_shape(const Problem& p, int heads, int64_t limit64, int64_t limit128, F f, G block) {
     auto sized = [&](auto dh) {
-        if (items <= (decltype(dh)::value == 64 ? 5000 : limit128)) f(dh, std::true_type{}, dim3((unsigned)n), dim3(F32_BLOCK<true>));
-        else f(dh, std::false_type{}, dim3((unsigned)((n + 3) / 4)), dim3(F32_BLOCK<false>));
+        const bool few = p.total_tokens * heads <= (decltype(dh)::value == 64 ? limit64 : limit128);
+        if (few) f(dh, dim3((unsigned)(p.total_tokens * heads)), dim3(F32_BLOCK<true>));
+        else block(dh, dim3((unsigned)((p.total_tokens + BLK - 1) / BLK * heads)), dim3(64 * F32_WAVES));
     };
     if (p.head_dim == 64) sized(std::integral_constant<int, 64>{}); else sized(std::integral_constant<int, 128>{});
 }
@@ -615,12 +979,13 @@ inline TabArg f32_table(const Problem& p) {
 }
 
 hipError_t launch_fwd_f32(const Problem& p, hipStream_t s) {
-    const int64_t n = p.total_tokens * p.Hq;
-    with_f32_shape(p, n, n, 800, [&](auto dh, auto wide, dim3 grid, dim3 block) {
-        hipLaunchKernelGGL((fwd_f32_kernel<decltype(dh)::value, decltype(wide)::value>), grid, block, 0, s, f32_table(p),
-                           (const float*)p.q, (const float*)p.k, (const float*)p.v, (float*)p.o_out, p.lse_out, p.total_tokens,
-                           p.Hq, p.Hkv, p.scale, p.resp_only);
-    });
+    auto go = [&](auto kernel, dim3 grid, dim3 block) {
+        hipLaunchKernelGGL(kernel, grid, block, 0, s, f32_table(p), (const float*)p.q, (const float*)p.k, (const float*)p.v,
+                           (float*)p.o_out, p.lse_out, p.total_tokens, p.Hq, p.Hkv, p.scale, p.resp_only);
+    };
+    with_f32_shape(p, p.Hq, 760, 550,
+        [&](auto dh, dim3 grid, dim3 block) { go(fwd_f32_kernel<decltype(dh)::value>, grid, block); },
+        [&](auto dh, dim3 grid, dim3 block) { go(fwd_f32_block_kernel<decltype(dh)::value>, grid, block); });
     return hipGetLastError();
 }
 
@@ -630,20 +995,26 @@ hipError_t launch_bwd_f32(const Problem& p, hipStream_t s) {
         hipError_t e = launch_rowsum(p, true, s);
         if (e != hipSuccess) return e;
     }
-    const int64_t nq = p.total_tokens * p.Hq, nk = p.total_tokens * p.Hkv;
-    if (p.stages & STAGE_DQ)
-        with_f32_shape(p, nq, nq, 800, [&](auto dh, auto wide, dim3 grid, dim3 block) {
-            hipLaunchKernelGGL((bwd_dq_f32_kernel<decltype(dh)::value, decltype(wide)::value>), grid, block, 0, s, f32_table(p),
-                               (const float*)p.q, (const float*)p.k, (const float*)p.v, (const float*)p.d_o,
-                               fused ? (const float*)p.o : nullptr, p.lse, p.Dbuf, (float*)p.dq,
+    if (p.stages & STAGE_DQ) {
+        auto go = [&](auto kernel, dim3 grid, dim3 block) {
+            hipLaunchKernelGGL(kernel, grid, block, 0, s, f32_table(p), (const float*)p.q, (const float*)p.k, (const float*)p.v,
+                               (const float*)p.d_o, fused ? (const float*)p.o : nullptr, p.lse, p.Dbuf, (float*)p.dq,
                                p.small.on ? p.small.tag : nullptr, p.total_tokens, p.Hq, p.Hkv, p.scale, p.resp_only);
-        });
-    if (p.stages & STAGE_DKDV)
-        with_f32_shape(p, nk, nk * p.Hkv / p.Hq, 600, [&](auto dh, auto wide, dim3 grid, dim3 block) {
-            hipLaunchKernelGGL((bwd_dkdv_f32_kernel<decltype(dh)::value, decltype(wide)::value>), grid, block, 0, s, f32_table(p),
-                               (const float*)p.q, (const float*)p.k, (const float*)p.v, (const float*)p.d_o, p.lse, p.Dbuf,
-                               (float*)p.dk, (float*)p.dv, p.total_tokens, p.Hq, p.Hkv, p.scale, p.resp_only, p.accumulate);
-        });
+        };
+        with_f32_shape(p, p.Hq, 760, 550,
+            [&](auto dh, dim3 grid, dim3 block) { go(bwd_dq_f32_kernel<decltype(dh)::value>, grid, block); },
+            [&](auto dh, dim3 grid, dim3 block) { go(bwd_dq_f32_block_kernel<decltype(dh)::value>, grid, block); });
+    }
+    if (p.stages & STAGE_DKDV) {
+        auto go = [&](auto kernel, dim3 grid, dim3 block) {
+            hipLaunchKernelGGL(kernel, grid, block, 0, s, f32_table(p), (const float*)p.q, (const float*)p.k, (const float*)p.v,
+                               (const float*)p.d_o, p.lse, p.Dbuf, (float*)p.dk, (float*)p.dv, p.total_tokens, p.Hq, p.Hkv, p.scale,
+                               p.resp_only, p.accumulate);
+        };
+        with_f32_shape(p, p.Hkv, 700, 760,
+            [&](auto dh, dim3 grid, dim3 block) { go(bwd_dkdv_f32_kernel<decltype(dh)::value>, grid, block); },
+            [&](auto dh, dim3 grid, dim3 block) { go(bwd_dkdv_f32_block_kernel<decltype(dh)::value>, grid, block); });
+    }
     return hipGetLastError();
 }
 
