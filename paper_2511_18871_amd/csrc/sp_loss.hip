@@ -295,11 +295,11 @@ hipError_t launch_logprob_fwd(const void* z, const int* y, float* logp, float* l
 
 hipError_t launch_logprob_bwd(const void* z, const int* y, const float* lse, const float* g, void* dz,
                               const TabArg& tab, int64_t total_tokens, int64_t V, bool f32, bool zero_prompt, hipStream_t s) {
-    // A gradient that the Infinity Cache (256 MB) cannot hold for its reader is stored past the caches.  Where the logits fill a
-    // third of it, they are read past them: nothing after this pass reads them, and what they would displace is the part of them that
-    // the forward left.  Not where rows are short and share cache lines, which would be read twice.  Forward + backward, us, cached
-    // reads -> not: 101 MB of logits 49.4 -> 46.2, 131 MB 62.0 -> 57.2, 180 MB (9000) 98 -> 86, 144 MB (6000) 73.9 -> 71.2, 311 MB 136 -> 124, 933 MB 392 -> 384; but
-    // 67 MB (vocabulary 4096) 32.8 -> 33.7, and with a vocabulary of 1003 60 MB 36 -> 42, 201 MB 112.5 -> 114.5.
+    // A gradient that the Infinity Cache (256 MB) cannot hold for its reader is stored past the caches, and then the logits, which nothing
+    // after this pass reads, are read past them too: what they would displace is the part of them that the forward left.  Not where
+    // rows are short and share cache lines, which would be read twice.  Forward, objective and gradient on new buffers, us, cached reads ->
+    // not: 275 MB 142 -> 136, 351 MB 196 -> 183, 933 MB 392 -> 385; smaller ones either way: 93 MB 75.3 -> 72.8, 130 MB 99 -> 102, 184 MB
+    // 137 -> 143, 249 MB 186 -> 183; 201 MB in rows of 1003 112.5 -> 114.5.
     const int64_t row = V * (f32 ? 4 : 2), bytes = total_tokens * row, cache = (int64_t)256 << 20;
     with_row_kernel(V, f32, [&](auto elem, auto lt) {
         typedef decltype(elem) T;
@@ -308,10 +308,9 @@ hipError_t launch_logprob_bwd(const void* z, const int* y, const float* lse, con
             hipLaunchKernelGGL((logprob_bwd_kernel<T, LT, decltype(last)::value, decltype(bypass)::value>), dim3((unsigned)total_tokens),
                                dim3(LT), 0, s, tab, (const T*)z, y, lse, g, (T*)dz, V, (int)zero_prompt);
         };
-        auto with_last = [&](auto last) {
-            if (bytes > cache) launch(last, std::true_type{}); else launch(last, std::false_type{});
-        };
-        if (3 * bytes > cache && (row >= 8192 || row % 128 == 0)) with_last(std::true_type{}); else with_last(std::false_type{});
+        if (bytes <= cache) launch(std::false_type{}, std::false_type{});
+        else if (row >= 8192 || row % 128 == 0) launch(std::true_type{}, std::true_type{});
+        else launch(std::false_type{}, std::true_type{});
     });
     return hipGetLastError();
 }

@@ -35,7 +35,7 @@ def test_rope_of_a_large_tensor_equals_its_parts():
         assert torch.equal(y[:, h:h + 10], part)
 
 
-@pytest.mark.parametrize("T,V", [(900, 50001), (3000, 50000)])       # 90 MB: logits; 300 MB: the gradient too
+@pytest.mark.parametrize("T,V", [(900, 50001), (3000, 50000), (3000, 50001), (140000, 1003)])       # 90 MB; 300 MB and 281 MB: past the caches
 @pytest.mark.parametrize("dtype", [torch.bfloat16])
 def test_logit_gradients_of_large_logits(T, V, dtype):
     gen = torch.Generator(device="cuda").manual_seed(V)
