@@ -18,7 +18,6 @@
 #include "sp_launch.hpp"
 #include "sp_edge.hpp"
 #include <algorithm>
-#include <functional>
 #include <type_traits>
 #include <vector>
 
@@ -1365,19 +1364,29 @@ int dkdv_waves(const Problem& p) {
 // packings of 1e8 to 2e11 operations 1.17 times as fast on average, on 18 larger ones 1.20, at worst 0.98.
 namespace {
 // When workgroups of `lens` steps and `fixed` more, `copies` of each, longest first, are through: each goes to the place that is free first.
-int play(std::vector<int>& lens, int places, int copies, int fixed, double* half = nullptr) {
-    std::sort(lens.begin(), lens.end(), std::greater<int>());
-    std::vector<int> at((size_t)places, 0);                    // a heap, the least on top
-    for (int n : lens)
-        for (int c = 0; c < copies; ++c) {
-            std::pop_heap(at.begin(), at.end(), std::greater<int>());
-            at.back() += n + fixed;
-            std::push_heap(at.begin(), at.end(), std::greater<int>());
+// That place's time never falls, so places are counted by the time at which they are free, and one look over the times serves all workgroups
+// (and lengths are sorted by counting).  The longest plan of 3000 drawn packings, on the host, a sort and a heap -> counts: 1150 -> 180 us.
+int play(const std::vector<int>& lens, int places, int copies, int fixed, double* half = nullptr) {
+    int longest = 0;
+    int64_t all = 0;
+    for (int n : lens) { longest = std::max(longest, n); all += n + fixed; }
+    std::vector<int> of_len((size_t)longest + 1, 0), at((size_t)(all * copies / places + longest + fixed + 1), 0);      // (a workgroup starts at the mean or before)
+    for (int n : lens) of_len[(size_t)n] += copies;
+    at[0] = places;
+    int first = 0, end = 0;
+    for (int n = longest; n >= 0; --n)
+        for (int left = of_len[(size_t)n]; left > 0;) {
+            while (at[(size_t)first] == 0) ++first;
+            const int now = std::min(left, at[(size_t)first]);
+            at[(size_t)first] -= now;
+            at[(size_t)(first + n + fixed)] += now;
+            end = std::max(end, first + n + fixed);
+            left -= now;
         }
-    const int end = *std::max_element(at.begin(), at.end());
     if (half) {
-        std::nth_element(at.begin(), at.begin() + places / 2, at.end());
-        *half = at[(size_t)places / 2];
+        int t = 0;
+        for (int before = at[0]; before <= places / 2; before += at[(size_t)t]) ++t;
+        *half = t;
     }
     return end;
 }
@@ -1429,7 +1438,7 @@ KeyPieces plan_key_pieces(const Problem& p, int slots, size_t max_words) {
     cus_of(p, bins, copies);
     const double even = (double)copies * (double)all / bins;
     if (longest + FIXED <= 1.25 * even) return out;
-    auto through = [&](std::vector<int>& lens) { return play(lens, bins, copies, FIXED); };
+    auto through = [&](const std::vector<int>& lens) { return play(lens, bins, copies, FIXED); };
     auto parts_of = [&](int steps, int len) { return steps <= len ? 1 : std::min((steps + len - 1) / len, 255); };
     std::vector<int> lens;
     auto cut = [&](int max_len, int each) {                    // (each: a tile's workgroups of equal share, whatever its length)
