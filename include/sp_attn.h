@@ -109,9 +109,9 @@ size_t sp_attn_row_parts_bytes(int64_t total_tokens, int32_t n_groups, int32_t n
 
 /* Bytes of a workspace with which a forward and its backward can do all that they know:
  *     sp_attn_workspace_bytes(1, ...) + sp_attn_reserve_bytes(...) + sp_attn_row_parts_bytes(...)
- * and behind them room for pieces of key tiles (bf16, up to 640 key tiles of 128, at most 48 MB): where few key tiles are seen by many
- * rows, a backward then gives the rows and q heads of such a tile to several workgroups, which changes the order in which dk
- * and dv are summed.  With less it runs without. */
+ * and behind them room for partial sums (bf16, up to 640 key tiles of 128, at most 48 MB): where few key tiles are seen by many
+ * rows, or few rows see many keys, such a tile's rows and q heads, or such rows' keys, then go to several workgroups, which
+ * changes the order in which dk and dv, or o, lse and dq, are summed.  With less both run without. */
 size_t sp_attn_full_workspace_bytes(int64_t total_tokens, int32_t n_groups, int64_t total_responses, int32_t n_q_heads,
                                     int32_t n_kv_heads, int32_t head_dim, sp_dtype dtype);
 

@@ -244,22 +244,30 @@ sp_status run(bool bwd, const void* q, const void* k, const void* v, const void*
     p.dkdv_partial2 = p.dkdv_parts == 2 ? (float*)((char*)workspace + parts_off) : nullptr;
 
     p.n_tiles256 = sp::count_tiles(p, 256); p.n_tiles128 = sp::count_tiles(p, 128);
-    const bool small_call = dtype == SP_BF16 && (!bwd || (stages == SP_BWD_STAGE_ALL && sp::rowsum_fast_path(p))) &&
-                            sp::use_small_call(p, L.words.size(), L.max_responses);
+    const bool small_table = dtype == SP_BF16 && sp::use_small_call(p, L.words.size(), L.max_responses);
     sp::KeyPieces pieces;
     sp::RowPieces row_pieces;
     if (pieces_fit) {
-        const size_t list_words = (size_t)sp::ARG_WORDS - (small_call ? L.words.size() : 0);
         p.piece_sums = (float*)((char*)workspace + pieces_off);
+        // Behind the table, if the call's kernels may have that as an argument; key pieces that find no room there and pay for the launch
+        // that takes the table to memory have all of it.  (Not by how this call is launched: stages and one call have the same parts.)
+        // A training pass, us, without pieces -> with, table in memory, 4 / 2 heads: 27 x (28 + 19 x 41) tokens 204 -> 160, 27 x (58 + 17 x 14) 91 ->
+        // 82; 24 x (23 + 21 x 7) 71 -> 80 if that launch does not count.
+        constexpr int TABLE_STEPS = 2;
+        const size_t room = (size_t)sp::ARG_WORDS - (small_table ? L.words.size() : 0);
         if (bwd && (stages & SP_BWD_STAGE_DKDV)) {
-            pieces = sp::plan_key_pieces(p, sp::piece_slots(L.total_tokens, n_groups, Hq, Hkv), list_words);
+            const int slots = sp::piece_slots(L.total_tokens, n_groups, Hq, Hkv);
+            pieces = sp::plan_key_pieces(p, slots, room, 0);
+            if (pieces.words.empty() && pieces.no_room && small_table) pieces = sp::plan_key_pieces(p, slots, sp::ARG_WORDS, TABLE_STEPS);
             if (!pieces.words.empty()) p.pieces = &pieces;
         }
         if ((!bwd && !p.naive) || (bwd && (stages & SP_BWD_STAGE_DQ))) {
-            row_pieces = sp::plan_row_pieces(p, pieces_len / sp::ROW_SLOT_BYTES / Hkv, list_words);
+            row_pieces = sp::plan_row_pieces(p, pieces_len / sp::ROW_SLOT_BYTES / Hkv, room);
             if (!row_pieces.words.empty()) p.row_pieces = &row_pieces;
         }
     }
+    const bool small_call = small_table && pieces.words.size() + L.words.size() <= (size_t)sp::ARG_WORDS &&
+                            (!bwd || (stages == SP_BWD_STAGE_ALL && sp::rowsum_fast_path(p)));
     const int key_order = !p.pieces && ordered && (stages & SP_BWD_STAGE_DKDV) ? sp::key_order(p) : sp::KEYS_AS_PACKED;
     p.sched.key_tiles = p.sched.tiles128;
     if (key_order != sp::KEYS_AS_PACKED) p.sched.key_tiles = (const sp::TileDesc*)((char*)workspace + key_tiles_off);

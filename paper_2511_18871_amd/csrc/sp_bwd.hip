@@ -1398,7 +1398,7 @@ void cus_of(const Problem& p, int& cus, int& copies) {
 }
 }  // namespace
 
-KeyPieces plan_key_pieces(const Problem& p, int slots, size_t max_words) {
+KeyPieces plan_key_pieces(const Problem& p, int slots, size_t max_words, int cost) {
     // steps' worth of time: of a workgroup without steps, of storing partial sums, of the launch that adds them up
     constexpr int FIXED = 5, STORE = 2, SUM_STEPS = 3;
     KeyPieces out;
@@ -1447,7 +1447,8 @@ KeyPieces plan_key_pieces(const Problem& p, int slots, size_t max_words) {
         for (const Tile& t : tiles) {
             const int parts = max_len ? parts_of(t.steps, max_len) : each * (each > 1 && t.steps / rep >= PART_STEPS ? p.dkdv_parts : 1);
             if (parts > 1) n_slots += parts;
-            if (max_len && (n_slots > slots || lens.size() + parts > max_words)) return false;
+            if (max_len && lens.size() + parts > max_words) out.no_room = true;
+            if (max_len && (n_slots > slots || out.no_room)) return false;
             for (int i = 0; i < parts; ++i) lens.push_back((t.steps + parts - 1) / parts + (parts > 1 ? STORE : 0));
         }
         return max_len == 0 || n_slots > 0;
@@ -1456,6 +1457,8 @@ KeyPieces plan_key_pieces(const Problem& p, int slots, size_t max_words) {
     cut(0, p.dkdv_partial ? rep : 1);
     int best = through(lens) - (p.dkdv_partial ? 0 : SUM_STEPS), len = 0;
     if (!p.dkdv_partial) best = best * 9 / 10;
+    best -= cost;
+    if (best <= std::max<double>(2 + STORE + FIXED, even)) return out;      // no pieces can be through sooner
     for (int l = longest * 3 / 4; l >= 3; l = std::min(l * 7 / 8, l - 1)) {
         if (!cut(l, 1)) break;
         const int end = through(lens);

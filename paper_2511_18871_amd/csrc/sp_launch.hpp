@@ -292,7 +292,7 @@ inline int dkdv_parts(const Problem& p) {
 // words for each such tile, its first slot | parts << 16 | keys - 1 << 24 and its first packed token).
 constexpr int PIECE_TILES = 640, PIECE_SLOTS = 384;       // most key tiles; most slots, all kv heads
 constexpr size_t PIECE_SLOT_BYTES = 2 * 128 * 128 * 4;    // dK and dV of a key tile, float32
-struct KeyPieces { std::vector<uint32_t> words, sums; int n_slots = 0; };
+struct KeyPieces { std::vector<uint32_t> words, sums; int n_slots = 0; bool no_room = false; };      // no_room: shorter pieces did not fit the list
 // slots of a kv head that a call can use, by its totals
 inline int piece_slots(int64_t total_tokens, int n_groups, int Hq, int Hkv) {
     const int64_t tiles = total_tokens / 128 + n_groups, rows = total_tokens / 64 + n_groups;
@@ -303,8 +303,8 @@ inline int piece_slots(int64_t total_tokens, int n_groups, int Hq, int Hkv) {
 inline size_t piece_bytes(int64_t total_tokens, int n_groups, int Hq, int Hkv) {
     return (size_t)piece_slots(total_tokens, n_groups, Hq, Hkv) * Hkv * PIECE_SLOT_BYTES;
 }
-// the pieces of a call (none where whole key tiles are as good), at most `slots` with partial sums
-KeyPieces plan_key_pieces(const Problem& p, int slots, size_t max_words);
+// the pieces of a call (none where whole key tiles are as good, or `cost` steps of a workgroup worse), at most `slots` with partial sums
+KeyPieces plan_key_pieces(const Problem& p, int slots, size_t max_words, int cost);
 
 // Key loops of the forward and the dq pass in parts: of the packings that use it, both take a list of (tile of 128 rows, workgroup of the tile,
 // part of its key tiles) from the kernel arguments behind the table, one of four-wave workgroups, longest first.  Workgroups with

@@ -40,6 +40,24 @@ def test_pieces(name, heads):
         gate(what, to64(got), ref, w.dtype)
 
 
+@pytest.mark.parametrize("groups,responses", [(24, 21), (19, 24), (23, 24)])
+def test_parts_do_not_depend_on_the_table(groups, responses):
+    """Tables of 593 to 763 words, beside which a kernel's arguments have no room for the list of pieces."""
+    w = W.Workload("tables", [W.Group(23, [7] * responses)] * groups, 4, 2, 128, torch.bfloat16, 783)
+    t = W.make_tensors(w)
+    pack, sc = (w.prompt_lens(), w.Gs(), w.resp_lens_flat()), w.softmax_scale
+    q, k, v, d_o = t.q.cuda(), t.k.cuda(), t.v.cuda(), t.d_o.cuda()
+    o, lse = B.sp_attn_fwd_batched(q, k, v, *pack, sc)
+    one = B.sp_attn_bwd_batched(q, k, v, o, lse, d_o, *pack, sc)
+    staged = [torch.full_like(x, float("nan")) for x in (q, k, v)]
+    for stage in (1, 4, 2):
+        B.sp_attn_bwd_batched_ex(q, k, v, o, lse, d_o, *pack, sc, 0, *staged, stages=stage)
+    torch.cuda.synchronize()
+    for what, x, y, ref in zip(("dQ", "dK", "dV"), one, staged, oracle_bwd(w, t)):
+        assert torch.equal(x, y)
+        gate(what, to64(x), ref, w.dtype)
+
+
 @pytest.mark.parametrize("name", list(PACKS))
 def test_pieces_of_response_rows_accumulate(name):
     w = W.Workload(name, PACKS[name], 8, 2, 128, torch.bfloat16, 781)
