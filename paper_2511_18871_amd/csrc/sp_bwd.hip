@@ -635,8 +635,6 @@ __global__ __launch_bounds__(256) void dq_pieces_kernel(RowSums list, BwdArgs a)
 // Row parts of a key tile of `steps` 64-row tiles in the head-split pass (see dkdv_parts())
 __device__ __forceinline__ int row_parts(const BwdArgs& a, int steps) { return a.head_split == 2 && steps >= PART_STEPS ? 2 : 1; }
 
-constexpr int SHORT_TILES = 2048;      // that the second sweep can list
-
 // PIECES: part `part` of `parts` of the tile's steps (row tile, q head); the sums go to `sums` where there are several
 template <int NW, bool SMALL, bool PIECES>
 __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const SmallGroup& sg, const TileDesc td, const int kvh, const int hr_only, const int part,
@@ -651,8 +649,6 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const SmallGroup& sg
     __shared__ __attribute__((aligned(1024))) char dkdv_lds[2][2 * QT_BYTES];                // [buffer][Q | dO]
     __shared__ __attribute__((aligned(256))) float dkdv_ldsLD[2][2][BQ];                     // [buffer][L2 | -D][row]
     __shared__ int dkdv_ldsEnd[K_REG ? BNK : 1];    // e_s of the tile's keys, below
-    __shared__ unsigned short dkdv_ldsShort[SHORT_TILES + 2];   // row tiles of the second sweep, below
-    __shared__ int dkdv_nShort;
     constexpr int RD = 3;      // LDS operand ring depth (prefetch distance RD - 1 MFMAs)
     const int s0 = ti * BNK;
     GroupDesc gd;
@@ -702,14 +698,6 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const SmallGroup& sg
         if (part >= n) return;
         if (n == 2) { if (part == 0) qt0 = mid; else qt1 = mid; }
     }
-    // The second sweep (below) runs the steps that can hold short rows: those of the first EDGE_LEN rows of the prompt, and under a
-    // shorter one those of the first EDGE_LEN - Lp rows of each response.  The latter's row tiles are listed by the last wave, last
-    // first, while K and V are on their way: a block of rows holds one if the segment of its last row begins less than that ahead of the block.  (Ahead of the
-    // main sweep, which keeps nothing of it; behind that, it cost 10 spilled registers and 5 % of the pass.)  Backward passes, us, all row
-    // tiles -> listed ones: 35 x (52 + 20 x 169), 28/4 heads 3027 -> 2358, 2 x (43 + 25 x 470), 32/8 1171 -> 832, 59 x (57 + 11 x 89),
-    // 4/2 277 -> 232; where every tile holds some, 62 x (45 + 29 x 32), 32/8 1810 -> 1810, ten tiles in all 38.2 -> 38.9
-    const int f_hi = Lp >= EDGE_LEN ? min(qt1, EDGE_LEN / BQ) : qt1;
-    const bool listed = Lp < EDGE_LEN && f_hi - qt0 <= SHORT_TILES;
     const int rep_all = a.rep;
     const int rep = NW == 8 && !PIECES && a.head_split ? 1 : rep_all;        // q heads this workgroup walks
     const int64_t q_stride = (int64_t)a.Hq * 128;
@@ -756,25 +744,6 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const SmallGroup& sg
             }
             __syncthreads();
         }
-    }
-    if (listed && w == NW - 1) {
-        int n = 0;
-        for (int i0 = 0; i0 < f_hi - qt0; i0 += 64) {
-            const int tile = f_hi - 1 - i0 - l;
-            unsigned entry = 0;
-#pragma unroll
-            for (int h = 0; h < BQ / 32; ++h) {
-                const int r0 = max(tile, 0) * BQ + 32 * h, last = min(r0 + 31, Tg - 1);
-                int st, en;
-                if constexpr (SMALL) small_segment(sg, last, st, en);
-                else st = a.sched.key_lo[gd.tok_base + last];
-                if (tile >= qt0 && r0 < Tg && (r0 < Lp || st + EDGE_LEN - Lp > r0)) entry |= 0x4000u << h;
-            }
-            const uint64_t some = __builtin_amdgcn_ballot_w64(entry != 0);
-            if (entry != 0) dkdv_ldsShort[n + __popcll(some & ((1ull << l) - 1))] = (unsigned short)(entry | (unsigned)(i0 + l));
-            n += __popcll(some);
-        }
-        if (l == 0) dkdv_nShort = n;
     }
     // Row tiles are walked from the LAST one down to the workgroup's own keys: workgroups that
     // start together (they share a kv head and an XCD) then stream the same Q/dO tiles at the
@@ -879,12 +848,12 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const SmallGroup& sg
     // Rows that see only a few keys carry weights P of order one, and a key's dK / dV can be made up almost
     // entirely of a handful of such terms, whose bf16 roundings of P and dS then do not average out.  The
     // steps that hold such rows (the first EDGE_LEN rows of a prompt; under a shorter prompt, conservatively,
-    // every step with response rows) are therefore swept a second time after the main sweep, with P and dS
+    // every step with response rows: with only the row tiles that hold short rows, dK and dV of 2 x (60 + 26 x 60..85) tokens
+    // were off from float64 by 2.0e-3 instead of 1.66e-3) are therefore swept a second time after the main sweep, with P and dS
     // replaced by what their rounding dropped, P - bf16(P) and dS - bf16(dS) (rounded to bf16 in turn): the
     // two sweeps together carry P and dS into dV and dK to about 2^-17.  The second sweep is the same code
     // with another packing function, outside the main loop, so it costs that loop neither registers nor time.
-    // (Its `n_tiles` row tiles may come from the list, as steps ahead of q_hi, which also says which of a tile's halves hold short rows.)
-    auto sweep = [&](auto lo_tag, const int q_hi, const int n_tiles) {      // row tiles q_hi - 1 down
+    auto sweep = [&](auto lo_tag, const int q_hi, const int q_lo) {      // row tiles q_hi - 1 down to q_lo
     constexpr bool LO = decltype(lo_tag)::value;
     auto pack2 = [&](float x, float y) -> unsigned {
         typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -892,27 +861,17 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const SmallGroup& sg
         if (LO) v = bf16x2{(__bf16)(x - (float)v[0]), (__bf16)(y - (float)v[1])};
         return __builtin_bit_cast(unsigned, v);
     };
-    int n_steps = max(n_tiles, 0) * rep;
-    int at_n = LO ? 0 : q_hi - 1, hr = 0;     // step 0: its row tile, or its place in the list
+    int n_steps = max(q_hi - q_lo, 0) * rep;
+    int qt = q_hi - 1, hr = 0;                // step 0
     if constexpr (PIECES) {
         const int from = n_steps * part / parts;
         n_steps = n_steps * (part + 1) / parts - from;
         unsigned r;
-        const int first = (int)divmod((unsigned)from, a.rep_div, r);
-        at_n += LO ? first : -first;
+        qt -= (int)divmod((unsigned)from, a.rep_div, r);
         hr = (int)r;
     }
-    unsigned halves = 0;                      // of the current tile (bits 2, 3) and of the next: do they hold short rows
-    auto tile_at = [&](int at) {
-        if constexpr (!LO) return at;
-        const int entry = listed ? __builtin_amdgcn_readfirstlane((int)dkdv_ldsShort[min(at, SHORT_TILES + 1)]) : 0xc000;
-        halves = halves << 2 | (unsigned)entry >> 14;
-        return q_hi - 1 - (listed ? entry & 0x3fff : at);
-    };
-    int qt = tile_at(at_n);
-    int hr_n = hr + 1;                        // step 1
-    if (hr_n == rep) { hr_n = 0; at_n += LO ? 1 : -1; }
-    int qt_n = tile_at(at_n);
+    int qt_n = qt, hr_n = hr + 1;             // step 1
+    if (hr_n == rep) { hr_n = 0; --qt_n; }
     if (n_steps > 0) issue_tile(qt, hr, 0);
     auto step = [&](const int it, auto buf_tag) {
         constexpr int buf = decltype(buf_tag)::value;
@@ -923,17 +882,11 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const SmallGroup& sg
         const float* ldsD = dkdv_ldsLD[buf][1];
         const int r0 = qt * BQ + 32 * qh;              // this wave's 32 rows
         const int qt_n_issue = qt_n, hr_n_issue = hr_n;
-        const bool none = LO && NW == 8 && !(halves >> (2 + qh) & 1);     // no short row in this wave's half
         qt = qt_n; hr = hr_n;
-        if constexpr (LO) halves = halves << 2 | (halves & 3);
-        if (++hr_n == rep) {
-            hr_n = 0;
-            if constexpr (LO) { halves >>= 2; qt_n = tile_at(++at_n); }
-            else { --at_n; qt_n = at_n; }
-        }
+        if (++hr_n == rep) { hr_n = 0; --qt_n; }
         // no row of this wave's half sees any key of this wave
         const bool skip = !wave_valid || r0 + 31 < max(ws0, row_lo) || r0 >= e_max ||
-                          none || (LO && !listed && r0 >= min(Lp, EDGE_LEN) && (Lp >= EDGE_LEN || r0 + 31 < Lp));       // or: no short row here
+                          (LO && !(r0 < min(Lp, EDGE_LEN) || (Lp < EDGE_LEN && r0 + 31 >= Lp)));   // or: no short row here
 
         // The LDS operands of the step's 32 MFMAs pass through one pair of rings, read RD - 1 MFMAs ahead
         // without a break between the four products (a product that primed rings of its own would start with
@@ -1054,10 +1007,13 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, const SmallGroup& sg
         if (it + 1 < n_steps) step(it + 1, std::integral_constant<int, 1>{});
     }
     };
-    sweep(std::false_type{}, qt1, qt1 - qt0);
-    if (f_hi > qt0) {
-        __syncthreads();                           // every wave has left the main sweep's last buffer
-        sweep(std::true_type{}, f_hi, listed ? __builtin_amdgcn_readfirstlane(dkdv_nShort) : f_hi - qt0);
+    sweep(std::false_type{}, qt1, qt0);
+    {   // the steps that can hold short rows: row tile 0 under a prompt of at least EDGE_LEN tokens, else all
+        const int f_hi = Lp >= EDGE_LEN ? min(qt1, EDGE_LEN / BQ) : qt1;
+        if (f_hi > qt0) {
+            __syncthreads();                       // every wave has left the main sweep's last buffer
+            sweep(std::true_type{}, f_hi, qt0);
+        }
     }
 
     const int64_t orow = ((int64_t)(gd.tok_base + (valid ? s : 0)) * a.Hkv + kvh) * 128 + 4 * hh;
@@ -1405,7 +1361,6 @@ KeyPieces plan_key_pieces(const Problem& p, int slots, size_t max_words, int cos
     const int rep = p.Hq / p.Hkv;
     struct Tile { int steps, id, tok, keys; };
     std::vector<Tile> tiles;
-    std::vector<int> shorts;
     tiles.reserve((size_t)p.n_tiles128);
     int longest = 0;
     int64_t all = 0;
@@ -1413,21 +1368,12 @@ KeyPieces plan_key_pieces(const Problem& p, int slots, size_t max_words, int cos
         const int32_t* e = p.host_table + TAB_HEADER + TAB_GROUP_WORDS * g;
         const int Lp = e[1], Tg = e[2];
         const int32_t* roff = p.host_table + e[3];
-        // row tiles of the second sweep below each row tile
-        shorts.clear();
-        if (Lp < EDGE_LEN)
-            for (int q = 0, j = 0, n = 0; q <= (Tg + 63) / 64; ++q) {
-                shorts.push_back(n);
-                const int last = std::min(64 * q + 64, Tg) - 1;
-                while (j + 1 < e[4] && roff[j + 1] <= last) ++j;
-                n += 64 * q < Lp || roff[j] + EDGE_LEN - Lp > 64 * q;
-            }
         for (int s0 = 0, j = 0; s0 < Tg; s0 += 128) {
             const int s1 = std::min(s0 + 128, Tg), from = p.resp_only && Lp > s0 ? Lp : s0;
             int to = Tg;
             if (s0 >= Lp) { while (roff[j + 1] < s1) ++j; to = roff[j + 1]; }
             const int q0 = from / 64, q1 = to > (p.resp_only ? Lp : 0) ? (to + 63) / 64 : q0;
-            const int lo = Lp >= EDGE_LEN ? std::max(std::min(q1, 1) - q0, 0) : q1 > q0 ? shorts[q1] - shorts[q0] : 0;
+            const int lo = std::max((Lp >= EDGE_LEN ? std::min(q1, 1) : q1) - q0, 0);
             const int steps = rep * (std::max(q1 - q0, 0) + lo);
             tiles.push_back(Tile{steps, (int)tiles.size(), e[0] + s0, s1 - s0});
             longest = std::max(longest, steps);

@@ -38,7 +38,7 @@ def test_short_rows_in_one_call_and_in_stages(heads, groups, steps):
 
 
 @pytest.mark.parametrize("heads", [1, 8])
-@pytest.mark.parametrize("responses", [300, 4000])       # 4000: more row tiles than the second sweep of the dkdv pass lists
+@pytest.mark.parametrize("responses", [300, 4000])
 def test_prompt_gradients_under_many_short_responses(responses, heads):
     """A prompt of 10 tokens under responses of 35, whose every row sees fewer than 64 keys, against batched per-sample attention."""
     Lp, n, d = 10, 35, 128
