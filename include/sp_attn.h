@@ -111,7 +111,8 @@ size_t sp_attn_row_parts_bytes(int64_t total_tokens, int32_t n_groups, int32_t n
  *     sp_attn_workspace_bytes(1, ...) + sp_attn_reserve_bytes(...) + sp_attn_row_parts_bytes(...)
  * and behind them room for partial sums (bf16, up to 640 key tiles of 128, at most 48 MB): where few key tiles are seen by many
  * rows, or few rows see many keys, such a tile's rows and q heads, or such rows' keys, then go to several workgroups, which
- * changes the order in which dk and dv, or o, lse and dq, are summed.  With less both run without. */
+ * changes the order in which dk and dv, or dq and the o and lse of a forward with SP_FLAG_RESPONSE_ROWS, are summed.  With less both run
+ * without.  The o and lse of a forward of all rows do not depend on the workspace. */
 size_t sp_attn_full_workspace_bytes(int64_t total_tokens, int32_t n_groups, int64_t total_responses, int32_t n_q_heads,
                                     int32_t n_kv_heads, int32_t head_dim, sp_dtype dtype);
 

@@ -261,7 +261,9 @@ sp_status run(bool bwd, const void* q, const void* k, const void* v, const void*
             if (pieces.words.empty() && pieces.no_room && small_table) pieces = sp::plan_key_pieces(p, slots, sp::ARG_WORDS, TABLE_STEPS);
             if (!pieces.words.empty()) p.pieces = &pieces;
         }
-        if ((!bwd && !p.naive) || (bwd && (stages & SP_BWD_STAGE_DQ))) {
+        // A forward of all rows has whole key loops whatever its workspace: o and lse are the same from every entry point, several
+        // sets in one call among them.
+        if (bwd ? (stages & SP_BWD_STAGE_DQ) != 0 : resp_only && !p.naive) {
             row_pieces = sp::plan_row_pieces(p, pieces_len / sp::ROW_SLOT_BYTES / Hkv, room);
             if (!row_pieces.words.empty()) p.row_pieces = &row_pieces;
         }

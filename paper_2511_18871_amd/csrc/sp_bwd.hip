@@ -1430,13 +1430,13 @@ KeyPieces plan_key_pieces(const Problem& p, int slots, size_t max_words, int cos
     return out;
 }
 
-// Key loops of the forward and the dq pass in parts, planned in the same way for four-wave workgroups, two to a CU.  Few rows under
+// Key loops of the dq pass, and of a forward of response rows, in parts, planned in the same way for four-wave workgroups, two to a CU.  Few rows under
 // long prompts leave CUs without a workgroup, or a last round of workgroups that are half as many as the places.  Either all workgroups
 // longer than some length are cut into equal parts, or only those that no full round takes, whichever is through sooner; neither unless it
 // gains a twentieth and the launch that brings the sums together, which up to LEAST steps cannot be.  Forward and dq pass, us, whole -> in parts
 // (prompt x answers, response rows only, q / kv heads): 3 x (10500 + 17 x 40), 4/2 259 -> 66 and 310 -> 77; 2 x (2260 + 58), 28/4
 // 51 -> 26; 8192 + 16 x 160, 40/8 (760 workgroups in 512 places) 439 -> 400 and 568 -> 553; on 66 drawn packings forward and backward
-// 1.06 times as fast on average.  Two waves of one workgroup to an item, without a second launch, walked in step and took 13 to 30 % longer.
+// 1.06 times as fast on average (forwards of all rows in parts too, which made o depend on the entry point).  Two waves of one workgroup to an item, without a second launch, walked in step and took 13 to 30 % longer.
 RowPieces plan_row_pieces(const Problem& p, size_t slots, size_t max_words) {
     // steps' worth of time: of a workgroup without steps, of storing sums, of the launch that brings them together
     constexpr int FIXED = 4, STORE = 1, SUM_STEPS = 8, LEAST = 16;       // (up to LEAST steps there is nothing to gain)

@@ -135,7 +135,7 @@ struct Problem {
     int accumulate;                                       // backward: dk, dv += instead of =
     int dkdv_parts;                                       // row parts of a key tile in the head-split pass
     const struct KeyPieces* pieces;                       // bf16 backward: the dkdv pass in pieces of key tiles (null: not)
-    const struct RowPieces* row_pieces;                   // the forward and the dq pass with key loops in parts (null: not)
+    const struct RowPieces* row_pieces;                   // the forward of response rows and the dq pass with key loops in parts (null: not)
     float* piece_sums;                                    // the partial sums of either
     float* dkdv_partial;                                  // bf16 backward on small problems: fp32 per-q-head partials
     float* dkdv_partial2;                                 // the second row part's
@@ -306,7 +306,7 @@ inline size_t piece_bytes(int64_t total_tokens, int n_groups, int Hq, int Hkv) {
 // the pieces of a call (none where whole key tiles are as good, or `cost` steps of a workgroup worse), at most `slots` with partial sums
 KeyPieces plan_key_pieces(const Problem& p, int slots, size_t max_words, int cost);
 
-// Key loops of the forward and the dq pass in parts: of the packings that use it, both take a list of (tile of 128 rows, workgroup of the tile,
+// Key loops of the dq pass, and of a forward of response rows, in parts: of the packings that use it, both take a list of (tile of 128 rows, workgroup of the tile,
 // part of its key tiles) from the kernel arguments behind the table, one of four-wave workgroups, longest first.  Workgroups with
 // several parts leave unnormalised float32 sums in slots, in the order of the list, where they lie next to one another from first_slot on, and a second
 // launch brings them together.  word: tile | workgroup << 10 | part << 16 | parts << 24; sums: three words for each such

@@ -1,4 +1,4 @@
-"""The forward and the dq pass with key loops in parts: few rows under long prompts, response rows only and all rows, ragged ends of
+"""The forward of response rows and the dq pass with key loops in parts: few rows under long prompts, response rows only and all rows, ragged ends of
 keys, rows that see no key of a part, all ways in which kv heads fall onto the chip; the gradients of stages and of a second call bit for
 bit, and what a workspace without the room gives."""
 import pytest
@@ -74,39 +74,61 @@ def test_response_rows_only(name, heads):
 @pytest.mark.parametrize("name", ["two_prompts", "long_response", "no_prompt"])
 def test_sums_stay_in_their_room(name):
     heads = (4, 2)
-    w, t, _, pk = _setup(name, heads, 792)
-    q, k, v = t.q.cuda(), t.k.cuda(), t.v.cuda()
+    w, t, resp, pk = _setup(name, heads, 792)
+    q, k, v, fl = t.q.cuda(), t.k.cuda(), t.v.cuda(), B.SP_FLAG_RESPONSE_ROWS
     n, r, T = len(w.groups), len(pk[2]), w.total_tokens
     behind = (B.workspace_bytes(True, T, n, r, *heads, 128, B.SP_BF16) + B.reserve_bytes(T, heads[0], 128, B.SP_BF16)
               + B.row_parts_bytes(T, n, *heads, B.SP_BF16))
     full = B.full_workspace_bytes(T, n, r, *heads, 128, B.SP_BF16)
     ws = torch.full((full + 4096,), 255, dtype=torch.uint8, device="cuda")
-    o, lse = B.sp_attn_fwd_batched(q, k, v, *pk, workspace=ws[:full])
+    o, lse = B.sp_attn_fwd_batched_ex(q, k, v, *pk, fl, workspace=ws[:full])
     torch.cuda.synchronize()
     assert (ws[behind:full] != 255).any() and (ws[full:] == 255).all()
     ws[:] = 255
-    whole, wlse = B.sp_attn_fwd_batched(q, k, v, *pk, workspace=ws[:full - 1])
+    whole, wlse = B.sp_attn_fwd_batched_ex(q, k, v, *pk, fl, workspace=ws[:full - 1])
     torch.cuda.synchronize()
     assert (ws[behind:] == 255).all()
+    o, whole, lse, wlse = o[resp], whole[resp], lse[:, resp], wlse[:, resp]
     assert float((o.float() - whole.float()).norm() / whole.float().norm()) < 4e-3      # weights rounded to bf16 against other references
     assert float((lse - wlse).abs().max()) < 2e-5
+
+
+@pytest.mark.parametrize("heads", [(4, 2), (8, 1)])
+@pytest.mark.parametrize("name", list(PACKS))
+def test_rows_of_a_full_forward_do_not_depend_on_the_call(name, heads):
+    """Several sets in one call, a call of one set on any workspace and one with a residual of its own: the same bits.  (The policy's
+    log-probabilities come from one of them, those of the old policy from another, and their ratio is one.)"""
+    w, t, _, pk = _setup(name, heads, 794)
+    q, k, v = t.q.cuda(), t.k.cuda(), t.v.cuda()
+    n, r, T = len(w.groups), len(pk[2]), w.total_tokens
+    os, lses = B.sp_attn_fwd_multi([q, q], [k, k], [v, v], *pk)
+    one = B.sp_attn_fwd_batched(q, k, v, *pk)
+    least = torch.empty(B.workspace_bytes(False, T, n, r, *heads, 128, B.SP_BF16), dtype=torch.uint8, device="cuda")
+    small = B.sp_attn_fwd_batched(q, k, v, *pk, workspace=least)
+    lo = B.sp_attn_fwd_batched_ex(q, k, v, *pk, 0, o_lo=torch.empty_like(q))
+    torch.cuda.synchronize()
+    for o, lse in (one, small, lo):
+        assert torch.equal(o, os[1]) and torch.equal(lse, lses[1])
 
 
 @pytest.mark.parametrize("log2_scale", [-118, 100])
 @pytest.mark.parametrize("name", ["two_prompts", "no_prompt"])
 def test_extreme_scales(name, log2_scale):
     """Rows that see no key of a part start from a reference point that stays finite, times the scale too (as test_gpu_scales.py)."""
-    w, t, _, pk = _setup(name, (4, 2), 793)
+    w, t, resp, pk = _setup(name, (4, 2), 793)
     e = -3 - log2_scale
     fq, fk = 2.0 ** (e // 2), 2.0 ** (e - e // 2)
     q, k, v, d_o = (t.q * fq).cuda(), (t.k * fk).cuda(), t.v.cuda(), t.d_o.cuda()
     o, lse = B.sp_attn_fwd_batched(q, k, v, *pk[:3], 2.0 ** log2_scale)
+    parts, plse = B.sp_attn_fwd_batched_ex(q, k, v, *pk[:3], 2.0 ** log2_scale, B.SP_FLAG_RESPONSE_ROWS)
     dq, dk, dv = B.sp_attn_bwd_batched(q, k, v, o, lse, d_o, *pk[:3], 2.0 ** log2_scale)
     torch.cuda.synchronize()
     w.scale = 2.0 ** -3
     rdq, rdk, rdv, ro, rlse = oracle_bwd(w, t)
     gate("O", to64(o), ro, w.dtype)
     gate_lse(to64(lse), rlse, w.dtype)
+    gate("O of response rows", to64(parts)[resp], ro[resp], w.dtype)
+    gate_lse(to64(plse)[:, resp], rlse[:, resp], w.dtype)
     gate("dQ", to64(dq) * fq, rdq, w.dtype)
     gate("dK", to64(dk) * fk, rdk, w.dtype)
     gate("dV", to64(dv), rdv, w.dtype)
