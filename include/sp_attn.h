@@ -425,6 +425,13 @@ sp_status sp_attn_row_tile(int32_t n_groups, const int32_t* prompt_lens, const i
 sp_status sp_attn_dkdv_waves(int32_t n_groups, const int32_t* prompt_lens, const int32_t* Gs, const int32_t* resp_lens_flat,
                              int32_t n_q_heads, int32_t n_kv_heads, uint32_t flags, int32_t* waves);
 
+/* How a float32 call on this packing spreads its rows (dkdv pass: keys): rows[0 .. 2] = rows per workgroup of the forward, the
+ * dq pass and the dkdv pass, 16 (eight waves, products on matrix instructions), 4 (a wave each) or 1 (eight waves each).  flags as in
+ * sp_attn_bwd_batched_ex.  Host arithmetic on the lengths; no device work; for tools and tests.  Errors as the host checks
+ * of sp_attn_bwd_batched_ex. */
+sp_status sp_attn_f32_rows(int32_t n_groups, const int32_t* prompt_lens, const int32_t* Gs, const int32_t* resp_lens_flat,
+                           int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim, uint32_t flags, int32_t* rows);
+
 /* Tuning knob, process-wide (no counterpart in the paper).  The bf16 kernels come in two workgroup
  * shapes: eight waves with one workgroup per CU, for long key loops, and four waves with two
  * workgroups per CU, whose fixed per-workgroup costs overlap, for batches of short or ragged groups.  By default a call

@@ -24,7 +24,7 @@ SP_FLAG_RESPONSE_ROWS, SP_FLAG_ACCUMULATE_DKDV, SP_FLAG_ZERO_PROMPT_ROWS = 1, 2,
 EXPORTS = ("sp_attn_workspace_bytes", "sp_attn_reserve_bytes", "sp_attn_row_parts_bytes", "sp_attn_full_workspace_bytes", "sp_attn_fwd", "sp_attn_bwd", "sp_attn_fwd_batched",
            "sp_attn_bwd_batched", "sp_attn_bwd_batched_static", "sp_attn_bwd_batched_stages", "sp_attn_fwd_multi", "sp_attn_rope", "sp_attn_rope_qk", "sp_attn_fwd_batched_ex", "sp_attn_bwd_batched_ex",
            "sp_attn_loss_workspace_bytes", "sp_attn_logprob_fwd", "sp_attn_logprob_bwd", "sp_attn_logprob_bwd_ex", "sp_attn_grpo_loss",
-           "sp_attn_segment_table", "sp_attn_row_tile", "sp_attn_dkdv_waves", "sp_attn_mfma_ceiling", "sp_attn_probe_atomic_add", "sp_attn_set_small_shape_steps", "sp_attn_last_error", "sp_attn_version")
+           "sp_attn_segment_table", "sp_attn_row_tile", "sp_attn_dkdv_waves", "sp_attn_f32_rows", "sp_attn_mfma_ceiling", "sp_attn_probe_atomic_add", "sp_attn_set_small_shape_steps", "sp_attn_last_error", "sp_attn_version")
 
 _lib = None
 
@@ -99,6 +99,8 @@ def load_library() -> ctypes.CDLL:
     lib.sp_attn_segment_table.argtypes = [i32, ip, ip, ip, ip, sz, ctypes.POINTER(sz)]
     lib.sp_attn_dkdv_waves.restype = ctypes.c_int
     lib.sp_attn_dkdv_waves.argtypes = [i32, ip, ip, ip, i32, i32, ctypes.c_uint32, ctypes.POINTER(ctypes.c_int32)]
+    lib.sp_attn_f32_rows.restype = ctypes.c_int
+    lib.sp_attn_f32_rows.argtypes = [i32, ip, ip, ip, i32, i32, i32, ctypes.c_uint32, ctypes.POINTER(ctypes.c_int32)]
     lib.sp_attn_row_tile.restype = ctypes.c_int
     lib.sp_attn_row_tile.argtypes = [i32, ip, ip, ip, ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_int64),
                                      ctypes.POINTER(ctypes.c_int64)]
@@ -152,6 +154,16 @@ def sp_attn_dkdv_waves(prompt_lens: Sequence[int], Gs: Sequence[int], resp_lens_
     _check(load_library().sp_attn_dkdv_waves(len(prompt_lens), _i32(prompt_lens), _i32(Gs), _i32(resp_lens_flat), n_q_heads,
                                              n_kv_heads, flags, ctypes.byref(waves)))
     return waves.value
+
+
+def sp_attn_f32_rows(prompt_lens: Sequence[int], Gs: Sequence[int], resp_lens_flat: Sequence[int], n_q_heads: int, n_kv_heads: int,
+                     head_dim: int, flags: int = 0):
+    """Rows (keys) per workgroup, 16, 4 or 1, of the forward, the dq pass and the dkdv pass of a float32 call on this packing.  Host
+    arithmetic only."""
+    rows = (ctypes.c_int32 * 3)()
+    _check(load_library().sp_attn_f32_rows(len(prompt_lens), _i32(prompt_lens), _i32(Gs), _i32(resp_lens_flat), n_q_heads, n_kv_heads,
+                                           head_dim, flags, rows))
+    return tuple(rows)
 
 
 def _i32(xs: Sequence[int]):

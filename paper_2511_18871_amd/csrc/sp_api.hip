@@ -662,6 +662,25 @@ sp_status sp_attn_dkdv_waves(int32_t n_groups, const int32_t* prompt_lens, const
     return SP_OK;
 }
 
+sp_status sp_attn_f32_rows(int32_t n_groups, const int32_t* prompt_lens, const int32_t* Gs, const int32_t* resp_lens_flat,
+                           int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim, uint32_t flags, int32_t* rows) {
+    g_err[0] = 0;
+    if (!rows) return fail(SP_ERR_INVALID_ARG, "rows is NULL");
+    if (flags & ~(unsigned)(SP_FLAG_RESPONSE_ROWS | SP_FLAG_ACCUMULATE_DKDV))
+        return fail(SP_ERR_INVALID_ARG, "unknown bits in flags=0x%x", flags);
+    sp_status st = check_geometry(n_q_heads, n_kv_heads, head_dim, 1.f, SP_F32);
+    if (st != SP_OK) return st;
+    Layout L;
+    st = build_table(n_groups, prompt_lens, Gs, resp_lens_flat, L);
+    if (st != SP_OK) return st;
+    sp::Problem p{};
+    p.n_groups = n_groups; p.total_tokens = L.total_tokens; p.Hq = n_q_heads; p.Hkv = n_kv_heads; p.head_dim = head_dim;
+    p.resp_only = (flags & SP_FLAG_RESPONSE_ROWS) != 0;
+    p.host_table = L.words.data();
+    for (int kernel = 0; kernel < 3; ++kernel) rows[kernel] = sp::f32_rows(p, kernel);
+    return SP_OK;
+}
+
 namespace {
 constexpr int MAX_DEVICES = 64;
 std::atomic<void*> g_scratch_ptr[MAX_DEVICES];      // device address of `scratch` on each GPU, 0 = not asked yet

@@ -5,6 +5,7 @@
 // the allowed keys / rows of the Section 4.3 mask in chunks, in float32 throughout: they exist to cross-check the bf16 path and to serve float32 callers.
 #include "sp_common.hpp"
 #include "sp_launch.hpp"
+#include <algorithm>
 #include <type_traits>
 
 namespace sp {
@@ -233,7 +234,7 @@ __global__ __launch_bounds__(256) void rowsum_bf16_kernel(const __bf16* __restri
 // Few rows (keys): a workgroup of eight waves per (row, head) or (key, kv head), bound by latency: every wave takes each eighth chunk
 // of 32 keys, two lanes per key, with one batch of loads for the scores and one (rows 32 at a time, lanes along a row) for
 // the sums.  The waves' sums meet in LDS, in a fixed order.  (WIDE; else one wave and chunks of 64 keys, a lane per key, the wave's
-// own row in scalar registers: for single rows of the blocks below.)
+// own row in scalar registers: where rows see few keys, and for single rows of the blocks below.  Which shape: f32_shape().)
 // With the rowsum within the dq kernel and the table as an argument, a training pass of 64 + 4 x 32 tokens, 2 heads of 64: 54.0 ->
 // 33.0 us.
 constexpr int F32_WAVES = 8;
@@ -247,18 +248,19 @@ __device__ __forceinline__ float dot_row(const float* __restrict__ x, const floa
     f32x4 v[N];
 #pragma unroll
     for (int i = 0; i < N; ++i) v[i] = *reinterpret_cast<const f32x4*>(y + at + 4 * i);
-    float acc = 0.f;
+    f32x4 part = {0.f, 0.f, 0.f, 0.f};             // four short sums, as in the blocks below
     if constexpr (WIDE) {
         f32x4 u[N];
 #pragma unroll
         for (int i = 0; i < N; ++i) u[i] = *reinterpret_cast<const f32x4*>(x + at + 4 * i);
+        __builtin_amdgcn_sched_barrier(0);         // all loads in flight: left alone, each waited for the products of the one before
 #pragma unroll
-        for (int i = 0; i < 4 * N; ++i) acc = __builtin_fmaf(u[i >> 2][i & 3], v[i >> 2][i & 3], acc);
-        return pair_sum(acc);
+        for (int i = 0; i < 4 * N; ++i) part[i & 3] = __builtin_fmaf(u[i >> 2][i & 3], v[i >> 2][i & 3], part[i & 3]);
+        return pair_sum((part[0] + part[1]) + (part[2] + part[3]));
     }
 #pragma unroll
-    for (int i = 0; i < 4 * N; ++i) acc = __builtin_fmaf(x[i], v[i >> 2][i & 3], acc);
-    return acc;
+    for (int i = 0; i < 4 * N; ++i) part[i & 3] = __builtin_fmaf(x[i], v[i >> 2][i & 3], part[i & 3]);
+    return (part[0] + part[1]) + (part[2] + part[3]);
 }
 __device__ __forceinline__ float lane_value(float x, int lane) {      // of a wave-uniform lane
     return __uint_as_float((unsigned)__builtin_amdgcn_readlane((int)__float_as_uint(x), lane));
@@ -316,6 +318,18 @@ struct KeyChunks {
     __device__ __forceinline__ int first(int i) const { return i < n1 ? C * i : st + C * (i - n1); }
     __device__ __forceinline__ int count(int i) const { return min(C, (i < n1 ? end1 : end) - first(i)); }
 };
+
+// The row (key) and head of a workgroup, or of its wave w; false past the last one
+template <bool WIDE>
+__device__ __forceinline__ bool row_and_head(int w, int64_t T_total, int heads, int& tok, int& h) {
+    if constexpr (WIDE) {
+        tok = (int)(blockIdx.x / (unsigned)heads); h = (int)(blockIdx.x % (unsigned)heads);
+        return true;
+    }
+    const int64_t item = (int64_t)blockIdx.x * 4 + w;
+    tok = (int)(item / heads); h = (int)(item % heads);
+    return item < T_total * heads;
+}
 
 // One row of one head: by one wave, or (WIDE) by the workgroup's eight
 template <int DH, bool WIDE>
@@ -382,15 +396,16 @@ __device__ __forceinline__ void fwd_f32_row(const GroupDesc& gd, int tok, int h,
     if (threadIdx.x == 0) lse[(int64_t)h * T_total + tok] = mt + logf(ls);
 }
 
-template <int DH>
-__global__ __launch_bounds__(F32_BLOCK<true>) void fwd_f32_kernel(TabArg table, const float* __restrict__ q, const float* __restrict__ k,
+template <int DH, bool WIDE>
+__global__ __launch_bounds__(F32_BLOCK<WIDE>) void fwd_f32_kernel(TabArg table, const float* __restrict__ q, const float* __restrict__ k,
                                                                  const float* __restrict__ v, float* __restrict__ o,
                                                                  float* __restrict__ lse, int64_t T_total, int Hq, int Hkv,
                                                                  float scale, int resp_only) {
     const int* const tab = table_of(table);
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
-    const int tok = (int)(blockIdx.x / (unsigned)Hq), h = (int)(blockIdx.x % (unsigned)Hq);
-    fwd_f32_row<DH, true>(load_group(tab, find_group_of_token(tab, tok)), tok, h, w, l, q, k, v, o, lse, T_total, Hq, Hkv, scale, resp_only);
+    int tok, h;
+    if (!row_and_head<WIDE>(w, T_total, Hq, tok, h)) return;
+    fwd_f32_row<DH, WIDE>(load_group(tab, find_group_of_token(tab, tok)), tok, h, w, l, q, k, v, o, lse, T_total, Hq, Hkv, scale, resp_only);
 }
 
 // dQ[t,h] = scale * sum_s dS[t,s] K[s],  dS = P * (dP - D)
@@ -451,17 +466,18 @@ __device__ __forceinline__ void dq_f32_row(const GroupDesc& gd, int tok, int h, 
     dq[row * DH + threadIdx.x] = scale * x;
 }
 
-template <int DH>
-__global__ __launch_bounds__(F32_BLOCK<true>, DH == 64 ? 4 : 1) void bwd_dq_f32_kernel(TabArg table, const float* __restrict__ q, const float* __restrict__ k,
+template <int DH, bool WIDE>
+__global__ __launch_bounds__(F32_BLOCK<WIDE>, WIDE && DH == 64 ? 4 : 1) void bwd_dq_f32_kernel(TabArg table, const float* __restrict__ q, const float* __restrict__ k,
                                                                     const float* __restrict__ v, const float* __restrict__ d_o,
                                                                     const float* __restrict__ o, const float* __restrict__ lse,
                                                                     float* __restrict__ D, float* __restrict__ dq, uint32_t* __restrict__ tag,
                                                                     int64_t T_total, int Hq, int Hkv, float scale, int resp_only) {
     const int* const tab = table_of(table);
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
-    const int tok = (int)(blockIdx.x / (unsigned)Hq), h = (int)(blockIdx.x % (unsigned)Hq);
+    int tok, h;
+    if (!row_and_head<WIDE>(w, T_total, Hq, tok, h)) return;
     if (tag && blockIdx.x == 0 && w == 0) tag[l] = 0u;
-    dq_f32_row<DH, true>(load_group(tab, find_group_of_token(tab, tok)), tok, h, w, l, q, k, v, d_o, o, lse, D, dq, T_total, Hq, Hkv, scale, resp_only);
+    dq_f32_row<DH, WIDE>(load_group(tab, find_group_of_token(tab, tok)), tok, h, w, l, q, k, v, d_o, o, lse, D, dq, T_total, Hq, Hkv, scale, resp_only);
 }
 
 // dK[s,g] = scale * sum_{h in g} sum_t dS[t,s] Q[t,h];  dV[s,g] = sum_{h in g} sum_t P[t,s] dO[t,h].
@@ -523,8 +539,8 @@ __device__ __forceinline__ void dkdv_f32_key(const GroupDesc& gd, int tok, int k
     }
 }
 
-template <int DH>
-__global__ __launch_bounds__(F32_BLOCK<true>) void bwd_dkdv_f32_kernel(TabArg table, const float* __restrict__ q, const float* __restrict__ k,
+template <int DH, bool WIDE>
+__global__ __launch_bounds__(F32_BLOCK<WIDE>) void bwd_dkdv_f32_kernel(TabArg table, const float* __restrict__ q, const float* __restrict__ k,
                                                                       const float* __restrict__ v, const float* __restrict__ d_o,
                                                                       const float* __restrict__ lse, const float* __restrict__ D,
                                                                       float* __restrict__ dk, float* __restrict__ dv,
@@ -532,8 +548,9 @@ __global__ __launch_bounds__(F32_BLOCK<true>) void bwd_dkdv_f32_kernel(TabArg ta
                                                                       int resp_only, int accumulate) {
     const int* const tab = table_of(table);
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
-    const int tok = (int)(blockIdx.x / (unsigned)Hkv), kvh = (int)(blockIdx.x % (unsigned)Hkv);
-    dkdv_f32_key<DH, true>(load_group(tab, find_group_of_token(tab, tok)), tok, kvh, w, l, q, k, v, d_o, lse, D, dk, dv, T_total, Hq, Hkv, scale,
+    int tok, kvh;
+    if (!row_and_head<WIDE>(w, T_total, Hkv, tok, kvh)) return;
+    dkdv_f32_key<DH, WIDE>(load_group(tab, find_group_of_token(tab, tok)), tok, kvh, w, l, q, k, v, d_o, lse, D, dk, dv, T_total, Hq, Hkv, scale,
                            resp_only, accumulate);
 }
 
@@ -956,21 +973,82 @@ hipError_t launch_rowsum(const Problem& p, bool f32, hipStream_t s) {
     return hipGetLastError();
 }
 
-// Calls f(head dimension, grid, workgroup) for few rows (keys) times heads, else block().  us, row by row and in blocks, one group, half of
-// it prompt, five answers, 4 / 2 heads:
-//   heads of 64    191 tokens: forward 9.2, 11.2, dq 13.5, 14.2, dkdv 16.4, 22.1; 253: 10.4, 11.1, 15.9, 14.3, 21.3, 24.6; 382: 19.5,
-//                  11.5, 27.7, 14.8, 40.1, 32.9; 800: 57, 16.6, 84, 20.9, 137, 59
-//   heads of 128   93 tokens: 9.2, 12.0, 12.2, 16.0, 13.3, 26.8; 150: 14.7, 13.9, 18.8, 18.6, 18.2, 34.0; 382: 38.9, 14.9, 54.3, 20.3,
-//                  53.6, 54.0; 800: 122, 23.6, 183, 32.4, 186, 100
-// Before, with one wave per row or key instead of blocks: forward and backward of 5 x (80 + 2 x 200) tokens, 4 / 4 heads of 128 161 -> 45
-// and 615 -> 157; 955 tokens, 4 / 2 80 -> 22 and 409 -> 101; 873, 43 -> 15 and 401 -> 127; 1759, 4 / 4 heads of 64 62 -> 23 and 211 -> 73.  Errors against float64 (o, dq, dk, dv, 1e-7): 955 tokens, heads of 128 3.4, 5.1, 7.6, 7.0 -> 1.8, 3.2,
-// 3.6, 3.2; 1152, heads of 64 1.7, 3.2, 3.6, 3.4 -> 1.6, 3.1, 3.5, 3.3.
+namespace {
+// Rows (keys) times heads of a float32 kernel; the chunks of 32 keys (rows) that they walk, and the longest one's; blocks of 16 times
+// heads, one for each group of which it holds tokens, and the most of them in one block.
+struct F32Counts { int64_t items = 0, chunks = 0, blocks = 0; int longest = 0, spans = 1; };
+// sum of ceil(i / 32) over i = 1 .. n
+inline int64_t chunks_to(int64_t n) { const int64_t c = n / 32; return 16 * c * (c + 1) + (n - 32 * c) * (c + 1); }
+inline F32Counts f32_counts(const Problem& p, bool keys) {
+    F32Counts n;
+    const int heads = keys ? p.Hkv : p.Hq, rep = keys ? p.Hq / p.Hkv : 1;
+    int spans = 0, block = -1;
+    for (int g = 0; g < p.n_groups; ++g) {
+        const int32_t* e = p.host_table + TAB_HEADER + TAB_GROUP_WORDS * g;
+        const int32_t* roff = p.host_table + e[3];
+        const int Lp = e[1], Tg = e[2], lo = p.resp_only ? Tg - Lp : Tg, prompt = (Lp + 31) / 32;      // lo: rows that see prompt key 0
+        if (keys) n.chunks += p.resp_only ? (int64_t)Lp * ((lo + 31) / 32) : chunks_to(Tg) - chunks_to(Tg - Lp);
+        else if (!p.resp_only) n.chunks += chunks_to(Lp);
+        int most = keys ? (Lp > 0 ? (lo + 31) / 32 : 0) : (p.resp_only ? 0 : prompt);
+        for (int i = 0; i < e[4]; ++i) {
+            const int len = roff[i + 1] - roff[i];
+            n.chunks += chunks_to(len) + (keys ? 0 : (int64_t)len * prompt);
+            most = std::max(most, (len + 31) / 32 + (keys || len == 0 ? 0 : prompt));
+        }
+        n.longest = std::max(n.longest, most * rep);
+        n.blocks += e[0] % BLK != 0;
+        spans = e[0] / BLK == block ? spans + 1 : 1 + (e[0] % BLK != 0);      // groups that begin in the block so far, and one that reaches into it
+        block = e[0] / BLK;
+        n.spans = std::max(n.spans, spans);
+    }
+    n.chunks *= p.Hq;
+    n.items = p.total_tokens * heads;
+    n.blocks = (n.blocks + (p.total_tokens + BLK - 1) / BLK) * heads;
+    return n;
+}
+// The shape with the least time by its counts: a launch takes `fixed` us, and behind that as long as its longest workgroup (`step` per round of
+// chunks, one of a lone wave, eight of eight waves, 16 in a block, and `span` for each further group of a block) or as all of them
+// together (`item` per row or block, `chunk` per chunk of a row or a block).  Fitted to 500 packings of 20 to 12000 tokens, one to 150 groups, 2 / 1 to
+// 16 / 4 heads, each timed in all three shapes: rms of an estimate 6 to 19 %; the shape taken costs 0.8 % over the best one on average.
+// By rows times heads alone (blocks from 760, 550 and 700 on, and no row by a wave) what takes few chunks, or holds many groups, had lost to
+// a wave or a workgroup per row; us, by rows times heads -> by counts: 8 + 100 x 30 tokens, 4 / 2 heads of 64, dkdv 210 -> 133; 32 + 40 x 20, 4 / 2
+// of 128, dkdv 115 -> 69; 25 x (3 x 3), 4 / 2 of 128, forward 20.5 -> 13.7; 3 x (5 + 3 x 20), 4 / 4 of 64, 45 -> 29 in all; 500 packings 0.94
+// of the time on average.
+enum F32Shape { BY_WAVE, BY_WORKGROUP, BY_BLOCK };       // rows (keys) per workgroup: 4, 1, 16
+struct F32Time { float fixed, step, item, chunk, span; };
+constexpr F32Time F32_TIMES[3][2][3] = {       // [forward, dq, dkdv][heads of 64, 128][F32Shape]
+    {{{4.8f, 1.7f, .0006f, .0010f, 0.f}, {3.8f, 2.4f, .0047f, .0012f, 0.f}, {4.5f, 5.5f, .028f, .0024f, 3.7f}},
+     {{5.4f, 2.9f, 0.f, .0026f, 0.f}, {3.5f, 6.2f, .0099f, .0027f, 0.f}, {5.3f, 6.9f, .033f, .0061f, 4.0f}}},
+    {{{6.3f, 2.0f, .0007f, .0016f, 0.f}, {3.9f, 2.6f, .0032f, .0023f, 0.f}, {5.5f, 6.1f, .024f, .0045f, 2.0f}},
+     {{7.2f, 3.8f, 0.f, .0042f, 0.f}, {4.4f, 6.1f, .0077f, .0044f, 0.f}, {6.9f, 7.7f, .027f, .011f, 3.1f}}},
+    {{{6.5f, 3.4f, 0.f, .0036f, 0.f}, {2.4f, 5.4f, .0050f, .0029f, 0.f}, {5.0f, 14.f, .041f, .0078f, 3.8f}},
+     {{5.3f, 6.3f, 0.f, .0057f, 0.f}, {1.0f, 9.5f, .013f, .0052f, 0.f}, {1.9f, 28.f, .085f, .014f, 6.5f}}}};
+F32Shape f32_shape(const F32Counts& n, int kernel, int head_dim) {
+    const F32Time* const t = F32_TIMES[kernel][head_dim == 64 ? 0 : 1];
+    auto time = [&](F32Shape s, int per_step, int64_t items, int per_chunk, int spans) {
+        return t[s].fixed + std::max(t[s].step * (float)((n.longest + per_step - 1) / per_step) + t[s].span * (float)(spans - 1),
+                                     t[s].item * (float)items + t[s].chunk * (float)n.chunks / (float)per_chunk);
+    };
+    const float wave = time(BY_WAVE, 1, n.items, 1, 1), group = time(BY_WORKGROUP, F32_WAVES, n.items, 1, 1);
+    const float block = time(BY_BLOCK, 2 * F32_WAVES, n.blocks, BLK, n.spans);
+    return block <= std::min(wave, group) ? BY_BLOCK : group <= wave ? BY_WORKGROUP : BY_WAVE;
+}
+}  // namespace
+
+int f32_rows(const Problem& p, int kernel) {
+    constexpr int ROWS[3] = {4, 1, BLK};
+    return ROWS[f32_shape(f32_counts(p, kernel == 2), kernel, p.head_dim)];
+}
+
+// Calls row(head dimension, WIDE, grid, workgroup) or block(head dimension, grid, workgroup).
 template <typename F, typename G>
-void with_f32_shape(const Problem& p, int heads, int64_t limit64, int64_t limit128, F f, G block) {
+void with_f32_shape(const Problem& p, int kernel, F row, G block) {
+    const int heads = kernel == 2 ? p.Hkv : p.Hq, rows = f32_rows(p, kernel);
+    const dim3 grid((unsigned)(rows == BLK ? (p.total_tokens + BLK - 1) / BLK * heads : (p.total_tokens * heads + rows - 1) / rows));
     auto sized = [&](auto dh) {
-        const bool few = p.total_tokens * heads <= (decltype(dh)::value == 64 ? limit64 : limit128);
-        if (few) f(dh, dim3((unsigned)(p.total_tokens * heads)), dim3(F32_BLOCK<true>));
-        else block(dh, dim3((unsigned)((p.total_tokens + BLK - 1) / BLK * heads)), dim3(64 * F32_WAVES));
+        if (rows == 4) row(dh, std::false_type{}, grid, dim3(F32_BLOCK<false>));
+        else if (rows == 1) row(dh, std::true_type{}, grid, dim3(F32_BLOCK<true>));
+        else block(dh, grid, dim3(64 * F32_WAVES));
     };
     if (p.head_dim == 64) sized(std::integral_constant<int, 64>{}); else sized(std::integral_constant<int, 128>{});
 }
@@ -983,8 +1061,8 @@ hipError_t launch_fwd_f32(const Problem& p, hipStream_t s) {
         hipLaunchKernelGGL(kernel, grid, block, 0, s, f32_table(p), (const float*)p.q, (const float*)p.k, (const float*)p.v,
                            (float*)p.o_out, p.lse_out, p.total_tokens, p.Hq, p.Hkv, p.scale, p.resp_only);
     };
-    with_f32_shape(p, p.Hq, 760, 550,
-        [&](auto dh, dim3 grid, dim3 block) { go(fwd_f32_kernel<decltype(dh)::value>, grid, block); },
+    with_f32_shape(p, 0,
+        [&](auto dh, auto wide, dim3 grid, dim3 block) { go(fwd_f32_kernel<decltype(dh)::value, decltype(wide)::value>, grid, block); },
         [&](auto dh, dim3 grid, dim3 block) { go(fwd_f32_block_kernel<decltype(dh)::value>, grid, block); });
     return hipGetLastError();
 }
@@ -1001,8 +1079,8 @@ hipError_t launch_bwd_f32(const Problem& p, hipStream_t s) {
                                (const float*)p.d_o, fused ? (const float*)p.o : nullptr, p.lse, p.Dbuf, (float*)p.dq,
                                p.small.on ? p.small.tag : nullptr, p.total_tokens, p.Hq, p.Hkv, p.scale, p.resp_only);
         };
-        with_f32_shape(p, p.Hq, 760, 550,
-            [&](auto dh, dim3 grid, dim3 block) { go(bwd_dq_f32_kernel<decltype(dh)::value>, grid, block); },
+        with_f32_shape(p, 1,
+            [&](auto dh, auto wide, dim3 grid, dim3 block) { go(bwd_dq_f32_kernel<decltype(dh)::value, decltype(wide)::value>, grid, block); },
             [&](auto dh, dim3 grid, dim3 block) { go(bwd_dq_f32_block_kernel<decltype(dh)::value>, grid, block); });
     }
     if (p.stages & STAGE_DKDV) {
@@ -1011,8 +1089,8 @@ hipError_t launch_bwd_f32(const Problem& p, hipStream_t s) {
                                (const float*)p.d_o, p.lse, p.Dbuf, (float*)p.dk, (float*)p.dv, p.total_tokens, p.Hq, p.Hkv, p.scale,
                                p.resp_only, p.accumulate);
         };
-        with_f32_shape(p, p.Hkv, 700, 760,
-            [&](auto dh, dim3 grid, dim3 block) { go(bwd_dkdv_f32_kernel<decltype(dh)::value>, grid, block); },
+        with_f32_shape(p, 2,
+            [&](auto dh, auto wide, dim3 grid, dim3 block) { go(bwd_dkdv_f32_kernel<decltype(dh)::value, decltype(wide)::value>, grid, block); },
             [&](auto dh, dim3 grid, dim3 block) { go(bwd_dkdv_f32_block_kernel<decltype(dh)::value>, grid, block); });
     }
     return hipGetLastError();

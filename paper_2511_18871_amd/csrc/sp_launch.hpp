@@ -349,6 +349,9 @@ inline TabArg with_list(TabArg t, const Problem& p, const std::vector<uint32_t>&
     return t;
 }
 
+// Rows (keys) per workgroup of a float32 kernel (0 forward, 1 dq, 2 dkdv): 16, 4 or 1 (rule and reasons: sp_f32.hip).
+int f32_rows(const Problem& p, int kernel);
+
 // Waves per workgroup (8 or 4) of a dkdv pass that is not split over the q heads (rule and reasons: sp_bwd.hip).
 int dkdv_waves(const Problem& p);
 

@@ -31,7 +31,7 @@ def test_an_infinite_last_row_stays_infinite(T, d):
 
 
 # a NaN among the keys reaches every row that sees it, also where it is alone in a chunk of keys, and no other row
-@pytest.mark.parametrize("d,heads", [(64, 2), (64, 56), (128, 2), (128, 12)])         # eight waves per row, one wave
+@pytest.mark.parametrize("d,heads", [(64, 2), (64, 56), (128, 2), (128, 12)])         # eight waves per row, blocks of 16 rows
 @pytest.mark.parametrize("key", [0, 31, 63, 64, 65, 104])
 def test_a_nan_key_reaches_the_rows_that_see_it(key, d, heads):
     prompt, resp = 64, [1, 40]
@@ -57,3 +57,21 @@ def test_a_chunk_of_nan_keys_is_not_passed_over(d, heads):
     o, lse = B.sp_attn_fwd(q.cuda(), k.cuda(), v.cuda(), T, [], d ** -0.5)
     torch.cuda.synchronize()
     assert o.isnan().all() and lse.isnan().all()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_a_nan_key_of_a_short_group_stays_in_its_group(d):
+    """Rows by a wave each (a block of 16 would span two groups)."""
+    n, prompt, resp, heads = 24, 7, [3, 1], 8
+    T, pack, gen = n * 11, ([prompt] * n, [2] * n, resp * n), torch.Generator().manual_seed(d)
+    assert B.sp_attn_f32_rows(*pack, heads, heads, d)[0] == 4
+    q, k, v = (torch.randn(T, heads, d, generator=gen) for _ in range(3))
+    clean, _ = B.sp_attn_fwd_batched(q.cuda(), k.cuda(), v.cuda(), *pack, d ** -0.5)
+    key = 5 * 11 + 8                                     # the second token of the sixth group's first response
+    k[key] = float("nan")
+    o, lse = B.sp_attn_fwd_batched(q.cuda(), k.cuda(), v.cuda(), *pack, d ** -0.5)
+    torch.cuda.synchronize()
+    sees = torch.zeros(T, dtype=torch.bool, device="cuda")
+    sees[key:key + 2] = True
+    assert o[sees].isnan().all() and lse[:, sees].isnan().all()
+    assert torch.equal(o[~sees], clean[~sees]) and lse[:, ~sees].isfinite().all()
