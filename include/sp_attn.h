@@ -112,9 +112,15 @@ size_t sp_attn_row_parts_bytes(int64_t total_tokens, int32_t n_groups, int32_t n
  * and behind them room for partial sums (bf16, up to 640 key tiles of 128, at most 48 MB): where few key tiles are seen by many
  * rows, or few rows see many keys, such a tile's rows and q heads, or such rows' keys, then go to several workgroups, which
  * changes the order in which dk and dv, or dq and the o and lse of a forward with SP_FLAG_RESPONSE_ROWS, are summed.  With less both run
- * without.  The o and lse of a forward of all rows do not depend on the workspace. */
+ * without.  The o and lse of a forward of all rows do not depend on the workspace.  No partial sum outlives its call: a caller that keeps
+ * a workspace from a forward to its backward can hand the room for them to each call apart (sp_attn_sums_bytes()). */
 size_t sp_attn_full_workspace_bytes(int64_t total_tokens, int32_t n_groups, int64_t total_responses, int32_t n_q_heads,
                                     int32_t n_kv_heads, int32_t head_dim, sp_dtype dtype);
+
+/* Its two parts: what a forward and its backward share, and the room for partial sums (see sp_attn_bwd_batched_sums()). */
+size_t sp_attn_kept_workspace_bytes(int64_t total_tokens, int32_t n_groups, int64_t total_responses, int32_t n_q_heads,
+                                    int32_t n_kv_heads, int32_t head_dim, sp_dtype dtype);
+size_t sp_attn_sums_bytes(int64_t total_tokens, int32_t n_groups, int32_t n_q_heads, int32_t n_kv_heads, sp_dtype dtype);
 
 /* Forward for one group (Section 4.3, modifications 1 and 3): writes
  * o [T, n_q_heads, head_dim] and lse [n_q_heads, T], T = prompt_len + sum(resp_lens).
@@ -267,6 +273,26 @@ sp_status sp_attn_bwd_batched_ex(const void* q, const void* k, const void* v,
                                  float softmax_scale, sp_dtype dtype, uint32_t stages,
                                  uint32_t flags, const void* o_lo,
                                  void* workspace, size_t workspace_bytes, void* stream);
+
+/* The same with the room for partial sums (sp_attn_sums_bytes()) apart from the workspace.
+ *   sums   DEVICE, 16-byte aligned, sums_bytes bytes; holds nothing before or after the call, so that one buffer may serve all calls
+ *          of a stream.  NULL: the call above.  With fewer bytes than sp_attn_sums_bytes() the call runs without. */
+sp_status sp_attn_fwd_batched_sums(const void* q, const void* k, const void* v, void* o, float* lse,
+                                   int32_t n_groups, const int32_t* prompt_lens,
+                                   const int32_t* Gs, const int32_t* resp_lens_flat,
+                                   int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim,
+                                   float softmax_scale, sp_dtype dtype, sp_schedule schedule,
+                                   uint32_t flags, void* o_lo, void* sums, size_t sums_bytes,
+                                   void* workspace, size_t workspace_bytes, void* stream);
+sp_status sp_attn_bwd_batched_sums(const void* q, const void* k, const void* v,
+                                   const void* o, const float* lse, const void* d_o,
+                                   void* dq, void* dk, void* dv,
+                                   int32_t n_groups, const int32_t* prompt_lens,
+                                   const int32_t* Gs, const int32_t* resp_lens_flat,
+                                   int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim,
+                                   float softmax_scale, sp_dtype dtype, uint32_t stages,
+                                   uint32_t flags, const void* o_lo, void* sums, size_t sums_bytes,
+                                   void* workspace, size_t workspace_bytes, void* stream);
 
 /* Forward for several tensor sets that share ONE packing, in one launch: the policy, old-policy
  * and reference models of a GRPO step score the same packed sequences, so their three

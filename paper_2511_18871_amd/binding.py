@@ -21,8 +21,8 @@ SP_SCHED_SHARED, SP_SCHED_NAIVE_CAUSAL = 0, 1
 SP_BWD_STAGE_ROWSUM, SP_BWD_STAGE_DKDV, SP_BWD_STAGE_DQ, SP_BWD_STAGE_ALL = 1, 2, 4, 7
 SP_FLAG_RESPONSE_ROWS, SP_FLAG_ACCUMULATE_DKDV, SP_FLAG_ZERO_PROMPT_ROWS = 1, 2, 4
 
-EXPORTS = ("sp_attn_workspace_bytes", "sp_attn_reserve_bytes", "sp_attn_row_parts_bytes", "sp_attn_full_workspace_bytes", "sp_attn_fwd", "sp_attn_bwd", "sp_attn_fwd_batched",
-           "sp_attn_bwd_batched", "sp_attn_bwd_batched_static", "sp_attn_bwd_batched_stages", "sp_attn_fwd_multi", "sp_attn_rope", "sp_attn_rope_qk", "sp_attn_fwd_batched_ex", "sp_attn_bwd_batched_ex",
+EXPORTS = ("sp_attn_workspace_bytes", "sp_attn_reserve_bytes", "sp_attn_row_parts_bytes", "sp_attn_full_workspace_bytes", "sp_attn_kept_workspace_bytes", "sp_attn_sums_bytes", "sp_attn_fwd", "sp_attn_bwd", "sp_attn_fwd_batched",
+           "sp_attn_bwd_batched", "sp_attn_bwd_batched_static", "sp_attn_bwd_batched_stages", "sp_attn_fwd_multi", "sp_attn_rope", "sp_attn_rope_qk", "sp_attn_fwd_batched_ex", "sp_attn_bwd_batched_ex", "sp_attn_fwd_batched_sums", "sp_attn_bwd_batched_sums",
            "sp_attn_loss_workspace_bytes", "sp_attn_logprob_fwd", "sp_attn_logprob_bwd", "sp_attn_logprob_bwd_ex", "sp_attn_grpo_loss",
            "sp_attn_segment_table", "sp_attn_row_tile", "sp_attn_dkdv_waves", "sp_attn_f32_rows", "sp_attn_mfma_ceiling", "sp_attn_probe_atomic_add", "sp_attn_set_small_shape_steps", "sp_attn_last_error", "sp_attn_version")
 
@@ -54,6 +54,10 @@ def load_library() -> ctypes.CDLL:
     lib.sp_attn_row_parts_bytes.argtypes = [i64, i32, i32, i32, ctypes.c_int]
     lib.sp_attn_full_workspace_bytes.restype = sz
     lib.sp_attn_full_workspace_bytes.argtypes = [i64, i32, i64, i32, i32, i32, ctypes.c_int]
+    lib.sp_attn_kept_workspace_bytes.restype = sz
+    lib.sp_attn_kept_workspace_bytes.argtypes = [i64, i32, i64, i32, i32, i32, ctypes.c_int]
+    lib.sp_attn_sums_bytes.restype = sz
+    lib.sp_attn_sums_bytes.argtypes = [i64, i32, i32, i32, ctypes.c_int]
     lib.sp_attn_fwd.restype = ctypes.c_int
     lib.sp_attn_fwd.argtypes = [vp, vp, vp, vp, vp, i32, ip, i32, i32, i32, i32, f32, ctypes.c_int, vp, sz, vp]
     lib.sp_attn_bwd.restype = ctypes.c_int
@@ -80,7 +84,12 @@ def load_library() -> ctypes.CDLL:
     lib.sp_attn_bwd_batched_ex.restype = ctypes.c_int
     lib.sp_attn_bwd_batched_ex.argtypes = [vp, vp, vp, vp, vp, vp, vp, vp, vp, i32, ip, ip, ip, i32, i32, i32, f32,
                                            ctypes.c_int, ctypes.c_uint32, ctypes.c_uint32, vp, vp, sz, vp]
-    i64 = ctypes.c_int64
+    lib.sp_attn_fwd_batched_sums.restype = ctypes.c_int
+    lib.sp_attn_fwd_batched_sums.argtypes = [vp, vp, vp, vp, vp, i32, ip, ip, ip, i32, i32, i32, f32, ctypes.c_int,
+                                             ctypes.c_int, ctypes.c_uint32, vp, vp, sz, vp, sz, vp]
+    lib.sp_attn_bwd_batched_sums.restype = ctypes.c_int
+    lib.sp_attn_bwd_batched_sums.argtypes = [vp, vp, vp, vp, vp, vp, vp, vp, vp, i32, ip, ip, ip, i32, i32, i32, f32,
+                                             ctypes.c_int, ctypes.c_uint32, ctypes.c_uint32, vp, vp, sz, vp, sz, vp]
     lib.sp_attn_loss_workspace_bytes.restype = sz
     lib.sp_attn_loss_workspace_bytes.argtypes = [i64, i32, i64]
     lib.sp_attn_logprob_fwd.restype = ctypes.c_int
@@ -204,23 +213,52 @@ def full_workspace_bytes(total_tokens: int, n_groups: int, total_responses: int,
                                                        dtype_code)
 
 
+def kept_workspace_bytes(total_tokens: int, n_groups: int, total_responses: int, n_q_heads: int, n_kv_heads: int, head_dim: int,
+                         dtype_code: int) -> int:
+    return load_library().sp_attn_kept_workspace_bytes(total_tokens, n_groups, total_responses, n_q_heads, n_kv_heads, head_dim,
+                                                       dtype_code)
+
+
+def sums_bytes(total_tokens: int, n_groups: int, n_q_heads: int, n_kv_heads: int, dtype_code: int) -> int:
+    return load_library().sp_attn_sums_bytes(total_tokens, n_groups, n_q_heads, n_kv_heads, dtype_code)
+
+
 def _workspace(is_bwd, q, n_groups, n_resp, n_kv_heads, workspace, o=None, reserve=False):
     """The workspace tensor of a call.  When the caller passes none: a forward allocates one that also has
-    room for the forward-to-backward reserve (and for row parts and pieces of key tiles) and hangs it on the output tensor it returns (attribute
+    room for the forward-to-backward reserve and for row parts and hangs it on the output tensor it returns (attribute
     ``_sp_workspace``); the backward that is given that output finds it there and passes it on, which is
-    all the library needs to use the reserve.  A backward with a residual of its own allocates the same.  Plumbing only:
+    all the library needs to use the reserve.  A backward with a residual of its own allocates the same.  The attribute ``_sp_sums`` of such
+    a workspace says that calls on it get room for partial sums (_sums), which is not kept.  Plumbing only:
     what the reserve is and whether it is valid is decided by the library."""
-    T, Hq, d = q.shape
     if workspace is not None:
         return workspace
-    if is_bwd and o is not None and getattr(o, "_sp_workspace", None) is not None:
-        return o._sp_workspace
-    need = (full_workspace_bytes(T, n_groups, n_resp, Hq, n_kv_heads, d, _dtype_code(q)) if reserve else
-            workspace_bytes(is_bwd, T, n_groups, n_resp, Hq, n_kv_heads, d, _dtype_code(q)))
+    if is_bwd:
+        workspace = getattr(o, "_sp_workspace", None)
+        if workspace is not None:
+            return workspace
+    T, Hq, d = q.shape
+    code = _dtype_code(q)
+    need = (load_library().sp_attn_kept_workspace_bytes(T, n_groups, n_resp, Hq, n_kv_heads, d, code) if reserve else
+            workspace_bytes(is_bwd, T, n_groups, n_resp, Hq, n_kv_heads, d, code))
     workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=q.device)
+    if reserve and code == SP_BF16:
+        workspace._sp_sums = True
     if reserve and not is_bwd and o is not None:
         o._sp_workspace = workspace        # sized for the backward too
     return workspace
+
+
+def _sums(workspace, q, n_groups, n_kv_heads, stream):
+    """Room for the partial sums of one call on a workspace of _workspace()'s, or None."""
+    if not getattr(workspace, "_sp_sums", False):
+        return None
+    need = sums_bytes(q.shape[0], n_groups, q.shape[1], n_kv_heads, _dtype_code(q))
+    if need == 0:
+        return None
+    sums = torch.empty(need, dtype=torch.uint8, device=q.device)
+    if stream is not None:
+        sums.record_stream(stream)         # let go when the call returns, while its kernels may still run
+    return sums
 
 
 def sp_attn_fwd(q, k, v, prompt_len: int, resp_lens: Sequence[int], softmax_scale: float,
@@ -248,10 +286,15 @@ def sp_attn_bwd(q, k, v, o, lse, d_o, prompt_len: int, resp_lens: Sequence[int],
     dk = torch.empty_like(k) if dk is None else dk
     dv = torch.empty_like(v) if dv is None else dv
     workspace = _workspace(True, q, 1, len(resp_lens), Hkv, workspace, o=o)
-    _check(lib.sp_attn_bwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), lse.data_ptr(), d_o.data_ptr(),
-                           dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), prompt_len, _i32(resp_lens),
-                           len(resp_lens), Hq, Hkv, d, softmax_scale, _dtype_code(q), workspace.data_ptr(),
-                           workspace.numel(), _stream_ptr(stream)))
+    sums = _sums(workspace, q, 1, Hkv, stream)
+    tensors = (q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), lse.data_ptr(), d_o.data_ptr(), dq.data_ptr(), dk.data_ptr(), dv.data_ptr())
+    shape = (Hq, Hkv, d, softmax_scale, _dtype_code(q))
+    room = (workspace.data_ptr(), workspace.numel(), _stream_ptr(stream))
+    if sums is None:
+        _check(lib.sp_attn_bwd(*tensors, prompt_len, _i32(resp_lens), len(resp_lens), *shape, *room))
+    else:
+        _check(lib.sp_attn_bwd_batched_sums(*tensors, 1, _i32([prompt_len]), _i32([len(resp_lens)]), _i32(resp_lens), *shape,
+                                            SP_BWD_STAGE_ALL, 0, None, sums.data_ptr(), sums.numel(), *room))
     return dq, dk, dv
 
 
@@ -299,11 +342,12 @@ def sp_attn_fwd_batched_ex(q, k, v, prompt_lens: Sequence[int], Gs: Sequence[int
     o = torch.empty_like(q) if o is None else o
     lse = torch.empty(Hq, T, dtype=torch.float32, device=q.device) if lse is None else lse
     workspace = _workspace(False, q, len(prompt_lens), len(resp_lens_flat), Hkv, workspace, o=o, reserve=o_lo is None)
-    _check(lib.sp_attn_fwd_batched_ex(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), lse.data_ptr(),
-                                      len(prompt_lens), _i32(prompt_lens), _i32(Gs), _i32(resp_lens_flat), Hq, Hkv, d,
-                                      softmax_scale, _dtype_code(q), schedule, flags,
-                                      None if o_lo is None else o_lo.data_ptr(), workspace.data_ptr(),
-                                      workspace.numel(), _stream_ptr(stream)))
+    sums = _sums(workspace, q, len(prompt_lens), Hkv, stream) if flags & SP_FLAG_RESPONSE_ROWS else None
+    args = (q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), lse.data_ptr(), len(prompt_lens), _i32(prompt_lens), _i32(Gs),
+            _i32(resp_lens_flat), Hq, Hkv, d, softmax_scale, _dtype_code(q), schedule, flags, None if o_lo is None else o_lo.data_ptr())
+    room = (workspace.data_ptr(), workspace.numel(), _stream_ptr(stream))
+    _check(lib.sp_attn_fwd_batched_ex(*args, *room) if sums is None else
+           lib.sp_attn_fwd_batched_sums(*args, sums.data_ptr(), sums.numel(), *room))
     return o, lse
 
 
@@ -318,11 +362,13 @@ def sp_attn_bwd_batched_ex(q, k, v, o, lse, d_o, prompt_lens: Sequence[int], Gs:
     dk = torch.empty_like(k) if dk is None else dk
     dv = torch.empty_like(v) if dv is None else dv
     workspace = _workspace(True, q, len(prompt_lens), len(resp_lens_flat), Hkv, workspace, o=o, reserve=o_lo is not None)
-    _check(lib.sp_attn_bwd_batched_ex(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), lse.data_ptr(),
-                                      d_o.data_ptr(), dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), len(prompt_lens),
-                                      _i32(prompt_lens), _i32(Gs), _i32(resp_lens_flat), Hq, Hkv, d, softmax_scale,
-                                      _dtype_code(q), stages, flags, None if o_lo is None else o_lo.data_ptr(),
-                                      workspace.data_ptr(), workspace.numel(), _stream_ptr(stream)))
+    sums = _sums(workspace, q, len(prompt_lens), Hkv, stream)
+    args = (q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), lse.data_ptr(), d_o.data_ptr(), dq.data_ptr(), dk.data_ptr(),
+            dv.data_ptr(), len(prompt_lens), _i32(prompt_lens), _i32(Gs), _i32(resp_lens_flat), Hq, Hkv, d, softmax_scale, _dtype_code(q),
+            stages, flags, None if o_lo is None else o_lo.data_ptr())
+    room = (workspace.data_ptr(), workspace.numel(), _stream_ptr(stream))
+    _check(lib.sp_attn_bwd_batched_ex(*args, *room) if sums is None else
+           lib.sp_attn_bwd_batched_sums(*args, sums.data_ptr(), sums.numel(), *room))
     return dq, dk, dv
 
 
@@ -426,10 +472,12 @@ def sp_attn_bwd_batched(q, k, v, o, lse, d_o, prompt_lens: Sequence[int], Gs: Se
     dk = torch.empty_like(k) if dk is None else dk
     dv = torch.empty_like(v) if dv is None else dv
     workspace = _workspace(True, q, len(prompt_lens), len(resp_lens_flat), Hkv, workspace, o=o)
-    _check(lib.sp_attn_bwd_batched(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), lse.data_ptr(),
-                                   d_o.data_ptr(), dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), len(prompt_lens),
-                                   _i32(prompt_lens), _i32(Gs), _i32(resp_lens_flat), Hq, Hkv, d, softmax_scale,
-                                   _dtype_code(q), workspace.data_ptr(), workspace.numel(), _stream_ptr(stream)))
+    sums = _sums(workspace, q, len(prompt_lens), Hkv, stream)
+    args = (q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), lse.data_ptr(), d_o.data_ptr(), dq.data_ptr(), dk.data_ptr(),
+            dv.data_ptr(), len(prompt_lens), _i32(prompt_lens), _i32(Gs), _i32(resp_lens_flat), Hq, Hkv, d, softmax_scale, _dtype_code(q))
+    room = (workspace.data_ptr(), workspace.numel(), _stream_ptr(stream))
+    _check(lib.sp_attn_bwd_batched(*args, *room) if sums is None else
+           lib.sp_attn_bwd_batched_sums(*args, SP_BWD_STAGE_ALL, 0, None, sums.data_ptr(), sums.numel(), *room))
     return dq, dk, dv
 
 
@@ -477,8 +525,9 @@ def sp_attn_bwd_batched_stages(q, k, v, o, lse, d_o, prompt_lens: Sequence[int],
     T, Hq, d = q.shape
     Hkv = k.shape[1]
     ptr = lambda x: None if x is None else x.data_ptr()
-    _check(lib.sp_attn_bwd_batched_stages(q.data_ptr(), k.data_ptr(), v.data_ptr(), ptr(o), lse.data_ptr(),
-                                          d_o.data_ptr(), ptr(dq), ptr(dk), ptr(dv), len(prompt_lens),
-                                          _i32(prompt_lens), _i32(Gs), _i32(resp_lens_flat), Hq, Hkv, d,
-                                          softmax_scale, _dtype_code(q), stages, workspace.data_ptr(),
-                                          workspace.numel(), _stream_ptr(stream)))
+    sums = _sums(workspace, q, len(prompt_lens), Hkv, stream)
+    args = (q.data_ptr(), k.data_ptr(), v.data_ptr(), ptr(o), lse.data_ptr(), d_o.data_ptr(), ptr(dq), ptr(dk), ptr(dv),
+            len(prompt_lens), _i32(prompt_lens), _i32(Gs), _i32(resp_lens_flat), Hq, Hkv, d, softmax_scale, _dtype_code(q), stages)
+    room = (workspace.data_ptr(), workspace.numel(), _stream_ptr(stream))
+    _check(lib.sp_attn_bwd_batched_stages(*args, *room) if sums is None else
+           lib.sp_attn_bwd_batched_sums(*args, 0, None, sums.data_ptr(), sums.numel(), *room))

@@ -157,8 +157,9 @@ sp_status run(bool bwd, const void* q, const void* k, const void* v, const void*
               int32_t n_groups, const int32_t* prompt_lens, const int32_t* Gs, const int32_t* resp_lens_flat,
               int32_t Hq, int32_t Hkv, int32_t d, float scale, sp_dtype dtype, sp_schedule schedule,
               unsigned stages, unsigned flags, void* workspace, size_t workspace_bytes, void* stream,
-              void* o_lo = nullptr, bool own_scratch = false) {
+              void* o_lo = nullptr, bool own_scratch = false, void* sums = nullptr, size_t sums_bytes = 0) {
     g_err[0] = 0;
+    if (misaligned(sums)) return fail(SP_ERR_INVALID_ARG, "sums pointer %p is not 16-byte aligned", sums);
     if (o_lo && misaligned(o_lo)) return fail(SP_ERR_INVALID_ARG, "o_lo pointer %p is not 16-byte aligned", o_lo);
     if (o_lo && dtype != SP_BF16) return fail(SP_ERR_UNSUPPORTED, "o_lo is a bf16 option (fp32 outputs are not rounded)");
     if (flags & ~(unsigned)(SP_FLAG_RESPONSE_ROWS | SP_FLAG_ACCUMULATE_DKDV))
@@ -196,10 +197,10 @@ sp_status run(bool bwd, const void* q, const void* k, const void* v, const void*
     // row parts change the order of sums: they go with the reserve, so that of the calls without one none has them
     const bool two_parts = ordered && reserve_fits && sp::dkdv_max_parts(L.total_tokens, n_groups, Hq, Hkv) == 2 &&
                            workspace_bytes >= parts_off + partial_bytes(L.total_tokens, Hq, Hkv);
-    // pieces of key tiles, likewise
+    // pieces of key tiles and key loops in parts: in room of the caller's apart from the workspace, or likewise
     const size_t pieces_off = parts_off + sp_attn_row_parts_bytes(L.total_tokens, n_groups, Hq, Hkv, dtype);
-    const size_t pieces_len = sp::piece_bytes(L.total_tokens, n_groups, Hq, Hkv);
-    const bool pieces_fit = dtype == SP_BF16 && reserve_fits && pieces_len > 0 && workspace_bytes >= pieces_off + pieces_len;
+    const size_t pieces_len = sp_attn_sums_bytes(L.total_tokens, n_groups, Hq, Hkv, dtype);
+    const bool pieces_fit = pieces_len > 0 && (sums ? sums_bytes >= pieces_len : reserve_fits && workspace_bytes >= pieces_off + pieces_len);
     void* const reserve = (char*)workspace + reserve_off;
     const bool resp_only = (flags & SP_FLAG_RESPONSE_ROWS) != 0;
     sp::ReserveTag tag{};
@@ -248,7 +249,7 @@ sp_status run(bool bwd, const void* q, const void* k, const void* v, const void*
     sp::KeyPieces pieces;
     sp::RowPieces row_pieces;
     if (pieces_fit) {
-        p.piece_sums = (float*)((char*)workspace + pieces_off);
+        p.piece_sums = sums ? (float*)sums : (float*)((char*)workspace + pieces_off);
         // Behind the table, if the call's kernels may have that as an argument; key pieces that find no room there and pay for the launch
         // that takes the table to memory have all of it.  (Not by how this call is launched: stages and one call have the same parts.)
         // A training pass, us, without pieces -> with, table in memory, 4 / 2 heads: 27 x (28 + 19 x 41) tokens 204 -> 160, 27 x (58 + 17 x 14) 91 ->
@@ -316,13 +317,23 @@ size_t sp_attn_row_parts_bytes(int64_t total_tokens, int32_t n_groups, int32_t n
     return sp::dkdv_max_parts(total_tokens, n_groups, n_q_heads, n_kv_heads) == 2 ? partial_bytes(total_tokens, n_q_heads, n_kv_heads) : 0;
 }
 
-size_t sp_attn_full_workspace_bytes(int64_t total_tokens, int32_t n_groups, int64_t total_responses, int32_t n_q_heads,
+size_t sp_attn_kept_workspace_bytes(int64_t total_tokens, int32_t n_groups, int64_t total_responses, int32_t n_q_heads,
                                     int32_t n_kv_heads, int32_t head_dim, sp_dtype dtype) {
     const size_t need = sp_attn_workspace_bytes(1, total_tokens, n_groups, total_responses, n_q_heads, n_kv_heads, head_dim, dtype);
     if (need == 0 || n_kv_heads < 1) return need;
     return need + sp_attn_reserve_bytes(total_tokens, n_q_heads, head_dim, dtype) +
-           sp_attn_row_parts_bytes(total_tokens, n_groups, n_q_heads, n_kv_heads, dtype) +
-           (dtype == SP_BF16 ? sp::piece_bytes(total_tokens, n_groups, n_q_heads, n_kv_heads) : 0);
+           sp_attn_row_parts_bytes(total_tokens, n_groups, n_q_heads, n_kv_heads, dtype);
+}
+
+size_t sp_attn_full_workspace_bytes(int64_t total_tokens, int32_t n_groups, int64_t total_responses, int32_t n_q_heads,
+                                    int32_t n_kv_heads, int32_t head_dim, sp_dtype dtype) {
+    return sp_attn_kept_workspace_bytes(total_tokens, n_groups, total_responses, n_q_heads, n_kv_heads, head_dim, dtype) +
+           sp_attn_sums_bytes(total_tokens, n_groups, n_q_heads, n_kv_heads, dtype);
+}
+
+size_t sp_attn_sums_bytes(int64_t total_tokens, int32_t n_groups, int32_t n_q_heads, int32_t n_kv_heads, sp_dtype dtype) {
+    if (total_tokens < 1 || n_groups < 1 || n_q_heads < 1 || n_kv_heads < 1 || dtype != SP_BF16) return 0;
+    return sp::piece_bytes(total_tokens, n_groups, n_q_heads, n_kv_heads);
 }
 
 sp_status sp_attn_fwd(const void* q, const void* k, const void* v, void* o, float* lse, int32_t prompt_len,
@@ -382,9 +393,8 @@ sp_status sp_attn_fwd_batched_ex(const void* q, const void* k, const void* v, vo
                                  int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim, float softmax_scale,
                                  sp_dtype dtype, sp_schedule schedule, uint32_t flags, void* o_lo, void* workspace,
                                  size_t workspace_bytes, void* stream) {
-    return run(false, q, k, v, nullptr, nullptr, nullptr, o, lse, nullptr, nullptr, nullptr, n_groups, prompt_lens,
-               Gs, resp_lens_flat, n_q_heads, n_kv_heads, head_dim, softmax_scale, dtype, schedule, SP_BWD_STAGE_ALL,
-               flags, workspace, workspace_bytes, stream, o_lo);
+    return sp_attn_fwd_batched_sums(q, k, v, o, lse, n_groups, prompt_lens, Gs, resp_lens_flat, n_q_heads, n_kv_heads, head_dim, softmax_scale,
+                                    dtype, schedule, flags, o_lo, nullptr, 0, workspace, workspace_bytes, stream);
 }
 
 sp_status sp_attn_bwd_batched_ex(const void* q, const void* k, const void* v, const void* o, const float* lse,
@@ -393,12 +403,32 @@ sp_status sp_attn_bwd_batched_ex(const void* q, const void* k, const void* v, co
                                  int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim, float softmax_scale,
                                  sp_dtype dtype, uint32_t stages, uint32_t flags, const void* o_lo,
                                  void* workspace, size_t workspace_bytes, void* stream) {
+    return sp_attn_bwd_batched_sums(q, k, v, o, lse, d_o, dq, dk, dv, n_groups, prompt_lens, Gs, resp_lens_flat, n_q_heads, n_kv_heads, head_dim,
+                                    softmax_scale, dtype, stages, flags, o_lo, nullptr, 0, workspace, workspace_bytes, stream);
+}
+
+sp_status sp_attn_fwd_batched_sums(const void* q, const void* k, const void* v, void* o, float* lse, int32_t n_groups,
+                                   const int32_t* prompt_lens, const int32_t* Gs, const int32_t* resp_lens_flat,
+                                   int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim, float softmax_scale,
+                                   sp_dtype dtype, sp_schedule schedule, uint32_t flags, void* o_lo, void* sums, size_t sums_bytes,
+                                   void* workspace, size_t workspace_bytes, void* stream) {
+    return run(false, q, k, v, nullptr, nullptr, nullptr, o, lse, nullptr, nullptr, nullptr, n_groups, prompt_lens,
+               Gs, resp_lens_flat, n_q_heads, n_kv_heads, head_dim, softmax_scale, dtype, schedule, SP_BWD_STAGE_ALL,
+               flags, workspace, workspace_bytes, stream, o_lo, false, sums, sums_bytes);
+}
+
+sp_status sp_attn_bwd_batched_sums(const void* q, const void* k, const void* v, const void* o, const float* lse,
+                                   const void* d_o, void* dq, void* dk, void* dv, int32_t n_groups,
+                                   const int32_t* prompt_lens, const int32_t* Gs, const int32_t* resp_lens_flat,
+                                   int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim, float softmax_scale,
+                                   sp_dtype dtype, uint32_t stages, uint32_t flags, const void* o_lo, void* sums, size_t sums_bytes,
+                                   void* workspace, size_t workspace_bytes, void* stream) {
     if (!(stages & SP_BWD_STAGE_ROWSUM) && !o) o = q;
     if (!(stages & SP_BWD_STAGE_DQ) && !dq) dq = const_cast<void*>(q);
     if (!(stages & SP_BWD_STAGE_DKDV)) { if (!dk) dk = const_cast<void*>(q); if (!dv) dv = const_cast<void*>(q); }
     return run(true, q, k, v, o, lse, d_o, nullptr, nullptr, dq, dk, dv, n_groups, prompt_lens, Gs, resp_lens_flat,
                n_q_heads, n_kv_heads, head_dim, softmax_scale, dtype, SP_SCHED_SHARED, stages, flags, workspace,
-               workspace_bytes, stream, const_cast<void*>(o_lo));
+               workspace_bytes, stream, const_cast<void*>(o_lo), false, sums, sums_bytes);
 }
 
 sp_status sp_attn_fwd_multi(int32_t n_sets, const void* const* q, const void* const* k, const void* const* v,

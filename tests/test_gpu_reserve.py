@@ -1,6 +1,8 @@
 """The forward-to-backward reserve: a forward whose workspace has room leaves the rounding residual of
 o there, and a backward given the same, untouched workspace forms D from o plus that residual.  The
 tag at the head of the workspace must make every other situation fall back to the bf16 o alone."""
+import gc
+
 import pytest
 import torch
 
@@ -175,3 +177,33 @@ def test_without_room_for_an_order_the_key_tiles_run_as_packed():
     got = B.sp_attn_bwd_batched(q, k, v, o, lse, d_o, *pk, workspace=_ws(least))
     torch.cuda.synchronize()
     assert all(torch.equal(x, y) for x, y in zip(got, want))
+
+
+@pytest.mark.parametrize("groups,heads", [([W.Group(1024, [256] * 8)], (28, 4)), ([W.Group(60, [85] * 26)] * 2, (4, 2)), ([W.Group(600, [64] * 4)] * 8, (8, 8))])
+@pytest.mark.parametrize("flags", [0, B.SP_FLAG_RESPONSE_ROWS])
+def test_a_forward_keeps_no_room_for_partial_sums(groups, heads, flags):
+    """What hangs on its output is what the backward finds there; room for sums comes and goes with each call, and with it the
+    gradients are those of a workspace with all of it (the first two packings run in pieces, which a workspace without that shows)."""
+    w, _, (q, k, v, d_o), pk = _setup(seed=87, groups=groups, heads=heads)
+    T, n, r = w.total_tokens, len(pk[0]), len(pk[2])
+    o, lse = torch.zeros_like(q), torch.zeros(heads[0], T, device="cuda")
+    gc.collect()                                     # (what earlier tests left, or it goes in between)
+    before = torch.cuda.memory_allocated()
+    B.sp_attn_fwd_batched_ex(q, k, v, *pk, flags, o=o, lse=lse)
+    kept = torch.cuda.memory_allocated() - before
+    size = (B.workspace_bytes(True, T, n, r, *heads, 128, B.SP_BF16) + B.reserve_bytes(T, heads[0], 128, B.SP_BF16)
+            + B.row_parts_bytes(T, n, *heads, B.SP_BF16))
+    assert o._sp_workspace.numel() == size and size <= kept < size + (2 << 20)       # (the allocator's granule)
+    grads = [torch.zeros_like(x) for x in (q, k, v)]
+    before = torch.cuda.memory_allocated()
+    B.sp_attn_bwd_batched_ex(q, k, v, o, lse, d_o, *pk, flags, *grads)
+    assert torch.cuda.memory_allocated() == before
+    out = []
+    for extra in (B.sums_bytes(T, n, *heads, B.SP_BF16), 0):
+        ws, o1, lse1 = _ws(size + extra), torch.zeros_like(o), torch.zeros_like(lse)
+        B.sp_attn_fwd_batched_ex(q, k, v, *pk, flags, o=o1, lse=lse1, workspace=ws)
+        out.append((o1, lse1, *B.sp_attn_bwd_batched_ex(q, k, v, o1, lse1, d_o, *pk, flags, *(torch.zeros_like(x) for x in (q, k, v)), workspace=ws)))
+    torch.cuda.synchronize()
+    assert all(torch.equal(x, y) for x, y in zip((o, lse, *grads), out[0]))
+    if heads != (8, 8):
+        assert not torch.equal(out[0][3], out[1][3])
