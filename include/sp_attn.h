@@ -451,6 +451,17 @@ sp_status sp_attn_row_tile(int32_t n_groups, const int32_t* prompt_lens, const i
 sp_status sp_attn_dkdv_waves(int32_t n_groups, const int32_t* prompt_lens, const int32_t* Gs, const int32_t* resp_lens_flat,
                              int32_t n_q_heads, int32_t n_kv_heads, uint32_t flags, int32_t* waves);
 
+/* The plan of a bf16 call with room for partial sums: key tiles of the dkdv pass in pieces (of_rows = 0), or key loops of the dq pass
+ * and of a forward with SP_FLAG_RESPONSE_ROWS in parts (of_rows = 1).  words receives info[0] words of the list (tile | part << 16 | parts << 24, with
+ * of_rows tile | workgroup << 10 | part << 16 | parts << 24) and behind them info[1] words of the sums (first slot | parts << 16 | keys - 1 << 24 and
+ * first token of each tile with several parts; first slot | parts << 16, first token of the tile and number within it of each workgroup
+ * with several parts); info[2] = place in the list of the first piece with a sum, info[3] = slots per kv head.  info[0] = 0: whole tiles, or whole loops.
+ * flags as in sp_attn_bwd_batched_ex.  Host arithmetic on the lengths; no device work; for tools and tests.  Errors as the host checks
+ * of sp_attn_bwd_batched_ex; SP_ERR_WORKSPACE if capacity (1536 words are enough) is too small. */
+sp_status sp_attn_pieces(int32_t n_groups, const int32_t* prompt_lens, const int32_t* Gs, const int32_t* resp_lens_flat,
+                         int32_t n_q_heads, int32_t n_kv_heads, uint32_t flags, int32_t of_rows, uint32_t* words, size_t capacity,
+                         int32_t* info);
+
 /* How a float32 call on this packing spreads its rows (dkdv pass: keys): rows[0 .. 2] = rows per workgroup of the forward, the
  * dq pass and the dkdv pass, 16 (eight waves, products on matrix instructions), 4 (a wave each) or 1 (eight waves each).  flags as in
  * sp_attn_bwd_batched_ex.  Host arithmetic on the lengths; no device work; for tools and tests.  Errors as the host checks

@@ -24,7 +24,7 @@ SP_FLAG_RESPONSE_ROWS, SP_FLAG_ACCUMULATE_DKDV, SP_FLAG_ZERO_PROMPT_ROWS = 1, 2,
 EXPORTS = ("sp_attn_workspace_bytes", "sp_attn_reserve_bytes", "sp_attn_row_parts_bytes", "sp_attn_full_workspace_bytes", "sp_attn_kept_workspace_bytes", "sp_attn_sums_bytes", "sp_attn_fwd", "sp_attn_bwd", "sp_attn_fwd_batched",
            "sp_attn_bwd_batched", "sp_attn_bwd_batched_static", "sp_attn_bwd_batched_stages", "sp_attn_fwd_multi", "sp_attn_rope", "sp_attn_rope_qk", "sp_attn_fwd_batched_ex", "sp_attn_bwd_batched_ex", "sp_attn_fwd_batched_sums", "sp_attn_bwd_batched_sums",
            "sp_attn_loss_workspace_bytes", "sp_attn_logprob_fwd", "sp_attn_logprob_bwd", "sp_attn_logprob_bwd_ex", "sp_attn_grpo_loss",
-           "sp_attn_segment_table", "sp_attn_row_tile", "sp_attn_dkdv_waves", "sp_attn_f32_rows", "sp_attn_mfma_ceiling", "sp_attn_probe_atomic_add", "sp_attn_set_small_shape_steps", "sp_attn_last_error", "sp_attn_version")
+           "sp_attn_segment_table", "sp_attn_row_tile", "sp_attn_dkdv_waves", "sp_attn_pieces", "sp_attn_f32_rows", "sp_attn_mfma_ceiling", "sp_attn_probe_atomic_add", "sp_attn_set_small_shape_steps", "sp_attn_last_error", "sp_attn_version")
 
 _lib = None
 
@@ -108,6 +108,8 @@ def load_library() -> ctypes.CDLL:
     lib.sp_attn_segment_table.argtypes = [i32, ip, ip, ip, ip, sz, ctypes.POINTER(sz)]
     lib.sp_attn_dkdv_waves.restype = ctypes.c_int
     lib.sp_attn_dkdv_waves.argtypes = [i32, ip, ip, ip, i32, i32, ctypes.c_uint32, ctypes.POINTER(ctypes.c_int32)]
+    lib.sp_attn_pieces.restype = ctypes.c_int
+    lib.sp_attn_pieces.argtypes = [i32, ip, ip, ip, i32, i32, ctypes.c_uint32, i32, ctypes.POINTER(ctypes.c_uint32), sz, ip]
     lib.sp_attn_f32_rows.restype = ctypes.c_int
     lib.sp_attn_f32_rows.argtypes = [i32, ip, ip, ip, i32, i32, i32, ctypes.c_uint32, ctypes.POINTER(ctypes.c_int32)]
     lib.sp_attn_row_tile.restype = ctypes.c_int
@@ -163,6 +165,16 @@ def sp_attn_dkdv_waves(prompt_lens: Sequence[int], Gs: Sequence[int], resp_lens_
     _check(load_library().sp_attn_dkdv_waves(len(prompt_lens), _i32(prompt_lens), _i32(Gs), _i32(resp_lens_flat), n_q_heads,
                                              n_kv_heads, flags, ctypes.byref(waves)))
     return waves.value
+
+
+def sp_attn_pieces(prompt_lens: Sequence[int], Gs: Sequence[int], resp_lens_flat: Sequence[int], n_q_heads: int, n_kv_heads: int,
+                   flags: int = 0, of_rows: bool = False):
+    """(list, sums, first_slot, n_slots): how a bf16 call with room for partial sums cuts the key tiles of its dkdv pass, or (of_rows) the key
+    loops of its dq pass and of a forward of response rows.  Host arithmetic only."""
+    words, info = (ctypes.c_uint32 * 1536)(), (ctypes.c_int32 * 4)()
+    _check(load_library().sp_attn_pieces(len(prompt_lens), _i32(prompt_lens), _i32(Gs), _i32(resp_lens_flat), n_q_heads, n_kv_heads,
+                                         flags, int(of_rows), words, len(words), info))
+    return list(words[:info[0]]), list(words[info[0]:info[0] + info[1]]), info[2], info[3]
 
 
 def sp_attn_f32_rows(prompt_lens: Sequence[int], Gs: Sequence[int], resp_lens_flat: Sequence[int], n_q_heads: int, n_kv_heads: int,

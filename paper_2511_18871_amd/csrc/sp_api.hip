@@ -152,6 +152,22 @@ sp_status build_table(int32_t n_groups, const int32_t* prompt_lens, const int32_
     return SP_OK;
 }
 
+// Pieces of key tiles and key loops in parts of a call with room for their sums.
+// Their lists go behind the table, if the call's kernels may have that as an argument; key pieces that find no room there and pay for the launch
+// that takes the table to memory have all of it.  (Not by how this call is launched: stages and one call have the same parts.)
+// A training pass, us, without pieces -> with, table in memory, 4 / 2 heads: 27 x (28 + 19 x 41) tokens 204 -> 160, 27 x (58 + 17 x 14) 91 ->
+// 82; 24 x (23 + 21 x 7) 71 -> 80 if that launch does not count.
+void plan_pieces(const sp::Problem& p, const Layout& L, bool small_table, bool of_keys, bool of_rows, sp::KeyPieces& keys, sp::RowPieces& rows) {
+    constexpr int TABLE_STEPS = 2;
+    const size_t room = (size_t)sp::ARG_WORDS - (small_table ? L.words.size() : 0);
+    if (of_keys) {
+        const int slots = sp::piece_slots(p.total_tokens, p.n_groups, p.Hq, p.Hkv);
+        keys = sp::plan_key_pieces(p, slots, room, 0);
+        if (keys.words.empty() && keys.no_room && small_table) keys = sp::plan_key_pieces(p, slots, sp::ARG_WORDS, TABLE_STEPS);
+    }
+    if (of_rows) rows = sp::plan_row_pieces(p, sp::piece_bytes(p.total_tokens, p.n_groups, p.Hq, p.Hkv) / sp::ROW_SLOT_BYTES / p.Hkv, room);
+}
+
 sp_status run(bool bwd, const void* q, const void* k, const void* v, const void* o, const float* lse,
               const void* d_o, void* o_out, float* lse_out, void* dq, void* dk, void* dv,
               int32_t n_groups, const int32_t* prompt_lens, const int32_t* Gs, const int32_t* resp_lens_flat,
@@ -250,24 +266,12 @@ sp_status run(bool bwd, const void* q, const void* k, const void* v, const void*
     sp::RowPieces row_pieces;
     if (pieces_fit) {
         p.piece_sums = sums ? (float*)sums : (float*)((char*)workspace + pieces_off);
-        // Behind the table, if the call's kernels may have that as an argument; key pieces that find no room there and pay for the launch
-        // that takes the table to memory have all of it.  (Not by how this call is launched: stages and one call have the same parts.)
-        // A training pass, us, without pieces -> with, table in memory, 4 / 2 heads: 27 x (28 + 19 x 41) tokens 204 -> 160, 27 x (58 + 17 x 14) 91 ->
-        // 82; 24 x (23 + 21 x 7) 71 -> 80 if that launch does not count.
-        constexpr int TABLE_STEPS = 2;
-        const size_t room = (size_t)sp::ARG_WORDS - (small_table ? L.words.size() : 0);
-        if (bwd && (stages & SP_BWD_STAGE_DKDV)) {
-            const int slots = sp::piece_slots(L.total_tokens, n_groups, Hq, Hkv);
-            pieces = sp::plan_key_pieces(p, slots, room, 0);
-            if (pieces.words.empty() && pieces.no_room && small_table) pieces = sp::plan_key_pieces(p, slots, sp::ARG_WORDS, TABLE_STEPS);
-            if (!pieces.words.empty()) p.pieces = &pieces;
-        }
         // A forward of all rows has whole key loops whatever its workspace: o and lse are the same from every entry point, several
         // sets in one call among them.
-        if (bwd ? (stages & SP_BWD_STAGE_DQ) != 0 : resp_only && !p.naive) {
-            row_pieces = sp::plan_row_pieces(p, pieces_len / sp::ROW_SLOT_BYTES / Hkv, room);
-            if (!row_pieces.words.empty()) p.row_pieces = &row_pieces;
-        }
+        plan_pieces(p, L, small_table, bwd && (stages & SP_BWD_STAGE_DKDV), bwd ? (stages & SP_BWD_STAGE_DQ) != 0 : resp_only && !p.naive,
+                    pieces, row_pieces);
+        if (!pieces.words.empty()) p.pieces = &pieces;
+        if (!row_pieces.words.empty()) p.row_pieces = &row_pieces;
     }
     const bool small_call = small_table && pieces.words.size() + L.words.size() <= (size_t)sp::ARG_WORDS &&
                             (!bwd || (stages == SP_BWD_STAGE_ALL && sp::rowsum_fast_path(p)));
@@ -689,6 +693,41 @@ sp_status sp_attn_dkdv_waves(int32_t n_groups, const int32_t* prompt_lens, const
     p.host_group_tokens = L.group_tokens.data();
     p.host_table = L.words.data();
     *waves = sp::dkdv_head_split(L.total_tokens, n_groups, n_q_heads, n_kv_heads) ? 8 : sp::dkdv_waves(p);
+    return SP_OK;
+}
+
+sp_status sp_attn_pieces(int32_t n_groups, const int32_t* prompt_lens, const int32_t* Gs, const int32_t* resp_lens_flat,
+                         int32_t n_q_heads, int32_t n_kv_heads, uint32_t flags, int32_t of_rows, uint32_t* words, size_t capacity,
+                         int32_t* info) {
+    g_err[0] = 0;
+    if (!words || !info) return fail(SP_ERR_INVALID_ARG, "words / info is NULL");
+    if (flags & ~(unsigned)(SP_FLAG_RESPONSE_ROWS | SP_FLAG_ACCUMULATE_DKDV))
+        return fail(SP_ERR_INVALID_ARG, "unknown bits in flags=0x%x", flags);
+    sp_status st = check_geometry(n_q_heads, n_kv_heads, 128, 1.f, SP_BF16);
+    if (st != SP_OK) return st;
+    Layout L;
+    st = build_table(n_groups, prompt_lens, Gs, resp_lens_flat, L);
+    if (st != SP_OK) return st;
+    sp::Problem p{};
+    p.n_groups = n_groups; p.total_tokens = L.total_tokens; p.Hq = n_q_heads; p.Hkv = n_kv_heads; p.head_dim = 128;
+    p.resp_only = (flags & SP_FLAG_RESPONSE_ROWS) != 0;
+    p.host_group_tokens = L.group_tokens.data();
+    p.host_table = L.words.data();
+    p.n_tiles128 = sp::count_tiles(p, 128);
+    float split;                                 // (only whether there is one)
+    p.dkdv_partial = sp::dkdv_head_split(L.total_tokens, n_groups, n_q_heads, n_kv_heads) ? &split : nullptr;
+    p.dkdv_parts = sp::dkdv_parts(p);
+    sp::KeyPieces keys;
+    sp::RowPieces rows;
+    if (sp::piece_bytes(L.total_tokens, n_groups, n_q_heads, n_kv_heads) > 0)
+        plan_pieces(p, L, sp::use_small_call(p, L.words.size(), L.max_responses), !of_rows, of_rows != 0, keys, rows);
+    const std::vector<uint32_t>& list = of_rows ? rows.words : keys.words;
+    const std::vector<uint32_t>& sums = of_rows ? rows.sums : keys.sums;
+    info[0] = (int32_t)list.size(); info[1] = (int32_t)sums.size();
+    info[2] = of_rows ? rows.first_slot : 0; info[3] = of_rows ? rows.n_slots : keys.n_slots;
+    if (capacity < list.size() + sums.size())
+        return fail(SP_ERR_WORKSPACE, "the plan needs %zu words, capacity is %zu", list.size() + sums.size(), capacity);
+    std::copy(sums.begin(), sums.end(), std::copy(list.begin(), list.end(), words));
     return SP_OK;
 }
 

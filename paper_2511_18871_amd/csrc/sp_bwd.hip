@@ -1319,33 +1319,37 @@ int dkdv_waves(const Problem& p) {
 // 32/8 2121 -> 516; 1024 + 8 x 256, 28/4 182 -> 170 (sums of prompt tiles only); 650 + 4 x (9 x 84), 32/8 258 -> 234; on 52 drawn
 // packings of 1e8 to 2e11 operations 1.17 times as fast on average, on 18 larger ones 1.20, at worst 0.98.
 namespace {
-// When workgroups of `lens` steps and `fixed` more, `copies` of each, longest first, are through: each goes to the place that is free first.
+// When workgroups of `lens` steps, `copies` of each, longest first, are through: each goes to the place that is free first.
 // That place's time never falls, so places are counted by the time at which they are free, and one look over the times serves all workgroups
 // (and lengths are sorted by counting).  The longest plan of 3000 drawn packings, on the host, a sort and a heap -> counts: 1150 -> 180 us.
-int play(const std::vector<int>& lens, int places, int copies, int fixed, double* half = nullptr) {
-    int longest = 0;
-    int64_t all = 0;
-    for (int n : lens) { longest = std::max(longest, n); all += n + fixed; }
-    std::vector<int> of_len((size_t)longest + 1, 0), at((size_t)(all * copies / places + longest + fixed + 1), 0);      // (a workgroup starts at the mean or before)
-    for (int n : lens) of_len[(size_t)n] += copies;
-    at[0] = places;
-    int first = 0, end = 0;
-    for (int n = longest; n >= 0; --n)
-        for (int left = of_len[(size_t)n]; left > 0;) {
-            while (at[(size_t)first] == 0) ++first;
-            const int now = std::min(left, at[(size_t)first]);
-            at[(size_t)first] -= now;
-            at[(size_t)(first + n + fixed)] += now;
-            end = std::max(end, first + n + fixed);
-            left -= now;
+struct Play {
+    std::vector<int> of_len, at;                     // kept from one play to the next
+    int operator()(const std::vector<int>& lens, int places, int copies, double* half = nullptr) {
+        int longest = 0;
+        int64_t all = 0;
+        for (int n : lens) { longest = std::max(longest, n); all += n; }
+        of_len.assign((size_t)longest + 1, 0);
+        at.assign((size_t)(all * copies / places + longest + 1), 0);      // (a workgroup starts at the mean or before)
+        for (int n : lens) of_len[(size_t)n] += copies;
+        at[0] = places;
+        int first = 0, end = 0;
+        for (int n = longest; n >= 0; --n)
+            for (int left = of_len[(size_t)n]; left > 0;) {
+                while (at[(size_t)first] == 0) ++first;
+                const int now = std::min(left, at[(size_t)first]);
+                at[(size_t)first] -= now;
+                at[(size_t)(first + n)] += now;
+                end = std::max(end, first + n);
+                left -= now;
+            }
+        if (half) {
+            int t = 0;
+            for (int before = at[0]; before <= places / 2; before += at[(size_t)t]) ++t;
+            *half = t;
         }
-    if (half) {
-        int t = 0;
-        for (int before = at[0]; before <= places / 2; before += at[(size_t)t]) ++t;
-        *half = t;
+        return end;
     }
-    return end;
-}
+};
 // CUs over which the workgroups of a kv head go, and kv heads that share them (ItemMap)
 void cus_of(const Problem& p, int& cus, int& copies) {
     const bool by_xcd = p.Hkv % 8 == 0 || 8 % p.Hkv == 0;
@@ -1384,9 +1388,15 @@ KeyPieces plan_key_pieces(const Problem& p, int slots, size_t max_words, int cos
     cus_of(p, bins, copies);
     const double even = (double)copies * (double)all / bins;
     if (longest + FIXED <= 1.25 * even) return out;
-    auto through = [&](const std::vector<int>& lens) { return play(lens, bins, copies, FIXED); };
+    // A launch is played in units of one step, of more where the longest tile (many q heads per kv head) has more than MOST: the plan of 40 + 130 x 600
+    // tokens, 128 / 1 heads, took 2.1 ms on the host, 64 / 1 0.7
+    constexpr int MOST = 2048;
+    const int unit = std::max((longest + MOST - 1) / MOST, 1);
+    Play play;
+    auto through = [&](const std::vector<int>& lens) { return unit * play(lens, bins, copies); };
     auto parts_of = [&](int steps, int len) { return steps <= len ? 1 : std::min((steps + len - 1) / len, 255); };
     std::vector<int> lens;
+    lens.reserve(tiles.size() + (size_t)slots);
     auto cut = [&](int max_len, int each) {                    // (each: a tile's workgroups of equal share, whatever its length)
         lens.clear();
         int64_t n_slots = 0;
@@ -1395,7 +1405,8 @@ KeyPieces plan_key_pieces(const Problem& p, int slots, size_t max_words, int cos
             if (parts > 1) n_slots += parts;
             if (max_len && lens.size() + parts > max_words) out.no_room = true;
             if (max_len && (n_slots > slots || out.no_room)) return false;
-            for (int i = 0; i < parts; ++i) lens.push_back((t.steps + parts - 1) / parts + (parts > 1 ? STORE : 0));
+            const int len = (t.steps + parts - 1) / parts + (parts > 1 ? STORE : 0) + FIXED;
+            lens.insert(lens.end(), (size_t)parts, unit == 1 ? len : (len + unit - 1) / unit);
         }
         return max_len == 0 || n_slots > 0;
     };
@@ -1481,7 +1492,9 @@ RowPieces plan_row_pieces(const Problem& p, size_t slots, size_t max_words) {
         const int steps = wgs[n].steps;
         return (int)n < whole || steps <= len ? 1 : std::min((steps + len - 1) / len, 255);
     };
+    Play play;
     std::vector<int> lens;
+    lens.reserve(max_words);
     auto end_of = [&](int whole, int len) {
         lens.clear();
         size_t n_slots = 0, n_sums = 0;
@@ -1489,10 +1502,10 @@ RowPieces plan_row_pieces(const Problem& p, size_t slots, size_t max_words) {
             const int parts = parts_of(n, whole, len);
             if (parts > 1) { n_slots += parts; ++n_sums; }
             if (n_slots > slots || n_sums > (size_t)ROW_SUMS || lens.size() + parts > max_words) return 1e30;
-            for (int i = 0; i < parts; ++i) lens.push_back((wgs[n].steps + parts - 1) / parts + (parts > 1 ? STORE : 0));
+            lens.insert(lens.end(), (size_t)parts, (wgs[n].steps + parts - 1) / parts + (parts > 1 ? STORE : 0) + FIXED);
         }
         double half;               // when half of the places are empty: from then on workgroups are alone on their CUs, 1.44 times as fast
-        const double end = play(lens, places, copies, FIXED, &half);
+        const double end = play(lens, places, copies, &half);
         return half + 0.69 * (end - half) + (n_slots ? SUM_STEPS : 0);
     };
     const int n_wgs = (int)wgs.size(), rounds = n_wgs - n_wgs % std::max(places / copies, 1);
