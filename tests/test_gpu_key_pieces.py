@@ -25,6 +25,7 @@ def test_pieces(name, heads):
     w = W.Workload(name, PACKS[name], *heads, 128, torch.bfloat16, 780)
     t = W.make_tensors(w)
     pack, sc = (w.prompt_lens(), w.Gs(), w.resp_lens_flat()), w.softmax_scale
+    assert B.sp_attn_pieces(*pack, *heads)[0]
     q, k, v, d_o = t.q.cuda(), t.k.cuda(), t.v.cuda(), t.d_o.cuda()
     o, lse = B.sp_attn_fwd_batched(q, k, v, *pack, sc)
     nan = lambda: [torch.full_like(x, float("nan")) for x in (q, k, v)]
@@ -40,10 +41,15 @@ def test_pieces(name, heads):
         gate(what, to64(got), ref, w.dtype)
 
 
-@pytest.mark.parametrize("groups,responses", [(24, 21), (19, 24), (23, 24)])
-def test_parts_do_not_depend_on_the_table(groups, responses):
-    """Tables of 593 to 763 words, beside which a kernel's arguments have no room for the list of pieces."""
-    w = W.Workload("tables", [W.Group(23, [7] * responses)] * groups, 4, 2, 128, torch.bfloat16, 783)
+@pytest.mark.parametrize("groups,prompt,responses,length,words,pieces", [
+    (27, 28, 19, 41, 760, 216), (27, 58, 17, 14, 706, 108),      # the list takes the arguments' place of the table
+    (19, 23, 24, 7, 631, 114),                                   # beside the table
+    (24, 23, 21, 7, 724, 0)])                                    # pieces do not pay for the launch that a table in memory takes
+def test_parts_do_not_depend_on_the_table(groups, prompt, responses, length, words, pieces):
+    """Tables of 631 to 760 words, beside most of which a kernel's arguments (768) have no room for the list of pieces."""
+    w = W.Workload("tables", [W.Group(prompt, [length] * responses)] * groups, 4, 2, 128, torch.bfloat16, 783)
+    pack = (w.prompt_lens(), w.Gs(), w.resp_lens_flat())
+    assert (len(B.sp_attn_segment_table(*pack)), len(B.sp_attn_pieces(*pack, 4, 2)[0])) == (words, pieces)
     t = W.make_tensors(w)
     pack, sc = (w.prompt_lens(), w.Gs(), w.resp_lens_flat()), w.softmax_scale
     q, k, v, d_o = t.q.cuda(), t.k.cuda(), t.v.cuda(), t.d_o.cuda()
@@ -67,6 +73,7 @@ def test_pieces_of_response_rows_accumulate(name):
         t.d_o[at:at + g.prompt_len] = 0
         at += g.total
     pack, sc = (w.prompt_lens(), w.Gs(), w.resp_lens_flat()), w.softmax_scale
+    assert bool(B.sp_attn_pieces(*pack, 8, 2, B.SP_FLAG_RESPONSE_ROWS)[0]) == (name != "prompt_alone")
     q, k, v, d_o = t.q.cuda(), t.k.cuda(), t.v.cuda(), t.d_o.cuda()
     o, lse = B.sp_attn_fwd_batched(q, k, v, *pack, sc)
     _, dk, dv = B.sp_attn_bwd_batched_ex(q, k, v, o, lse, d_o, *pack, sc, B.SP_FLAG_RESPONSE_ROWS | B.SP_FLAG_ACCUMULATE_DKDV,

@@ -30,10 +30,15 @@ def _setup(name, heads, seed, resp_only=False):
     return w, t, resp, (w.prompt_lens(), w.Gs(), w.resp_lens_flat(), w.softmax_scale)
 
 
+# all rows of these fill the chip, or nearly: whole key loops
+WHOLE = {(n, (28, 4)) for n in PACKS} | {("two_prompts", (8, 8)), ("two_prompts", (8, 1))}
+
+
 @pytest.mark.parametrize("heads", [(4, 2), (28, 4), (8, 8), (6, 3), (8, 1)])
 @pytest.mark.parametrize("name", list(PACKS))
 def test_all_rows(name, heads):
     w, t, _, pk = _setup(name, heads, 790)
+    assert bool(B.sp_attn_pieces(*pk[:3], *heads, 0, True)[0]) == ((name, heads) not in WHOLE)
     q, k, v, d_o = t.q.cuda(), t.k.cuda(), t.v.cuda(), t.d_o.cuda()
     o, lse = B.sp_attn_fwd_batched(q, k, v, *pk)
     nan = lambda: [torch.full_like(x, float("nan")) for x in (q, k, v)]
@@ -56,6 +61,7 @@ def test_all_rows(name, heads):
 @pytest.mark.parametrize("name", ["two_prompts", "long_response"])
 def test_response_rows_only(name, heads):
     w, t, resp, pk = _setup(name, heads, 791, True)
+    assert bool(B.sp_attn_pieces(*pk[:3], *heads, B.SP_FLAG_RESPONSE_ROWS, True)[0]) == ((name, heads) != ("long_response", (28, 4)))
     q, k, v, d_o = t.q.cuda(), t.k.cuda(), t.v.cuda(), t.d_o.cuda()
     fl = B.SP_FLAG_RESPONSE_ROWS
     o, lse = B.sp_attn_fwd_batched_ex(q, k, v, *pk, fl, o=torch.full_like(q, 7.0), lse=torch.full((heads[0], w.total_tokens), 7.0, device="cuda"))
@@ -69,6 +75,41 @@ def test_response_rows_only(name, heads):
     gate("dQ", to64(dq)[resp], rdq[resp], w.dtype)
     gate("dK", to64(dk), rdk, w.dtype)
     gate("dV", to64(dv), rdv, w.dtype)
+
+
+def test_the_last_round_in_parts():
+    """More workgroups than places: those of full rounds stay whole, the last round's are cut; a table in memory.  Against float64, one kv
+    head and its q heads."""
+    Lp, lens, heads, kvh, rep, d, fl = 8192, W.ragged_lengths(5100, 16, 64, 256), (40, 8), 3, 5, 128, B.SP_FLAG_RESPONSE_ROWS
+    T, pk = Lp + sum(lens), ([Lp], [16], lens)
+    words, sums, first_slot, n_slots = B.sp_attn_pieces(*pk, *heads, fl, True)
+    assert first_slot == 64 and n_slots > 0 and -(-T // 128) * heads[0] > 2048       # (a small call has its table in the arguments)
+    gen = torch.Generator(device="cuda").manual_seed(795)
+    q, d_o = (torch.randn(T, heads[0], d, generator=gen, device="cuda").to(torch.bfloat16) for _ in range(2))
+    k, v = (torch.randn(T, heads[1], d, generator=gen, device="cuda").to(torch.bfloat16) for _ in range(2))
+    o, lse = B.sp_attn_fwd_batched_ex(q, k, v, *pk, d ** -0.5, fl, o=torch.full_like(q, 7.0), lse=torch.full((heads[0], T), 7.0, device="cuda"))
+    dq, dk, dv = B.sp_attn_bwd_batched_ex(q, k, v, o, lse, d_o, *pk, d ** -0.5, fl, dq=torch.full_like(q, 7.0))
+    torch.cuda.synchronize()
+    assert (o[:Lp] == 7).all() and (lse[:, :Lp] == 7).all() and (dq[:Lp] == 7).all()
+    starts = torch.repeat_interleave(Lp + torch.tensor([0, *lens[:-1]]).cumsum(0), torch.tensor(lens)).cuda()
+    key, row = torch.arange(T, device="cuda"), torch.arange(Lp, T, device="cuda")
+    hidden = (key[None] > row[:, None]) | ((key[None] >= Lp) & (key[None] < starts[:, None]))
+    K, V = (x[:, kvh].double().contiguous() for x in (k, v))
+    rdk, rdv = torch.zeros_like(K), torch.zeros_like(V)
+    for h in range(kvh * rep, (kvh + 1) * rep):
+        Q, G = q[Lp:, h].double().contiguous(), d_o[Lp:, h].double().contiguous()
+        S = (Q @ K.t().contiguous() * d ** -0.5).masked_fill_(hidden, float("-inf"))
+        rlse = torch.logsumexp(S, 1)
+        P = torch.exp(S - rlse[:, None])
+        ro = P @ V
+        dS = P * (G @ V.t().contiguous() - (G * ro).sum(1, keepdim=True))
+        gate(f"O head {h}", to64(o[Lp:, h]), to64(ro), q.dtype)
+        gate_lse(to64(lse[h:h + 1, Lp:]), to64(rlse[None]), q.dtype)
+        gate(f"dQ head {h}", to64(dq[Lp:, h]), to64(dS @ K * d ** -0.5), q.dtype)
+        rdk += dS.t().contiguous() @ Q * d ** -0.5
+        rdv += P.t().contiguous() @ G
+    gate("dK", to64(dk[:, kvh]), to64(rdk), q.dtype)
+    gate("dV", to64(dv[:, kvh]), to64(rdv), q.dtype)
 
 
 @pytest.mark.parametrize("name", ["two_prompts", "long_response", "no_prompt"])
