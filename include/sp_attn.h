@@ -16,7 +16,7 @@
  *       k, v, dk, dv  : [T_total, n_kv_heads, head_dim]
  *       lse           : [n_q_heads, T_total]  float32, natural log of
  *                       sum over allowed keys of exp(softmax_scale * <q, k>)
- *     Element type is bf16 (SP_BF16) or float32 (SP_F32, a plain-ALU debug path).
+ *     Element type is bf16 (SP_BF16) or float32 (SP_F32: float32 throughout, for cross-checks and small problems).
  *     Base pointers must be 16-byte aligned.
  *   - q head h reads kv head h / (n_q_heads / n_kv_heads) (contiguous blocks).
  *   - q and k arrive already position-encoded: the restarted position ids of
@@ -60,7 +60,7 @@ typedef enum {
 typedef enum {
     SP_BF16 = 0,              /* bf16 tensors, bf16 MFMA contractions, fp32 softmax/accumulate;
                                  head_dim must be 128 */
-    SP_F32 = 1                /* float32 tensors, plain-ALU debug path; head_dim 64 or 128 */
+    SP_F32 = 1                /* float32 tensors, products and sums in float32; head_dim 64 or 128 */
 } sp_dtype;
 
 /* Which kernel schedule the forward uses.  SP_SCHED_SHARED is the product path:

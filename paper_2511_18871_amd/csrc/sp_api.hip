@@ -483,7 +483,7 @@ sp_status sp_attn_fwd_multi(int32_t n_sets, const void* const* q, const void* co
             for (int i = 0; i < n_sets; ++i) { p.qs[i] = q[i]; p.ks[i] = k[i]; p.vs[i] = v[i]; p.os[i] = o[i]; p.lses[i] = lse[i]; }
             if (n_sets == 1) { p.q = q[0]; p.k = k[0]; p.v = v[0]; p.o_out = o[0]; p.lse_out = lse[0]; }
             e = sp::launch_fwd_bf16(p, s);
-        } else {                 // the fp32 debug kernels take one set per launch
+        } else {                 // the float32 kernels take one set per launch
             for (int i = 0; i < n_sets && e == hipSuccess; ++i) {
                 p.q = q[i]; p.k = k[i]; p.v = v[i]; p.o_out = o[i]; p.lse_out = lse[i];
                 e = sp::launch_fwd_f32(p, s);

@@ -107,9 +107,10 @@ hipError_t launch_rope(const void* x, void* y, int H, const void* x2, void* y2, 
     RopeFreq f{};
     for (int i = 0; i < d / 2; ++i) f.theta[i] = pow(base, -2.0 * (double)i / (double)d);
     const unsigned grid = (unsigned)((total_tokens + 512 / d - 1) / (512 / d));
-    // Outputs that (nearly) fill the Infinity Cache (256 MB) are stored past the caches.  us, cached -> not, 40 heads, outputs in
-    // four buffers in turn: 210 MB of outputs 73.9 -> 70.7, with a forward of short groups behind 219 -> 221; 252 MB 88.0 -> 84.0, 261 ->
-    // 262; 336 MB 118 -> 111, 338 -> 335.  In one buffer again and again, which stays in the cache: 210 MB 63 -> 70, 252 MB 75 -> 84, 336 MB 117 -> 111.
+    // Outputs that (nearly) fill the Infinity Cache (256 MB) are stored past the caches.  us, cached -> not, 40 heads.  Outputs in
+    // four buffers in turn, as those of a model's layers: 210 MB 73.9 -> 70.7, 252 MB 88.0 -> 84.0, 336 MB 118 -> 111; with a forward of short groups
+    // behind, which reads them, 219 -> 221, 261 -> 262, 338 -> 335.  The line is where the pass gains more than its reader loses; a
+    // buffer that is written again and again stays in the cache and would have it at 300 MB (210 MB 63 -> 70, 252 MB 75 -> 84, 336 MB 117 -> 111).
     const bool bypass = total_tokens * (H + (x2 ? H2 : 0)) * d * (f32 ? 4 : 2) > (int64_t)240 << 20;
     auto launch = [&](auto elem, auto dim, auto past) {
         typedef decltype(elem) T;
